@@ -34,10 +34,9 @@
 //     them in LDS; an element costs one bit-field extract, one address add and
 //     one ds_read per moment;
 //   * the p-quantile is exact: each lane sorts its 8 values with min3/med3/max3
-//     (32 instructions), parks the sorted column in LDS, and the group runs r
-//     rounds of "row minimum by DPP, the lane that holds it pops its column";
-//     a scalar population count detects the rounds in which two lanes tie and
-//     only those rounds pay for the tie-break;
+//     (32 instructions) and the group runs r rounds of "row minimum by DPP, the
+//     lowest lane that holds it pops its column"; four scalar instructions pick
+//     that lane for all groups, ties or not;
 //   * the two per-block divisions share one IEEE division sequence (even lanes
 //     divide x_p by Delta_v, odd lanes L by Delta_m);
 //   * the base alpha = rho^(1/K) is found by testing G consecutive binary32
@@ -520,9 +519,8 @@ __device__ __forceinline__ void wave_lds_sync()
 // LDS of one wavefront, one contiguous slab of 32-bit words (all offsets are compile-time
 // constants, so the sub-arrays are reached with instruction offsets from very few address
 // registers):
-//   columns   64 x 12 words  per-lane sorted keys + sentinel; doubles as the staging area of
-//                            the layout transposition at the start of an iteration
-//                            (E = 16, the wide path: 64 x 18 words)
+//   columns   64 x 12 words  staging area of the layout transpositions (E = 16, the wide path:
+//                            64 x 18 words, then the lanes' sorted keys + sentinel)
 //   img_m/v   the super-tile's code words (loaded once, updated in place, written back once)
 //   tv, tm    level tables of the blocks of the current iteration
 //   sc        3 block scalars (Delta_m, Delta_v, alpha) per block of the super-tile
@@ -689,52 +687,114 @@ __device__ __forceinline__ void store_state_image(const StepArgs &a, uint64_t ti
     }
 }
 
+// The lowest set bit of every G-bit field of a ballot, one field per group of lanes.  Every field
+// has a bit set (the lanes whose key equals the group's minimum), so ~h + 1 does not carry out of
+// its field and one 64-bit add serves all groups: four scalar instructions, no branch on ties.
+// (A population count with a branch into a vector tie-break cost about as much without ties and
+// six more vector instructions in every round with one: 2^24 elements, 3-bit/3-bit, nine of ten
+// gradients zero, so that every round ties: 44.9 us with the branch, 40.1 without.)
+template <int G>
+__device__ __forceinline__ uint64_t lowest_holders(uint64_t h)
+{
+    constexpr uint64_t kOnes = G == 16 ? 0x0001000100010001ull : G == 8 ? 0x0101010101010101ull : 0x1111111111111111ull;
+    return h & (~h + kOnes);
+}
+
 // The r-th smallest key of every group of G lanes (full blocks).  Each lane has parked its sorted
 // column at col_addr (the +inf sentinel behind it) and passes its two smallest keys.  A round:
-// group minimum of the heads by DPP; the lane that holds it pops its column.  The pop is written
-// out (the holders run under their own exec mask), so a round is straight-line code with the
-// loop's back edge as its only branch.  A lane keeps the key behind its head in a register: a pop
-// moves it up and fetches the one after it, whose LDS latency then lies outside the chain of
-// rounds (it is waited for only when the same lane pops again).  A scalar population count
-// detects the rounds in which two lanes of a group tie; then only the lowest holder of a group
-// pops, so exactly one key leaves a group per round: a lane counts the holders below it in the
-// wavefront (two mbcnt), the count of the group's first lane is spread over the group by DPP,
-// and the lowest holder is the one whose count equals it.  A few vector instructions, no loop
-// over the groups and no register that lives across the rounds.
+// group minimum of the heads by DPP; the lowest lane that holds it pops its column, so exactly one
+// key leaves a group per round and the r-th minimum is the order statistic, multiplicities
+// included.  The pop is written out (the popping lanes run under their own exec mask), so a round
+// is straight-line code with the loop's back edge as its only branch.  A lane keeps the key behind
+// its head in a register: a pop moves it up and fetches the one after it, whose LDS latency then
+// lies outside the chain of rounds.  (All 64 lanes of the wavefront are active here.)
 template <int G>
 __device__ __forceinline__ uint32_t extract_rth(uint32_t head, uint32_t behind, uint32_t haddr, uint32_t rank)
 {
-    constexpr int NG = 64 / G;
-    uint32_t xp_bits = 0;
-    for (uint32_t k = 0; k < rank; ++k) {
+    for (uint32_t k = 1; k < rank; ++k) {
         const uint32_t mn = group_reduce<G>(head, UMin());
-        uint64_t holders = __builtin_amdgcn_ballot_w64(head == mn);
-        if (__builtin_expect(__builtin_popcountll(holders) != NG, 0)) {
-            const uint32_t c = __builtin_amdgcn_mbcnt_hi((uint32_t)(holders >> 32),
-                                                         __builtin_amdgcn_mbcnt_lo((uint32_t)holders, 0u));
-            uint32_t c0 = dpp<0x00>(c);                     // quad_perm [0,0,0,0]
-            if (G >= 8)                                     // lanes 4-7 and 12-15 of a row <- four lanes down
-                c0 = (uint32_t)__builtin_amdgcn_update_dpp((int)c0, (int)c0, 0x114, 0xF, 0xA, false);
-            if (G == 16)                                    // lanes 8-15 of a row <- eight lanes down
-                c0 = (uint32_t)__builtin_amdgcn_update_dpp((int)c0, (int)c0, 0x118, 0xF, 0xC, false);
-            holders &= __builtin_amdgcn_ballot_w64(c == c0);
-        }
-        xp_bits = mn;
-        uint64_t saved;
-        asm volatile("s_mov_b64 %[saved], exec\n\t"
-                     "s_mov_b64 exec, %[holders]\n\t"
+        const uint64_t pop = lowest_holders<G>(__builtin_amdgcn_ballot_w64(head == mn));
+        asm volatile("s_mov_b64 exec, %[pop]\n\t"
                      "s_waitcnt lgkmcnt(0)\n\t"
                      "v_mov_b32_e32 %[head], %[behind]\n\t"
                      "ds_read_b32 %[behind], %[haddr] offset:8\n\t"
                      "v_add_u32_e32 %[haddr], 4, %[haddr]\n\t"
-                     "s_mov_b64 exec, %[saved]"
-                     : [head] "+v"(head), [behind] "+v"(behind), [haddr] "+v"(haddr), [saved] "=&s"(saved)
-                     : [holders] "s"(holders)
+                     "s_mov_b64 exec, -1"
+                     : [head] "+v"(head), [behind] "+v"(behind), [haddr] "+v"(haddr)
+                     : [pop] "s"(pop)
                      : "memory");
     }
     // the last fetch may still be in flight: its register is free only once it has landed
     asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(behind) : : "memory");
-    return xp_bits;
+    return group_reduce<G>(head, UMin());
+}
+
+// The lanes of `pop` drop the first of their sorted keys: the N keys behind it move up by one
+// (N = 8: the seventh and the +inf behind the column).  The two wait states that a DPP read of
+// k[0] needs behind its write are the instructions that follow it.
+template <int N>
+__device__ __forceinline__ void pop_column(uint32_t (&k)[8], uint64_t pop)
+{
+#define SOLO_MOVE(D_, S_) "v_mov_b32_e32 " D_ ", " S_ "\n\t"
+#define SOLO_POP(MOVES_)                                                                                  \
+    asm volatile("s_mov_b64 exec, %8\n\t" MOVES_ "s_mov_b64 exec, -1"                                   \
+                 : "+v"(k[0]), "+v"(k[1]), "+v"(k[2]), "+v"(k[3]), "+v"(k[4]), "+v"(k[5]), "+v"(k[6]), "+v"(k[7]) \
+                 : "s"(pop))
+#define SOLO_M1 SOLO_MOVE("%0", "%1")
+#define SOLO_M2 SOLO_M1 SOLO_MOVE("%1", "%2")
+#define SOLO_M3 SOLO_M2 SOLO_MOVE("%2", "%3")
+#define SOLO_M4 SOLO_M3 SOLO_MOVE("%3", "%4")
+#define SOLO_M5 SOLO_M4 SOLO_MOVE("%4", "%5")
+#define SOLO_M6 SOLO_M5 SOLO_MOVE("%5", "%6")
+#define SOLO_M7 SOLO_M6 SOLO_MOVE("%6", "%7")
+    if (N == 1) SOLO_POP(SOLO_M1 "s_nop 0\n\t");
+    else if (N == 2) SOLO_POP(SOLO_M2);
+    else if (N == 3) SOLO_POP(SOLO_M3);
+    else if (N == 4) SOLO_POP(SOLO_M4);
+    else if (N == 5) SOLO_POP(SOLO_M5);
+    else if (N == 6) SOLO_POP(SOLO_M6);
+    else if (N == 7) SOLO_POP(SOLO_M7);
+    else SOLO_POP(SOLO_M7 SOLO_MOVE("%7", "0x7f800000"));
+#undef SOLO_M1
+#undef SOLO_M2
+#undef SOLO_M3
+#undef SOLO_M4
+#undef SOLO_M5
+#undef SOLO_M6
+#undef SOLO_M7
+#undef SOLO_POP
+#undef SOLO_MOVE
+}
+
+// One round of the selection on columns that live in registers: the group's minimum, which the
+// lowest lane that holds it drops.
+template <int G, int N>
+__device__ __forceinline__ uint32_t extract_round8(uint32_t (&k)[8])
+{
+    const uint32_t mn = group_reduce<G>(k[0], UMin());
+    pop_column<N>(k, lowest_holders<G>(__builtin_amdgcn_ballot_w64(k[0] == mn)));
+    return mn;
+}
+
+// The r-th smallest key of every group of G lanes, each with its 8 sorted keys in registers: a pop
+// shifts the column instead of fetching from LDS.  More moves than extract_rth(), but no LDS
+// latency in the chain of rounds, which is what a short buffer's time is made of (a round of the
+// LDS form takes 185-280 cycles with one wavefront on a SIMD; a launch of 4096 elements went from
+// 6.63 to 6.25 us, of 2^20 with 4-bit codes from 7.52 to 6.91).  The last seven rounds shift only
+// the keys that can still come up.
+template <int G>
+__device__ __forceinline__ uint32_t extract_rth8(uint32_t (&k)[8], uint32_t rank)
+{
+    if (rank >= 8) {
+#pragma unroll 1
+        for (uint32_t i = 8; i < rank; ++i) extract_round8<G, 8>(k);
+        extract_round8<G, 7>(k); extract_round8<G, 6>(k); extract_round8<G, 5>(k); extract_round8<G, 4>(k);
+        extract_round8<G, 3>(k); extract_round8<G, 2>(k); extract_round8<G, 1>(k);
+    } else {
+#pragma unroll 1
+        for (uint32_t i = 1; i < rank; ++i) extract_round8<G, 7>(k);
+    }
+    return group_reduce<G>(k[0], UMin());
 }
 
 // Per-block constants of the two encoders, from the new block statistics.
@@ -1058,12 +1118,9 @@ __device__ __forceinline__ void step_tile(const StepArgs &a, const uint64_t tile
     constexpr int VT = K + 1;                      // entries of a block's v level table (4, 8, 16)
     constexpr int MT = MDE ? 2 * L + 2 : 2 * L + 1; // entries of a block's m level table (3, 7, 15; DE: 4, 8, 16)
     constexpr int MTS = Lay::MTS;                  // stride of the m tables
-    constexpr uint32_t GMASK = (G == 16) ? 0xFFFFu : 0xFFu;
-    // A runaway column address (possible only with non-finite input) stays inside the slab.
     constexpr int kOffCol = Lay::kOffCol, kOffImgM = Lay::kOffImgM, kOffImgV = Lay::kOffImgV;
-    constexpr int kOffTv = Lay::kOffTv, kOffTm = Lay::kOffTm, kOffSc = Lay::kOffSc, kSlab = Lay::kSlab;
+    constexpr int kOffTv = Lay::kOffTv, kOffTm = Lay::kOffTm, kOffSc = Lay::kOffSc;
     constexpr bool kDeTable = Lay::kDeTable;
-    static_assert(kSlab >= 64 * kColStride + 140, "column slack");
 
     const uint64_t nblk = (a.n + B - 1) / B;
     const uint64_t m_total = (a.n + CM - 1) / CM, v_total = (a.n + CV - 1) / CV;
@@ -1071,7 +1128,6 @@ __device__ __forceinline__ void step_tile(const StepArgs &a, const uint64_t tile
 
     uint32_t *const img_m = slab + kOffImgM, *const img_v = slab + kOffImgV;
     float *const sc = reinterpret_cast<float *>(slab + kOffSc);
-    uint32_t *const col = slab + kOffCol + lane * kColStride;
 
     // first parameters and gradients: in flight while the state image is staged
     const int it_begin = alone ? chunk : 0, it_end = alone ? chunk + 1 : TILE / kIter;
@@ -1124,11 +1180,9 @@ __device__ __forceinline__ void step_tile(const StepArgs &a, const uint64_t tile
     const uint32_t lig = lane & (G - 1);               // lane in group
     const uint32_t grp = lane / G;                     // group (block) inside the iteration
     const uint32_t gshift = lane & 31u & ~(uint32_t)(G - 1);   // group's first lane inside its 32-lane half
-    const uint32_t below = (1u << lig) - 1u;
     float *const my_tv = reinterpret_cast<float *>(slab + kOffTv) + grp * VT;
     float *const my_tm = reinterpret_cast<float *>(slab + kOffTm) + grp * MTS;
     const uint32_t tv_addr = lds_addr(my_tv), tm_addr = lds_addr(my_tm);   // aligned to the table size
-    const uint32_t col_addr = lds_addr(col);
 
     // DE codebook: the levels of the table entries this lane fills (entries lig, lig + G)
     float de_level[(16 + G - 1) / G];
@@ -1201,34 +1255,20 @@ __device__ __forceinline__ void step_tile(const StepArgs &a, const uint64_t tile
         if (dv < kTiny) dv = 0.0f;
 
         // ---- the r-th smallest v^ of the block
-        col[8] = kInfBits;                      // sentinel behind the lane's 8 keys (the staging overwrote it)
-        *reinterpret_cast<uint4 *>(col) = make_uint4(key[0], key[1], key[2], key[3]);
-        *reinterpret_cast<uint4 *>(col + 4) = make_uint4(key[4], key[5], key[6], key[7]);
-        uint32_t r_mine = a.rank_full;
-        if (TAIL) {
-            const float x = __builtin_ceilf(a.quantile_p * (float)nb);
-            r_mine = x < 1.0f ? 1u : (uint32_t)x;
-            r_mine = r_mine > nb ? nb : r_mine;
-        }
-        uint32_t head = key[0], haddr = col_addr, xp_bits = 0;
-        auto extract_round = [&](uint32_t k) {
-            const uint32_t mn = group_reduce<G>(head, UMin());
-            bool pop = head == mn;
-            const uint64_t holders = __builtin_amdgcn_ballot_w64(pop);
-            // one holder per group is the common case; a tie costs three more instructions:
-            // only the lowest holder of a group pops, so exactly one key leaves per round
-            if (__builtin_popcountll(holders) != NG)
-                pop = pop && (group_bits(holders, lane, gshift, GMASK) & below) == 0u;
-            if (TAIL) { if (k + 1 == r_mine) xp_bits = mn; } else xp_bits = mn;
-            if (pop) {
-                haddr = TAIL ? umin(haddr + 4u, col_addr + 32u) : haddr + 4u;
-                head = lds_u32(haddr);
-            }
-        };
+        uint32_t xp_bits;
         if (!TAIL) {
-            xp_bits = extract_rth<G>(key[0], key[1], col_addr, a.rank_full);
+            xp_bits = extract_rth8<G>(key, a.rank_full);
         } else {
-            for (uint32_t k = 0; k < a.rank_full; ++k) extract_round(k);
+            // (a shorter last block has a smaller rank; absent elements are +inf behind the others)
+            const float x = __builtin_ceilf(a.quantile_p * (float)nb);
+            uint32_t r_mine = x < 1.0f ? 1u : (uint32_t)x;
+            r_mine = r_mine > nb ? nb : r_mine;
+            xp_bits = 0;
+#pragma unroll 1
+            for (uint32_t k = 1; k <= a.rank_full; ++k) {
+                const uint32_t mn = extract_round8<G, 8>(key);
+                xp_bits = k == r_mine ? mn : xp_bits;
+            }
         }
 
         // ---- the block's encoder constants, then this lane's 8 codes of each moment
