@@ -340,10 +340,9 @@ def main():
     # the kernel that takes the time (the library picks it from the format, the size and the launch)
     if w.block_size == 2048:
         kernel_name = "solo::multi_big_wide_kernel" if args.launch == "multi" else "solo::big_wide_kernel"
-    elif args.launch == "multi":
-        kernel_name = "solo::multi_chunk_kernel" if (w.grad_dtype == "fp32" and w.m_codebook == "linear") else "solo::multi_kernel"
     else:
-        kernel_name = "solo::step_kernel"
+        per_lane = 8 if n <= 3 << 18 else 16
+        kernel_name = f"solo::{'multi_' if args.launch == 'multi' else ''}chunk{per_lane}_kernel"
     out = {
         "metric": "updated_params_per_sec", "value": n / (wall / args.steps), "unit": "params/s",
         "n_gpus": 1, "steps": args.steps, "warmup": args.warmup, "ms_per_step": ms_per_step,

@@ -207,11 +207,11 @@ typedef struct solo_tensor {
     uint64_t n;            /* elements                                       */
 } solo_tensor;
 
-/* Number of work units the tensors are cut into for cfg's state format and gradient type (a unit
- * is the 2560 or 5120 elements one wavefront of that format's kernel owns, the ragged end of a
- * tensor counts one unit per 512 elements; with fp32 gradients and the linear codebook a unit is
- * 2560 elements or a tensor's shorter end, shared by five wavefronts); 0 if cfg is invalid.  At
- * most 2^24 tensors per table.  With blocks of 2048 elements a unit is one block. */
+/* Number of work units the tensors are cut into for cfg's state format and gradient type: one per
+ * full 5120 elements (2560 for the wider formats) plus one per 512 elements of a tensor's ragged end;
+ * with fp32 gradients and the linear codebook one per 2560 elements, a tensor's shorter end
+ * included.  0 if cfg is invalid.  At most 2^24 tensors per table.  With blocks of 2048 elements
+ * a unit is one block. */
 uint64_t solo_multi_units(const solo_tensor *tensors, uint32_t count, const solo_config *cfg);
 
 /* Bytes of the table for `count` tensors and `units` units. */

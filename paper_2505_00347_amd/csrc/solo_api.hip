@@ -285,7 +285,7 @@ uint64_t solo_multi_units(const solo_tensor *tensors, uint32_t count, const solo
         for (uint32_t k = 0; k < count; ++k) units += (tensors[k].n + solo::kTileUnit - 1) / solo::kTileUnit;
         return units;
     }
-    const uint64_t unit = (uint64_t)solo::unit_elems(cfg->bits_m, cfg->bits_v, cfg->block_size, mde);
+    const uint64_t unit = (uint64_t)solo::unit_elems(cfg->bits_m, cfg->bits_v, cfg->block_size);
     for (uint32_t k = 0; k < count; ++k) units += solo::multi_full_units(tensors[k].n, unit) + solo::multi_ragged_chunks(tensors[k].n, unit);
     return units;
 }
@@ -305,8 +305,7 @@ int solo_multi_table_build(const solo_tensor *tensors, uint32_t count, const sol
     if (units > (1ull << 31)) return SOLO_E_UNSUPPORTED;
     const bool big = cfg->block_size == solo::kLargeBlock;
     const uint64_t unit = big ? solo::kLargeBlock
-                              : (uint64_t)solo::unit_elems(cfg->bits_m, cfg->bits_v, cfg->block_size,
-                                                           (cfg->flags & SOLO_FLAG_M_DYNAMIC_EXPONENT) != 0);
+                              : (uint64_t)solo::unit_elems(cfg->bits_m, cfg->bits_v, cfg->block_size);
     const bool chunked = !big && solo::multi_chunked(cfg->grad_dtype == SOLO_GRAD_BF16,
                                              (cfg->flags & SOLO_FLAG_M_DYNAMIC_EXPONENT) != 0);
     solo::TensorEntry *entries = static_cast<solo::TensorEntry *>(table_host);
@@ -362,9 +361,6 @@ int solo_adamw_step_multi(const void *table_device, uint32_t count, uint64_t uni
     ma.any_bf16_copy = (table_flags & SOLO_TABLE_BF16_COPY) ? 1u : 0u;
     const bool bf16 = cfg->grad_dtype == SOLO_GRAD_BF16;
     const bool mde = (cfg->flags & SOLO_FLAG_M_DYNAMIC_EXPONENT) != 0;
-    // wavefronts of the launch: one per unit, or five per 2560-element unit of a chunked format
-    const uint64_t slots = solo::multi_chunked(bf16, mde) ? units * (solo::kTileUnit / solo::kIter) : units;
-    ma.groups_per_xcd = ((slots + solo::kWaves - 1) / solo::kWaves + solo::kXcds - 1) / solo::kXcds;
     hipStream_t s = (hipStream_t)stream;
     hipError_t e;
     if (cfg->block_size == solo::kLargeBlock) {

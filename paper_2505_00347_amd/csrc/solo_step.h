@@ -1,30 +1,29 @@
 // Device code of the fused SOLO AdamW step for gfx950 (wave64).
 //
-// Work decomposition.  A buffer is cut into super-tiles of 2560 or 5120
-// elements (2560 is a multiple of every block size and of 16, 10 and 8 codes
-// per word, so a super-tile owns whole blocks and whole code words; the
-// larger size is used wherever the LDS image of the tile's state still lets
-// five workgroups share a CU).  One wavefront owns one super-tile and walks
-// it in iterations of 512 elements; a lane owns 8 consecutive elements per
-// iteration, so a block of 128 (64) elements is held by 16 (8) neighbouring
-// lanes, i.e. one DPP row (half row), and every per-block reduction is a few
-// DPP steps.  Nothing is shared between wavefronts but a constant table: the
-// only workgroup barrier sits before the first tile is touched.
+// Work decomposition.  A wavefront steps one chunk of consecutive elements on its own, from the
+// first load to the last store: 1024 elements, 16 per lane (step_chunk16), or 512, 8 per lane
+// (step_chunk8).  A block of 128 (64) elements is held by 8 (4) or 16 (8) neighbouring lanes, i.e.
+// by half a DPP row or a row, and every per-block reduction is a few DPP steps.  Nothing is shared
+// between wavefronts but a constant table: the only workgroup barrier sits before the first
+// element is touched.  No software prefetch: 60-100 registers leave room for five to seven
+// wavefronts per SIMD, which hide each other's memory latency, and the whole machine sweeps one
+// compact window of memory.
 //
-// step_tile() is the whole step for one super-tile; step_kernel runs it over
-// a flat buffer (full tiles, and the ragged end with bounds checks),
-// multi_kernel over the tensors of a caller-built table.  Full super-tiles of
-// formats whose state image is small enough take step_tile16() instead: 16
-// elements per lane, 8 (4) lanes per block, 1024 elements per iteration, four
-// wavefronts per SIMD instead of five (fewer instructions per element; see
-// there).  A ragged end, a short or mid-size buffer (chunked_up_to()) and the
-// formats whose streaming code sits at the register limit run step_tile() in
-// its `alone` form: one wavefront per 512-element iteration, which stages and
-// writes back only its own words (multi_chunk_kernel: the same over a table).
-// The pieces that these functions and the large-block functions of
-// solo_step_big.h have in common (layout transposition, level tables, EMAs
-// and parameter, encoders, image update, write-back) exist once, as inlined
-// helpers in front of step_tile().
+// Which of the two: what is done once per lane and block (level tables, maxima, divisions, the
+// base, the hash, packing) is spread over twice as many elements with 16 per lane, so that form
+// needs an eighth fewer instructions and is the faster one as soon as there is work for every
+// SIMD; a buffer that is shorter than that takes the latency of one wavefront, and 8 elements
+// per lane have the shorter one (narrow_up_to()).  The ragged end of a buffer always runs the
+// 8-per-lane form with bounds checks.  chunk8_kernel and chunk16_kernel run over a flat buffer,
+// multi_chunk8_kernel and multi_chunk16_kernel over the tensors of a caller-built table.
+//
+// (Measured against one wavefront that walks a super-tile of 5120 elements in five iterations
+// and prefetches one iteration ahead, the form of the large bf16 buffers before: 2^24 elements
+// 2-bit/3-bit 43.5 -> 35.9 us, 2^28 elements 594 -> 508 us, 6.7e9 elements 13.62 -> 13.47 ms.)
+//
+// The pieces that these functions and the large-block functions of solo_step_big.h have in common
+// (layout transposition, level tables, EMAs and parameter, encoders, code words) exist once, as
+// inlined helpers in front of them.
 //
 // The kernel is bound by vector-ALU issue as much as by HBM (packed FP32 is
 // off, so a CU retires 64 lane-operations per clock: about 80 per parameter at
@@ -57,24 +56,16 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
-#ifndef SOLO_MIN_WAVES
-#define SOLO_MIN_WAVES 5   // wavefronts per SIMD the register allocator must leave room for
-#endif
-
 namespace solo {
 
+
 constexpr int kTileUnit = 2560;    // lcm of the block sizes and of 16, 10 and 8 codes per word
-constexpr int kIter = 512;         // elements per iteration (64 lanes x 8)
-constexpr int kLdsPerCu = 160 * 1024;
-#ifndef SOLO_WAVES
-#define SOLO_WAVES 4
-#endif
-constexpr int kWaves = SOLO_WAVES; // wavefronts per workgroup
-constexpr int kXcds = 8;           // accelerator dies of an MI355X (each has its own L2)
-constexpr int kColStride = 12;     // words per lane in the sorted-column area (8 keys, +inf, pad)
-constexpr int kIter16 = 1024;      // elements per iteration of the wide path (64 lanes x 16)
-constexpr int kColStride16 = 18;   // its column stride (16 keys, +inf, pad; columns are written 8 bytes at a time)
-constexpr int kWideWaves = 4;      // wavefronts per SIMD the wide path is compiled for
+constexpr int kIter = 512;         // elements of a chunk with 8 per lane
+constexpr int kIter16 = 1024;      // elements of a chunk with 16 per lane
+constexpr int kWaves = 4;          // wavefronts per workgroup
+constexpr int kMinWaves = 5;       // wavefronts per SIMD that the register allocator must leave room for, 8 elements per lane
+constexpr int kMinWaves16 = 4;     // and 16 per lane (81-96 registers, i.e. five, in most formats; forcing five spills in the others and gains nothing)
+constexpr int kColStride16 = 18;   // words per lane of the sorted columns (16 keys, +inf, pad; written 8 bytes at a time)
 constexpr float kTiny = 0x1p-100f; // block maxima below this are stored as 0
 constexpr float kRhoMin = 0x1p-64f;
 constexpr uint32_t kInfBits = 0x7F800000u;
@@ -89,10 +80,8 @@ struct StepArgs {
     float *v_scale;
     float *v_base;
     uint64_t n;             // elements
-    uint64_t n_tiles_full;  // super-tiles that lie entirely inside [0, n)
-    uint64_t tail_tile0;    // first 2560-element unit behind them (the ragged end)
-    uint64_t tail_chunks;   // 512-element iterations of the ragged end, one wavefront each
-    uint64_t wg_per_xcd;    // workgroups per XCD: ceil(ceil(n_tiles_full / kWaves) / 8)
+    uint64_t rest;          // 512-element iterations behind the last whole chunk, up to the end of the last code word
+    uint64_t block0;        // first block of a launch of the large-block tail kernel
     uint64_t index_offset;  // global index of element 0 (multiple of 8)
     float beta1, omb1, beta2, omb2;
     float decay;            // 1 - lr * weight_decay
@@ -135,9 +124,7 @@ constexpr int kMapChunkShift = 24;
 inline uint64_t multi_full_units(uint64_t n, uint64_t unit) { return n / unit; }
 inline uint64_t multi_ragged_chunks(uint64_t n, uint64_t unit)
 {
-    // up to the end of the last code word (80 = lcm of 16, 10 and 8 codes per word), whose unused
-    // fields are written as zeros like every other field
-    return n % unit ? ((n + 79) / 80 * 80 - n / unit * unit + 511) / 512 : 0;
+    return n % unit ? ((n + 79) / 80 * 80 - n / unit * unit + 511) / 512 : 0;      // (end_of_words)
 }
 
 struct MultiArgs {
@@ -145,12 +132,21 @@ struct MultiArgs {
     const TensorEntry *entries;
     const uint32_t *unit_map;     // tensor index of every unit
     uint64_t total_units;
-    uint64_t groups_per_xcd;      // groups of kWaves units per XCD
     uint32_t any_bf16_copy;       // some tensor of the table has a bf16 copy to write
 };
 
-// Elements per unit of a multi-tensor table for a format: the super-tile size of its kernels.
-inline int unit_elems(uint32_t bits_m, uint32_t bits_v, uint32_t block_size, bool mde);
+// The layout of a multi-tensor table (what a map entry stands for).  fp32 gradients with the linear
+// codebook: one entry per 2560 elements, a tensor's shorter end included.  Every other format: one
+// entry per full unit of 5120 or 2560 elements, and one per 512-element iteration of a ragged end.
+constexpr bool multi_chunked(bool bf16, bool mde) { return !bf16 && !mde; }
+constexpr int unit_elems(uint32_t bits_m, uint32_t bits_v, uint32_t block_size)
+{
+    return bits_m + bits_v <= (block_size == 128 ? 6u : 5u) ? 2 * kTileUnit : kTileUnit;
+}
+
+// Elements up to the end of the last code word of n elements (80 = lcm of 16, 10 and 8 codes per
+// word): a word's unused fields are written as zeros like every other field.
+__host__ __device__ constexpr uint64_t end_of_words(uint64_t n) { return (n + 79) / 80 * 80; }
 
 // ---------------------------------------------------------------- cross-lane
 
@@ -516,176 +512,20 @@ __device__ __forceinline__ void wave_lds_sync()
     __builtin_amdgcn_wave_barrier();
 }
 
-// LDS of one wavefront, one contiguous slab of 32-bit words (all offsets are compile-time
-// constants, so the sub-arrays are reached with instruction offsets from very few address
-// registers):
-//   columns   64 x 12 words  staging area of the layout transpositions (E = 16, the wide path:
-//                            64 x 18 words, then the lanes' sorted keys + sentinel)
-//   img_m/v   the super-tile's code words (loaded once, updated in place, written back once)
-//   tv, tm    level tables of the blocks of the current iteration
-//   sc        3 block scalars (Delta_m, Delta_v, alpha) per block of the super-tile
-template <int BM, int BV, int B, bool MDE, int TILE, int E = 8>
-struct SlabLayout {
-    static constexpr int NG = 64 / (B / E);
-    static constexpr int kCol = E == 8 ? kColStride : kColStride16;
-    static constexpr int NBT = TILE / B;
-    static constexpr int MW = TILE / (32 / BM), VW = TILE / (32 / BV);
-    static constexpr int VT = 1 << BV;
-    static constexpr int MTS = BM == 2 ? 4 : BM == 3 ? 8 : 16;   // stride of the m tables: a power of two >= their entries
-    static constexpr int kOffCol = 0;
-    static constexpr int kOffImgM = 64 * kCol;
-    static constexpr int kOffImgV = kOffImgM + ((MW + 4 + 3) / 4) * 4;
-    static constexpr int kOffTv = ((kOffImgV + VW + 4 + 15) / 16) * 16;      // 64-byte aligned
-    static constexpr int kOffTm = kOffTv + ((NG * VT + 15) / 16) * 16;
-    static constexpr int kOffSc = kOffTm + NG * MTS;
-    static constexpr int kSlab = ((kOffSc + 3 * NBT + 15) / 16) * 16;
-    static constexpr bool kDeTable = MDE && BM >= 3;     // DE rounding by bucket table (two boundaries: compares are cheaper)
-    static constexpr int kDeWords = kDeTable ? 4 * DeBuckets<BM>::N : 16;
-    static constexpr int kBytesPerWg = 4 * (kWaves * kSlab + kDeWords);
-};
+template <int BM>
+constexpr int m_table_stride() { return BM == 2 ? 4 : BM == 3 ? 8 : 16; }   // a power of two >= the entries of a block's m table
 
-// Elements per wavefront super-tile: a longer tile spreads a wavefront's start-up (kernel
-// arguments, first loads) over more work, so the tile is doubled wherever the larger state
-// image still leaves room for SOLO_MIN_WAVES wavefronts per SIMD.
-// The wide path (16 elements per lane, see step_tile16) serves the full super-tiles of a format
-// whenever its larger LDS slab lets kWideWaves wavefronts per SIMD run.
-#ifndef SOLO_WIDE
-#define SOLO_WIDE 1
-#endif
-// Up to how many elements a flat buffer runs one wavefront per 512-element iteration instead of
-// one per super-tile.  Measured on MI355X (per-call time over sizes from 2^12 to 2^29, every
-// format): the one-iteration wavefronts need about 60 registers and run seven to a SIMD, which
-// hides the memory latency without any software prefetch, so a tensor of 2^20 elements takes
-// 8-9 us instead of 22-30.  With fp32 gradients and the linear codebook they stay ahead of the
-// streaming kernels at every size (by 13 % at 2^26, 5 % at 2^29 elements: the streaming kernels
-// of these formats sit at the register limit), with fp32 gradients and the dynamic-exponent
-// codebook up to 2^28; with bf16 gradients the streaming kernels take over between 2^25
-// (128-element blocks) and 2^27 elements (64-element blocks) and lead by 2-15 % at 2^29.
-#ifndef SOLO_MID_SCALE
-#define SOLO_MID_SCALE 1
-#endif
-template <int B, bool BF16, bool MDE>
-constexpr uint64_t chunked_up_to()
-{
-    if (SOLO_MID_SCALE == 0) return 4 * (uint64_t)kTileUnit;           // (tuning builds: streaming wherever possible)
-    if (SOLO_MID_SCALE < 0) return ~0ull;                               // (tuning builds: never streaming)
-    if (!BF16) return MDE ? (256ull << 20) : ~0ull;
-    return B == 64 ? (128ull << 20) : (32ull << 20);
-}
+// Words of the workgroup's DE bucket table (rounding by two boundaries: compares are cheaper).
+template <int BM, bool MDE>
+constexpr int de_words() { return MDE && BM >= 3 ? 4 * DeBuckets<BM>::N : 16; }
 
-#ifndef SOLO_WIDE_B64
-#define SOLO_WIDE_B64 1
-#endif
-template <int BM, int BV, int B, bool MDE>
-constexpr bool wide_path()
-{
-    constexpr int wgs = kWideWaves * 4 / kWaves;
-    return SOLO_WIDE && (SOLO_WIDE_B64 || B == 128) && SlabLayout<BM, BV, B, MDE, 2 * kTileUnit, 16>::kBytesPerWg * wgs <= kLdsPerCu;
-}
-
-template <int BM, int BV, int B, bool MDE>
-constexpr int tile_elems()
-{
-    constexpr int wgs = SOLO_MIN_WAVES * 4 / kWaves;              // workgroups per CU at that occupancy
-    if (wide_path<BM, BV, B, MDE>()) return 2 * kTileUnit;
-    return SlabLayout<BM, BV, B, MDE, 2 * kTileUnit>::kBytesPerWg * wgs <= kLdsPerCu ? 2 * kTileUnit : kTileUnit;
-}
-
-inline int unit_elems(uint32_t bits_m, uint32_t bits_v, uint32_t block_size, bool mde)
-{
-#define SOLO_U(BM_, BV_, B_)                                                                  \
-    if (bits_m == BM_ && bits_v == BV_ && block_size == B_)                                   \
-        return mde ? tile_elems<BM_, BV_, B_, true>() : tile_elems<BM_, BV_, B_, false>();
-#define SOLO_UB(BM_, BV_) SOLO_U(BM_, BV_, 64) SOLO_U(BM_, BV_, 128)
-    SOLO_UB(2, 2) SOLO_UB(2, 3) SOLO_UB(2, 4) SOLO_UB(3, 2) SOLO_UB(3, 3) SOLO_UB(3, 4)
-    SOLO_UB(4, 2) SOLO_UB(4, 3) SOLO_UB(4, 4)
-#undef SOLO_UB
-#undef SOLO_U
-    return 0;
-}
-
-// The formats whose flat buffers run one wavefront per 512-element iteration at every size do so
-// in a multi-tensor launch as well: their tables hold one entry per 2560-element unit (a tensor's
-// shorter end included), and five wavefronts share a unit.
-inline bool multi_chunked(bool bf16, bool mde)
-{
-    return bf16 ? chunked_up_to<128, true, false>() == ~0ull
-                : (mde ? chunked_up_to<128, false, true>() == ~0ull : chunked_up_to<128, false, false>() == ~0ull);
-}
-
-// ---- pieces shared by the two tile functions
-
-// Stages a full super-tile's state in LDS (coalesced, 16 bytes per lane): every load is issued
-// before the first one is waited for, one memory round trip instead of five.
-template <int BM, int BV, int MW, int VW, int NBT>
-__device__ __forceinline__ void load_state_image(const StepArgs &a, uint64_t tile, uint32_t lane,
-                                                 uint32_t *img_m, uint32_t *img_v, float *sc)
-{
-    static_assert(MW % 4 == 0 && VW % 4 == 0, "128-bit staging");
-    constexpr int RM = (MW / 4 + 63) / 64, RV = (VW / 4 + 63) / 64, RS = (NBT + 63) / 64;
-    const u32x4_t *gm = reinterpret_cast<const u32x4_t *>(a.m_words + tile * MW);
-    const u32x4_t *gv = reinterpret_cast<const u32x4_t *>(a.v_words + tile * VW);
-    u32x4_t xm[RM], xv[RV];
-    float s_dm[RS], s_dv[RS], s_al[RS];
-#pragma unroll
-    for (int r = 0; r < RM; ++r) {
-        const uint32_t q = lane + 64u * r;
-        if (q < MW / 4) xm[r] = __builtin_nontemporal_load(gm + q);
-    }
-#pragma unroll
-    for (int r = 0; r < RV; ++r) {
-        const uint32_t q = lane + 64u * r;
-        if (q < VW / 4) xv[r] = __builtin_nontemporal_load(gv + q);
-    }
-#pragma unroll
-    for (int r = 0; r < RS; ++r) {
-        const uint32_t bb = lane + 64u * r;
-        if (bb < NBT) {
-            const uint64_t gb = tile * NBT + bb;
-            s_dm[r] = a.m_scale[gb]; s_dv[r] = a.v_scale[gb]; s_al[r] = a.v_base[gb];
-        }
-    }
-#pragma unroll
-    for (int r = 0; r < RM; ++r) {
-        const uint32_t q = lane + 64u * r;
-        if (q < MW / 4) {
-            if (BM == 3) xm[r] &= 0x3FFFFFFFu;
-            *reinterpret_cast<u32x4_t *>(img_m + 4 * q) = xm[r];
-        }
-    }
-#pragma unroll
-    for (int r = 0; r < RV; ++r) {
-        const uint32_t q = lane + 64u * r;
-        if (q < VW / 4) {
-            if (BV == 3) xv[r] &= 0x3FFFFFFFu;
-            *reinterpret_cast<u32x4_t *>(img_v + 4 * q) = xv[r];
-        }
-    }
-#pragma unroll
-    for (int r = 0; r < RS; ++r) {
-        const uint32_t bb = lane + 64u * r;
-        if (bb < NBT) { sc[bb] = s_dm[r]; sc[NBT + bb] = s_dv[r]; sc[2 * NBT + bb] = s_al[r]; }
-    }
-}
-
-// Writes a full super-tile's state back (coalesced, streamed).
-template <int MW, int VW, int NBT>
-__device__ __forceinline__ void store_state_image(const StepArgs &a, uint64_t tile, uint32_t lane,
-                                                  const uint32_t *img_m, const uint32_t *img_v, const float *sc)
-{
-    u32x4_t *gm = reinterpret_cast<u32x4_t *>(a.m_words + tile * MW);
-    u32x4_t *gv = reinterpret_cast<u32x4_t *>(a.v_words + tile * VW);
-    for (uint32_t q = lane; q < MW / 4; q += 64)
-        stream_store_u4(gm + q, *reinterpret_cast<const u32x4_t *>(img_m + 4 * q));
-    for (uint32_t q = lane; q < VW / 4; q += 64)
-        stream_store_u4(gv + q, *reinterpret_cast<const u32x4_t *>(img_v + 4 * q));
-    for (uint32_t b = lane; b < NBT; b += 64) {
-        const uint64_t gb = tile * NBT + b;
-        a.m_scale[gb] = sc[b];
-        a.v_scale[gb] = sc[NBT + b];
-        a.v_base[gb] = sc[2 * NBT + b];
-    }
-}
+// Up to how many elements a flat buffer (or the units of a table) runs 8 elements per lane.
+// Measured on MI355X, us per launch, 8 | 16 per lane:
+//                        2^18          2^19          2^20          2^21
+//   2-bit/3-bit bf16     5.30 | 5.90   5.72 | 6.09   6.89 | 6.39   9.12 | 8.25
+//   4-bit/4-bit fp32     4.72 | 5.53   5.39 | 5.67   6.36 | 5.87   8.48 | 7.94
+//   3-bit/3-bit DE B 64  5.12 | 6.24   5.63 | 6.37   6.72 | 6.63   9.02 | 8.54
+constexpr uint64_t narrow_up_to() { return 3ull << 18; }
 
 // The lowest set bit of every G-bit field of a ballot, one field per group of lanes.  Every field
 // has a bit set (the lanes whose key equals the group's minimum), so ~h + 1 does not carry out of
@@ -1089,218 +929,189 @@ __device__ __forceinline__ void write_back_word(uint32_t *const word, const uint
     else if (fin != own) atomicXor(word, fin ^ own);
 }
 
-// One super-tile of TILE elements, processed by the calling wavefront: the whole step for the
-// elements [tile * TILE, (tile + 1) * TILE) of the buffers in `a` (TAIL: clipped to a.n, with
-// bounds checks on every element).  `slab` is this wavefront's LDS, `lds_de` the workgroup's DE
-// bucket table.
+// The code words of the 512 elements that a wavefront steps on its own (8 consecutive elements per
+// lane): staged in LDS, at most one word of each stream per lane, and written back by the lane
+// that staged them.  The first word may begin in the share before (ten-to-a-word codes).
+// TAIL: words behind the buffer are left alone.
+template <int BM, int BV, bool TAIL>
+struct ChunkWords8 {
+    static constexpr int CM = 32 / BM, CV = 32 / BV;   // codes per word
+    static constexpr int kImage = 68;                  // words of a stream's image (<= 64, + 1)
+    static_assert(kIter / 8 <= 64, "one staged word per lane and code stream");
+    uint64_t gw_m, gw_v;                       // the words this lane stages
+    bool has_m, has_v;
+    uint32_t own_m, own_v;                     // as they were loaded
+    uint32_t wm, sm, wv, sv;                   // word (of the image) and slot of the lane's first code
+
+    // ew0: first element of the wavefront's share.  Issues the loads.
+    __device__ __forceinline__ void load(const StepArgs &a, const uint64_t ew0, const uint32_t lane)
+    {
+        const uint64_t gm_lo = ew0 / CM, gv_lo = ew0 / CV;
+        const uint32_t rm0 = (uint32_t)(ew0 - gm_lo * CM), rv0 = (uint32_t)(ew0 - gv_lo * CV);   // slot of the first element
+        gw_m = gm_lo + lane; gw_v = gv_lo + lane;
+        has_m = lane < (rm0 + kIter + CM - 1) / CM && (!TAIL || gw_m < (a.n + CM - 1) / CM);
+        has_v = lane < (rv0 + kIter + CV - 1) / CV && (!TAIL || gw_v < (a.n + CV - 1) / CV);
+        own_m = 0; own_v = 0;
+        if (has_m) own_m = a.m_words[gw_m];
+        if (has_v) own_v = a.v_words[gw_v];
+        const uint32_t qm = rm0 + lane * 8u, qv = rv0 + lane * 8u;      // < 520: e / 10 by multiplication
+        wm = (CM == 10) ? __umul24(qm, 52429u) >> 19 : qm / CM; sm = qm - wm * CM;
+        wv = (CV == 10) ? __umul24(qv, 52429u) >> 19 : qv / CV; sv = qv - wv * CV;
+    }
+    __device__ __forceinline__ void stage(uint32_t *const img_m, uint32_t *const img_v, const uint32_t lane)
+    {
+        if (BM == 3) own_m &= 0x3FFFFFFFu;
+        if (BV == 3) own_v &= 0x3FFFFFFFu;
+        img_m[lane] = own_m;
+        img_v[lane] = own_v;
+        // (a 3-bit run that ends with its word reads the word behind it without using it)
+        if (lane == 0) { img_m[64] = 0; img_v[64] = 0; }
+    }
+    __device__ __forceinline__ void codes(const uint32_t *const img_m, const uint32_t *const img_v,
+                                          uint32_t &mc8, uint32_t &vc8) const
+    {
+        const uint32_t mw0 = img_m[wm], mw1 = (BM == 3) ? img_m[wm + 1] : 0u;
+        const uint32_t vw0 = img_v[wv], vw1 = (BV == 3) ? img_v[wv + 1] : 0u;
+        mc8 = extract8<BM>(mw0, mw1, sm) & (uint32_t)((1ull << (8 * BM)) - 1ull);
+        vc8 = extract8<BV>(vw0, vw1, sv) & (uint32_t)((1ull << (8 * BV)) - 1ull);
+    }
+    __device__ __forceinline__ void write_back(const StepArgs &a, const uint32_t *const img_m, const uint32_t *const img_v,
+                                               const uint32_t lane) const
+    {
+        if (has_m) write_back_word<BM>(&a.m_words[gw_m], img_m[lane], own_m);
+        if (has_v) write_back_word<BV>(&a.v_words[gw_v], img_v[lane], own_v);
+    }
+};
+
+// LDS of a wavefront that steps one 512-element chunk (32-bit words; offsets are compile-time
+// constants, so the parts are reached with instruction offsets from very few address registers).
+constexpr int kStage8 = (kIter / 4 + kIter / 32) * 4;          // the padded transposition
+template <int BM, int BV, int B>
+struct ChunkLayout8 {
+    static constexpr int NG = kIter / B;
+    static constexpr int VT = 1 << BV;
+    static constexpr int MTS = m_table_stride<BM>();
+    static constexpr int kOffImgM = kStage8;
+    static constexpr int kOffImgV = kOffImgM + ChunkWords8<BM, BV, false>::kImage;
+    static constexpr int kOffTv = ((kOffImgV + ChunkWords8<BM, BV, false>::kImage + 15) / 16) * 16;   // 64-byte aligned
+    static constexpr int kOffTm = kOffTv + ((NG * VT + 15) / 16) * 16;
+    static constexpr int kSlab = kOffTm + ((NG * MTS + 15) / 16) * 16;
+};
+
+// The whole step for the 512 elements from 512 * chunk on (TAIL: clipped to a.n, with bounds checks
+// on every element), by the calling wavefront on its own.  `slab` is its LDS, `lds_de` the
+// workgroup's DE bucket table.
 // EXT: the code that also serves the variants of the step (gradient scale, coupled decay,
 // AdaBelief, bf16 weight copy); the plain AdamW step runs the one without them.
-template <int BM, int BV, int B, bool BF16, bool MDE, bool TAIL, bool EXT, int TILE, bool ALONE = TAIL>
-__device__ __forceinline__ void step_tile(const StepArgs &a, const uint64_t tile, const uint32_t lane,
-                                          uint32_t *const slab, const uint32_t *const lds_de, const int chunk = -1)
+template <int BM, int BV, int B, bool BF16, bool MDE, bool TAIL, bool EXT>
+__device__ __forceinline__ void step_chunk8(const StepArgs &a, const uint64_t chunk, const uint32_t lane,
+                                            uint32_t *const slab, const uint32_t *const lds_de)
 {
-    // ALONE: this wavefront runs iteration `chunk` of the tile alone, next to other wavefronts
-    // that run the other iterations (short and mid-size tensors, whose super-tiles are too few to
-    // fill the machine; always so for a ragged end).  It stages the tile's state for reading and
-    // applies its code changes to the global words directly (atomic XOR: the fields that
-    // different wavefronts own in a shared word are disjoint) instead of writing the tile back.
-    static_assert(ALONE || !TAIL, "a ragged end is always cut into its iterations");
-    constexpr bool alone = ALONE;
     constexpr int G = B / 8;                       // lanes per block
-    constexpr int NG = 64 / G;                     // blocks per iteration
-    constexpr int kTile = TILE;
-    using Lay = SlabLayout<BM, BV, B, MDE, kTile>;
-    constexpr int NBT = kTile / B;                 // blocks per super-tile
+    constexpr int NG = 64 / G;                     // blocks of the chunk
     constexpr int L = (1 << (BM - 1)) - 1;
-    constexpr int K = (1 << BV) - 1;
-    constexpr int CM = 32 / BM, CV = 32 / BV;      // codes per word
-    constexpr int MW = kTile / CM, VW = kTile / CV; // words per super-tile
-    constexpr int VT = K + 1;                      // entries of a block's v level table (4, 8, 16)
-    constexpr int MT = MDE ? 2 * L + 2 : 2 * L + 1; // entries of a block's m level table (3, 7, 15; DE: 4, 8, 16)
-    constexpr int MTS = Lay::MTS;                  // stride of the m tables
-    constexpr int kOffCol = Lay::kOffCol, kOffImgM = Lay::kOffImgM, kOffImgV = Lay::kOffImgV;
-    constexpr int kOffTv = Lay::kOffTv, kOffTm = Lay::kOffTm, kOffSc = Lay::kOffSc;
-    constexpr bool kDeTable = Lay::kDeTable;
+    constexpr int VT = 1 << BV;
+    constexpr int MT = MDE ? 2 * L + 2 : 2 * L + 1;    // entries of a block's m level table (3, 7, 15; DE: 4, 8, 16)
+    using Lay = ChunkLayout8<BM, BV, B>;
+    constexpr bool kDeTable = MDE && BM >= 3;
 
-    const uint64_t nblk = (a.n + B - 1) / B;
-    const uint64_t m_total = (a.n + CM - 1) / CM, v_total = (a.n + CV - 1) / CV;
-    const uint64_t tile_e0 = tile * kTile;
-
-    uint32_t *const img_m = slab + kOffImgM, *const img_v = slab + kOffImgV;
-    float *const sc = reinterpret_cast<float *>(slab + kOffSc);
-
-    // first parameters and gradients: in flight while the state image is staged
-    const int it_begin = alone ? chunk : 0, it_end = alone ? chunk + 1 : TILE / kIter;
-    RawPG raw = load_pg<BF16, TAIL>(a, tile_e0 + (uint32_t)it_begin * kIter, lane);
-    const float gscale = (EXT && a.grad_scale) ? *a.grad_scale : 1.0f;      // uniform: the gradient is transformed first
+    const uint64_t ew0 = chunk * kIter, e0 = ew0 + lane * 8u;
+    const uint32_t lig = lane & (G - 1);               // lane in group
+    const uint32_t grp = lane / G;                     // group (block) inside the chunk
+    const uint32_t gshift = lane & 31u & ~(uint32_t)(G - 1);   // group's first lane inside its 32-lane half
+    uint32_t *const img_m = slab + Lay::kOffImgM, *const img_v = slab + Lay::kOffImgV;
+    float *const my_tv = reinterpret_cast<float *>(slab + Lay::kOffTv) + grp * VT;
+    float *const my_tm = reinterpret_cast<float *>(slab + Lay::kOffTm) + grp * Lay::MTS;
+    const uint32_t tv_addr = lds_addr(my_tv), tm_addr = lds_addr(my_tm);   // aligned to the table size
     // one pad vector after every 8 keeps both the coalesced (index = lane) and the per-lane
     // (index = 2 lane, 2 lane + 1) accesses of the transposition free of bank conflicts
-    static_assert((kIter / 4 + kIter / 32) * 4 <= 64 * kColStride, "staging must fit the column area");
-    float4 *const stage = reinterpret_cast<float4 *>(slab + kOffCol);
+    float4 *const stage = reinterpret_cast<float4 *>(slab);
     float4 *const st_c = stage + (lane + lane / 8u);        // coalesced slots: st_c[0] and st_c[72] (= slot 64 + lane)
     float4 *const st_l = stage + (2u * lane + lane / 4u);   // this lane's 8 elements: st_l[0], st_l[1]
 
-    // ---- stage the state in LDS.  A wavefront that owns the super-tile stages all of it (coalesced,
-    // 16 bytes per lane).  One that runs a single iteration stages that iteration's part: at most
-    // 64 words of each code stream, one per lane, which the same lane writes back at the end (the
-    // first and the last 3-bit word may be shared with the neighbouring iterations' wavefronts),
-    // and the scalars of its blocks.
-    static_assert(kOffImgM % 4 == 0 && kOffImgV % 4 == 0, "128-bit staging");
-    static_assert(kIter / 8 <= 64, "one staged word per lane and code stream");
-    uint32_t own_m = 0, own_v = 0;                 // the staged words as they were loaded
-    const uint32_t e_lo = alone ? (uint32_t)chunk * kIter : 0u, e_hi = e_lo + kIter - 1u;
-    const uint32_t wm_lo = e_lo / CM, wm_hi = e_hi / CM, wv_lo = e_lo / CV, wv_hi = e_hi / CV;
-    if (alone) {
-        const uint32_t w_m = wm_lo + lane, w_v = wv_lo + lane;
-        const uint64_t gw_m = tile * MW + w_m, gw_v = tile * VW + w_v;
-        const uint32_t b = (uint32_t)chunk * (kIter / B) + lane;
-        const uint64_t gb = tile * NBT + b;
-        const bool has_m = w_m <= wm_hi && (!TAIL || gw_m < m_total);
-        const bool has_v = w_v <= wv_hi && (!TAIL || gw_v < v_total);
-        const bool has_b = lane < (uint32_t)(kIter / B) && (!TAIL || gb < nblk);
-        // every load is issued before the first one is waited for
-        float s_dm = 0.0f, s_dv = 0.0f, s_al = 1.0f;
-        if (has_m) own_m = a.m_words[gw_m];
-        if (has_v) own_v = a.v_words[gw_v];
-        if (has_b) { s_dm = a.m_scale[gb]; s_dv = a.v_scale[gb]; s_al = a.v_base[gb]; }
-        if (BM == 3) own_m &= 0x3FFFFFFFu;
-        if (BV == 3) own_v &= 0x3FFFFFFFu;
-        if (w_m <= wm_hi) img_m[w_m] = own_m;
-        if (w_v <= wv_hi) img_v[w_v] = own_v;
-        if (lane < (uint32_t)(kIter / B)) { sc[b] = s_dm; sc[NBT + b] = s_dv; sc[2 * NBT + b] = s_al; }
-        // (a 3-bit run that ends with its word reads the word behind it without using it)
-        if (lane == 0) { img_m[wm_hi + 1] = 0; img_v[wv_hi + 1] = 0; }
-    } else {
-        load_state_image<BM, BV, MW, VW, NBT>(a, tile, lane, img_m, img_v, sc);
+    // elements of this lane's block that exist (B except in the last block)
+    const uint64_t gb = chunk * NG + grp;
+    uint32_t nb = B;
+    bool blk_ok = true;
+    bool ok[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) ok[j] = !TAIL || (e0 + j) < a.n;
+    if (TAIL) {
+        blk_ok = gb < (a.n + B - 1) / B;
+        const uint64_t bstart = gb * B;
+        nb = blk_ok ? (uint32_t)((a.n - bstart) < (uint64_t)B ? (a.n - bstart) : (uint64_t)B) : 0u;
     }
-    if (!alone && lane < 4) { img_m[MW + lane] = 0; img_v[VW + lane] = 0; }
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
 
-    const uint32_t lig = lane & (G - 1);               // lane in group
-    const uint32_t grp = lane / G;                     // group (block) inside the iteration
-    const uint32_t gshift = lane & 31u & ~(uint32_t)(G - 1);   // group's first lane inside its 32-lane half
-    float *const my_tv = reinterpret_cast<float *>(slab + kOffTv) + grp * VT;
-    float *const my_tm = reinterpret_cast<float *>(slab + kOffTm) + grp * MTS;
-    const uint32_t tv_addr = lds_addr(my_tv), tm_addr = lds_addr(my_tm);   // aligned to the table size
+    // ---- every load is issued before the first one is waited for
+    ChunkWords8<BM, BV, TAIL> words;
+    words.load(a, ew0, lane);
+    float dm_old = 0.0f, dv_old = 0.0f, al_old = 1.0f;
+    if (blk_ok) { dm_old = a.m_scale[gb]; dv_old = a.v_scale[gb]; al_old = a.v_base[gb]; }
+    const RawPG raw = load_pg<BF16, TAIL>(a, ew0, lane);
+    const float gscale = (EXT && a.grad_scale) ? *a.grad_scale : 1.0f;      // uniform: the gradient is transformed first
+    words.stage(img_m, img_v, lane);
 
-    // DE codebook: the levels of the table entries this lane fills (entries lig, lig + G)
-    float de_level[(16 + G - 1) / G];
+    // ---- level tables of this lane's block: entries lig, lig + G, ...
+    float de_level[(16 + G - 1) / G];                  // DE codebook: the levels of the entries this lane fills
     uint32_t de_base = 0;                              // bucket table address, less the first bucket's index
     if (MDE) {
 #pragma unroll
         for (int r = 0; r < (MT + G - 1) / G; ++r) de_level[r] = DeLevels<BM>::level(lig + r * G);
         if (kDeTable) de_base = lds_addr(lds_de) - 16u * DeBuckets<BM>::kLo;
     }
+    fill_level_tables<BM, BV, MDE, G>(my_tv, my_tm, lig, dm_old, dv_old, al_old, de_level);
+    wave_lds_sync();
+    uint32_t mc8, vc8;
+    words.codes(img_m, img_v, mc8, vc8);
 
+    // ---- dequantize (table look-up), EMA, parameter
+    float p[8], g[8];
+    lane_layout8<BF16, TAIL>(raw, st_c, st_l, p, g);
+    if (EXT) {                                 // g <- fl(g * scale), then one fused g + l2 * p (l2 = 0: exact)
+#pragma unroll
+        for (int j = 0; j < 8; ++j) g[j] = __builtin_fmaf(a.l2, p[j], g[j] * gscale);
+    }
+    float mh[8], vh[8];
+    float m_absmax, v_max;                     // (v_max of full chunks: the last sorted key below)
+    ema_param<8, BM, BV, EXT, TAIL, TAIL>(a, tm_addr, tv_addr, &mc8, &vc8, ok, p, g, mh, vh, m_absmax, v_max);
+    store_params8<EXT, TAIL>(a, ew0, e0, lane, ok, p, st_c, st_l);
+
+    // ---- the lane's v^ sorted (non-negative floats order like their bit patterns); block maxima
+    uint32_t key[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) key[j] = (TAIL && !ok[j]) ? kInfBits : f2u(vh[j]);
+    sort8(key);
+    float dm = u2f(group_reduce<G>(f2u(m_absmax), UMax()));
+    float dv = u2f(group_reduce<G>(TAIL ? f2u(v_max) : key[7], UMax()));
+    if (dm < kTiny) dm = 0.0f;
+    if (dv < kTiny) dv = 0.0f;
+
+    // ---- the r-th smallest v^ of the block
+    uint32_t xp_bits;
+    if (!TAIL) {
+        xp_bits = extract_rth8<G>(key, a.rank_full);
+    } else {
+        // (a shorter last block has a smaller rank; absent elements are +inf behind the others)
+        const float x = __builtin_ceilf(a.quantile_p * (float)nb);
+        uint32_t r_mine = x < 1.0f ? 1u : (uint32_t)x;
+        r_mine = r_mine > nb ? nb : r_mine;
+        xp_bits = 0;
 #pragma unroll 1
-    for (int it = it_begin; it < it_end; ++it) {
-        const uint32_t e_loc = (uint32_t)it * kIter + lane * 8u;   // element inside the tile
-        const uint64_t e0 = tile_e0 + e_loc;
-        const uint32_t bl = (uint32_t)it * NG + grp;               // block inside the tile
-        // word and slot of this lane's first code (recomputed in every iteration: cheaper in
-        // registers than carrying them; e / 10 by multiplication, exact far beyond the tile size)
-        static_assert(kTile <= 20480, "range of the division by 10");
-        const uint32_t wm = (CM == 10) ? __umul24(e_loc, 52429u) >> 19 : e_loc / CM, sm = e_loc - wm * CM;
-        const uint32_t wv = (CV == 10) ? __umul24(e_loc, 52429u) >> 19 : e_loc / CV, sv = e_loc - wv * CV;
-        // elements of this lane's block that exist (B except in the last block)
-        uint32_t nb = B;
-        bool blk_ok = true;
-        bool ok[8];
-#pragma unroll
-        for (int j = 0; j < 8; ++j) ok[j] = !TAIL || (e0 + j) < a.n;
-        if (TAIL) {
-            const uint64_t blk = tile * NBT + bl;
-            blk_ok = blk < nblk;
-            const uint64_t bstart = blk * B;
-            nb = blk_ok ? (uint32_t)((a.n - bstart) < (uint64_t)B ? (a.n - bstart) : (uint64_t)B) : 0u;
+        for (uint32_t k = 1; k <= a.rank_full; ++k) {
+            const uint32_t mn = extract_round8<G, 8>(key);
+            xp_bits = k == r_mine ? mn : xp_bits;
         }
-
-        // ---- old state of the block and of this lane's elements (LDS)
-        const float dm_old = sc[bl], dv_old = sc[NBT + bl], al_old = sc[2 * NBT + bl];
-        const uint32_t mw0 = img_m[wm], mw1 = (BM == 3) ? img_m[wm + 1] : 0u;
-        const uint32_t vw0 = img_v[wv], vw1 = (BV == 3) ? img_v[wv + 1] : 0u;
-        const uint32_t mc8 = extract8<BM>(mw0, mw1, sm) & (uint32_t)((1ull << (8 * BM)) - 1ull);
-        const uint32_t vc8 = extract8<BV>(vw0, vw1, sv) & (uint32_t)((1ull << (8 * BV)) - 1ull);
-
-        // ---- level tables of this lane's block: entries lig, lig + G, ...
-        {
-            fill_level_tables<BM, BV, MDE, G>(my_tv, my_tm, lig, dm_old, dv_old, al_old, de_level);
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-            __builtin_amdgcn_wave_barrier();
-        }
-
-        // ---- dequantize (table look-up), EMA, parameter
-        float p[8], g[8];
-        lane_layout8<BF16, TAIL>(raw, st_c, st_l, p, g);
-        if (EXT) {                             // g <- fl(g * scale), then one fused g + l2 * p (l2 = 0: exact)
-#pragma unroll
-            for (int j = 0; j < 8; ++j) g[j] = __builtin_fmaf(a.l2, p[j], g[j] * gscale);
-        }
-        // next iteration's parameters and gradients, a whole iteration ahead of their use
-        if (it + 1 < it_end) raw = load_pg<BF16, TAIL>(a, tile_e0 + (uint32_t)(it + 1) * kIter, lane);
-        float mh[8], vh[8];
-        float m_absmax, v_max;                 // (v_max of full tiles: the last sorted key below)
-        ema_param<8, BM, BV, EXT, TAIL, TAIL>(a, tm_addr, tv_addr, &mc8, &vc8, ok, p, g, mh, vh, m_absmax, v_max);
-        store_params8<EXT, TAIL>(a, tile_e0 + (uint32_t)it * kIter, e0, lane, ok, p, st_c, st_l);
-
-        // ---- the lane's v^ sorted (non-negative floats order like their bit patterns); block maxima
-        uint32_t key[8];
-#pragma unroll
-        for (int j = 0; j < 8; ++j) key[j] = (TAIL && !ok[j]) ? kInfBits : f2u(vh[j]);
-        sort8(key);
-        float dm = u2f(group_reduce<G>(f2u(m_absmax), UMax()));
-        float dv = u2f(group_reduce<G>(TAIL ? f2u(v_max) : key[7], UMax()));
-        if (dm < kTiny) dm = 0.0f;
-        if (dv < kTiny) dv = 0.0f;
-
-        // ---- the r-th smallest v^ of the block
-        uint32_t xp_bits;
-        if (!TAIL) {
-            xp_bits = extract_rth8<G>(key, a.rank_full);
-        } else {
-            // (a shorter last block has a smaller rank; absent elements are +inf behind the others)
-            const float x = __builtin_ceilf(a.quantile_p * (float)nb);
-            uint32_t r_mine = x < 1.0f ? 1u : (uint32_t)x;
-            r_mine = r_mine > nb ? nb : r_mine;
-            xp_bits = 0;
-#pragma unroll 1
-            for (uint32_t k = 1; k <= a.rank_full; ++k) {
-                const uint32_t mn = extract_round8<G, 8>(key);
-                xp_bits = k == r_mine ? mn : xp_bits;
-            }
-        }
-
-        // ---- the block's encoder constants, then this lane's 8 codes of each moment
-        const BlockCodec codec = block_codec<BV, G, L, MDE>(xp_bits, dm, dv, lane, lig, gshift);
-        const float alpha = codec.alpha;
-        uint32_t m8, v8;
-        encode_run<BM, BV, MDE, TAIL>(a, e0, mh, vh, ok, codec, de_base, m8, v8);
-
-        xor_into_image8<BM, BV>(img_m, img_v, wm, sm, wv, sv, mc8 ^ m8, vc8 ^ v8);
-        if (alone) {
-            if (lig == 0 && blk_ok) {
-                const uint64_t gb = tile * NBT + bl;
-                a.m_scale[gb] = dm; a.v_scale[gb] = dv; a.v_base[gb] = alpha;
-            }
-        } else {
-            if (lig == 0) { sc[bl] = dm; sc[NBT + bl] = dv; sc[2 * NBT + bl] = alpha; }
-        }
-        (void)blk_ok;
     }
 
-    // ---- write the super-tile's state back (coalesced)
+    // ---- the block's encoder constants, then this lane's 8 codes of each moment
+    const BlockCodec codec = block_codec<BV, G, L, MDE>(xp_bits, dm, dv, lane, lig, gshift);
+    uint32_t m8, v8;
+    encode_run<BM, BV, MDE, TAIL>(a, e0, mh, vh, ok, codec, de_base, m8, v8);
+    xor_into_image8<BM, BV>(img_m, img_v, words.wm, words.sm, words.wv, words.sv, mc8 ^ m8, vc8 ^ v8);
+    if (lig == 0 && blk_ok) { a.m_scale[gb] = dm; a.v_scale[gb] = dv; a.v_base[gb] = codec.alpha; }
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     __builtin_amdgcn_wave_barrier();
-    if (alone) {
-        // every lane writes back the word it staged
-        const uint32_t w_m = wm_lo + lane, w_v = wv_lo + lane;
-        const uint64_t gw_m = tile * MW + w_m, gw_v = tile * VW + w_v;
-        if (w_m <= wm_hi && (!TAIL || gw_m < m_total)) write_back_word<BM>(&a.m_words[gw_m], img_m[w_m], own_m);
-        if (w_v <= wv_hi && (!TAIL || gw_v < v_total)) write_back_word<BV>(&a.v_words[gw_v], img_v[w_v], own_v);
-    } else {
-        store_state_image<MW, VW, NBT>(a, tile, lane, img_m, img_v, sc);
-    }
+    words.write_back(a, img_m, img_v, lane);
 }
 
 // Sixteen keys: two eight-sorts and Batcher's odd-even merge of the halves (25 exchanges).
@@ -1322,7 +1133,24 @@ __device__ __forceinline__ void sort16(uint32_t (&k)[16])
     for (int i = 1; i < 15; i += 2) cswap(k[i], k[i + 1]);
 }
 
-// Parameters and gradients of one lane and one 1024-element iteration of the wide path, in the
+// The largest (dv, values below kTiny as 0) and the rank-th smallest (returned) v^ of every group of G
+// lanes that hold 16 of them each.  `col`: the lane's column in LDS.
+template <int G>
+__device__ __forceinline__ uint32_t quantile16(const float (&vh)[16], uint32_t *const col, const uint32_t rank, float &dv)
+{
+    uint32_t key[16];                              // (non-negative floats order like their bit patterns)
+#pragma unroll
+    for (int j = 0; j < 16; ++j) key[j] = f2u(vh[j]);
+    sort16(key);
+    dv = u2f(group_reduce<G>(key[15], UMax()));
+    if (dv < kTiny) dv = 0.0f;
+    col[16] = kInfBits;
+#pragma unroll
+    for (int c = 0; c < 8; ++c) *reinterpret_cast<uint2 *>(col + 2 * c) = make_uint2(key[2 * c], key[2 * c + 1]);
+    return extract_rth<G>(key[0], key[1], lds_addr(col), rank);
+}
+
+// Parameters and gradients of one lane and one 1024-element chunk, in the
 // coalesced layout they are loaded in (vector k of a lane is vector lane + 64 k of the chunk).
 template <bool BF16>
 struct RawPG16 { float4 p[4]; uint4 g[BF16 ? 2 : 4]; };
@@ -1470,90 +1298,60 @@ __device__ __forceinline__ void encode_into_image16(const StepArgs &a, const uin
     }
 }
 
-// The wide path: the same step as step_tile() for a full super-tile, with 16 consecutive
-// elements per lane and 1024 per iteration.  A block is held by 8 lanes (4 for B = 64), so the
-// work that is done once per lane and block (level tables, the division, the base, the hash,
-// packing) is spread over twice as many elements, a group reduction is three DPP steps instead
-// of four, and a block still needs only r extraction rounds.  The price is registers (four
-// wavefronts per SIMD instead of five) and a 16-key sort per lane.
-template <int BM, int BV, int B, bool BF16, bool MDE, bool EXT, int TILE>
-__device__ __forceinline__ void step_tile16(const StepArgs &a, const uint64_t tile, const uint32_t lane,
-                                            uint32_t *const slab, const uint32_t *const lds_de)
-{
-    constexpr int E = 16;
-    constexpr int G = B / E;                       // lanes per block (8; 4 for 64-element blocks)
-    constexpr int NG = 64 / G;                     // blocks per iteration (8; 16)
-    constexpr int kTile = TILE;
-    constexpr int kIters = kTile / kIter16;
-    static_assert(kTile % kIter16 == 0, "whole iterations");
-    using Lay = SlabLayout<BM, BV, B, MDE, kTile, E>;
-    constexpr int NBT = kTile / B;
-    constexpr int L = (1 << (BM - 1)) - 1;
-    constexpr int K = (1 << BV) - 1;
-    constexpr int CM = 32 / BM, CV = 32 / BV;
-    constexpr int MW = kTile / CM, VW = kTile / CV;
-    constexpr int VT = K + 1;
-    constexpr int MT = MDE ? 2 * L + 2 : 2 * L + 1;
-    constexpr int MTS = Lay::MTS;
-    constexpr int kOffCol = Lay::kOffCol, kOffImgM = Lay::kOffImgM, kOffImgV = Lay::kOffImgV;
-    constexpr int kOffTv = Lay::kOffTv, kOffTm = Lay::kOffTm, kOffSc = Lay::kOffSc, kSlab = Lay::kSlab;
-    constexpr bool kDeTable = Lay::kDeTable;
-    // A runaway column address (possible only with non-finite input) stays inside the slab.
-    static_assert(kSlab >= 64 * kColStride16 + 140, "column slack");
+// The code words of the 1024 elements that a wavefront steps on its own (16 consecutive elements
+// per lane): staged in LDS, one or two words of each stream per lane, and written back by the lane
+// that staged them.  The first word may begin in the share before (ten-to-a-word codes).
+template <int BM, int BV>
+struct ChunkWords16 {
+    static constexpr int CM = 32 / BM, CV = 32 / BV;                 // codes per word
+    static constexpr int KM = CM == 16 ? 1 : 2, KV = CV == 16 ? 1 : 2;   // words of a stream per lane (64 x K >= words of 1024 elements)
+    static constexpr int kImage = 132;                               // words of a stream's image (<= 128, + 4)
+    uint64_t gm_lo, gv_lo;                     // first word of each stream
+    uint32_t nwm, nwv;                         // words touched (<= 128)
+    uint32_t own_m[KM], own_v[KV];             // the staged words as they were loaded
+    uint32_t wm[2], sm[2], wv[2], sv[2];       // word (of the image) and slot of the first code of the lane's two runs of 8
 
-    const uint64_t tile_e0 = tile * kTile;
-    uint32_t *const img_m = slab + kOffImgM, *const img_v = slab + kOffImgV;
-    float *const sc = reinterpret_cast<float *>(slab + kOffSc);
-    uint32_t *const col = slab + kOffCol + lane * kColStride16;
-
-    RawPG16<BF16> raw = load_pg16<BF16>(a, tile_e0, lane);
-    const float gscale = (EXT && a.grad_scale) ? *a.grad_scale : 1.0f;
-    static_assert(288 * 4 <= 64 * kColStride16, "staging must fit the column area");
-    const Stage16 st(reinterpret_cast<float4 *>(slab + kOffCol), lane);
-
-    // ---- stage the super-tile's state in LDS
-    static_assert(kOffImgM % 4 == 0 && kOffImgV % 4 == 0, "128-bit staging");
-    load_state_image<BM, BV, MW, VW, NBT>(a, tile, lane, img_m, img_v, sc);
-    if (lane < 4) { img_m[MW + lane] = 0; img_v[VW + lane] = 0; }
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-
-    const uint32_t lig = lane & (G - 1);
-    const uint32_t grp = lane / G;
-    const uint32_t gshift = lane & 31u & ~(uint32_t)(G - 1);
-    float *const my_tv = reinterpret_cast<float *>(slab + kOffTv) + grp * VT;
-    float *const my_tm = reinterpret_cast<float *>(slab + kOffTm) + grp * MTS;
-    const uint32_t tv_addr = lds_addr(my_tv), tm_addr = lds_addr(my_tm);
-    const uint32_t col_addr = lds_addr(col);
-
-    float de_level[(16 + G - 1) / G];
-    uint32_t de_base = 0;
-    if (MDE) {
+    // ew0: first element of the wavefront's share.  Issues the loads.
+    __device__ __forceinline__ void load(const StepArgs &a, const uint64_t ew0, const uint32_t lane)
+    {
+        gm_lo = ew0 / CM; gv_lo = ew0 / CV;
+        const uint32_t rm0 = (uint32_t)(ew0 - gm_lo * CM), rv0 = (uint32_t)(ew0 - gv_lo * CV);   // slot of the first element
+        nwm = (rm0 + kIter16 + CM - 1) / CM; nwv = (rv0 + kIter16 + CV - 1) / CV;
 #pragma unroll
-        for (int r = 0; r < (MT + G - 1) / G; ++r) de_level[r] = DeLevels<BM>::level(lig + r * G);
-        if (kDeTable) de_base = lds_addr(lds_de) - 16u * DeBuckets<BM>::kLo;
-    }
-
-#pragma unroll 1
-    for (int it = 0; it < kIters; ++it) {
-        const uint32_t e_loc = (uint32_t)it * kIter16 + lane * 16u;
-        const uint64_t e0 = tile_e0 + e_loc;
-        const uint32_t bl = (uint32_t)it * NG + grp;
-        // word and slot of the first code of the lane's two runs of 8 (recomputed in every
-        // iteration: cheaper in registers than carrying them; e / 10 by multiplication, exact far
-        // beyond the tile size)
-        static_assert(kTile <= 20480, "range of the division by 10");
-        uint32_t wm[2], sm[2], wv[2], sv[2];
+        for (int k = 0; k < KM; ++k) {
+            own_m[k] = 0;
+            if (lane + 64u * k < nwm) own_m[k] = a.m_words[gm_lo + lane + 64u * k];
+        }
+#pragma unroll
+        for (int k = 0; k < KV; ++k) {
+            own_v[k] = 0;
+            if (lane + 64u * k < nwv) own_v[k] = a.v_words[gv_lo + lane + 64u * k];
+        }
 #pragma unroll
         for (int r = 0; r < 2; ++r) {
-            const uint32_t e = e_loc + 8u * r;
-            wm[r] = (CM == 10) ? __umul24(e, 52429u) >> 19 : e / CM; sm[r] = e - wm[r] * CM;
-            wv[r] = (CV == 10) ? __umul24(e, 52429u) >> 19 : e / CV; sv[r] = e - wv[r] * CV;
+            const uint32_t qm = rm0 + lane * 16u + 8u * r, qv = rv0 + lane * 16u + 8u * r;   // < 1040: e / 10 by multiplication
+            wm[r] = (CM == 10) ? __umul24(qm, 52429u) >> 19 : qm / CM; sm[r] = qm - wm[r] * CM;
+            wv[r] = (CV == 10) ? __umul24(qv, 52429u) >> 19 : qv / CV; sv[r] = qv - wv[r] * CV;
         }
-
-        // ---- old state of the block and of this lane's elements (LDS)
-        const float dm_old = sc[bl], dv_old = sc[NBT + bl], al_old = sc[2 * NBT + bl];
-        uint32_t mc8[2], vc8[2];
+    }
+    __device__ __forceinline__ void stage(uint32_t *const img_m, uint32_t *const img_v, const uint32_t lane)
+    {
+#pragma unroll
+        for (int k = 0; k < KM; ++k) {
+            if (BM == 3) own_m[k] &= 0x3FFFFFFFu;
+            img_m[lane + 64u * k] = own_m[k];
+        }
+#pragma unroll
+        for (int k = 0; k < KV; ++k) {
+            if (BV == 3) own_v[k] &= 0x3FFFFFFFu;
+            img_v[lane + 64u * k] = own_v[k];
+        }
+        if (lane < 4) { img_m[64 * KM + lane] = 0; img_v[64 * KV + lane] = 0; }
+    }
+    // the lane's old codes, eight to a run, out of the staged words
+    __device__ __forceinline__ void codes(const uint32_t *const img_m, const uint32_t *const img_v,
+                                          uint32_t (&mc8)[2], uint32_t (&vc8)[2]) const
+    {
 #pragma unroll
         for (int r = 0; r < 2; ++r) {
             // (2-bit codes: both runs of the lane lie in one word)
@@ -1562,59 +1360,103 @@ __device__ __forceinline__ void step_tile16(const StepArgs &a, const uint64_t ti
             mc8[r] = extract8<BM>(mw0, mw1, BM == 2 ? 8u * r : sm[r]) & (uint32_t)((1ull << (8 * BM)) - 1ull);
             vc8[r] = extract8<BV>(vw0, vw1, BV == 2 ? 8u * r : sv[r]) & (uint32_t)((1ull << (8 * BV)) - 1ull);
         }
-
-        // ---- level tables of this lane's block: entries lig, lig + G
-        fill_level_tables<BM, BV, MDE, G>(my_tv, my_tm, lig, dm_old, dv_old, al_old, de_level);
-
-        // ---- coalesced layout -> 16 consecutive elements per lane
-        float p[16], g[16];
-        lane_layout16<BF16>(raw, st, p, g);
-        if (EXT) {
-#pragma unroll
-            for (int j = 0; j < 16; ++j) g[j] = __builtin_fmaf(a.l2, p[j], g[j] * gscale);
-        }
-        // next iteration's parameters and gradients, a whole iteration ahead of their use
-        if (it + 1 < kIters) raw = load_pg16<BF16>(a, tile_e0 + (uint32_t)(it + 1) * kIter16, lane);
-
-        // ---- dequantize (table look-up), EMA, parameter; new parameters streamed out
-        float mh[16], vh[16];
-        float m_absmax, v_unused;               // (the largest v^ is the lane's last sorted key below)
-        ema_param<16, BM, BV, EXT, false, false>(a, tm_addr, tv_addr, mc8, vc8, nullptr, p, g, mh, vh, m_absmax, v_unused);
-        store_params16<EXT>(a, tile_e0 + (uint32_t)it * kIter16, lane, p, st);
-        wave_lds_sync();                        // the staging area becomes the column area
-
-        // ---- the lane's v^ sorted (non-negative floats order like their bit patterns), the block
-        // maxima (the lane's largest v^ is its last key), the r-th smallest v^ of the block
-        float dm = u2f(group_reduce<G>(f2u(m_absmax), UMax()));
-        if (dm < kTiny) dm = 0.0f;
-        float dv;
-        uint32_t xp_bits = 0;
-        {
-            uint32_t key[16];
-#pragma unroll
-            for (int j = 0; j < 16; ++j) key[j] = f2u(vh[j]);
-            sort16(key);
-            dv = u2f(group_reduce<G>(key[15], UMax()));
-            if (dv < kTiny) dv = 0.0f;
-            col[16] = kInfBits;
-#pragma unroll
-            for (int c = 0; c < 8; ++c) *reinterpret_cast<uint2 *>(col + 2 * c) = make_uint2(key[2 * c], key[2 * c + 1]);
-            xp_bits = extract_rth<G>(key[0], key[1], col_addr, a.rank_full);
-        }
-
-        // ---- the block's encoder constants
-        const BlockCodec codec = block_codec<BV, G, L, MDE>(xp_bits, dm, dv, lane, lig, gshift);
-        const float alpha = codec.alpha;
-
-        // ---- encode and update the state image, one run of 8 elements at a time
-        encode_into_image16<BM, BV, MDE>(a, e0, mh, vh, codec, de_base, img_m, img_v, wm, sm, wv, sv, mc8, vc8);
-        if (lig == 0) { sc[bl] = dm; sc[NBT + bl] = dv; sc[2 * NBT + bl] = alpha; }
     }
+    __device__ __forceinline__ void write_back(const StepArgs &a, const uint32_t *const img_m, const uint32_t *const img_v,
+                                               const uint32_t lane) const
+    {
+#pragma unroll
+        for (int k = 0; k < KM; ++k)
+            if (lane + 64u * k < nwm) write_back_word<BM>(&a.m_words[gm_lo + lane + 64u * k], img_m[lane + 64u * k], own_m[k]);
+#pragma unroll
+        for (int k = 0; k < KV; ++k)
+            if (lane + 64u * k < nwv) write_back_word<BV>(&a.v_words[gv_lo + lane + 64u * k], img_v[lane + 64u * k], own_v[k]);
+    }
+};
 
-    // ---- write the super-tile's state back (coalesced)
+// LDS of a wavefront that steps one 1024-element chunk on its own (32-bit words).
+template <int BM, int BV, int B>
+struct ChunkLayout16 {
+    static constexpr int NG = kIter16 / B;
+    static constexpr int VT = 1 << BV;
+    static constexpr int MTS = m_table_stride<BM>();
+    static constexpr int kOffCol = 0;                          // staging of the transpositions, then the sorted columns
+    static constexpr int kOffImgM = 64 * kColStride16;
+    static constexpr int kOffImgV = kOffImgM + ChunkWords16<BM, BV>::kImage;
+    static constexpr int kOffTv = ((kOffImgV + ChunkWords16<BM, BV>::kImage + 15) / 16) * 16;      // 64-byte aligned
+    static constexpr int kOffTm = kOffTv + ((NG * VT + 15) / 16) * 16;
+    static constexpr int kSlab = kOffTm + ((NG * MTS + 15) / 16) * 16;
+};
+
+// The whole step for the 1024 elements from 1024 * chunk on (whole blocks, all of them present),
+// by the calling wavefront on its own, 16 consecutive elements per lane.
+template <int BM, int BV, int B, bool BF16, bool MDE, bool EXT>
+__device__ __forceinline__ void step_chunk16(const StepArgs &a, const uint64_t chunk, const uint32_t lane,
+                                             uint32_t *const slab, const uint32_t *const lds_de)
+{
+    constexpr int G = B / 16;                      // lanes per block
+    constexpr int NG = 64 / G;                     // blocks of the chunk
+    constexpr int L = (1 << (BM - 1)) - 1;
+    constexpr int VT = 1 << BV;
+    constexpr int MT = MDE ? 2 * L + 2 : 2 * L + 1;
+    using Lay = ChunkLayout16<BM, BV, B>;
+    constexpr bool kDeTable = MDE && BM >= 3;
+    // A runaway column address (possible only with non-finite input) stays inside the slab.
+    static_assert(Lay::kSlab >= 64 * kColStride16 + 140, "column slack");
+
+    const uint64_t ew0 = chunk * kIter16, e0 = ew0 + lane * 16u;
+    const uint32_t lig = lane & (G - 1), grp = lane / G, gshift = lane & 31u & ~(uint32_t)(G - 1);
+    uint32_t *const img_m = slab + Lay::kOffImgM, *const img_v = slab + Lay::kOffImgV;
+    uint32_t *const col = slab + Lay::kOffCol + lane * kColStride16;
+    float *const my_tv = reinterpret_cast<float *>(slab + Lay::kOffTv) + grp * VT;
+    float *const my_tm = reinterpret_cast<float *>(slab + Lay::kOffTm) + grp * Lay::MTS;
+    const uint32_t tv_addr = lds_addr(my_tv), tm_addr = lds_addr(my_tm);
+
+    // ---- every load is issued before the first one is waited for
+    ChunkWords16<BM, BV> words;
+    words.load(a, ew0, lane);
+    const uint64_t gb = chunk * NG + grp;
+    const float dm_old = a.m_scale[gb], dv_old = a.v_scale[gb], al_old = a.v_base[gb];
+    const RawPG16<BF16> raw = load_pg16<BF16>(a, ew0, lane);
+    const float gscale = (EXT && a.grad_scale) ? *a.grad_scale : 1.0f;
+    const Stage16 st(reinterpret_cast<float4 *>(slab + Lay::kOffCol), lane);
+
+    words.stage(img_m, img_v, lane);
+    float de_level[(16 + G - 1) / G];
+    uint32_t de_base = 0;
+    if (MDE) {
+#pragma unroll
+        for (int r = 0; r < (MT + G - 1) / G; ++r) de_level[r] = DeLevels<BM>::level(lig + r * G);
+        if (kDeTable) de_base = lds_addr(lds_de) - 16u * DeBuckets<BM>::kLo;
+    }
+    fill_level_tables<BM, BV, MDE, G>(my_tv, my_tm, lig, dm_old, dv_old, al_old, de_level);
+    wave_lds_sync();
+    uint32_t mc8[2], vc8[2];
+    words.codes(img_m, img_v, mc8, vc8);
+
+    float p[16], g[16];
+    lane_layout16<BF16>(raw, st, p, g);
+    if (EXT) {
+#pragma unroll
+        for (int j = 0; j < 16; ++j) g[j] = __builtin_fmaf(a.l2, p[j], g[j] * gscale);
+    }
+    float mh[16], vh[16];
+    float m_absmax, v_unused;                   // (the largest v^ is the lane's last sorted key below)
+    ema_param<16, BM, BV, EXT, false, false>(a, tm_addr, tv_addr, mc8, vc8, nullptr, p, g, mh, vh, m_absmax, v_unused);
+    store_params16<EXT>(a, ew0, lane, p, st);
+    wave_lds_sync();                            // the staging area becomes the column area
+
+    float dm = u2f(group_reduce<G>(f2u(m_absmax), UMax()));
+    if (dm < kTiny) dm = 0.0f;
+    float dv;
+    const uint32_t xp_bits = quantile16<G>(vh, col, a.rank_full, dv);
+
+    const BlockCodec codec = block_codec<BV, G, L, MDE>(xp_bits, dm, dv, lane, lig, gshift);
+    encode_into_image16<BM, BV, MDE>(a, e0, mh, vh, codec, de_base, img_m, img_v,
+                                     words.wm, words.sm, words.wv, words.sv, mc8, vc8);
+    if (lig == 0) { a.m_scale[gb] = dm; a.v_scale[gb] = dv; a.v_base[gb] = codec.alpha; }
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     __builtin_amdgcn_wave_barrier();
-    store_state_image<MW, VW, NBT>(a, tile, lane, img_m, img_v, sc);
+    words.write_back(a, img_m, img_v, lane);
 }
 
 // The DE bucket table of a workgroup: copied from constant memory once, before any wavefront
@@ -1629,125 +1471,153 @@ __device__ __forceinline__ void load_de_table(uint32_t *lds_de)
     }
 }
 
-// The step over one flat buffer.  Full super-tiles: one workgroup per kWaves of them.  TAIL: the
-// ragged end, cut into 2560-element units and these into their 512-element iterations, one
-// wavefront each (a short tensor is a latency problem: five iterations in sequence would take
-// five times as long).
-template <int BM, int BV, int B, bool BF16, bool MDE, bool TAIL, bool EXT>
-__global__ __launch_bounds__(kWaves * 64, (!TAIL && wide_path<BM, BV, B, MDE>()) ? kWideWaves : SOLO_MIN_WAVES)
-void step_kernel(const StepArgs a)
+// The step over one flat buffer, 8 elements per lane: one wavefront per 512 elements, the last
+// ones (a.rest: up to the end of the last code word) with bounds checks where the buffer ends.
+template <int BM, int BV, int B, bool BF16, bool MDE, bool EXT>
+__global__ __launch_bounds__(kWaves * 64, kMinWaves)
+void chunk8_kernel(const StepArgs a)
 {
-    constexpr int kTile = TAIL ? kTileUnit : tile_elems<BM, BV, B, MDE>();
-    constexpr bool kWide = !TAIL && wide_path<BM, BV, B, MDE>();
-    using Lay = SlabLayout<BM, BV, B, MDE, kTile, kWide ? 16 : 8>;
+    using Lay = ChunkLayout8<BM, BV, B>;
     __shared__ __attribute__((aligned(64))) uint32_t lds_slab[kWaves * Lay::kSlab];
-    __shared__ __attribute__((aligned(64))) uint32_t lds_de[Lay::kDeWords];
-    load_de_table<BM, MDE, Lay::kDeWords>(lds_de);
-
+    __shared__ __attribute__((aligned(64))) uint32_t lds_de[de_words<BM, MDE>()];
+    load_de_table<BM, MDE, de_words<BM, MDE>()>(lds_de);
     const uint32_t lane = threadIdx.x & 63u;
-    // the wavefront index is uniform: keeping it (and every address derived from the tile) in
+    // the wavefront index is uniform: keeping it (and every address derived from the chunk) in
     // scalar registers frees vector registers
     const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    // Workgroup ids are dealt round-robin to the 8 XCDs; workgroup (x + 8 i) takes the i-th
-    // group of super-tiles of XCD x's contiguous eighth of the buffer, so the wavefronts that
-    // run at the same time on one XCD stream through one narrow address window.
-    const uint64_t wg = (uint64_t)(blockIdx.x & (kXcds - 1)) * a.wg_per_xcd + (blockIdx.x / kXcds);
-    if (TAIL) {
-        // one wavefront per 512-element iteration of the 2560-element units from tail_tile0 on:
-        // the ragged end of a large buffer, or the whole of a short or mid-size one.  A unit that
-        // lies inside the buffer runs the code without bounds checks.
-        constexpr int kChunks = kTileUnit / kIter;
-        const uint64_t c = (uint64_t)blockIdx.x * kWaves + wave;
-        if (c >= a.tail_chunks) return;
-        const uint64_t unit = a.tail_tile0 + c / kChunks;
-        if ((unit + 1) * kTileUnit <= a.n)
-            step_tile<BM, BV, B, BF16, MDE, false, EXT, kTileUnit, true>(a, unit, lane, lds_slab + wave * Lay::kSlab,
-                                                                         lds_de, (int)(c % kChunks));
-        else
-            step_tile<BM, BV, B, BF16, MDE, true, EXT, kTileUnit>(a, unit, lane, lds_slab + wave * Lay::kSlab,
-                                                                  lds_de, (int)(c % kChunks));
-        return;
-    }
-    const uint64_t tile = wg * kWaves + wave;
-    if (tile >= a.n_tiles_full) return;
-    if constexpr (kWide)
-        step_tile16<BM, BV, B, BF16, MDE, EXT, kTile>(a, tile, lane, lds_slab + wave * Lay::kSlab, lds_de);
-    else if constexpr (!TAIL)
-        step_tile<BM, BV, B, BF16, MDE, false, EXT, kTile>(a, tile, lane, lds_slab + wave * Lay::kSlab, lds_de);
+    const uint64_t c = (uint64_t)blockIdx.x * kWaves + wave;
+    uint32_t *const slab = lds_slab + wave * Lay::kSlab;
+    if ((c + 1) * kIter <= a.n)
+        step_chunk8<BM, BV, B, BF16, MDE, false, EXT>(a, c, lane, slab, lds_de);
+    else if (c < a.rest)
+        step_chunk8<BM, BV, B, BF16, MDE, true, EXT>(a, c, lane, slab, lds_de);
 }
 
-// The step over many tensors in one launch.  Every tensor is cut into units of the format's
-// super-tile size and its ragged end into 512-element iterations; one wavefront takes one entry
-// of the map, finds its tensor in the table (a scalar look-up) and runs the full-tile code on a
-// unit or the bounds-checked code on one iteration of a ragged end.  Blocks never span tensors:
-// each tensor is quantized on its own.
+// The step over one flat buffer, 16 elements per lane: one wavefront per 1024 elements.  The first
+// a.rest wavefronts take what is left behind the last whole chunk (the slower, bounds-checked
+// code, so it starts first), 512 elements each.
 template <int BM, int BV, int B, bool BF16, bool MDE, bool EXT>
-__global__ __launch_bounds__(kWaves * 64, (wide_path<BM, BV, B, MDE>() ? kWideWaves : SOLO_MIN_WAVES))
-void multi_kernel(const MultiArgs ma)
+__global__ __launch_bounds__(kWaves * 64, kMinWaves16)
+void chunk16_kernel(const StepArgs a)
 {
-    constexpr int kUnit = tile_elems<BM, BV, B, MDE>();
-    constexpr bool kWide = wide_path<BM, BV, B, MDE>();
-    using Lay = SlabLayout<BM, BV, B, MDE, kUnit, kWide ? 16 : 8>;        // the wide slab is the larger one
-    static_assert(Lay::kSlab >= SlabLayout<BM, BV, B, MDE, kUnit, 8>::kSlab, "one slab serves both code paths");
+    using Lay = ChunkLayout16<BM, BV, B>;
+    static_assert(Lay::kSlab >= ChunkLayout8<BM, BV, B>::kSlab, "one slab serves both forms");
     __shared__ __attribute__((aligned(64))) uint32_t lds_slab[kWaves * Lay::kSlab];
-    __shared__ __attribute__((aligned(64))) uint32_t lds_de[Lay::kDeWords];
-    load_de_table<BM, MDE, Lay::kDeWords>(lds_de);
-
+    __shared__ __attribute__((aligned(64))) uint32_t lds_de[de_words<BM, MDE>()];
+    load_de_table<BM, MDE, de_words<BM, MDE>()>(lds_de);
     const uint32_t lane = threadIdx.x & 63u;
     const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    const uint64_t wg = (uint64_t)(blockIdx.x & (kXcds - 1)) * ma.groups_per_xcd + (blockIdx.x / kXcds);
-    const uint64_t unit = wg * kWaves + wave;
-    if (unit >= ma.total_units) return;
-    const uint32_t me = ma.unit_map[unit];                      // uniform: scalar loads
-    const TensorEntry &e = ma.entries[me & kMapTensorMask];
+    const uint64_t c = (uint64_t)blockIdx.x * kWaves + wave;
+    uint32_t *const slab = lds_slab + wave * Lay::kSlab;
+    if (c >= a.rest) {
+        if (c - a.rest < a.n / kIter16)
+            step_chunk16<BM, BV, B, BF16, MDE, EXT>(a, c - a.rest, lane, slab, lds_de);
+    } else {
+        step_chunk8<BM, BV, B, BF16, MDE, true, EXT>(a, a.n / kIter16 * (kIter16 / kIter) + c, lane, slab, lds_de);
+    }
+}
+
+// ---- many tensors in one launch.  Blocks never span tensors: each tensor is quantized on its own.
+
+// The elements [begin, begin + elems) of its tensor that a map entry stands for.
+template <int UNIT>
+struct UnitRange {
+    const TensorEntry *e;
+    uint64_t begin;
+    uint32_t elems;
+    __device__ __forceinline__ UnitRange(const MultiArgs &ma, uint64_t unit)
+    {
+        const uint32_t me = ma.unit_map[unit];                      // uniform: scalar loads
+        e = &ma.entries[me & kMapTensorMask];
+        const bool ragged = (me & kMapRagged) != 0;
+        begin = ragged ? e->n / UNIT * UNIT + (uint64_t)((me >> kMapChunkShift) & 0x7Fu) * kIter : (unit - e->unit0) * UNIT;
+        elems = ragged ? kIter : UNIT;
+    }
+    // first chunk of `size` elements that begins inside the range, and the first one behind it
+    __device__ __forceinline__ uint64_t first(uint32_t size) const { return (begin + size - 1) / size; }
+    __device__ __forceinline__ uint64_t last(uint32_t size) const { return (begin + elems + size - 1) / size; }
+};
+
+__device__ __forceinline__ StepArgs tensor_args(const MultiArgs &ma, const TensorEntry &e)
+{
     StepArgs a = ma.common;
     a.param = e.param; a.param_bf16 = e.param_bf16; a.grad = e.grad;
     a.m_words = e.m_words; a.m_scale = e.m_scale;
     a.v_words = e.v_words; a.v_scale = e.v_scale; a.v_base = e.v_base;
     a.n = e.n; a.index_offset = e.index_offset;
-    uint32_t *const slab = lds_slab + wave * Lay::kSlab;
-    if (!(me & kMapRagged)) {
-        const uint64_t tile = unit - e.unit0;
-        if constexpr (kWide) step_tile16<BM, BV, B, BF16, MDE, EXT, kUnit>(a, tile, lane, slab, lds_de);
-        else step_tile<BM, BV, B, BF16, MDE, false, EXT, kUnit>(a, tile, lane, slab, lds_de);
-    } else {
-        step_tile<BM, BV, B, BF16, MDE, true, true, kUnit>(a, a.n / kUnit, lane, slab, lds_de,
-                                                           (int)((me >> kMapChunkShift) & 0x7Fu));
-    }
+    return a;
 }
 
-// The multi-tensor step of the formats that always run one wavefront per 512-element iteration:
-// a map entry stands for a 2560-element unit of its tensor (the last one of a tensor may be
-// shorter), five consecutive wavefronts take its five iterations.
-template <int BM, int BV, int B, bool BF16, bool MDE, bool EXT>
-__global__ __launch_bounds__(kWaves * 64, SOLO_MIN_WAVES)
-void multi_chunk_kernel(const MultiArgs ma)
-{
-    constexpr int kChunks = kTileUnit / kIter;
-    using Lay = SlabLayout<BM, BV, B, MDE, kTileUnit, 8>;
-    __shared__ __attribute__((aligned(64))) uint32_t lds_slab[kWaves * Lay::kSlab];
-    __shared__ __attribute__((aligned(64))) uint32_t lds_de[Lay::kDeWords];
-    load_de_table<BM, MDE, Lay::kDeWords>(lds_de);
+template <int BM, int BV, int B, bool BF16, bool MDE>
+constexpr int table_unit() { return multi_chunked(BF16, MDE) ? kTileUnit : unit_elems(BM, BV, B); }
 
+// 8 elements per lane, for tables of few elements: UNIT / 512 wavefronts per map entry.
+template <int BM, int BV, int B, bool BF16, bool MDE>
+__global__ __launch_bounds__(kWaves * 64, kMinWaves)
+void multi_chunk8_kernel(const MultiArgs ma)
+{
+    constexpr int kUnit = table_unit<BM, BV, B, BF16, MDE>();
+    using Lay = ChunkLayout8<BM, BV, B>;
+    __shared__ __attribute__((aligned(64))) uint32_t lds_slab[kWaves * Lay::kSlab];
+    __shared__ __attribute__((aligned(64))) uint32_t lds_de[de_words<BM, MDE>()];
+    load_de_table<BM, MDE, de_words<BM, MDE>()>(lds_de);
     const uint32_t lane = threadIdx.x & 63u;
     const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const uint64_t slot = (uint64_t)blockIdx.x * kWaves + wave;
-    const uint64_t unit = slot / kChunks;
-    const int chunk = (int)(slot % kChunks);
+    const uint64_t unit = slot / (kUnit / kIter);
     if (unit >= ma.total_units) return;
-    const uint32_t me = ma.unit_map[unit];                      // uniform: scalar loads
-    const TensorEntry &e = ma.entries[me & kMapTensorMask];
-    StepArgs a = ma.common;
-    a.param = e.param; a.param_bf16 = e.param_bf16; a.grad = e.grad;
-    a.m_words = e.m_words; a.m_scale = e.m_scale;
-    a.v_words = e.v_words; a.v_scale = e.v_scale; a.v_base = e.v_base;
-    a.n = e.n; a.index_offset = e.index_offset;
+    const UnitRange<kUnit> r(ma, unit);
+    const uint64_t c = r.first(kIter) + slot % (kUnit / kIter);
+    if (c >= r.last(kIter)) return;
+    const StepArgs a = tensor_args(ma, *r.e);
     uint32_t *const slab = lds_slab + wave * Lay::kSlab;
-    const uint64_t tile = unit - e.unit0;
-    if ((tile + 1) * kTileUnit <= a.n)
-        step_tile<BM, BV, B, BF16, MDE, false, EXT, kTileUnit, true>(a, tile, lane, slab, lds_de, chunk);
-    else if (tile * kTileUnit + (uint64_t)chunk * kIter < (a.n + 79) / 80 * 80)   // up to the end of the last code word
-        step_tile<BM, BV, B, BF16, MDE, true, true, kTileUnit>(a, tile, lane, slab, lds_de, chunk);
+    if ((c + 1) * kIter <= a.n)
+        step_chunk8<BM, BV, B, BF16, MDE, false, true>(a, c, lane, slab, lds_de);
+    else if (c * kIter < end_of_words(a.n))
+        step_chunk8<BM, BV, B, BF16, MDE, true, true>(a, c, lane, slab, lds_de);
+}
+
+// 16 elements per lane.  A map entry owns the 1024-element chunks of its tensor that begin inside
+// its range: five wavefronts for an entry of 5120 elements, five for two entries of 2560 (two or
+// three chunks each; where two tensors meet it can be six, and the fifth wavefront takes two).
+// An entry of a ragged end owns one or none.  The chunk that a tensor does not fill, and such a
+// sixth chunk, run in their 512-element iterations, with bounds checks (a loop around the
+// 16-per-lane code spills registers).
+template <int BM, int BV, int B, bool BF16, bool MDE, bool EXT>
+__global__ __launch_bounds__(kWaves * 64, kMinWaves16)
+void multi_chunk16_kernel(const MultiArgs ma)
+{
+    constexpr int kUnit = table_unit<BM, BV, B, BF16, MDE>();
+    using Lay = ChunkLayout16<BM, BV, B>;
+    __shared__ __attribute__((aligned(64))) uint32_t lds_slab[kWaves * Lay::kSlab];
+    __shared__ __attribute__((aligned(64))) uint32_t lds_de[de_words<BM, MDE>()];
+    load_de_table<BM, MDE, de_words<BM, MDE>()>(lds_de);
+    const uint32_t lane = threadIdx.x & 63u;
+    const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const uint64_t slot = (uint64_t)blockIdx.x * kWaves + wave;
+    const uint32_t sub = (uint32_t)(slot % 5);
+    const uint64_t unit0 = slot / 5 * (2 * kTileUnit / kUnit);
+    if (unit0 >= ma.total_units) return;
+    UnitRange<kUnit> r(ma, unit0);
+    uint64_t c = r.first(kIter16) + sub;
+    bool two = false;                              // the fifth wavefront where two entries own six chunks
+    if (c >= r.last(kIter16)) {
+        if (kUnit == 2 * kTileUnit || unit0 + 1 >= ma.total_units) return;
+        const uint32_t here = (uint32_t)(r.last(kIter16) - r.first(kIter16));
+        r = UnitRange<kUnit>(ma, unit0 + 1);
+        c = r.first(kIter16) + (sub - here);
+        if (c >= r.last(kIter16)) return;
+        two = sub == 4 && c + 1 < r.last(kIter16);
+    }
+    const StepArgs a = tensor_args(ma, *r.e);
+    uint32_t *const slab = lds_slab + wave * Lay::kSlab;
+    const bool whole = (c + 1) * kIter16 <= a.n;
+    if (whole) step_chunk16<BM, BV, B, BF16, MDE, EXT>(a, c, lane, slab, lds_de);
+    // the chunk that the tensor does not fill, and the sixth chunk of two entries
+    const uint64_t i0 = 2 * c + (whole ? 2 : 0), i1 = 2 * c + (two ? 4 : 2);
+#pragma unroll 1
+    for (uint64_t i = i0; i < i1 && i * kIter < end_of_words(a.n); ++i)
+        step_chunk8<BM, BV, B, BF16, MDE, true, EXT>(a, i, lane, slab, lds_de);
 }
 
 // Host-side launcher of one instantiation family (fixed bits_m and 1st-moment codebook);
@@ -1760,38 +1630,20 @@ template <int BM, int BV, int B, bool BF16, bool MDE>
 hipError_t launch_one(const StepArgs &args_in, hipStream_t stream)
 {
     StepArgs args = args_in;                   // the tiling belongs to the instantiation
-    constexpr int kTile = tile_elems<BM, BV, B, MDE>();
-    // A short or mid-size tensor is all latency: its super-tiles would be too few to fill the
-    // machine (a wavefront walks a super-tile in 5 or 10 dependent iterations), so it goes as a
-    // whole, in one launch, to the kernel of the ragged end: one wavefront per 512 elements.
-    const bool small = args.n <= chunked_up_to<B, BF16, MDE>();
-    args.n_tiles_full = small ? 0 : args.n / kTile;
-    args.wg_per_xcd = ((args.n_tiles_full + kWaves - 1) / kWaves + kXcds - 1) / kXcds;
-    const bool has_tail = small ? args.n != 0 : (args.n % kTile) != 0;
-    args.tail_tile0 = args.n_tiles_full * (kTile / kTileUnit);
-    // its 512-element iterations, up to the end of the last code word (80 = lcm of 16, 10 and 8
-    // codes per word): the unused fields of that word are written as zeros like every other field
-    const uint64_t tail_e0 = args.tail_tile0 * kTileUnit;
-    args.tail_chunks = ((args.n + 79) / 80 * 80 - tail_e0 + kIter - 1) / kIter;
+    if (args.n == 0) return hipSuccess;
+    const bool narrow = args.n <= narrow_up_to();
+    const uint64_t whole = narrow ? 0 : args.n / kIter16;
+    args.rest = args.n == whole * kIter16 ? 0 : (end_of_words(args.n) - whole * kIter16 + kIter - 1) / kIter;
+    const uint64_t groups = (whole + args.rest + kWaves - 1) / kWaves;
+    if (groups > 0x7FFFFFFFull) return hipErrorInvalidValue;
     const bool ext = args.param_bf16 || args.grad_scale || args.belief || args.l2 != 0.0f;
-    if (args.n_tiles_full) {
-        const uint64_t grid = args.wg_per_xcd * kXcds;
-        if (grid > 0x7FFFFFFFull) return hipErrorInvalidValue;
-        if (ext)
-            hipLaunchKernelGGL((step_kernel<BM, BV, B, BF16, MDE, false, true>), dim3((uint32_t)grid), dim3(kWaves * 64), 0, stream, args);
-        else
-            hipLaunchKernelGGL((step_kernel<BM, BV, B, BF16, MDE, false, false>), dim3((uint32_t)grid), dim3(kWaves * 64), 0, stream, args);
-        hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return e;
-    }
-    if (has_tail) {                            // the ragged end: one wavefront per 512 elements, always the full-featured kernel
-        if ((args.tail_chunks + kWaves - 1) / kWaves > 0x7FFFFFFFull) return hipErrorInvalidValue;
-        const uint32_t tail_groups = (uint32_t)((args.tail_chunks + kWaves - 1) / kWaves);
-        hipLaunchKernelGGL((step_kernel<BM, BV, B, BF16, MDE, true, true>), dim3(tail_groups), dim3(kWaves * 64), 0, stream, args);
-        hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return e;
-    }
-    return hipSuccess;
+    if (narrow)                                // (always the full-featured kernel: all latency)
+        hipLaunchKernelGGL((chunk8_kernel<BM, BV, B, BF16, MDE, true>), dim3((uint32_t)groups), dim3(kWaves * 64), 0, stream, args);
+    else if (ext)
+        hipLaunchKernelGGL((chunk16_kernel<BM, BV, B, BF16, MDE, true>), dim3((uint32_t)groups), dim3(kWaves * 64), 0, stream, args);
+    else
+        hipLaunchKernelGGL((chunk16_kernel<BM, BV, B, BF16, MDE, false>), dim3((uint32_t)groups), dim3(kWaves * 64), 0, stream, args);
+    return hipGetLastError();
 }
 
 template <int BM, bool MDE>
@@ -1802,24 +1654,30 @@ template <int BM, bool MDE>
 hipError_t launch_multi_impl(uint32_t bits_v, uint32_t block_size, bool bf16, const MultiArgs &args,
                              hipStream_t stream)
 {
-    const uint64_t grid = args.groups_per_xcd * kXcds;
-    if (grid == 0 || grid > 0x7FFFFFFFull) return hipErrorInvalidValue;
     const StepArgs &c = args.common;
     const bool ext = args.any_bf16_copy || c.grad_scale || c.belief || c.l2 != 0.0f;
-    const bool chunked = multi_chunked(bf16, MDE);
-#define SOLO_LAUNCH(BV_, B_, BF_, EXT_)                                                                 \
+#define SOLO_LAUNCH(BV_, B_, BF_)                                                                       \
     do {                                                                                                \
-        if (chunked)                                                                                    \
-            hipLaunchKernelGGL((multi_chunk_kernel<BM, BV_, B_, BF_, MDE, EXT_>), dim3((uint32_t)grid), \
+        constexpr uint64_t unit = table_unit<BM, BV_, B_, BF_, MDE>();                                  \
+        const bool narrow = args.total_units <= narrow_up_to() / unit;                                  \
+        /* wavefronts: one per 512 elements of a unit, or five per 5120 elements */                     \
+        const uint64_t slots = narrow ? args.total_units * (unit / kIter)                               \
+                                      : (args.total_units + 2 * kTileUnit / unit - 1) / (2 * kTileUnit / unit) * 5; \
+        const uint64_t grid = (slots + kWaves - 1) / kWaves;                                            \
+        if (grid == 0 || grid > 0x7FFFFFFFull) return hipErrorInvalidValue;                             \
+        if (narrow)                                                                                     \
+            hipLaunchKernelGGL((multi_chunk8_kernel<BM, BV_, B_, BF_, MDE>), dim3((uint32_t)grid),      \
+                               dim3(kWaves * 64), 0, stream, args);                                     \
+        else if (ext)                                                                                   \
+            hipLaunchKernelGGL((multi_chunk16_kernel<BM, BV_, B_, BF_, MDE, true>), dim3((uint32_t)grid), \
                                dim3(kWaves * 64), 0, stream, args);                                     \
         else                                                                                            \
-            hipLaunchKernelGGL((multi_kernel<BM, BV_, B_, BF_, MDE, EXT_>), dim3((uint32_t)grid),       \
+            hipLaunchKernelGGL((multi_chunk16_kernel<BM, BV_, B_, BF_, MDE, false>), dim3((uint32_t)grid), \
                                dim3(kWaves * 64), 0, stream, args);                                     \
     } while (0)
 #define SOLO_CASE(BV_, B_)                                                                              \
     if (bits_v == BV_ && block_size == B_) {                                                            \
-        if (bf16) { if (ext) SOLO_LAUNCH(BV_, B_, true, true); else SOLO_LAUNCH(BV_, B_, true, false); } \
-        else      { if (ext) SOLO_LAUNCH(BV_, B_, false, true); else SOLO_LAUNCH(BV_, B_, false, false); } \
+        if (bf16) SOLO_LAUNCH(BV_, B_, true); else SOLO_LAUNCH(BV_, B_, false);                         \
         return hipGetLastError();                                                                       \
     }
     SOLO_CASE(2, 64) SOLO_CASE(2, 128) SOLO_CASE(3, 64) SOLO_CASE(3, 128) SOLO_CASE(4, 64) SOLO_CASE(4, 128)

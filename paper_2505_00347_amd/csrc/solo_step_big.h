@@ -52,7 +52,7 @@ static_assert(kBigWaves == 4, "one workgroup of four wavefronts per block");
 // Four pad words follow every 64 words: the rows that the 64 lanes sum with 128-bit reads (32 or
 // 16 words each) then start in 16 different groups of four banks.
 struct BigLayout {
-    static constexpr int kStage = 64 * kColStride;            // per wavefront
+    static constexpr int kStage = 64 * 12;                    // per wavefront (whole 128-bit words per lane)
     static constexpr int kHistA = 0, kHistB = 2048 + 2048 / 64 * 4;
     static constexpr int kHists = kHistB + 1024 + 1024 / 64 * 4;                // 3264 words
     static constexpr int kWork = kHists > 4 * kStage ? kHists : 4 * kStage;
@@ -161,11 +161,9 @@ __device__ __forceinline__ void step_block_big(const StepArgs &a, const uint64_t
                                                uint32_t *const xch, const uint32_t *const lds_de)
 {
     constexpr int L = (1 << (BM - 1)) - 1;
-    constexpr int CM = 32 / BM, CV = 32 / BV;
     constexpr bool kDeTable = MDE && BM >= 3;
 
     const uint32_t tid = wave * 64u + lane;
-    const uint64_t m_total = (a.n + CM - 1) / CM, v_total = (a.n + CV - 1) / CV;
     const uint64_t ew0 = blk * kBigBlock + (uint64_t)wave * kIter;    // first element of this wavefront
     const uint64_t e0 = ew0 + lane * 8u;                              // first element of this lane
     uint32_t *const img_m = slab + BigLayout::kOffImgM, *const img_v = slab + BigLayout::kOffImgV;
@@ -179,22 +177,10 @@ __device__ __forceinline__ void step_block_big(const StepArgs &a, const uint64_t
     float4 *const stage = reinterpret_cast<float4 *>(work + wave * BigLayout::kStage);
     float4 *const st_c = stage + (lane + lane / 8u);
     float4 *const st_l = stage + (2u * lane + lane / 4u);
-    // words of the wavefront's 512 elements: the first may start inside a word (ten-to-a-word codes)
-    const uint64_t gm_lo = ew0 / CM, gv_lo = ew0 / CV;
-    const uint32_t rm0 = (uint32_t)(ew0 - gm_lo * CM), rv0 = (uint32_t)(ew0 - gv_lo * CV);   // slot of the first element
-    const uint32_t nwm = (rm0 + kIter + CM - 1) / CM, nwv = (rv0 + kIter + CV - 1) / CV;      // words touched (<= 64)
-    const uint64_t gw_m = gm_lo + lane, gw_v = gv_lo + lane;
-    const bool has_m = lane < nwm && (!TAIL || gw_m < m_total);
-    const bool has_v = lane < nwv && (!TAIL || gw_v < v_total);
-    uint32_t own_m = 0, own_v = 0;
-    if (has_m) own_m = a.m_words[gw_m];
-    if (has_v) own_v = a.v_words[gw_v];
+    ChunkWords8<BM, BV, TAIL> words;
+    words.load(a, ew0, lane);
     const float dm_old = a.m_scale[blk], dv_old = a.v_scale[blk], al_old = a.v_base[blk];
-    if (BM == 3) own_m &= 0x3FFFFFFFu;
-    if (BV == 3) own_v &= 0x3FFFFFFFu;
-    img_m[lane] = own_m;
-    img_v[lane] = own_v;
-    if (lane == 0) { img_m[64] = 0; img_v[64] = 0; }
+    words.stage(img_m, img_v, lane);
 
     // ---- level tables of the block (every wavefront its own copy)
     {
@@ -204,13 +190,8 @@ __device__ __forceinline__ void step_block_big(const StepArgs &a, const uint64_t
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
 
-    // word and slot of this lane's first code inside the wavefront's words
-    const uint32_t qm = rm0 + lane * 8u, qv = rv0 + lane * 8u;
-    const uint32_t wm = qm / CM, sm = qm - wm * CM, wv = qv / CV, sv = qv - wv * CV;
-    const uint32_t mw0 = img_m[wm], mw1 = (BM == 3) ? img_m[wm + 1] : 0u;
-    const uint32_t vw0 = img_v[wv], vw1 = (BV == 3) ? img_v[wv + 1] : 0u;
-    const uint32_t mc8 = extract8<BM>(mw0, mw1, sm) & (uint32_t)((1ull << (8 * BM)) - 1ull);
-    const uint32_t vc8 = extract8<BV>(vw0, vw1, sv) & (uint32_t)((1ull << (8 * BV)) - 1ull);
+    uint32_t mc8, vc8;
+    words.codes(img_m, img_v, mc8, vc8);
 
     bool ok[8];
 #pragma unroll
@@ -274,18 +255,17 @@ __device__ __forceinline__ void step_block_big(const StepArgs &a, const uint64_t
     const BlockCodec codec = block_codec<BV, 16, L, MDE>(xp_bits, dm, dv, lane, lig, gshift);
     uint32_t m8, v8;
     encode_run<BM, BV, MDE, TAIL>(a, e0, mh, vh, ok, codec, de_base, m8, v8);
-    xor_into_image8<BM, BV>(img_m, img_v, wm, sm, wv, sv, mc8 ^ m8, vc8 ^ v8);
+    xor_into_image8<BM, BV>(img_m, img_v, words.wm, words.sm, words.wv, words.sv, mc8 ^ m8, vc8 ^ v8);
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     __builtin_amdgcn_wave_barrier();
-    if (has_m) write_back_word<BM>(&a.m_words[gw_m], img_m[lane], own_m);
-    if (has_v) write_back_word<BV>(&a.v_words[gw_v], img_v[lane], own_v);
+    words.write_back(a, img_m, img_v, lane);
     if (tid == 0) { a.m_scale[blk] = dm; a.v_scale[blk] = dv; a.v_base[blk] = codec.alpha; }
 }
 
 // ---- the wide form of a full block: two wavefronts, 16 consecutive elements per lane
 //
-// The element-wise part is that of one 1024-element iteration of the wide streaming path
-// (step_tile16), the block statistics are those of step_block_big() with two wavefronts instead of
+// The element-wise part is that of a 1024-element chunk
+// (step_chunk16), the block statistics are those of step_block_big() with two wavefronts instead of
 // four.  What is done once per lane and block (level tables, the two divisions, the base, the
 // hash of a group of eight, the scans of the selection) is spread over twice as many elements, and
 // the scans are run by two wavefronts instead of four.
@@ -313,9 +293,7 @@ __device__ __forceinline__ void step_block_wide(const StepArgs &a, const uint64_
                                                 uint32_t *const xch, const uint32_t *const lds_de)
 {
     constexpr int L = (1 << (BM - 1)) - 1;
-    constexpr int CM = 32 / BM, CV = 32 / BV;
     constexpr bool kDeTable = MDE && BM >= 3;
-    constexpr int KM = CM == 16 ? 1 : 2, KV = CV == 16 ? 1 : 2;      // words of a stream per lane (64 x K >= words of 1024 elements)
 
     const uint32_t tid = wave * 64u + lane;
     const uint64_t ew0 = blk * kBigBlock + (uint64_t)wave * kIter16;  // first element of this wavefront
@@ -329,34 +307,10 @@ __device__ __forceinline__ void step_block_wide(const StepArgs &a, const uint64_
     RawPG16<BF16> raw = load_pg16<BF16>(a, ew0, lane);
     const float gscale = (EXT && a.grad_scale) ? *a.grad_scale : 1.0f;
     const Stage16 st(reinterpret_cast<float4 *>(work + wave * WideBigLayout::kStage), lane);
-    // words of the wavefront's 1024 elements: the first may start inside a word (ten-to-a-word
-    // codes); all of them exist, the block is a full one
-    const uint64_t gm_lo = ew0 / CM, gv_lo = ew0 / CV;
-    const uint32_t rm0 = (uint32_t)(ew0 - gm_lo * CM), rv0 = (uint32_t)(ew0 - gv_lo * CV);   // slot of the first element
-    const uint32_t nwm = (rm0 + kIter16 + CM - 1) / CM, nwv = (rv0 + kIter16 + CV - 1) / CV;  // words touched (<= 128)
-    uint32_t own_m[KM], own_v[KV];
-#pragma unroll
-    for (int k = 0; k < KM; ++k) {
-        own_m[k] = 0;
-        if (lane + 64u * k < nwm) own_m[k] = a.m_words[gm_lo + lane + 64u * k];
-    }
-#pragma unroll
-    for (int k = 0; k < KV; ++k) {
-        own_v[k] = 0;
-        if (lane + 64u * k < nwv) own_v[k] = a.v_words[gv_lo + lane + 64u * k];
-    }
+    ChunkWords16<BM, BV> words;
+    words.load(a, ew0, lane);
     const float dm_old = a.m_scale[blk], dv_old = a.v_scale[blk], al_old = a.v_base[blk];
-#pragma unroll
-    for (int k = 0; k < KM; ++k) {
-        if (BM == 3) own_m[k] &= 0x3FFFFFFFu;
-        img_m[lane + 64u * k] = own_m[k];
-    }
-#pragma unroll
-    for (int k = 0; k < KV; ++k) {
-        if (BV == 3) own_v[k] &= 0x3FFFFFFFu;
-        img_v[lane + 64u * k] = own_v[k];
-    }
-    if (lane < 4) { img_m[64 * KM + lane] = 0; img_v[64 * KV + lane] = 0; }
+    words.stage(img_m, img_v, lane);
 
     // ---- level tables of the block (every wavefront its own copy)
     {
@@ -366,23 +320,8 @@ __device__ __forceinline__ void step_block_wide(const StepArgs &a, const uint64_
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
 
-    // word and slot of the first code of the lane's two runs of 8 inside the wavefront's words
-    uint32_t wm[2], sm[2], wv[2], sv[2];
     uint32_t mc8[2], vc8[2];
-#pragma unroll
-    for (int r = 0; r < 2; ++r) {
-        const uint32_t qm = rm0 + lane * 16u + 8u * r, qv = rv0 + lane * 16u + 8u * r;   // < 1040: e / 10 by multiplication
-        wm[r] = (CM == 10) ? __umul24(qm, 52429u) >> 19 : qm / CM; sm[r] = qm - wm[r] * CM;
-        wv[r] = (CV == 10) ? __umul24(qv, 52429u) >> 19 : qv / CV; sv[r] = qv - wv[r] * CV;
-    }
-#pragma unroll
-    for (int r = 0; r < 2; ++r) {
-        // (2-bit codes: both runs of the lane lie in one word)
-        const uint32_t mw0 = img_m[wm[BM == 2 ? 0 : r]], mw1 = (BM == 3) ? img_m[wm[r] + 1] : 0u;
-        const uint32_t vw0 = img_v[wv[BV == 2 ? 0 : r]], vw1 = (BV == 3) ? img_v[wv[r] + 1] : 0u;
-        mc8[r] = extract8<BM>(mw0, mw1, BM == 2 ? 8u * r : sm[r]) & (uint32_t)((1ull << (8 * BM)) - 1ull);
-        vc8[r] = extract8<BV>(vw0, vw1, BV == 2 ? 8u * r : sv[r]) & (uint32_t)((1ull << (8 * BV)) - 1ull);
-    }
+    words.codes(img_m, img_v, mc8, vc8);
 
     // ---- coalesced layout -> 16 consecutive elements per lane
     float p[16], g[16];
@@ -434,15 +373,11 @@ __device__ __forceinline__ void step_block_wide(const StepArgs &a, const uint64_
     uint32_t de_base = 0;
     if (kDeTable) de_base = lds_addr(lds_de) - 16u * DeBuckets<BM>::kLo;
     const BlockCodec codec = block_codec<BV, 16, L, MDE>(xp_bits, dm, dv, lane, lig, gshift);
-    encode_into_image16<BM, BV, MDE>(a, e0, mh, vh, codec, de_base, img_m, img_v, wm, sm, wv, sv, mc8, vc8);
+    encode_into_image16<BM, BV, MDE>(a, e0, mh, vh, codec, de_base, img_m, img_v,
+                                     words.wm, words.sm, words.wv, words.sv, mc8, vc8);
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     __builtin_amdgcn_wave_barrier();
-#pragma unroll
-    for (int k = 0; k < KM; ++k)
-        if (lane + 64u * k < nwm) write_back_word<BM>(&a.m_words[gm_lo + lane + 64u * k], img_m[lane + 64u * k], own_m[k]);
-#pragma unroll
-    for (int k = 0; k < KV; ++k)
-        if (lane + 64u * k < nwv) write_back_word<BV>(&a.v_words[gv_lo + lane + 64u * k], img_v[lane + 64u * k], own_v[k]);
+    words.write_back(a, img_m, img_v, lane);
     if (tid == 0) { a.m_scale[blk] = dm; a.v_scale[blk] = dv; a.v_base[blk] = codec.alpha; }
 }
 
@@ -450,13 +385,13 @@ __device__ __forceinline__ void step_block_wide(const StepArgs &a, const uint64_
 // (Registers: the plain step with bf16 gradients fits five wavefronts per SIMD without spilling,
 // except with two ten-to-a-word streams; LDS allows five for every format.)
 template <int BM, int BV, bool BF16, bool EXT>
-constexpr int big_wide_waves() { return (BF16 && !EXT && !(BM == 3 && BV == 3)) ? kWideWaves + 1 : kWideWaves; }
+constexpr int big_wide_waves() { return (BF16 && !EXT && !(BM == 3 && BV == 3)) ? kMinWaves : kMinWaves - 1; }
 
 template <int BM, int BV, bool BF16, bool MDE, bool EXT>
 __global__ __launch_bounds__(kWideBigWaves * 64, (big_wide_waves<BM, BV, BF16, EXT>()))
 void big_wide_kernel(const StepArgs a)
 {
-    constexpr int kDeWords = (MDE && BM >= 3) ? 4 * DeBuckets<BM>::N : 16;
+    constexpr int kDeWords = de_words<BM, MDE>();
     __shared__ __attribute__((aligned(64))) uint32_t lds_work[BigLayout::kWork];
     __shared__ __attribute__((aligned(64))) uint32_t lds_slab[kWideBigWaves * WideBigLayout::kSlab];
     __shared__ __attribute__((aligned(64))) uint32_t lds_xch[16];   // block maxima; bin and rank of every pass
@@ -468,12 +403,12 @@ void big_wide_kernel(const StepArgs a)
                                             lds_work, lds_xch, lds_de);
 }
 
-// One workgroup of four wavefronts per block of 2048 elements, from block a.tail_tile0 on.
+// One workgroup of four wavefronts per block of 2048 elements, from block a.block0 on.
 template <int BM, int BV, bool BF16, bool MDE, bool EXT>
-__global__ __launch_bounds__(kBigWaves * 64, SOLO_MIN_WAVES)
+__global__ __launch_bounds__(kBigWaves * 64, kMinWaves)
 void big_kernel(const StepArgs a)
 {
-    constexpr int kDeWords = (MDE && BM >= 3) ? 4 * DeBuckets<BM>::N : 16;
+    constexpr int kDeWords = de_words<BM, MDE>();
     __shared__ __attribute__((aligned(64))) uint32_t lds_work[BigLayout::kWork];
     __shared__ __attribute__((aligned(64))) uint32_t lds_slab[kBigWaves * BigLayout::kSlab];
     __shared__ __attribute__((aligned(64))) uint32_t lds_xch[16];   // block maxima; bin and rank of every pass
@@ -481,7 +416,7 @@ void big_kernel(const StepArgs a)
     load_de_table<BM, MDE, kDeWords>(lds_de);
     const uint32_t lane = threadIdx.x & 63u;
     const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    const uint64_t blk = a.tail_tile0 + blockIdx.x;
+    const uint64_t blk = a.block0 + blockIdx.x;
     uint32_t *const slab = lds_slab + wave * BigLayout::kSlab;
     if constexpr (!SOLO_BIG_WIDE) {
         if ((blk + 1) * kBigBlock <= a.n) {
@@ -497,21 +432,11 @@ void big_kernel(const StepArgs a)
 // workgroup of multi_big_wide_kernel takes one entry and, unless it is flagged, runs the full
 // block; workgroup k of multi_big_tail_kernel runs the shorter last block of tensor k, if it has
 // one.  Blocks never span tensors.
-__device__ __forceinline__ StepArgs tensor_args(const MultiArgs &ma, const TensorEntry &e)
-{
-    StepArgs a = ma.common;
-    a.param = e.param; a.param_bf16 = e.param_bf16; a.grad = e.grad;
-    a.m_words = e.m_words; a.m_scale = e.m_scale;
-    a.v_words = e.v_words; a.v_scale = e.v_scale; a.v_base = e.v_base;
-    a.n = e.n; a.index_offset = e.index_offset;
-    return a;
-}
-
 template <int BM, int BV, bool BF16, bool MDE, bool EXT>
 __global__ __launch_bounds__(kWideBigWaves * 64, (big_wide_waves<BM, BV, BF16, EXT>()))
 void multi_big_wide_kernel(const MultiArgs ma)
 {
-    constexpr int kDeWords = (MDE && BM >= 3) ? 4 * DeBuckets<BM>::N : 16;
+    constexpr int kDeWords = de_words<BM, MDE>();
     __shared__ __attribute__((aligned(64))) uint32_t lds_work[BigLayout::kWork];
     __shared__ __attribute__((aligned(64))) uint32_t lds_slab[kWideBigWaves * WideBigLayout::kSlab];
     __shared__ __attribute__((aligned(64))) uint32_t lds_xch[16];
@@ -530,10 +455,10 @@ void multi_big_wide_kernel(const MultiArgs ma)
 }
 
 template <int BM, int BV, bool BF16, bool MDE>
-__global__ __launch_bounds__(kBigWaves * 64, SOLO_MIN_WAVES)
+__global__ __launch_bounds__(kBigWaves * 64, kMinWaves)
 void multi_big_tail_kernel(const MultiArgs ma, const uint32_t count)
 {
-    constexpr int kDeWords = (MDE && BM >= 3) ? 4 * DeBuckets<BM>::N : 16;
+    constexpr int kDeWords = de_words<BM, MDE>();
     __shared__ __attribute__((aligned(64))) uint32_t lds_work[BigLayout::kWork];
     __shared__ __attribute__((aligned(64))) uint32_t lds_slab[kBigWaves * BigLayout::kSlab];
     __shared__ __attribute__((aligned(64))) uint32_t lds_xch[16];
@@ -593,7 +518,7 @@ hipError_t launch_big_impl(uint32_t bits_v, bool bf16, const StepArgs &args, hip
     const bool ext = args.param_bf16 || args.grad_scale || args.belief || args.l2 != 0.0f;
     const uint64_t wide_blocks = SOLO_BIG_WIDE ? full : 0;
     StepArgs rest = args;
-    rest.tail_tile0 = wide_blocks;               // the four-wavefront kernel starts behind them
+    rest.block0 = wide_blocks;               // the four-wavefront kernel starts behind them
 #define SOLO_LAUNCH(BV_, BF_, EXT_)                                                                 \
     do {                                                                                            \
         if (wide_blocks)                                                                            \
