@@ -7,6 +7,7 @@ files go to paper_2505_00347_amd/_build/.
 import os
 import subprocess
 import sys
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
@@ -16,6 +17,7 @@ LIBDIR = os.path.join(HERE, "lib")
 LIB = os.path.join(LIBDIR, "libsolo.so")
 PROBE = os.path.join(LIBDIR, "stream_probe")
 EXAMPLE = os.path.join(LIBDIR, "solo_c_example")
+NATIVE = os.path.join(LIBDIR, "_solo_native" + sysconfig.get_config_var("EXT_SUFFIX"))
 SOURCES = ["solo_api.hip", "solo_step_m2.hip", "solo_step_m3.hip", "solo_step_m4.hip",
            "solo_step_m2_de.hip", "solo_step_m3_de.hip", "solo_step_m4_de.hip",
            "solo_step_big.hip", "solo_step_big_de.hip"]
@@ -39,12 +41,15 @@ def build(force=True, verbose=False):
     os.makedirs(LIBDIR, exist_ok=True)
     deps = [os.path.join(CSRC, f) for f in os.listdir(CSRC)] + [
         os.path.join(HERE, "..", "include", "solo.h")]
-    if not force and os.path.exists(LIB) and all(
+    if not force and os.path.exists(LIB) and os.path.exists(NATIVE) and all(
             os.path.getmtime(LIB) >= os.path.getmtime(d) for d in deps):
         return LIB
     with ThreadPoolExecutor(len(SOURCES)) as ex:
         objs = list(ex.map(_compile, SOURCES))
     subprocess.check_call([HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB, *objs])
+    # the step calls of the Python binding (host code only)
+    subprocess.check_call(["g++", "-O2", "-std=c++17", "-shared", "-fPIC", "-Wall", "-fvisibility=hidden",
+                           "-I" + sysconfig.get_paths()["include"], os.path.join(CSRC, "solo_py.cpp"), "-o", NATIVE])
     # stand-alone memory-ceiling probe (read / write / copy / step-shaped streams)
     subprocess.check_call([HIPCC, "-O3", "--offload-arch=gfx950", "-std=c++17",
                            "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",

@@ -4,14 +4,18 @@ Every function has the name and meaning of the C entry point it calls; all of th
 optimizer step runs in the HIP kernels of the library.  Tensors are torch tensors
 on an AMD GPU (torch is used for device memory and streams only); a tensor is
 passed as its device pointer, the stream as the current torch stream's handle.
-The module fails loudly when the library has not been built: there is no
-fallback path.
+The calls of a step are marshalled by a small native module (csrc/solo_py.cpp), the
+others through ctypes.  The module fails loudly when the library has not been built:
+there is no fallback path.
 """
 import ctypes as C
+import importlib.util
 import os
+import sysconfig
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "lib", "libsolo.so")
+NATIVE_PATH = os.path.join(_HERE, "lib", "_solo_native" + sysconfig.get_config_var("EXT_SUFFIX"))
 
 SOLO_OK, SOLO_E_INVALID, SOLO_E_UNSUPPORTED, SOLO_E_HIP = 0, -1, -2, -3
 SOLO_GRAD_FP32, SOLO_GRAD_BF16 = 0, 1
@@ -53,15 +57,17 @@ class SoloError(RuntimeError):
 
 
 _lib = None
+_native = None
 
 
 def lib():
     """Load libsolo.so (built by ``python -m paper_2505_00347_amd.build``)."""
-    global _lib
+    global _lib, _native
     if _lib is None:
-        if not os.path.exists(LIB_PATH):
-            raise ImportError(f"{LIB_PATH} is missing: build it with "
-                              "`python -m paper_2505_00347_amd.build` (needs hipcc)")
+        for path in (LIB_PATH, NATIVE_PATH):
+            if not os.path.exists(path):
+                raise ImportError(f"{path} is missing: build it with "
+                                  "`python -m paper_2505_00347_amd.build` (needs hipcc)")
         # torch first: the wheel brings a HIP runtime of its own and exports it to the process.
         # Loaded after it, libsolo binds to that runtime, the one the tensors and streams of the
         # callers belong to; loaded before it, libsolo would bind to the system's copy, and every
@@ -89,8 +95,27 @@ def lib():
         L.solo_multi_table_build.argtypes = [tp, u32, cfgp, vp, C.c_size_t, C.POINTER(C.c_uint32)]
         L.solo_adamw_step_multi.restype = C.c_int
         L.solo_adamw_step_multi.argtypes = [vp, u32, u64, u32, vp, u64, cfgp, vp]
-        _lib = L
+        spec = importlib.util.spec_from_file_location("_solo_native", NATIVE_PATH)
+        native = importlib.util.module_from_spec(spec)
+        spec.loader.exec_module(native)
+        native.bind(C.cast(L.solo_adamw_step_mp, vp).value, C.cast(L.solo_adamw_step_multi, vp).value,
+                    solo_config, C.ArgumentError, _stream_of_now,
+                    getattr(torch._C, "_cuda_getDevice", None), getattr(torch._C, "_cuda_getCurrentRawStream", None))
+        os.register_at_fork(after_in_child=native.forked)
+        _lib, _native = L, native
     return _lib
+
+
+def _step_calls():
+    """The native module (see csrc/solo_py.cpp)."""
+    if _native is None:
+        lib()
+    return _native
+
+
+def _stream_of_now():
+    import torch
+    return torch.cuda.current_stream().cuda_stream
 
 
 def _ptr(t):
@@ -102,8 +127,7 @@ def _ptr(t):
 
 def _stream(stream):
     if stream is None:
-        import torch
-        return torch.cuda.current_stream().cuda_stream
+        return _stream_of_now()
     return stream if isinstance(stream, int) else stream.cuda_stream
 
 
@@ -125,9 +149,8 @@ def solo_state_init(m_codes, m_scale, v_codes, v_scale, v_base, n, cfg, stream=N
 
 def solo_adamw_step(param, grad, m_codes, m_scale, v_codes, v_scale, v_base, n, step, cfg,
                     stream=None, check=True):
-    rc = lib().solo_adamw_step(_ptr(param), _ptr(grad), _ptr(m_codes), _ptr(m_scale),
-                               _ptr(v_codes), _ptr(v_scale), _ptr(v_base), n, step,
-                               C.byref(cfg), _stream(stream) if n else None)
+    # (solo_adamw_step of the library is this call with both extras NULL)
+    rc = _step_calls().step(param, None, grad, None, m_codes, m_scale, v_codes, v_scale, v_base, n, step, cfg, stream)
     if check and rc != SOLO_OK:
         raise SoloError(rc)
     return rc
@@ -136,9 +159,8 @@ def solo_adamw_step(param, grad, m_codes, m_scale, v_codes, v_scale, v_base, n, 
 def solo_adamw_step_mp(param, param_bf16, grad, grad_scale, m_codes, m_scale, v_codes, v_scale,
                        v_base, n, step, cfg, stream=None, check=True):
     """param_bf16 (bf16 tensor) and grad_scale (one-element float32 device tensor) may be None."""
-    rc = lib().solo_adamw_step_mp(_ptr(param), _ptr(param_bf16), _ptr(grad), _ptr(grad_scale),
-                                  _ptr(m_codes), _ptr(m_scale), _ptr(v_codes), _ptr(v_scale),
-                                  _ptr(v_base), n, step, C.byref(cfg), _stream(stream) if n else None)
+    rc = _step_calls().step(param, param_bf16, grad, grad_scale, m_codes, m_scale, v_codes, v_scale, v_base,
+                            n, step, cfg, stream)
     if check and rc != SOLO_OK:
         raise SoloError(rc)
     return rc
@@ -159,8 +181,7 @@ def solo_multi_table_build(tensors, count, cfg, table_host, table_bytes, check=T
 
 def solo_adamw_step_multi(table_device, count, units, table_flags, grad_scale, step, cfg, stream=None,
                           check=True):
-    rc = lib().solo_adamw_step_multi(_ptr(table_device), count, units, table_flags, _ptr(grad_scale), step,
-                                     C.byref(cfg), _stream(stream) if units else None)
+    rc = _step_calls().multi(table_device, count, units, table_flags, grad_scale, step, cfg, stream)
     if check and rc != SOLO_OK:
         raise SoloError(rc)
     return rc
@@ -247,7 +268,5 @@ class SoloState:
         return (self.m_codes, self.m_scale, self.v_codes, self.v_scale, self.v_base)
 
     def step(self, param, grad, step, stream=None, param_bf16=None, grad_scale=None):
-        if param_bf16 is None and grad_scale is None:
-            return solo_adamw_step(param, grad, *self.buffers(), self.n, step, self.cfg, stream)
         return solo_adamw_step_mp(param, param_bf16, grad, grad_scale, *self.buffers(), self.n, step,
                                   self.cfg, stream)
