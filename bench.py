@@ -339,7 +339,7 @@ def main():
 
     # the kernel that takes the time (the library picks it from the format, the size and the launch)
     if w.block_size == 2048:
-        kernel_name = "solo::multi_big_wide_kernel" if args.launch == "multi" else "solo::big_wide_kernel"
+        kernel_name = "solo::multi_big_kernel" if args.launch == "multi" else "solo::big_kernel"
     else:
         per_lane = 8 if n <= 3 << 18 else 16
         kernel_name = f"solo::{'multi_' if args.launch == 'multi' else ''}chunk{per_lane}_kernel"

@@ -221,7 +221,7 @@ size_t solo_multi_table_bytes(uint32_t count, uint64_t units);
  * array of descriptors holding DEVICE pointers) and set *table_flags (SOLO_TABLE_*), which
  * solo_adamw_step_multi takes back.  Checks every pointer's alignment. */
 #define SOLO_TABLE_BF16_COPY 1u   /* some tensor has a bf16 copy to write */
-#define SOLO_TABLE_SHORT_BLOCK 2u /* blocks of 2048: some tensor ends in a shorter block (a second launch) */
+#define SOLO_TABLE_SHORT_BLOCK 2u /* blocks of 2048: some tensor ends in a shorter block */
 int solo_multi_table_build(const solo_tensor *tensors, uint32_t count, const solo_config *cfg,
                            void *table_host, size_t table_bytes, uint32_t *table_flags);
 

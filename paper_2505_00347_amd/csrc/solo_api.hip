@@ -39,14 +39,13 @@ template <> hipError_t launch_big<3, true>(uint32_t, bool, const StepArgs &, hip
 template <> hipError_t launch_big<4, true>(uint32_t, bool, const StepArgs &, hipStream_t);
 
 template <int BM, bool MDE>
-hipError_t launch_multi_big(uint32_t bits_v, bool bf16, const MultiArgs &args, uint32_t count, bool ragged,
-                            hipStream_t stream);
-template <> hipError_t launch_multi_big<2, false>(uint32_t, bool, const MultiArgs &, uint32_t, bool, hipStream_t);
-template <> hipError_t launch_multi_big<3, false>(uint32_t, bool, const MultiArgs &, uint32_t, bool, hipStream_t);
-template <> hipError_t launch_multi_big<4, false>(uint32_t, bool, const MultiArgs &, uint32_t, bool, hipStream_t);
-template <> hipError_t launch_multi_big<2, true>(uint32_t, bool, const MultiArgs &, uint32_t, bool, hipStream_t);
-template <> hipError_t launch_multi_big<3, true>(uint32_t, bool, const MultiArgs &, uint32_t, bool, hipStream_t);
-template <> hipError_t launch_multi_big<4, true>(uint32_t, bool, const MultiArgs &, uint32_t, bool, hipStream_t);
+hipError_t launch_multi_big(uint32_t bits_v, bool bf16, const MultiArgs &args, hipStream_t stream);
+template <> hipError_t launch_multi_big<2, false>(uint32_t, bool, const MultiArgs &, hipStream_t);
+template <> hipError_t launch_multi_big<3, false>(uint32_t, bool, const MultiArgs &, hipStream_t);
+template <> hipError_t launch_multi_big<4, false>(uint32_t, bool, const MultiArgs &, hipStream_t);
+template <> hipError_t launch_multi_big<2, true>(uint32_t, bool, const MultiArgs &, hipStream_t);
+template <> hipError_t launch_multi_big<3, true>(uint32_t, bool, const MultiArgs &, hipStream_t);
+template <> hipError_t launch_multi_big<4, true>(uint32_t, bool, const MultiArgs &, hipStream_t);
 
 constexpr uint32_t kLargeBlock = 2048;      // the large-block setting (one workgroup per block)
 
@@ -364,14 +363,13 @@ int solo_adamw_step_multi(const void *table_device, uint32_t count, uint64_t uni
     hipStream_t s = (hipStream_t)stream;
     hipError_t e;
     if (cfg->block_size == solo::kLargeBlock) {
-        const bool ragged = (table_flags & SOLO_TABLE_SHORT_BLOCK) != 0;
         switch (cfg->bits_m) {
-        case 2: e = mde ? solo::launch_multi_big<2, true>(cfg->bits_v, bf16, ma, count, ragged, s)
-                        : solo::launch_multi_big<2, false>(cfg->bits_v, bf16, ma, count, ragged, s); break;
-        case 3: e = mde ? solo::launch_multi_big<3, true>(cfg->bits_v, bf16, ma, count, ragged, s)
-                        : solo::launch_multi_big<3, false>(cfg->bits_v, bf16, ma, count, ragged, s); break;
-        case 4: e = mde ? solo::launch_multi_big<4, true>(cfg->bits_v, bf16, ma, count, ragged, s)
-                        : solo::launch_multi_big<4, false>(cfg->bits_v, bf16, ma, count, ragged, s); break;
+        case 2: e = mde ? solo::launch_multi_big<2, true>(cfg->bits_v, bf16, ma, s)
+                        : solo::launch_multi_big<2, false>(cfg->bits_v, bf16, ma, s); break;
+        case 3: e = mde ? solo::launch_multi_big<3, true>(cfg->bits_v, bf16, ma, s)
+                        : solo::launch_multi_big<3, false>(cfg->bits_v, bf16, ma, s); break;
+        case 4: e = mde ? solo::launch_multi_big<4, true>(cfg->bits_v, bf16, ma, s)
+                        : solo::launch_multi_big<4, false>(cfg->bits_v, bf16, ma, s); break;
         default: return SOLO_E_UNSUPPORTED;
         }
         return e == hipSuccess ? SOLO_OK : SOLO_E_HIP;

@@ -81,7 +81,6 @@ struct StepArgs {
     float *v_base;
     uint64_t n;             // elements
     uint64_t rest;          // 512-element iterations behind the last whole chunk, up to the end of the last code word
-    uint64_t block0;        // first block of a launch of the large-block tail kernel
     uint64_t index_offset;  // global index of element 0 (multiple of 8)
     float beta1, omb1, beta2, omb2;
     float decay;            // 1 - lr * weight_decay
@@ -1155,21 +1154,42 @@ __device__ __forceinline__ uint32_t quantile16(const float (&vh)[16], uint32_t *
 template <bool BF16>
 struct RawPG16 { float4 p[4]; uint4 g[BF16 ? 2 : 4]; };
 
-template <bool BF16>
+// TAIL: loaded per lane (its own 16 elements, those that exist).
+template <bool BF16, bool TAIL = false>
 __device__ __forceinline__ RawPG16<BF16> load_pg16(const StepArgs &a, uint64_t chunk_e0, uint32_t lane)
 {
     RawPG16<BF16> r;
-    const float *pp = a.param + chunk_e0 + lane * 4u;
+    if (!TAIL) {
+        const float *pp = a.param + chunk_e0 + lane * 4u;
 #pragma unroll
-    for (int k = 0; k < 4; ++k) r.p[k] = stream_load_f4(pp + 256 * k);
-    if (BF16) {
-        const uint16_t *gp = static_cast<const uint16_t *>(a.grad) + chunk_e0 + lane * 8u;
+        for (int k = 0; k < 4; ++k) r.p[k] = stream_load_f4(pp + 256 * k);
+        if (BF16) {
+            const uint16_t *gp = static_cast<const uint16_t *>(a.grad) + chunk_e0 + lane * 8u;
 #pragma unroll
-        for (int k = 0; k < 2; ++k) r.g[k] = stream_load_u4(gp + 512 * k);
+            for (int k = 0; k < 2; ++k) r.g[k] = stream_load_u4(gp + 512 * k);
+        } else {
+            const float *gp = static_cast<const float *>(a.grad) + chunk_e0 + lane * 4u;
+#pragma unroll
+            for (int k = 0; k < (BF16 ? 2 : 4); ++k) r.g[k] = stream_load_u4(gp + 256 * k);
+        }
     } else {
-        const float *gp = static_cast<const float *>(a.grad) + chunk_e0 + lane * 4u;
+        const uint64_t e0 = chunk_e0 + lane * 16u;
+        float p[16]; uint32_t g[16];
 #pragma unroll
-        for (int k = 0; k < (BF16 ? 2 : 4); ++k) r.g[k] = stream_load_u4(gp + 256 * k);
+        for (int j = 0; j < 16; ++j) {
+            const bool ok = e0 + j < a.n;
+            p[j] = ok ? a.param[e0 + j] : 0.0f;
+            if (BF16) g[j] = ok ? (uint32_t)static_cast<const uint16_t *>(a.grad)[e0 + j] : 0u;
+            else      g[j] = ok ? static_cast<const uint32_t *>(a.grad)[e0 + j] : 0u;
+        }
+#pragma unroll
+        for (int k = 0; k < 4; ++k) r.p[k] = make_float4(p[4 * k], p[4 * k + 1], p[4 * k + 2], p[4 * k + 3]);
+#pragma unroll
+        for (int k = 0; k < (BF16 ? 2 : 4); ++k) {
+            if (BF16) r.g[k] = make_uint4(g[8 * k] | (g[8 * k + 1] << 16), g[8 * k + 2] | (g[8 * k + 3] << 16),
+                                          g[8 * k + 4] | (g[8 * k + 5] << 16), g[8 * k + 6] | (g[8 * k + 7] << 16));
+            else      r.g[k] = make_uint4(g[4 * k], g[4 * k + 1], g[4 * k + 2], g[4 * k + 3]);
+        }
     }
     return r;
 }
@@ -1186,44 +1206,47 @@ struct Stage16 {
           c2(stage + (lane + lane / 8u)), l2(stage + (2u * lane + lane / 4u)) {}
 };
 
-// A lane's 16 consecutive elements out of the coalesced layout they were loaded in.
-template <bool BF16>
+// A lane's 16 consecutive elements out of the coalesced layout they were loaded in (TAIL: loaded
+// per lane already).
+template <bool BF16, bool TAIL = false>
 __device__ __forceinline__ void lane_layout16(const RawPG16<BF16> &raw, const Stage16 &st,
                                               float (&p)[16], float (&g)[16])
 {
-#pragma unroll
-    for (int k = 0; k < 4; ++k) st.c4[72 * k] = raw.p[k];
-    wave_lds_sync();                   // (also orders the level tables before their readers)
     float4 t[4];
+    uint4 h[BF16 ? 2 : 4];
+    if (TAIL) {
 #pragma unroll
-    for (int c = 0; c < 4; ++c) t[c] = st.l4[c];
+        for (int c = 0; c < 4; ++c) t[c] = raw.p[c];
 #pragma unroll
-    for (int c = 0; c < 4; ++c) { p[4 * c] = t[c].x; p[4 * c + 1] = t[c].y; p[4 * c + 2] = t[c].z; p[4 * c + 3] = t[c].w; }
-    wave_lds_sync();
-    if (BF16) {
-#pragma unroll
-        for (int k = 0; k < 2; ++k)
-            st.c2[72 * k] = make_float4(u2f(raw.g[k].x), u2f(raw.g[k].y), u2f(raw.g[k].z), u2f(raw.g[k].w));
-        wave_lds_sync();
-#pragma unroll
-        for (int c = 0; c < 2; ++c) {
-            const float4 x = st.l2[c];
-            const uint32_t w[4] = {f2u(x.x), f2u(x.y), f2u(x.z), f2u(x.w)};
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                g[8 * c + 2 * i] = u2f(w[i] << 16);
-                g[8 * c + 2 * i + 1] = u2f(w[i] & 0xFFFF0000u);
-            }
-        }
+        for (int c = 0; c < (BF16 ? 2 : 4); ++c) h[c] = raw.g[c];
     } else {
 #pragma unroll
-        for (int k = 0; k < (BF16 ? 2 : 4); ++k)
-            st.c4[72 * k] = make_float4(u2f(raw.g[k].x), u2f(raw.g[k].y), u2f(raw.g[k].z), u2f(raw.g[k].w));
+        for (int k = 0; k < 4; ++k) st.c4[72 * k] = raw.p[k];
+        wave_lds_sync();                   // (also orders the level tables before their readers)
+#pragma unroll
+        for (int c = 0; c < 4; ++c) t[c] = st.l4[c];
         wave_lds_sync();
 #pragma unroll
-        for (int c = 0; c < 4; ++c) {
-            const float4 x = st.l4[c];
-            g[4 * c] = x.x; g[4 * c + 1] = x.y; g[4 * c + 2] = x.z; g[4 * c + 3] = x.w;
+        for (int k = 0; k < (BF16 ? 2 : 4); ++k) {
+            const float4 x = make_float4(u2f(raw.g[k].x), u2f(raw.g[k].y), u2f(raw.g[k].z), u2f(raw.g[k].w));
+            if (BF16) st.c2[72 * k] = x; else st.c4[72 * k] = x;
+        }
+        wave_lds_sync();
+#pragma unroll
+        for (int c = 0; c < (BF16 ? 2 : 4); ++c) {
+            const float4 x = BF16 ? st.l2[c] : st.l4[c];
+            h[c] = make_uint4(f2u(x.x), f2u(x.y), f2u(x.z), f2u(x.w));
+        }
+    }
+#pragma unroll
+    for (int c = 0; c < 4; ++c) { p[4 * c] = t[c].x; p[4 * c + 1] = t[c].y; p[4 * c + 2] = t[c].z; p[4 * c + 3] = t[c].w; }
+#pragma unroll
+    for (int c = 0; c < (BF16 ? 2 : 4); ++c) {
+        const uint32_t w[4] = {h[c].x, h[c].y, h[c].z, h[c].w};
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            if (BF16) { g[8 * c + 2 * i] = u2f(w[i] << 16); g[8 * c + 2 * i + 1] = u2f(w[i] & 0xFFFF0000u); }
+            else g[4 * c + i] = u2f(w[i]);
         }
     }
 }
@@ -1231,10 +1254,21 @@ __device__ __forceinline__ void lane_layout16(const RawPG16<BF16> &raw, const St
 // The new parameters of a lane's 16 elements (and their bf16 copy, if asked for: 32 bytes per
 // lane, two vectors, first) back to the coalesced layout and streamed out; chunk_e0: first
 // element of the wavefront's 1024.
-template <bool EXT>
+template <bool EXT, bool TAIL = false>
 __device__ __forceinline__ void store_params16(const StepArgs &a, const uint64_t chunk_e0, const uint32_t lane,
                                                const float (&p)[16], const Stage16 &st)
 {
+    if (TAIL) {                                    // element-wise, those that exist
+        const uint64_t e0 = chunk_e0 + lane * 16u;
+#pragma unroll
+        for (int j = 0; j < 16; ++j) {
+            if (e0 + j < a.n) {
+                a.param[e0 + j] = p[j];
+                if (EXT && a.param_bf16) a.param_bf16[e0 + j] = (uint16_t)pack_bf16(p[j], 0.0f);
+            }
+        }
+        return;
+    }
     wave_lds_sync();
     if (EXT && a.param_bf16) {
 #pragma unroll
@@ -1262,8 +1296,9 @@ __device__ __forceinline__ void store_params16(const StepArgs &a, const uint64_t
 // image of the code words.  3-bit codes share words between lanes: XOR turns this lane's old
 // fields into the new ones and leaves the neighbours' alone.  2- and 4-bit words belong to one lane
 // (2-bit: both runs lie in word wm[0]).
-template <int BM, int BV, bool MDE>
+template <int BM, int BV, bool MDE, bool TAIL = false>
 __device__ __forceinline__ void encode_into_image16(const StepArgs &a, const uint64_t e0, const float *mh, const float *vh,
+                                                    const bool *ok,
                                                     const BlockCodec &codec, const uint32_t de_base,
                                                     uint32_t *const img_m, uint32_t *const img_v,
                                                     const uint32_t (&wm)[2], const uint32_t (&sm)[2],
@@ -1274,7 +1309,7 @@ __device__ __forceinline__ void encode_into_image16(const StepArgs &a, const uin
 #pragma unroll
     for (int r = 0; r < 2; ++r) {
         uint32_t m8, v8;
-        encode_run<BM, BV, MDE, false>(a, e0 + 8u * r, mh + 8 * r, vh + 8 * r, nullptr, codec, de_base, m8, v8);
+        encode_run<BM, BV, MDE, TAIL>(a, e0 + 8u * r, mh + 8 * r, vh + 8 * r, TAIL ? ok + 8 * r : nullptr, codec, de_base, m8, v8);
         if (BM == 3) {
             const uint32_t xm = mc8[r] ^ m8;
             atomicXor(&img_m[wm[r]], (xm << (3u * sm[r])) & 0x3FFFFFFFu);
@@ -1301,7 +1336,8 @@ __device__ __forceinline__ void encode_into_image16(const StepArgs &a, const uin
 // The code words of the 1024 elements that a wavefront steps on its own (16 consecutive elements
 // per lane): staged in LDS, one or two words of each stream per lane, and written back by the lane
 // that staged them.  The first word may begin in the share before (ten-to-a-word codes).
-template <int BM, int BV>
+// TAIL: words behind the buffer are left alone.
+template <int BM, int BV, bool TAIL = false>
 struct ChunkWords16 {
     static constexpr int CM = 32 / BM, CV = 32 / BV;                 // codes per word
     static constexpr int KM = CM == 16 ? 1 : 2, KV = CV == 16 ? 1 : 2;   // words of a stream per lane (64 x K >= words of 1024 elements)
@@ -1317,6 +1353,11 @@ struct ChunkWords16 {
         gm_lo = ew0 / CM; gv_lo = ew0 / CV;
         const uint32_t rm0 = (uint32_t)(ew0 - gm_lo * CM), rv0 = (uint32_t)(ew0 - gv_lo * CV);   // slot of the first element
         nwm = (rm0 + kIter16 + CM - 1) / CM; nwv = (rv0 + kIter16 + CV - 1) / CV;
+        if (TAIL) {
+            const uint64_t m_left = (a.n + CM - 1) / CM, v_left = (a.n + CV - 1) / CV;    // words of the buffer
+            nwm = m_left <= gm_lo ? 0u : m_left - gm_lo < nwm ? (uint32_t)(m_left - gm_lo) : nwm;
+            nwv = v_left <= gv_lo ? 0u : v_left - gv_lo < nwv ? (uint32_t)(v_left - gv_lo) : nwv;
+        }
 #pragma unroll
         for (int k = 0; k < KM; ++k) {
             own_m[k] = 0;
@@ -1451,7 +1492,7 @@ __device__ __forceinline__ void step_chunk16(const StepArgs &a, const uint64_t c
     const uint32_t xp_bits = quantile16<G>(vh, col, a.rank_full, dv);
 
     const BlockCodec codec = block_codec<BV, G, L, MDE>(xp_bits, dm, dv, lane, lig, gshift);
-    encode_into_image16<BM, BV, MDE>(a, e0, mh, vh, codec, de_base, img_m, img_v,
+    encode_into_image16<BM, BV, MDE>(a, e0, mh, vh, nullptr, codec, de_base, img_m, img_v,
                                      words.wm, words.sm, words.wv, words.sv, mc8, vc8);
     if (lig == 0) { a.m_scale[gb] = dm; a.v_scale[gb] = dv; a.v_base[gb] = codec.alpha; }
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");

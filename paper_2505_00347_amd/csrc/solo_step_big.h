@@ -1,68 +1,63 @@
 // The fused SOLO AdamW step for blocks of 2048 elements (the large-block setting of the paper's
 // block-size comparison, Sec. 4.2), gfx950, wave64.
 //
-// A block of 2048 elements is held by one workgroup.  Two forms:
-//   * a full block: two wavefronts, 1024 elements each, sixteen consecutive elements per lane
-//     (step_block_wide, big_wide_kernel);
-//   * the shorter last block of a buffer: four wavefronts, 512 elements each, eight per lane,
-//     bounds checks on every element (step_block_big, big_kernel; a launch of its own).
+// A block of 2048 elements is held by one workgroup of two wavefronts, 1024 elements each, sixteen
+// consecutive elements per lane; the shorter last block of a buffer by one more workgroup of the
+// same launch (the first one, since its code, with bounds checks on every element, takes longest;
+// a launch of its own behind the full blocks made 1,000,003 elements take 15.9 us instead of 10.2).
 // The element-wise part (decode by table look-up, both EMAs, the parameter, the encoders, the
-// 32-bit words of the code streams) is that of an iteration of solo_step.h, one iteration per
-// wavefront, and runs without any exchange between the wavefronts.  What a block of this size
-// changes is the block statistics:
+// 32-bit words of the code streams) is that of a 1024-element chunk of solo_step.h and runs
+// without any exchange between the wavefronts.  What a block of this size changes is the block
+// statistics:
 //   * Delta_m' and Delta_v' are maxima over the wavefronts: DPP inside a row, four lane reads
 //     across the rows, a few words of LDS and one barrier across the wavefronts;
 //   * the p-quantile is the rank-205 element of 2048 values (p = 0.1), far too deep for rounds
-//     of "extract the minimum".  It is found by a radix select on the bit patterns (non-negative
-//     floats order like their bits): four passes over 8 + 8 + 8 + 7 bits, each a histogram of the
-//     keys that still match the selected prefix (LDS atomics), one barrier, a prefix sum (DPP
-//     scan) by which one wavefront finds the bin that holds the rank, and a second barrier.
-//     After the last pass the prefix is the order statistic itself, multiplicities included,
-//     exactly.  Nine barriers per block in all.
+//     of "extract the minimum".  It is found by histograms over ever narrower ranges of the bit
+//     patterns and, once a few keys are left, by comparing those (select_rank);
 //   * the base alpha, the divisions and the level tables are computed by every wavefront (every
 //     16 lanes) for itself: cheaper than another barrier.
-// LDS sets the number of workgroups on a CU, and that the speed (measured on MI355X: 17.3 ms for
-// 6.7e9 parameters at 3.5 wavefronts per SIMD, 15.7 ms at 5), so the histograms are kept small:
-// see BigLayout.  Every wavefront stages and writes back the words of its own elements (whole
-// 128-byte lines for 2- and 4-bit codes; ten-to-a-word codes by one atomic XOR per word at the
-// memory side, since a wavefront's share does not end on a word).
+// The kernel is bound by vector-ALU issue and, through the number of workgroups on a CU, by LDS
+// (17.3 ms for 6.7e9 parameters at 3.5 wavefronts per SIMD, 15.7 ms at 5), so the histogram is
+// kept small: see BigLayout.  Every wavefront stages and writes back the words of its own elements
+// (whole 128-byte lines for 2- and 4-bit codes; ten-to-a-word codes by one atomic XOR per word at
+// the memory side, since a wavefront's share does not end on a word).
 #pragma once
 #include "solo_step.h"
 
 namespace solo {
 
 constexpr int kBigBlock = 2048;
-constexpr int kBigWaves = kBigBlock / kIter;      // 4 wavefronts, one workgroup per block
-static_assert(kBigWaves == 4, "one workgroup of four wavefronts per block");
+constexpr int kBigWaves = kBigBlock / kIter16;
+static_assert(kBigWaves == 2, "one workgroup of two wavefronts per block");
 
 // LDS of a workgroup (32-bit words).  `work` first serves the wavefronts as the staging areas of
 // their layout transpositions, then, behind the barrier of the block maxima, the whole workgroup as
-// the histograms of the selection (four passes over 8 + 8 + 8 + 7 bits).
+// the histograms of the selection.
 // The second moments of a block that has been trained for a while sit in a few tight clusters, one
 // per level of the previous code, so most of the 64 lanes of an instruction add to the same one or
 // two bins, and LDS applies the adds to one bank one after the other (measured on MI355X with one
 // counter per bin: the step slowed down by half between the first and the thousandth update of a
-// state, all of it LDS bank conflicts).  Every bin therefore has 8 (4) counters in neighbouring
-// words, i.e. in different banks, and a lane always uses the one its number selects.
-//   hist A: 256 bins x 8 counters; the lower halves of its words count the first pass, the upper
-//           halves the second (a count is at most 2048, so the halves do not carry into each
-//           other, and a wavefront that is still reading the lower halves is not disturbed by one
-//           that already counts the next pass in the upper ones);
-//   hist B: 256 bins x 4 counters; lower halves: third pass, upper halves: fourth (128 bins).
-// Four pad words follow every 64 words: the rows that the 64 lanes sum with 128-bit reads (32 or
-// 16 words each) then start in 16 different groups of four banks.
+// state, all of it LDS bank conflicts).  Every bin therefore has 4 counters in neighbouring words, i.e.
+// in different banks, and a lane always uses the one its number selects: 512 bins x 4 counters, the
+// lower halves of the words for the first pass, the upper halves for the second (a count is at
+// most 2048, so the halves do not carry into each other, and a wavefront that is still reading the
+// lower halves is not disturbed by one that already counts the next pass in the upper ones).
+constexpr uint32_t kFewKeys = 32;      // so many keys are compared instead of counted (a power of two, at most 64)
 struct BigLayout {
-    static constexpr int kStage = 64 * 12;                    // per wavefront (whole 128-bit words per lane)
-    static constexpr int kHistA = 0, kHistB = 2048 + 2048 / 64 * 4;
-    static constexpr int kHists = kHistB + 1024 + 1024 / 64 * 4;                // 3264 words
-    static constexpr int kWork = kHists > 4 * kStage ? kHists : 4 * kStage;
-    static constexpr int kOffImgM = 0;                        // per wavefront: its words of each code stream (<= 64, + 1)
-    static constexpr int kOffImgV = 68;
-    static constexpr int kOffTv = 144;                        // level tables, 64-byte aligned
-    static constexpr int kOffTm = 160;
-    static constexpr int kSlab = 176;
+    static constexpr int kStage = 64 * kColStride16;          // per wavefront: staging of the layout transpositions
+    static constexpr int kWork = kBigWaves * kStage;
+    static constexpr int kOffImgM = 0;                        // per wavefront: its words of each code stream
+    static constexpr int kOffImgV = 132;
+    static constexpr int kOffTv = 272;                        // level tables, 64-byte aligned
+    static constexpr int kOffTm = 288;
+    static constexpr int kSlab = 304;
+    // exchange between the wavefronts: block maxima; ranges of two passes; counts of the guess; the
+    // keys that are left
+    static constexpr int kMax = 0, kPass = 4, kCounts = 14, kLeft = 18, kList = 20, kXch = kList + 2 * (int)kFewKeys;
 };
-static_assert(BigLayout::kWork >= kBigWaves * BigLayout::kStage, "the staging areas lie inside the work area");
+static_assert(BigLayout::kWork >= 2048, "the histogram lies inside the work area");
+static_assert(288 * 4 <= BigLayout::kStage, "the padded transposition (Stage16) fits a staging area");
+static_assert(ChunkWords16<3, 4>::kImage <= 132, "images");
 
 // Maximum over the 64 lanes of a wavefront (uniform result).
 __device__ __forceinline__ uint32_t wave_max(uint32_t x)
@@ -86,211 +81,177 @@ __device__ __forceinline__ uint32_t wave_inclusive_sum(uint32_t x)
     return x;
 }
 
-// The rank-th smallest (1-based, uniform over the workgroup) of the NK keys that each thread of
-// the workgroup holds (2048 in all): bit patterns of non-negative floats, +inf for absent elements
-// (the rank never reaches those).  Radix select over 8 + 8 + 8 + 7 bits.  A pass: every thread
-// adds its keys that still match the selected prefix to its counters of the pass's histogram (in
-// `work`, zeroed before the workgroup's first barrier), one barrier, and then one wavefront finds
-// the bin of the rank: a lane sums the counters of its four (two) consecutive bins, a prefix sum
-// over the wavefront names the lane whose bins hold the rank, and that lane's bin sums name the
-// bin; `res` (8 words of LDS) hands bin and rank to the other wavefronts behind a second barrier.
-template <int NK>
-__device__ __forceinline__ uint32_t select_rank(const uint32_t (&key)[NK], uint32_t rank, uint32_t lane, uint32_t wave,
-                                                uint32_t *work, uint32_t *res)
+// Where the selection stands: the rank-th of the `count` keys in [base, base + len).  `guess`: a key
+// of that range which many of them may equal (kNoGuess: none known).
+struct Narrowed { uint32_t base, len, rank, count, guess; };
+constexpr uint32_t kNoGuess = 0xFFFFFFFFu;
+
+// The bin of the histogram (512 bins of 4 counters each, in the halves `half` of its words) that holds
+// the rank-th key, by one wavefront: a lane sums the 32 words of its own 8 bins (128-bit reads in an
+// order that starts neighbouring lanes in different banks), a prefix sum over the wavefront names
+// the lane whose bins hold the rank, and that lane's words are read once more, one per lane, for a
+// second prefix sum that names the bin.  Returns the bin, its rank and its count.
+__device__ __forceinline__ uint32_t find_bin(const uint32_t *const h, const uint32_t half, uint32_t &rank, uint32_t &count,
+                                             const uint32_t lane)
 {
-    uint32_t prefix = 0;
+    const uint32_t first = 32u * lane + 4u * ((lane + (lane >> 2)) & 7u);
+    uint32_t acc = 0;                              // (sums of the halves do not carry: 2048 keys at most)
 #pragma unroll
-    for (int pass = 0; pass < 4; ++pass) {
-        constexpr int kBits[4] = {8, 8, 8, 7}, kShift[4] = {23, 15, 7, 0};      // (bit 31 of a key is 0)
-        const int bits = kBits[pass], sh = kShift[pass];
-        const int lr = pass < 2 ? 3 : 2;                                        // log2(counters per bin)
-        const uint32_t R = 1u << lr;
-        uint32_t *const h = work + (pass < 2 ? BigLayout::kHistA : BigLayout::kHistB);
-        const uint32_t one = (pass & 1) ? 0x10000u : 1u;
-        const uint32_t mine = lane & (R - 1u);
-#pragma unroll
-        for (int j = 0; j < NK; ++j) {
-            const bool match = pass == 0 || (key[j] >> (sh + bits)) == prefix;
-            const uint32_t w = ((((key[j] >> sh) & ((1u << bits) - 1u))) << lr) | mine;
-            if (match) atomicAdd(&h[w + ((w >> 6) << 2)], one);
-        }
-        __syncthreads();
-        // One wavefront finds the bin (wavefronts 0 and 1 take turns) and leaves it and the rank
-        // inside it in LDS for the others: a second barrier costs less than every wavefront
-        // summing the whole histogram for itself.
-        if (wave == (uint32_t)(pass & 1)) {
-            // this lane's bins: 4 of 256 (2 of 128), `per` words from word per * lane, behind the pads in front of it
-            const uint32_t nb = (1u << bits) / 64u;                                 // bins per lane
-            const uint32_t per = nb * R;                                            // words per lane: 32, 32, 16, 8
-            const uint32_t row = per * lane + (((per * lane) >> 6) << 2);
-            uint32_t c[4] = {0, 0, 0, 0};
-#pragma unroll
-            for (uint32_t k = 0; k < nb; ++k) {
-#pragma unroll
-                for (uint32_t i = 0; i < R / 4u; ++i) {
-                    const uint4 c4 = *reinterpret_cast<const uint4 *>(h + row + k * R + 4u * i);
-                    c[k] += (c4.x + c4.y) + (c4.z + c4.w);
-                }
-                c[k] = (pass & 1) ? c[k] >> 16 : c[k] & 0xFFFFu;
-            }
-            const uint32_t s = (c[0] + c[1]) + (c[2] + c[3]);
-            const uint32_t incl = wave_inclusive_sum(s);
-            const uint64_t holder = __builtin_amdgcn_ballot_w64(incl - s < rank && rank <= incl);   // one lane
-            const uint32_t sel = (uint32_t)__builtin_ctzll(holder | (1ull << 63));
-            rank -= (uint32_t)__builtin_amdgcn_readlane((int)(incl - s), (int)sel);
-            uint32_t sel2 = 0;
-#pragma unroll
-            for (uint32_t k = 0; k + 1 < nb; ++k) {
-                const uint32_t e = (uint32_t)__builtin_amdgcn_readlane((int)c[k], (int)sel);
-                if (sel2 == k && rank > e) { rank -= e; sel2 = k + 1; }
-            }
-            if (lane == 0) { res[2 * pass] = sel * nb + sel2; res[2 * pass + 1] = rank; }
-        }
-        __syncthreads();
-        prefix = (prefix << bits) | res[2 * pass];
-        rank = res[2 * pass + 1];
+    for (uint32_t i = 0; i < 8; ++i) {
+        const uint4 c4 = *reinterpret_cast<const uint4 *>(h + (first ^ (4u * i)));
+        acc += (c4.x + c4.y) + (c4.z + c4.w);
     }
-    return prefix;
+    const uint32_t s = (acc >> half) & 0xFFFFu, incl = wave_inclusive_sum(s);
+    const uint32_t sel = (uint32_t)__builtin_ctzll(__builtin_amdgcn_ballot_w64(rank <= incl) | (1ull << 63));
+    rank -= (uint32_t)__builtin_amdgcn_readlane((int)(incl - s), (int)sel);
+    const uint32_t in_row = wave_inclusive_sum((h[32u * sel + (lane & 31u)] >> half) & 0xFFFFu);   // (lanes 0-31 matter)
+    const uint32_t bin = (uint32_t)__builtin_ctzll(__builtin_amdgcn_ballot_w64(rank <= in_row) | (1ull << 31)) / 4u;
+    const uint32_t before = bin ? (uint32_t)__builtin_amdgcn_readlane((int)in_row, (int)(4u * bin - 1u)) : 0u;
+    count = (uint32_t)__builtin_amdgcn_readlane((int)in_row, (int)(4u * bin + 3u)) - before;
+    rank -= before;
+    return 8u * sel + bin;
+}
+
+// One pass of the selection: the keys in the range are counted by (key - base) >> shift, one barrier,
+// one of the two wavefronts (they take turns) finds the bin of the rank and leaves the new range in
+// LDS, a second barrier (it costs less than both wavefronts summing the histogram for themselves).
+// FIRST: every key counts, those below the range in its first bin, and what only a non-finite input
+// can put above it in the last one.
+template <int NK, bool FIRST>
+__device__ __forceinline__ void narrow(Narrowed &at, const uint32_t (&key)[NK], const uint32_t lane, const bool mine,
+                                       uint32_t *const h, const uint32_t half, uint32_t *const res)
+{
+    const uint32_t wide = 32u - (uint32_t)__builtin_clz(at.len - 1u);          // (len > 1)
+    const uint32_t shift = FIRST ? 19u : wide > 9u ? wide - 9u : 0u, one = 1u << half;
+    const uint32_t counter = 4u * (lane & 3u);
+    char *const bytes = reinterpret_cast<char *>(h);
+#pragma unroll
+    for (int j = 0; j < NK; ++j) {
+        const uint32_t d = FIRST ? __builtin_elementwise_sub_sat(key[j], at.base) : key[j] - at.base;
+        const uint32_t bin = FIRST ? umin(d >> shift, 511u) : d >> shift;
+        if (FIRST || d < at.len) atomicAdd(reinterpret_cast<uint32_t *>(bytes + ((bin << 4) | counter)), one);
+    }
+    __syncthreads();
+    if (mine) {
+        uint32_t rank = at.rank, count;
+        const uint32_t bin = find_bin(h, half, rank, count, lane);
+        uint32_t base = at.base, len = at.base + (1u << shift);
+        if (FIRST && bin == 0) {                   // everything below the first bin's end
+            base = 0;
+        } else {
+            const uint32_t begin = bin << shift, left = at.len - begin;
+            base += begin;
+            len = left < (1u << shift) ? left : 1u << shift;
+        }
+        uint32_t guess = kNoGuess;
+        if (FIRST) {                               // do the wavefront's first keys of the new range look all the same?
+            const uint64_t in0 = __builtin_amdgcn_ballot_w64(key[0] - base < len);
+            const uint32_t v = (uint32_t)__builtin_amdgcn_readlane((int)key[0], (int)__builtin_ctzll(in0 | (1ull << 63)));
+            const uint64_t same = __builtin_amdgcn_ballot_w64(key[0] == v) & in0;
+            if (2 * __builtin_popcountll(same) > __builtin_popcountll(in0) + 2) guess = v;
+        }
+        if (lane == 0) { res[0] = base; res[1] = len; res[2] = rank; res[3] = count; if (FIRST) res[4] = guess; }
+    }
+    __syncthreads();
+    at.base = (uint32_t)__builtin_amdgcn_readfirstlane((int)res[0]);
+    at.len = (uint32_t)__builtin_amdgcn_readfirstlane((int)res[1]);
+    at.rank = (uint32_t)__builtin_amdgcn_readfirstlane((int)res[2]);
+    at.count = (uint32_t)__builtin_amdgcn_readfirstlane((int)res[3]);
+    if (FIRST) at.guess = (uint32_t)__builtin_amdgcn_readfirstlane((int)res[4]);
+}
+
+// The keys of the range below the guess and equal to it are counted (by ballot: nothing that many
+// equal keys could slow down); the rank's side of it becomes the range.  Returns whether the guess
+// is the answer.
+template <int NK>
+__device__ __forceinline__ bool try_guess(Narrowed &at, const uint32_t (&key)[NK], const uint32_t lane, const uint32_t wave,
+                                          uint32_t *const counts)
+{
+    uint32_t below = 0, same = 0;
+#pragma unroll
+    for (int j = 0; j < NK; ++j) {
+        below += (uint32_t)__builtin_popcountll(__builtin_amdgcn_ballot_w64(key[j] - at.base < at.guess - at.base));
+        same += (uint32_t)__builtin_popcountll(__builtin_amdgcn_ballot_w64(key[j] == at.guess));
+    }
+    if (lane == 0) { counts[2 * wave] = below; counts[2 * wave + 1] = same; }
+    __syncthreads();
+    below = (uint32_t)__builtin_amdgcn_readfirstlane((int)(counts[0] + counts[2]));
+    same = (uint32_t)__builtin_amdgcn_readfirstlane((int)(counts[1] + counts[3]));
+    if (at.rank <= below) {
+        at.len = at.guess - at.base;
+        at.count = below;
+        return false;
+    }
+    if (at.rank <= below + same) return true;
+    at.rank -= below + same;
+    at.count -= below + same;
+    at.len -= at.guess + 1u - at.base;
+    at.base = at.guess + 1u;
+    return false;
+}
+
+// The rank-th smallest (1-based, uniform over the workgroup) of the NK keys that each thread of the
+// workgroup holds, 2048 in all: bit patterns of non-negative floats, none above kmax.  The first
+// pass counts sixteenths of an octave below the maximum (2^28 consecutive patterns in 512 bins), the
+// next ones 512ths of the bin that holds the rank.  As soon as at most kFewKeys are left, both
+// wavefronts compare those with each other instead: after two passes on scattered values and on
+// the clusters of a trained state.  Elements without a gradient share the few decoded values:
+// then, after the first pass, one of the keys that are left is tried as it is.  A rank below the first pass's range (28
+// octaves under the maximum, or zeros) starts over from 0.
+// (Against four fixed passes over 8 + 8 + 8 + 7 bits, the first of which only told binades apart, on
+// 2^26 elements of 2-bit/3-bit codes: 163.6 -> 153.7 us, with nine of ten gradients at zero
+// 203 -> 140 us, all gradients alike 236 -> 155 us; 72 -> 65 vector instructions per parameter, of
+// which about 15 are the selection.)
+template <int NK>
+__device__ __forceinline__ uint32_t select_rank(const uint32_t (&key)[NK], const uint32_t kmax, const uint32_t rank,
+                                                const uint32_t lane, const uint32_t wave,
+                                                uint32_t *const work, uint32_t *const xch)
+{
+    constexpr uint32_t kReach = 1u << 28;
+    uint32_t *const res = xch + BigLayout::kPass;
+    Narrowed at = {kmax >= kReach ? kmax - (kReach - 1u) : 0u, kReach, rank, (uint32_t)kBigBlock, kNoGuess};
+    narrow<NK, true>(at, key, lane, wave == 0, work, 0, res);
+    if (at.guess != kNoGuess && try_guess<NK>(at, key, lane, wave, xch + BigLayout::kCounts)) return at.guess;
+#pragma unroll 1
+    for (uint32_t pass = 1; at.count > kFewKeys && at.len > 1u; ++pass) {
+        if (pass >= 2) {                           // both halves have been used
+            uint4 *const z = reinterpret_cast<uint4 *>(work);
+            for (uint32_t i = wave * 64u + lane; i < 512u; i += kBigWaves * 64) z[i] = make_uint4(0, 0, 0, 0);
+            __syncthreads();
+        }
+        narrow<NK, false>(at, key, lane, wave == (pass & 1u), work, pass == 1 ? 16u : 0u, res + 5 * (pass & 1u));
+    }
+    if (at.len == 1u) return at.base;
+    // few keys: every wavefront packs its own into LDS, then each lane compares one with all of
+    // them: the answer is the largest key with fewer than `rank` keys below it
+    uint32_t *const list = xch + BigLayout::kList + wave * kFewKeys;
+    uint32_t mine = 0;
+#pragma unroll
+    for (int j = 0; j < NK; ++j) {
+        const bool in = key[j] - at.base < at.len;
+        const uint64_t who = __builtin_amdgcn_ballot_w64(in);
+        const uint32_t to = __builtin_amdgcn_mbcnt_hi((uint32_t)(who >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)who, mine));
+        if (in) list[to & (kFewKeys - 1u)] = key[j];
+        mine += (uint32_t)__builtin_popcountll(who);
+    }
+    if (lane == 0) xch[BigLayout::kLeft + wave] = mine;
+    __syncthreads();
+    const uint32_t first = (uint32_t)__builtin_amdgcn_readfirstlane((int)xch[BigLayout::kLeft]);
+    const uint32_t my = xch[BigLayout::kList + (lane < first ? lane : kFewKeys + lane - first) % (2u * kFewKeys)];
+    uint32_t below = 0;
+    for (uint32_t i = 0; i < at.count; ++i)
+        below += (uint32_t)__builtin_amdgcn_readlane((int)my, (int)i) < my ? 1u : 0u;
+    return wave_max(lane < at.count && below < at.rank ? my : 0u);
 }
 
 // The whole step for block `blk` of 2048 elements (TAIL: the last, shorter block of the buffer,
-// with bounds checks on every element), executed by the four wavefronts of the calling workgroup.
-template <int BM, int BV, bool BF16, bool MDE, bool TAIL, bool EXT>
-__device__ __forceinline__ void step_block_big(const StepArgs &a, const uint64_t blk, const uint32_t lane,
-                                               const uint32_t wave, uint32_t *const slab, uint32_t *const work,
-                                               uint32_t *const xch, const uint32_t *const lds_de)
-{
-    constexpr int L = (1 << (BM - 1)) - 1;
-    constexpr bool kDeTable = MDE && BM >= 3;
-
-    const uint32_t tid = wave * 64u + lane;
-    const uint64_t ew0 = blk * kBigBlock + (uint64_t)wave * kIter;    // first element of this wavefront
-    const uint64_t e0 = ew0 + lane * 8u;                              // first element of this lane
-    uint32_t *const img_m = slab + BigLayout::kOffImgM, *const img_v = slab + BigLayout::kOffImgV;
-    float *const my_tv = reinterpret_cast<float *>(slab + BigLayout::kOffTv);
-    float *const my_tm = reinterpret_cast<float *>(slab + BigLayout::kOffTm);
-    const uint32_t tv_addr = lds_addr(my_tv), tm_addr = lds_addr(my_tm);
-
-    // ---- loads: parameters and gradients, the wavefront's code words, the block's scalars
-    RawPG raw = load_pg<BF16, TAIL>(a, ew0, lane);
-    const float gscale = (EXT && a.grad_scale) ? *a.grad_scale : 1.0f;
-    float4 *const stage = reinterpret_cast<float4 *>(work + wave * BigLayout::kStage);
-    float4 *const st_c = stage + (lane + lane / 8u);
-    float4 *const st_l = stage + (2u * lane + lane / 4u);
-    ChunkWords8<BM, BV, TAIL> words;
-    words.load(a, ew0, lane);
-    const float dm_old = a.m_scale[blk], dv_old = a.v_scale[blk], al_old = a.v_base[blk];
-    words.stage(img_m, img_v, lane);
-
-    // ---- level tables of the block (every wavefront its own copy)
-    {
-        const float de_level = MDE ? DeLevels<BM>::level(lane) : 0.0f;
-        fill_level_tables<BM, BV, MDE, 64>(my_tv, my_tm, lane, dm_old, dv_old, al_old, &de_level);
-    }
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-
-    uint32_t mc8, vc8;
-    words.codes(img_m, img_v, mc8, vc8);
-
-    bool ok[8];
-#pragma unroll
-    for (int j = 0; j < 8; ++j) ok[j] = !TAIL || (e0 + j) < a.n;
-    uint32_t nb = kBigBlock;                       // elements of the block that exist
-    if (TAIL) nb = (uint32_t)(a.n - blk * kBigBlock);
-
-    // ---- coalesced layout -> 8 consecutive elements per lane
-    float p[8], g[8];
-    lane_layout8<BF16, TAIL>(raw, st_c, st_l, p, g);
-    if (EXT) {
-#pragma unroll
-        for (int j = 0; j < 8; ++j) g[j] = __builtin_fmaf(a.l2, p[j], g[j] * gscale);
-    }
-
-    // ---- dequantize (table look-up), EMA, parameter; new parameters streamed out
-    float mh[8], vh[8];
-    float m_absmax, v_max;
-    ema_param<8, BM, BV, EXT, TAIL, true>(a, tm_addr, tv_addr, &mc8, &vc8, ok, p, g, mh, vh, m_absmax, v_max);
-    store_params8<EXT, TAIL>(a, ew0, e0, lane, ok, p, st_c, st_l);
-
-    // ---- the work area becomes the histograms of the selection: a wavefront clears its own staging
-    // area (it is done with it; the others may still be using theirs) and its share of the rest
-    {
-        uint4 *const own = reinterpret_cast<uint4 *>(work + wave * BigLayout::kStage);
-        wave_lds_sync();
-#pragma unroll
-        for (int i = 0; i < BigLayout::kStage / 4 / 64; ++i) own[lane + 64u * (uint32_t)i] = make_uint4(0, 0, 0, 0);
-        constexpr int kRest = (BigLayout::kWork - kBigWaves * BigLayout::kStage) / 4;    // 128-bit words behind the staging areas
-        uint4 *const rest = reinterpret_cast<uint4 *>(work + kBigWaves * BigLayout::kStage);
-        for (uint32_t i = tid; i < (uint32_t)kRest; i += kBigWaves * 64) rest[i] = make_uint4(0, 0, 0, 0);
-    }
-
-    // ---- block maxima over the four wavefronts
-    {
-        const uint32_t wm_max = wave_max(f2u(m_absmax)), wv_max = wave_max(f2u(v_max));
-        if (lane == 0) { xch[wave] = wm_max; xch[4 + wave] = wv_max; }
-    }
-    __syncthreads();
-    float dm = u2f(umax(umax(xch[0], xch[1]), umax(xch[2], xch[3])));
-    float dv = u2f(umax(umax(xch[4], xch[5]), umax(xch[6], xch[7])));
-    if (dm < kTiny) dm = 0.0f;
-    if (dv < kTiny) dv = 0.0f;
-
-    // ---- the r-th smallest v^ of the block
-    uint32_t rank = a.rank_full;
-    if (TAIL) {
-        const float x = __builtin_ceilf(a.quantile_p * (float)nb);
-        rank = x < 1.0f ? 1u : (uint32_t)x;
-        rank = rank > nb ? nb : rank;
-    }
-    uint32_t key[8];
-#pragma unroll
-    for (int j = 0; j < 8; ++j) key[j] = (TAIL && !ok[j]) ? kInfBits : f2u(vh[j]);
-    const uint32_t xp_bits = select_rank<8>(key, rank, lane, wave, work, xch + 8);
-
-    // ---- encoder constants (every 16 lanes for themselves), codes, the wavefront's words
-    const uint32_t lig = lane & 15u, gshift = lane & 16u;
-    uint32_t de_base = 0;
-    if (kDeTable) de_base = lds_addr(lds_de) - 16u * DeBuckets<BM>::kLo;
-    const BlockCodec codec = block_codec<BV, 16, L, MDE>(xp_bits, dm, dv, lane, lig, gshift);
-    uint32_t m8, v8;
-    encode_run<BM, BV, MDE, TAIL>(a, e0, mh, vh, ok, codec, de_base, m8, v8);
-    xor_into_image8<BM, BV>(img_m, img_v, words.wm, words.sm, words.wv, words.sv, mc8 ^ m8, vc8 ^ v8);
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    words.write_back(a, img_m, img_v, lane);
-    if (tid == 0) { a.m_scale[blk] = dm; a.v_scale[blk] = dv; a.v_base[blk] = codec.alpha; }
-}
-
-// ---- the wide form of a full block: two wavefronts, 16 consecutive elements per lane
-//
-// The element-wise part is that of a 1024-element chunk
-// (step_chunk16), the block statistics are those of step_block_big() with two wavefronts instead of
-// four.  What is done once per lane and block (level tables, the two divisions, the base, the
-// hash of a group of eight, the scans of the selection) is spread over twice as many elements, and
-// the scans are run by two wavefronts instead of four.
-constexpr int kWideBigWaves = kBigBlock / kIter16;
-static_assert(kWideBigWaves == 2, "one workgroup of two wavefronts per block");
-
-#ifndef SOLO_BIG_WIDE
-#define SOLO_BIG_WIDE 1            // (tuning builds: 0 runs full blocks on four wavefronts, too)
-#endif
-
-struct WideBigLayout {
-    static constexpr int kStage = 64 * kColStride16;          // per wavefront: staging of the layout transpositions
-    static constexpr int kOffImgM = 0;                        // per wavefront: its words of each code stream (<= 128, + 4)
-    static constexpr int kOffImgV = 132;
-    static constexpr int kOffTv = 272;                        // level tables, 64-byte aligned
-    static constexpr int kOffTm = 288;
-    static constexpr int kSlab = 304;
-};
-static_assert(BigLayout::kWork >= kWideBigWaves * WideBigLayout::kStage, "the staging areas lie inside the work area");
-static_assert(288 * 4 <= WideBigLayout::kStage, "the padded transposition (Stage16) fits a staging area");
-
-template <int BM, int BV, bool BF16, bool MDE, bool EXT>
-__device__ __forceinline__ void step_block_wide(const StepArgs &a, const uint64_t blk, const uint32_t lane,
-                                                const uint32_t wave, uint32_t *const slab, uint32_t *const work,
-                                                uint32_t *const xch, const uint32_t *const lds_de)
+// with bounds checks on every element), executed by the two wavefronts of the calling workgroup.
+// What is done once per lane and block (level tables, the two divisions, the base, the hash of a
+// group of eight) is spread over 16 elements.
+template <int BM, int BV, bool BF16, bool MDE, bool EXT, bool TAIL>
+__device__ __forceinline__ void step_block(const StepArgs &a, const uint64_t blk, const uint32_t lane,
+                                           const uint32_t wave, uint32_t *const slab, uint32_t *const work,
+                                           uint32_t *const xch, const uint32_t *const lds_de)
 {
     constexpr int L = (1 << (BM - 1)) - 1;
     constexpr bool kDeTable = MDE && BM >= 3;
@@ -298,16 +259,19 @@ __device__ __forceinline__ void step_block_wide(const StepArgs &a, const uint64_
     const uint32_t tid = wave * 64u + lane;
     const uint64_t ew0 = blk * kBigBlock + (uint64_t)wave * kIter16;  // first element of this wavefront
     const uint64_t e0 = ew0 + lane * 16u;                             // first element of this lane
-    uint32_t *const img_m = slab + WideBigLayout::kOffImgM, *const img_v = slab + WideBigLayout::kOffImgV;
-    float *const my_tv = reinterpret_cast<float *>(slab + WideBigLayout::kOffTv);
-    float *const my_tm = reinterpret_cast<float *>(slab + WideBigLayout::kOffTm);
+    uint32_t *const img_m = slab + BigLayout::kOffImgM, *const img_v = slab + BigLayout::kOffImgV;
+    float *const my_tv = reinterpret_cast<float *>(slab + BigLayout::kOffTv);
+    float *const my_tm = reinterpret_cast<float *>(slab + BigLayout::kOffTm);
     const uint32_t tv_addr = lds_addr(my_tv), tm_addr = lds_addr(my_tm);
+    bool ok[16];                                   // the lane's elements that exist
+#pragma unroll
+    for (int j = 0; j < 16; ++j) ok[j] = !TAIL || e0 + j < a.n;
 
     // ---- loads: parameters and gradients, the wavefront's code words, the block's scalars
-    RawPG16<BF16> raw = load_pg16<BF16>(a, ew0, lane);
+    const RawPG16<BF16> raw = load_pg16<BF16, TAIL>(a, ew0, lane);
     const float gscale = (EXT && a.grad_scale) ? *a.grad_scale : 1.0f;
-    const Stage16 st(reinterpret_cast<float4 *>(work + wave * WideBigLayout::kStage), lane);
-    ChunkWords16<BM, BV> words;
+    const Stage16 st(reinterpret_cast<float4 *>(work + wave * BigLayout::kStage), lane);
+    ChunkWords16<BM, BV, TAIL> words;
     words.load(a, ew0, lane);
     const float dm_old = a.m_scale[blk], dv_old = a.v_scale[blk], al_old = a.v_base[blk];
     words.stage(img_m, img_v, lane);
@@ -317,15 +281,13 @@ __device__ __forceinline__ void step_block_wide(const StepArgs &a, const uint64_
         const float de_level = MDE ? DeLevels<BM>::level(lane) : 0.0f;
         fill_level_tables<BM, BV, MDE, 64>(my_tv, my_tm, lane, dm_old, dv_old, al_old, &de_level);
     }
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-
+    wave_lds_sync();
     uint32_t mc8[2], vc8[2];
     words.codes(img_m, img_v, mc8, vc8);
 
     // ---- coalesced layout -> 16 consecutive elements per lane
     float p[16], g[16];
-    lane_layout16<BF16>(raw, st, p, g);
+    lane_layout16<BF16, TAIL>(raw, st, p, g);
     if (EXT) {
 #pragma unroll
         for (int j = 0; j < 16; ++j) g[j] = __builtin_fmaf(a.l2, p[j], g[j] * gscale);
@@ -334,165 +296,143 @@ __device__ __forceinline__ void step_block_wide(const StepArgs &a, const uint64_
     // ---- dequantize (table look-up), EMA, parameter; new parameters streamed out
     float mh[16], vh[16];
     float m_absmax, v_max;
-    ema_param<16, BM, BV, EXT, false, true>(a, tm_addr, tv_addr, mc8, vc8, nullptr, p, g, mh, vh, m_absmax, v_max);
-    store_params16<EXT>(a, ew0, lane, p, st);
+    ema_param<16, BM, BV, EXT, TAIL, true>(a, tm_addr, tv_addr, mc8, vc8, ok, p, g, mh, vh, m_absmax, v_max);
+    store_params16<EXT, TAIL>(a, ew0, lane, p, st);
 
     // ---- the work area becomes the histograms of the selection: a wavefront clears its own staging
-    // area (it is done with it; the other may still be using its own) and its share of the rest
+    // area (it is done with it; the other may still be using its own)
     {
-        uint4 *const own = reinterpret_cast<uint4 *>(work + wave * WideBigLayout::kStage);
+        uint4 *const own = reinterpret_cast<uint4 *>(work + wave * BigLayout::kStage);
         wave_lds_sync();
-        constexpr int kOwn = WideBigLayout::kStage / 4;                                     // 128-bit words
+        constexpr int kOwn = BigLayout::kStage / 4;                                     // 128-bit words
 #pragma unroll
         for (int i = 0; i < (kOwn + 63) / 64; ++i)
             if (lane + 64u * (uint32_t)i < (uint32_t)kOwn) own[lane + 64u * (uint32_t)i] = make_uint4(0, 0, 0, 0);
-        constexpr int kRest = (BigLayout::kWork - kWideBigWaves * WideBigLayout::kStage) / 4;
-        uint4 *const rest = reinterpret_cast<uint4 *>(work + kWideBigWaves * WideBigLayout::kStage);
-        for (uint32_t i = tid; i < (uint32_t)kRest; i += kWideBigWaves * 64) rest[i] = make_uint4(0, 0, 0, 0);
     }
 
     // ---- block maxima over the two wavefronts
     {
         const uint32_t wm_max = wave_max(f2u(m_absmax)), wv_max = wave_max(f2u(v_max));
-        if (lane == 0) { xch[wave] = wm_max; xch[2 + wave] = wv_max; }
+        if (lane == 0) { xch[BigLayout::kMax + wave] = wm_max; xch[BigLayout::kMax + 2 + wave] = wv_max; }
     }
     __syncthreads();
-    float dm = u2f(umax(xch[0], xch[1]));
-    float dv = u2f(umax(xch[2], xch[3]));
+    float dm = u2f(umax(xch[BigLayout::kMax], xch[BigLayout::kMax + 1]));
+    const uint32_t kmax = (uint32_t)__builtin_amdgcn_readfirstlane(
+        (int)umax(xch[BigLayout::kMax + 2], xch[BigLayout::kMax + 3]));
+    float dv = u2f(kmax);
     if (dm < kTiny) dm = 0.0f;
     if (dv < kTiny) dv = 0.0f;
 
     // ---- the r-th smallest v^ of the block
+    uint32_t rank = a.rank_full;
+    if (TAIL) {
+        const uint32_t nb = (uint32_t)(a.n - blk * kBigBlock);
+        const float x = __builtin_ceilf(a.quantile_p * (float)nb);
+        rank = x < 1.0f ? 1u : (uint32_t)x;
+        rank = rank > nb ? nb : rank;
+    }
     uint32_t key[16];
 #pragma unroll
-    for (int j = 0; j < 16; ++j) key[j] = f2u(vh[j]);
-    const uint32_t xp_bits = select_rank<16>(key, a.rank_full, lane, wave, work, xch + 8);
+    for (int j = 0; j < 16; ++j) key[j] = TAIL && !ok[j] ? kmax : f2u(vh[j]);   // (absent: further maxima, which no rank reaches)
+    const uint32_t xp_bits = select_rank<16>(key, kmax, rank, lane, wave, work, xch);
 
     // ---- encoder constants (every 16 lanes for themselves), codes, the wavefront's words
     const uint32_t lig = lane & 15u, gshift = lane & 16u;
     uint32_t de_base = 0;
     if (kDeTable) de_base = lds_addr(lds_de) - 16u * DeBuckets<BM>::kLo;
     const BlockCodec codec = block_codec<BV, 16, L, MDE>(xp_bits, dm, dv, lane, lig, gshift);
-    encode_into_image16<BM, BV, MDE>(a, e0, mh, vh, codec, de_base, img_m, img_v,
-                                     words.wm, words.sm, words.wv, words.sv, mc8, vc8);
+    encode_into_image16<BM, BV, MDE, TAIL>(a, e0, mh, vh, ok, codec, de_base, img_m, img_v,
+                                           words.wm, words.sm, words.wv, words.sv, mc8, vc8);
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     __builtin_amdgcn_wave_barrier();
     words.write_back(a, img_m, img_v, lane);
     if (tid == 0) { a.m_scale[blk] = dm; a.v_scale[blk] = dv; a.v_base[blk] = codec.alpha; }
 }
 
-// One workgroup of two wavefronts per full block of 2048 elements.
 // (Registers: the plain step with bf16 gradients fits five wavefronts per SIMD without spilling,
 // except with two ten-to-a-word streams; LDS allows five for every format.)
 template <int BM, int BV, bool BF16, bool EXT>
-constexpr int big_wide_waves() { return (BF16 && !EXT && !(BM == 3 && BV == 3)) ? kMinWaves : kMinWaves - 1; }
+constexpr int big_waves() { return (BF16 && !EXT && !(BM == 3 && BV == 3)) ? kMinWaves : kMinWaves - 1; }
 
-template <int BM, int BV, bool BF16, bool MDE, bool EXT>
-__global__ __launch_bounds__(kWideBigWaves * 64, (big_wide_waves<BM, BV, BF16, EXT>()))
-void big_wide_kernel(const StepArgs a)
+#define SOLO_BIG_LDS                                                                                   \
+    constexpr int kDeWords = de_words<BM, MDE>();                                                      \
+    __shared__ __attribute__((aligned(64))) uint32_t lds_work[BigLayout::kWork];                       \
+    __shared__ __attribute__((aligned(64))) uint32_t lds_slab[kBigWaves * BigLayout::kSlab];           \
+    __shared__ __attribute__((aligned(64))) uint32_t lds_xch[BigLayout::kXch];                         \
+    __shared__ __attribute__((aligned(64))) uint32_t lds_de[kDeWords]
+
+// The kernel's arguments, loaded behind this point.  The bounds-checked code needs far more scalar
+// registers than there are; arguments loaded in front of the branch to it would be spilled for the
+// full blocks, too (86 vector instructions per 16 elements).
+template <typename T>
+__device__ __forceinline__ T arguments_here()
 {
-    constexpr int kDeWords = de_words<BM, MDE>();
-    __shared__ __attribute__((aligned(64))) uint32_t lds_work[BigLayout::kWork];
-    __shared__ __attribute__((aligned(64))) uint32_t lds_slab[kWideBigWaves * WideBigLayout::kSlab];
-    __shared__ __attribute__((aligned(64))) uint32_t lds_xch[16];   // block maxima; bin and rank of every pass
-    __shared__ __attribute__((aligned(64))) uint32_t lds_de[kDeWords];
-    load_de_table<BM, MDE, kDeWords>(lds_de);
-    const uint32_t lane = threadIdx.x & 63u;
-    const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    step_block_wide<BM, BV, BF16, MDE, EXT>(a, blockIdx.x, lane, wave, lds_slab + wave * WideBigLayout::kSlab,
-                                            lds_work, lds_xch, lds_de);
+    typedef const __attribute__((address_space(4))) T arg_t;
+    arg_t *p = (arg_t *)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(p));
+    T a;
+    __builtin_memcpy(&a, (const T *)p, sizeof(T));
+    return a;
 }
 
-// One workgroup of four wavefronts per block of 2048 elements, from block a.block0 on.
+// One workgroup of two wavefronts per block; the shorter last block, if there is one, is block 0 of
+// the grid.
 template <int BM, int BV, bool BF16, bool MDE, bool EXT>
-__global__ __launch_bounds__(kBigWaves * 64, kMinWaves)
-void big_kernel(const StepArgs a)
+__global__ __launch_bounds__(kBigWaves * 64, (big_waves<BM, BV, BF16, EXT>()))
+void big_kernel(const StepArgs args)
 {
-    constexpr int kDeWords = de_words<BM, MDE>();
-    __shared__ __attribute__((aligned(64))) uint32_t lds_work[BigLayout::kWork];
-    __shared__ __attribute__((aligned(64))) uint32_t lds_slab[kBigWaves * BigLayout::kSlab];
-    __shared__ __attribute__((aligned(64))) uint32_t lds_xch[16];   // block maxima; bin and rank of every pass
-    __shared__ __attribute__((aligned(64))) uint32_t lds_de[kDeWords];
+    SOLO_BIG_LDS;
     load_de_table<BM, MDE, kDeWords>(lds_de);
     const uint32_t lane = threadIdx.x & 63u;
     const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    const uint64_t blk = a.block0 + blockIdx.x;
     uint32_t *const slab = lds_slab + wave * BigLayout::kSlab;
-    if constexpr (!SOLO_BIG_WIDE) {
-        if ((blk + 1) * kBigBlock <= a.n) {
-            step_block_big<BM, BV, BF16, MDE, false, EXT>(a, blk, lane, wave, slab, lds_work, lds_xch, lds_de);
-            return;
-        }
+    const uint32_t ragged = (uint32_t)args.rest;
+    if (blockIdx.x < ragged) {
+        const StepArgs a = arguments_here<StepArgs>();
+        step_block<BM, BV, BF16, MDE, EXT, true>(a, a.n / kBigBlock, lane, wave, slab, lds_work, lds_xch, lds_de);
+    } else {
+        const StepArgs a = arguments_here<StepArgs>();
+        step_block<BM, BV, BF16, MDE, EXT, false>(a, blockIdx.x - ragged, lane, wave, slab, lds_work, lds_xch, lds_de);
     }
-    step_block_big<BM, BV, BF16, MDE, true, EXT>(a, blk, lane, wave, slab, lds_work, lds_xch, lds_de);
 }
 
 // The step over many tensors in one launch, blocks of 2048 elements.  The map of the table holds
-// one entry per block of every tensor (the tensor's index; a shorter last block is flagged).  A
-// workgroup of multi_big_wide_kernel takes one entry and, unless it is flagged, runs the full
-// block; workgroup k of multi_big_tail_kernel runs the shorter last block of tensor k, if it has
-// one.  Blocks never span tensors.
+// one entry per block of every tensor (the tensor's index; a shorter last block is flagged).
+// Blocks never span tensors.
 template <int BM, int BV, bool BF16, bool MDE, bool EXT>
-__global__ __launch_bounds__(kWideBigWaves * 64, (big_wide_waves<BM, BV, BF16, EXT>()))
-void multi_big_wide_kernel(const MultiArgs ma)
+__global__ __launch_bounds__(kBigWaves * 64, (big_waves<BM, BV, BF16, EXT>()))
+void multi_big_kernel(const MultiArgs args)
 {
-    constexpr int kDeWords = de_words<BM, MDE>();
-    __shared__ __attribute__((aligned(64))) uint32_t lds_work[BigLayout::kWork];
-    __shared__ __attribute__((aligned(64))) uint32_t lds_slab[kWideBigWaves * WideBigLayout::kSlab];
-    __shared__ __attribute__((aligned(64))) uint32_t lds_xch[16];
-    __shared__ __attribute__((aligned(64))) uint32_t lds_de[kDeWords];
-    const uint64_t unit = blockIdx.x;
-    if (unit >= ma.total_units) return;
-    const uint32_t me = ma.unit_map[unit];                      // uniform: scalar loads
-    if (me & kMapRagged) return;                                // (the whole workgroup: no barrier has been reached)
+    SOLO_BIG_LDS;
     load_de_table<BM, MDE, kDeWords>(lds_de);
+    const uint32_t me = args.unit_map[blockIdx.x];              // uniform: scalar loads
+    const uint32_t lane = threadIdx.x & 63u;
+    const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    uint32_t *const slab = lds_slab + wave * BigLayout::kSlab;
+    const MultiArgs ma = arguments_here<MultiArgs>();
     const TensorEntry &e = ma.entries[me & kMapTensorMask];
-    const StepArgs a = tensor_args(ma, e);
-    const uint32_t lane = threadIdx.x & 63u;
-    const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    step_block_wide<BM, BV, BF16, MDE, EXT>(a, unit - e.unit0, lane, wave, lds_slab + wave * WideBigLayout::kSlab,
-                                            lds_work, lds_xch, lds_de);
+    const uint64_t blk = blockIdx.x - e.unit0;
+    if (me & kMapRagged) {
+        StepArgs a = tensor_args(ma, e);
+        step_block<BM, BV, BF16, MDE, EXT, true>(a, blk, lane, wave, slab, lds_work, lds_xch, lds_de);
+    } else {
+        step_block<BM, BV, BF16, MDE, EXT, false>(tensor_args(ma, e), blk, lane, wave, slab, lds_work, lds_xch, lds_de);
+    }
 }
-
-template <int BM, int BV, bool BF16, bool MDE>
-__global__ __launch_bounds__(kBigWaves * 64, kMinWaves)
-void multi_big_tail_kernel(const MultiArgs ma, const uint32_t count)
-{
-    constexpr int kDeWords = de_words<BM, MDE>();
-    __shared__ __attribute__((aligned(64))) uint32_t lds_work[BigLayout::kWork];
-    __shared__ __attribute__((aligned(64))) uint32_t lds_slab[kBigWaves * BigLayout::kSlab];
-    __shared__ __attribute__((aligned(64))) uint32_t lds_xch[16];
-    __shared__ __attribute__((aligned(64))) uint32_t lds_de[kDeWords];
-    if (blockIdx.x >= count) return;
-    const TensorEntry &e = ma.entries[blockIdx.x];
-    if (e.n % kBigBlock == 0) return;                           // (the whole workgroup)
-    load_de_table<BM, MDE, kDeWords>(lds_de);
-    const StepArgs a = tensor_args(ma, e);
-    const uint32_t lane = threadIdx.x & 63u;
-    const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    step_block_big<BM, BV, BF16, MDE, true, true>(a, e.n / kBigBlock, lane, wave, lds_slab + wave * BigLayout::kSlab,
-                                                  lds_work, lds_xch, lds_de);
-}
+#undef SOLO_BIG_LDS
 
 template <int BM, bool MDE>
-hipError_t launch_multi_big(uint32_t bits_v, bool bf16, const MultiArgs &args, uint32_t count, bool ragged,
-                            hipStream_t stream);
+hipError_t launch_multi_big(uint32_t bits_v, bool bf16, const MultiArgs &args, hipStream_t stream);
 
 template <int BM, bool MDE>
-hipError_t launch_multi_big_impl(uint32_t bits_v, bool bf16, const MultiArgs &args, uint32_t count, bool ragged,
-                                 hipStream_t stream)
+hipError_t launch_multi_big_impl(uint32_t bits_v, bool bf16, const MultiArgs &args, hipStream_t stream)
 {
-    if (args.total_units == 0 || args.total_units > 0x7FFFFFFFull || count == 0) return hipErrorInvalidValue;
+    if (args.total_units == 0 || args.total_units > 0x7FFFFFFFull) return hipErrorInvalidValue;
     const StepArgs &c = args.common;
     const bool ext = args.any_bf16_copy || c.grad_scale || c.belief || c.l2 != 0.0f;
 #define SOLO_LAUNCH(BV_, BF_, EXT_)                                                                 \
-    do {                                                                                            \
-        hipLaunchKernelGGL((multi_big_wide_kernel<BM, BV_, BF_, MDE, EXT_>), dim3((uint32_t)args.total_units), \
-                           dim3(kWideBigWaves * 64), 0, stream, args);                              \
-        if (ragged)                                                                                 \
-            hipLaunchKernelGGL((multi_big_tail_kernel<BM, BV_, BF_, MDE>), dim3(count),             \
-                               dim3(kBigWaves * 64), 0, stream, args, count);                       \
-    } while (0)
+    hipLaunchKernelGGL((multi_big_kernel<BM, BV_, BF_, MDE, EXT_>), dim3((uint32_t)args.total_units), \
+                       dim3(kBigWaves * 64), 0, stream, args)
 #define SOLO_CASE(BV_)                                                                              \
     if (bits_v == BV_) {                                                                            \
         if (bf16) { if (ext) SOLO_LAUNCH(BV_, true, true); else SOLO_LAUNCH(BV_, true, false); }    \
@@ -508,26 +448,17 @@ hipError_t launch_multi_big_impl(uint32_t bits_v, bool bf16, const MultiArgs &ar
 template <int BM, bool MDE>
 hipError_t launch_big(uint32_t bits_v, bool bf16, const StepArgs &args, hipStream_t stream);
 
-// Full blocks run on two wavefronts each; a shorter last block is a launch of its own, one
-// workgroup of four wavefronts with bounds checks on every element.
 template <int BM, bool MDE>
-hipError_t launch_big_impl(uint32_t bits_v, bool bf16, const StepArgs &args, hipStream_t stream)
+hipError_t launch_big_impl(uint32_t bits_v, bool bf16, const StepArgs &args_in, hipStream_t stream)
 {
-    const uint64_t full = args.n / kBigBlock, blocks = (args.n + kBigBlock - 1) / kBigBlock;
+    StepArgs args = args_in;
+    const uint64_t blocks = (args.n + kBigBlock - 1) / kBigBlock;
     if (blocks == 0 || blocks > 0x7FFFFFFFull) return hipErrorInvalidValue;
+    args.rest = args.n % kBigBlock ? 1 : 0;
     const bool ext = args.param_bf16 || args.grad_scale || args.belief || args.l2 != 0.0f;
-    const uint64_t wide_blocks = SOLO_BIG_WIDE ? full : 0;
-    StepArgs rest = args;
-    rest.block0 = wide_blocks;               // the four-wavefront kernel starts behind them
 #define SOLO_LAUNCH(BV_, BF_, EXT_)                                                                 \
-    do {                                                                                            \
-        if (wide_blocks)                                                                            \
-            hipLaunchKernelGGL((big_wide_kernel<BM, BV_, BF_, MDE, EXT_>), dim3((uint32_t)wide_blocks),    \
-                               dim3(kWideBigWaves * 64), 0, stream, args);                          \
-        if (blocks > wide_blocks)                                                                   \
-            hipLaunchKernelGGL((big_kernel<BM, BV_, BF_, MDE, EXT_>), dim3((uint32_t)(blocks - wide_blocks)), \
-                               dim3(kBigWaves * 64), 0, stream, rest);                              \
-    } while (0)
+    hipLaunchKernelGGL((big_kernel<BM, BV_, BF_, MDE, EXT_>), dim3((uint32_t)blocks),               \
+                       dim3(kBigWaves * 64), 0, stream, args)
 #define SOLO_CASE(BV_)                                                                              \
     if (bits_v == BV_) {                                                                            \
         if (bf16) { if (ext) SOLO_LAUNCH(BV_, true, true); else SOLO_LAUNCH(BV_, true, false); }    \

@@ -1,5 +1,5 @@
 """GPU parity of the kernels that give a lane 16 elements: flat buffers of more than 3 * 2^18
-elements, and tables of more units than that.  Same bar as test_gpu_parity.py."""
+elements, tables of more units than that, blocks of 2048.  Same bar as test_gpu_parity.py."""
 import numpy as np
 import pytest
 
@@ -90,3 +90,32 @@ def test_tables(gpu, bm, bv, B, bf16, de, ext):  # noqa: F811
         assert h is None or torch.equal(hs[k].view(torch.int16), h.view(torch.int16)), sizes[k]
         for a, b in zip(sts[k].buffers(), st.buffers()):
             assert torch.equal(a.view(torch.int32), b.view(torch.int32)), sizes[k]
+
+
+@pytest.mark.parametrize("p", (0.0, 0.1, 0.5, 0.97))
+@pytest.mark.parametrize("bm,bv,tail", [(2, 3, 1), (4, 4, 1030), (3, 2, 2047), (2, 2, 0)])
+def test_selection_in_blocks_of_2048(so, gpu, bm, bv, tail, p):  # noqa: F811
+    """The quantile of a large block over everything its passes tell apart: scattered values, clusters,
+    many equal values, zeros, magnitudes far below the maximum (below the first pass's range), and
+    a shorter last block of each kind."""
+    from paper_2505_00347_amd import synth
+    n = 14 * 2048 + tail
+    rng = np.random.default_rng(bm * 100 + bv)
+    kind = (np.arange(n) // 2048 + tail) % 7
+    for de in (False, True):
+        oc, gc = make_cfgs(so, gpu, bm, bv, 2048, False, p=p, de=de)
+        prm, st = synth.make_params(n), so.State(n, oc)
+        side = GpuSide(gpu, n, gc)
+        flips = 0
+        for step in range(1, 7):
+            x = rng.standard_normal(n).astype(np.float32)
+            far = x * 10.0 ** rng.uniform(-11, 3, n)
+            g = np.select([kind == 0, kind == 1, kind == 2, kind == 3, kind == 4, kind == 5],
+                          [x, far, np.where(rng.random(n) < 0.5, 0.0, far), np.where(rng.random(n) < 0.9, 0.0, x),
+                           np.rint(x), np.full(n, 1.0)], np.zeros(n)).astype(np.float32) * np.float32(1e-3)
+            side.load(prm, st)
+            side.step(dev(g), step)
+            before = prm.astype(np.float64)
+            margin = so.step_packed(prm, g, st, step, oc, want_margin=True, threads=8)
+            flips += compare_step(so, oc, n, prm, st, margin, side.fetch(), 1e-6, 2e-6 * oc.lr, p_before=before)
+        assert flips <= flip_budget(6 * n)
