@@ -340,9 +340,11 @@ def main():
     # the kernel that takes the time (the library picks it from the format, the size and the launch)
     if w.block_size == 2048:
         kernel_name = "solo::multi_big_kernel" if args.launch == "multi" else "solo::big_kernel"
+    elif args.launch == "multi":
+        kernel_name = f"solo::multi_chunk{8 if n <= 3 << 18 else 16}_kernel"
     else:
-        per_lane = 8 if n <= 3 << 18 else 16
-        kernel_name = f"solo::{'multi_' if args.launch == 'multi' else ''}chunk{per_lane}_kernel"
+        up_to = 5 << 20 if w.grad_dtype != "bf16" else 3 << 18 if mp else 3 << 20
+        kernel_name = f"solo::chunk{8 if n <= up_to else 16}_kernel"
     out = {
         "metric": "updated_params_per_sec", "value": n / (wall / args.steps), "unit": "params/s",
         "n_gpus": 1, "steps": args.steps, "warmup": args.warmup, "ms_per_step": ms_per_step,

@@ -11,11 +11,12 @@
 //
 // Which of the two: what is done once per lane and block (level tables, maxima, divisions, the
 // base, the hash, packing) is spread over twice as many elements with 16 per lane, so that form
-// needs an eighth fewer instructions and is the faster one as soon as there is work for every
-// SIMD; a buffer that is shorter than that takes the latency of one wavefront, and 8 elements
-// per lane have the shorter one (narrow_up_to()).  The ragged end of a buffer always runs the
-// 8-per-lane form with bounds checks.  chunk8_kernel and chunk16_kernel run over a flat buffer,
-// multi_chunk8_kernel and multi_chunk16_kernel over the tensors of a caller-built table.
+// needs an eighth fewer instructions and is the faster one as soon as there is work for several
+// rounds of wavefronts on every SIMD; a buffer that is shorter than that takes the latency of one
+// wavefront, and 8 elements per lane have the shorter one (narrow_up_to()).  The ragged end of a
+// buffer always runs the 8-per-lane form with bounds checks.  chunk8_kernel and chunk16_kernel run
+// over a flat buffer, multi_chunk8_kernel and multi_chunk16_kernel over the tensors of a
+// caller-built table.
 //
 // (Measured against one wavefront that walks a super-tile of 5120 elements in five iterations
 // and prefetches one iteration ahead, the form of the large bf16 buffers before: 2^24 elements
@@ -465,29 +466,28 @@ __device__ __forceinline__ uint32_t pack_bf16(float lo, float hi)
 
 template <bool V> struct BoolTag { static constexpr bool value = V; };
 
-// Parameters and gradients of one lane and iteration as they come from memory.  In the
-// full-tile kernel the fp32 streams arrive in the coalesced layout (lane l holds elements
-// 4l..4l+3 and 256+4l..256+4l+3 of the 512-element chunk) and are transposed through LDS
-// to the lane's 8 consecutive elements; bf16 gradients (16 bytes per lane) already are
-// both.  The tail kernel loads element by element with bounds checks.
+// Parameters and gradients of a lane's 8 consecutive elements: two (bf16 gradients: one) 16-byte
+// accesses per lane and stream.  A wavefront's access then covers every other 16 bytes of its two
+// kilobytes, twice the requests of a coalesced one, but nothing has to be turned around through LDS:
+// the code for 8 elements per lane runs where a launch is all latency (the transposition and its
+// waits were 500 of the 6400-7200 cycles of a wavefront).  TAIL: element by element, bounds-checked.
 struct RawPG { float4 p0, p1; uint4 g0, g1; };
 
 template <bool BF16, bool TAIL>
-__device__ __forceinline__ RawPG load_pg(const StepArgs &a, uint64_t chunk_e0, uint32_t lane)
+__device__ __forceinline__ RawPG load_pg(const StepArgs &a, const uint64_t e0)
 {
     RawPG r;
+    r.g1 = make_uint4(0, 0, 0, 0);
     if (!TAIL) {
-        const float *pp = a.param + chunk_e0 + lane * 4u;
-        r.p0 = stream_load_f4(pp); r.p1 = stream_load_f4(pp + 256);
+        const float4 *pp = reinterpret_cast<const float4 *>(a.param + e0);
+        r.p0 = pp[0]; r.p1 = pp[1];
         if (BF16) {
-            r.g0 = stream_load_u4(static_cast<const uint16_t *>(a.grad) + chunk_e0 + lane * 8u);
-            r.g1 = make_uint4(0, 0, 0, 0);
+            r.g0 = *reinterpret_cast<const uint4 *>(static_cast<const uint16_t *>(a.grad) + e0);
         } else {
-            const float *gp = static_cast<const float *>(a.grad) + chunk_e0 + lane * 4u;
-            r.g0 = stream_load_u4(gp); r.g1 = stream_load_u4(gp + 256);
+            const uint4 *gp = reinterpret_cast<const uint4 *>(static_cast<const float *>(a.grad) + e0);
+            r.g0 = gp[0]; r.g1 = gp[1];
         }
-    } else {                                   // element-wise, bounds-checked
-        const uint64_t e0 = chunk_e0 + lane * 8u;
+    } else {
         float p[8]; uint32_t g[8];
 #pragma unroll
         for (int j = 0; j < 8; ++j) {
@@ -497,7 +497,7 @@ __device__ __forceinline__ RawPG load_pg(const StepArgs &a, uint64_t chunk_e0, u
             else      g[j] = ok ? static_cast<const uint32_t *>(a.grad)[e0 + j] : 0u;
         }
         r.p0 = make_float4(p[0], p[1], p[2], p[3]); r.p1 = make_float4(p[4], p[5], p[6], p[7]);
-        if (BF16) { r.g0 = make_uint4(g[0] | (g[1] << 16), g[2] | (g[3] << 16), g[4] | (g[5] << 16), g[6] | (g[7] << 16)); r.g1 = make_uint4(0, 0, 0, 0); }
+        if (BF16) r.g0 = make_uint4(g[0] | (g[1] << 16), g[2] | (g[3] << 16), g[4] | (g[5] << 16), g[6] | (g[7] << 16));
         else      { r.g0 = make_uint4(g[0], g[1], g[2], g[3]); r.g1 = make_uint4(g[4], g[5], g[6], g[7]); }
     }
     return r;
@@ -518,13 +518,26 @@ constexpr int m_table_stride() { return BM == 2 ? 4 : BM == 3 ? 8 : 16; }   // a
 template <int BM, bool MDE>
 constexpr int de_words() { return MDE && BM >= 3 ? 4 * DeBuckets<BM>::N : 16; }
 
-// Up to how many elements a flat buffer (or the units of a table) runs 8 elements per lane.
-// Measured on MI355X, us per launch, 8 | 16 per lane:
-//                        2^18          2^19          2^20          2^21
-//   2-bit/3-bit bf16     5.30 | 5.90   5.72 | 6.09   6.89 | 6.39   9.12 | 8.25
-//   4-bit/4-bit fp32     4.72 | 5.53   5.39 | 5.67   6.36 | 5.87   8.48 | 7.94
-//   3-bit/3-bit DE B 64  5.12 | 6.24   5.63 | 6.37   6.72 | 6.63   9.02 | 8.54
-constexpr uint64_t narrow_up_to() { return 3ull << 18; }
+// Up to how many elements a flat buffer runs 8 elements per lane, for a quantile of rank `rank` in a
+// full block; `copy`: a bf16 copy of the parameters is written.  Measured on MI355X over six
+// states in turn, us per launch, 8 | 16 per lane:
+//                                    2^19          2^20          2^21          2^22            2^23
+//   2-bit/3-bit bf16                 5.48 | 6.45   6.65 | 6.75   8.98 | 9.04   13.34 | 13.34   22.94 | 21.36
+//   4-bit/2-bit DE bf16, copy        5.85 | 6.70   7.59 | 6.99   10.70 | 9.75  16.27 | 15.90   29.16 | 26.04
+//   4-bit/4-bit fp32                 5.08 | 5.87   6.53 | 6.24   9.37 | 9.84   14.08 | 14.93   26.85 | 24.64
+//   3-bit/3-bit DE fp32, B 64        5.18 | 6.85   6.82 | 7.21   9.20 | 10.66  13.81 | 15.15   25.69 | 25.49
+//   2-bit/3-bit bf16, rank 39        7.63 | 7.79   9.24 | 8.13   11.83 | 10.74 17.99 | 15.59   29.51 | 24.42
+//   3-bit/4-bit fp32, B 64, rank 20  5.80 | 6.63   7.10 | 7.01   10.07 | 10.78 15.46 | 15.91   27.09 | 26.17
+// The form with 8 saves layout transpositions, most of them with fp32 gradients; its rounds of the
+// selection cost twice the instructions, which a large rank makes the larger part.
+constexpr uint64_t narrow_up_to(bool bf16, bool copy, uint32_t rank)
+{
+    if (rank > 24) return 1ull << 19;
+    if (!bf16) return 5ull << 20;
+    return copy ? 3ull << 18 : 3ull << 20;
+}
+// Up to how many elements in its units a table does (there the ragged ends leave wavefronts idle).
+constexpr uint64_t narrow_table_up_to() { return 3ull << 18; }
 
 // The lowest set bit of every G-bit field of a ballot, one field per group of lanes.  Every field
 // has a bit set (the lanes whose key equals the group's minimum), so ~h + 1 does not carry out of
@@ -777,39 +790,19 @@ __device__ __forceinline__ void fill_level_tables(float *const my_tv, float *con
 }
 
 
-// A lane's 8 consecutive elements out of the coalesced layout they were loaded in, through the
-// wavefront's staging area: st_c = stage + lane + lane / 8 (coalesced slots st_c[0], st_c[72]),
-// st_l = stage + 2 lane + lane / 4 (the lane's own two vectors).  TAIL: loaded per lane already.
-template <bool BF16, bool TAIL>
-__device__ __forceinline__ void lane_layout8(const RawPG &raw, float4 *const st_c, float4 *const st_l,
-                                             float (&p)[8], float (&g)[8])
+template <bool BF16>
+__device__ __forceinline__ void unpack_pg(const RawPG &raw, float (&p)[8], float (&g)[8])
 {
-    float4 pa = raw.p0, pb = raw.p1;
-    uint4 ga = raw.g0, gb = raw.g1;
-    if (!TAIL) {                       // coalesced layout -> 8 consecutive elements per lane
-        st_c[0] = pa; st_c[72] = pb;
-        wave_lds_sync();
-        pa = st_l[0]; pb = st_l[1];
-        if (!BF16) {
-            wave_lds_sync();
-            st_c[0] = make_float4(u2f(ga.x), u2f(ga.y), u2f(ga.z), u2f(ga.w));
-            st_c[72] = make_float4(u2f(gb.x), u2f(gb.y), u2f(gb.z), u2f(gb.w));
-            wave_lds_sync();
-            const float4 t0 = st_l[0], t1 = st_l[1];
-            ga = make_uint4(f2u(t0.x), f2u(t0.y), f2u(t0.z), f2u(t0.w));
-            gb = make_uint4(f2u(t1.x), f2u(t1.y), f2u(t1.z), f2u(t1.w));
-        }
-    }
-    p[0] = pa.x; p[1] = pa.y; p[2] = pa.z; p[3] = pa.w;
-    p[4] = pb.x; p[5] = pb.y; p[6] = pb.z; p[7] = pb.w;
+    p[0] = raw.p0.x; p[1] = raw.p0.y; p[2] = raw.p0.z; p[3] = raw.p0.w;
+    p[4] = raw.p1.x; p[5] = raw.p1.y; p[6] = raw.p1.z; p[7] = raw.p1.w;
     if (BF16) {
-        g[0] = u2f(ga.x << 16); g[1] = u2f(ga.x & 0xFFFF0000u);
-        g[2] = u2f(ga.y << 16); g[3] = u2f(ga.y & 0xFFFF0000u);
-        g[4] = u2f(ga.z << 16); g[5] = u2f(ga.z & 0xFFFF0000u);
-        g[6] = u2f(ga.w << 16); g[7] = u2f(ga.w & 0xFFFF0000u);
+        g[0] = u2f(raw.g0.x << 16); g[1] = u2f(raw.g0.x & 0xFFFF0000u);
+        g[2] = u2f(raw.g0.y << 16); g[3] = u2f(raw.g0.y & 0xFFFF0000u);
+        g[4] = u2f(raw.g0.z << 16); g[5] = u2f(raw.g0.z & 0xFFFF0000u);
+        g[6] = u2f(raw.g0.w << 16); g[7] = u2f(raw.g0.w & 0xFFFF0000u);
     } else {
-        g[0] = u2f(ga.x); g[1] = u2f(ga.y); g[2] = u2f(ga.z); g[3] = u2f(ga.w);
-        g[4] = u2f(gb.x); g[5] = u2f(gb.y); g[6] = u2f(gb.z); g[7] = u2f(gb.w);
+        g[0] = u2f(raw.g0.x); g[1] = u2f(raw.g0.y); g[2] = u2f(raw.g0.z); g[3] = u2f(raw.g0.w);
+        g[4] = u2f(raw.g1.x); g[5] = u2f(raw.g1.y); g[6] = u2f(raw.g1.z); g[7] = u2f(raw.g1.w);
     }
 }
 
@@ -865,35 +858,25 @@ __device__ __forceinline__ void ema_param(const StepArgs &a, const uint32_t tm_a
     }
 }
 
-// The new parameters of a lane's 8 elements (and their bf16 copy, if asked for) back to the
-// coalesced layout and streamed out; chunk_e0: first element of the wavefront's 512, e0: of the lane.
+// The new parameters of a lane's 8 elements and their bf16 copy, if asked for.
 template <bool EXT, bool TAIL>
-__device__ __forceinline__ void store_params8(const StepArgs &a, const uint64_t chunk_e0, const uint64_t e0,
-                                              const uint32_t lane, const bool *ok, const float (&p)[8],
-                                              float4 *const st_c, float4 *const st_l)
+__device__ __forceinline__ void store_params8(const StepArgs &a, const uint64_t e0, const bool *ok, const float (&p)[8])
 {
-    if (EXT && a.param_bf16) {                    // 16-bit copy of the new parameters, 16 bytes per lane
-        if (!TAIL) {
-            const u32x4_t h = {pack_bf16(p[0], p[1]), pack_bf16(p[2], p[3]),
-                             pack_bf16(p[4], p[5]), pack_bf16(p[6], p[7])};
-            stream_store_u4(a.param_bf16 + e0, h);
-        } else {
-#pragma unroll
-            for (int j = 0; j < 8; ++j)
-                if (ok[j]) a.param_bf16[e0 + j] = (uint16_t)pack_bf16(p[j], 0.0f);
-        }
-    }
-    if (!TAIL) {                           // back to the coalesced layout, streamed out
-        wave_lds_sync();
-        st_l[0] = make_float4(p[0], p[1], p[2], p[3]);
-        st_l[1] = make_float4(p[4], p[5], p[6], p[7]);
-        wave_lds_sync();
-        float *pp = a.param + chunk_e0 + lane * 4u;
-        stream_store_f4(pp, st_c[0]);
-        stream_store_f4(pp + 256, st_c[72]);
+    if (!TAIL) {
+        float4 *const pp = reinterpret_cast<float4 *>(a.param + e0);
+        pp[0] = make_float4(p[0], p[1], p[2], p[3]);
+        pp[1] = make_float4(p[4], p[5], p[6], p[7]);
+        if (EXT && a.param_bf16)
+            *reinterpret_cast<uint4 *>(a.param_bf16 + e0) = make_uint4(pack_bf16(p[0], p[1]), pack_bf16(p[2], p[3]),
+                                                                       pack_bf16(p[4], p[5]), pack_bf16(p[6], p[7]));
     } else {
 #pragma unroll
-        for (int j = 0; j < 8; ++j) if (ok[j]) a.param[e0 + j] = p[j];
+        for (int j = 0; j < 8; ++j) {
+            if (ok[j]) {
+                a.param[e0 + j] = p[j];
+                if (EXT && a.param_bf16) a.param_bf16[e0 + j] = (uint16_t)pack_bf16(p[j], 0.0f);
+            }
+        }
     }
 }
 
@@ -984,13 +967,12 @@ struct ChunkWords8 {
 
 // LDS of a wavefront that steps one 512-element chunk (32-bit words; offsets are compile-time
 // constants, so the parts are reached with instruction offsets from very few address registers).
-constexpr int kStage8 = (kIter / 4 + kIter / 32) * 4;          // the padded transposition
 template <int BM, int BV, int B>
 struct ChunkLayout8 {
     static constexpr int NG = kIter / B;
     static constexpr int VT = 1 << BV;
     static constexpr int MTS = m_table_stride<BM>();
-    static constexpr int kOffImgM = kStage8;
+    static constexpr int kOffImgM = 0;
     static constexpr int kOffImgV = kOffImgM + ChunkWords8<BM, BV, false>::kImage;
     static constexpr int kOffTv = ((kOffImgV + ChunkWords8<BM, BV, false>::kImage + 15) / 16) * 16;   // 64-byte aligned
     static constexpr int kOffTm = kOffTv + ((NG * VT + 15) / 16) * 16;
@@ -1022,12 +1004,6 @@ __device__ __forceinline__ void step_chunk8(const StepArgs &a, const uint64_t ch
     float *const my_tv = reinterpret_cast<float *>(slab + Lay::kOffTv) + grp * VT;
     float *const my_tm = reinterpret_cast<float *>(slab + Lay::kOffTm) + grp * Lay::MTS;
     const uint32_t tv_addr = lds_addr(my_tv), tm_addr = lds_addr(my_tm);   // aligned to the table size
-    // one pad vector after every 8 keeps both the coalesced (index = lane) and the per-lane
-    // (index = 2 lane, 2 lane + 1) accesses of the transposition free of bank conflicts
-    float4 *const stage = reinterpret_cast<float4 *>(slab);
-    float4 *const st_c = stage + (lane + lane / 8u);        // coalesced slots: st_c[0] and st_c[72] (= slot 64 + lane)
-    float4 *const st_l = stage + (2u * lane + lane / 4u);   // this lane's 8 elements: st_l[0], st_l[1]
-
     // elements of this lane's block that exist (B except in the last block)
     const uint64_t gb = chunk * NG + grp;
     uint32_t nb = B;
@@ -1046,7 +1022,7 @@ __device__ __forceinline__ void step_chunk8(const StepArgs &a, const uint64_t ch
     words.load(a, ew0, lane);
     float dm_old = 0.0f, dv_old = 0.0f, al_old = 1.0f;
     if (blk_ok) { dm_old = a.m_scale[gb]; dv_old = a.v_scale[gb]; al_old = a.v_base[gb]; }
-    const RawPG raw = load_pg<BF16, TAIL>(a, ew0, lane);
+    const RawPG raw = load_pg<BF16, TAIL>(a, e0);
     const float gscale = (EXT && a.grad_scale) ? *a.grad_scale : 1.0f;      // uniform: the gradient is transformed first
     words.stage(img_m, img_v, lane);
 
@@ -1065,7 +1041,7 @@ __device__ __forceinline__ void step_chunk8(const StepArgs &a, const uint64_t ch
 
     // ---- dequantize (table look-up), EMA, parameter
     float p[8], g[8];
-    lane_layout8<BF16, TAIL>(raw, st_c, st_l, p, g);
+    unpack_pg<BF16>(raw, p, g);
     if (EXT) {                                 // g <- fl(g * scale), then one fused g + l2 * p (l2 = 0: exact)
 #pragma unroll
         for (int j = 0; j < 8; ++j) g[j] = __builtin_fmaf(a.l2, p[j], g[j] * gscale);
@@ -1073,7 +1049,7 @@ __device__ __forceinline__ void step_chunk8(const StepArgs &a, const uint64_t ch
     float mh[8], vh[8];
     float m_absmax, v_max;                     // (v_max of full chunks: the last sorted key below)
     ema_param<8, BM, BV, EXT, TAIL, TAIL>(a, tm_addr, tv_addr, &mc8, &vc8, ok, p, g, mh, vh, m_absmax, v_max);
-    store_params8<EXT, TAIL>(a, ew0, e0, lane, ok, p, st_c, st_l);
+    store_params8<EXT, TAIL>(a, e0, ok, p);
 
     // ---- the lane's v^ sorted (non-negative floats order like their bit patterns); block maxima
     uint32_t key[8];
@@ -1672,18 +1648,17 @@ hipError_t launch_one(const StepArgs &args_in, hipStream_t stream)
 {
     StepArgs args = args_in;                   // the tiling belongs to the instantiation
     if (args.n == 0) return hipSuccess;
-    const bool narrow = args.n <= narrow_up_to();
+    const bool narrow = args.n <= narrow_up_to(BF16, args.param_bf16 != nullptr, args.rank_full);
     const uint64_t whole = narrow ? 0 : args.n / kIter16;
     args.rest = args.n == whole * kIter16 ? 0 : (end_of_words(args.n) - whole * kIter16 + kIter - 1) / kIter;
     const uint64_t groups = (whole + args.rest + kWaves - 1) / kWaves;
     if (groups > 0x7FFFFFFFull) return hipErrorInvalidValue;
     const bool ext = args.param_bf16 || args.grad_scale || args.belief || args.l2 != 0.0f;
-    if (narrow)                                // (always the full-featured kernel: all latency)
-        hipLaunchKernelGGL((chunk8_kernel<BM, BV, B, BF16, MDE, true>), dim3((uint32_t)groups), dim3(kWaves * 64), 0, stream, args);
-    else if (ext)
-        hipLaunchKernelGGL((chunk16_kernel<BM, BV, B, BF16, MDE, true>), dim3((uint32_t)groups), dim3(kWaves * 64), 0, stream, args);
-    else
-        hipLaunchKernelGGL((chunk16_kernel<BM, BV, B, BF16, MDE, false>), dim3((uint32_t)groups), dim3(kWaves * 64), 0, stream, args);
+#define SOLO_LAUNCH(KERNEL_, EXT_)                                                                              \
+    hipLaunchKernelGGL((KERNEL_<BM, BV, B, BF16, MDE, EXT_>), dim3((uint32_t)groups), dim3(kWaves * 64), 0, stream, args)
+    if (narrow) { if (ext) SOLO_LAUNCH(chunk8_kernel, true); else SOLO_LAUNCH(chunk8_kernel, false); }
+    else        { if (ext) SOLO_LAUNCH(chunk16_kernel, true); else SOLO_LAUNCH(chunk16_kernel, false); }
+#undef SOLO_LAUNCH
     return hipGetLastError();
 }
 
@@ -1700,7 +1675,7 @@ hipError_t launch_multi_impl(uint32_t bits_v, uint32_t block_size, bool bf16, co
 #define SOLO_LAUNCH(BV_, B_, BF_)                                                                       \
     do {                                                                                                \
         constexpr uint64_t unit = table_unit<BM, BV_, B_, BF_, MDE>();                                  \
-        const bool narrow = args.total_units <= narrow_up_to() / unit;                                  \
+        const bool narrow = args.total_units <= narrow_table_up_to() / unit;                            \
         /* wavefronts: one per 512 elements of a unit, or five per 5120 elements */                     \
         const uint64_t slots = narrow ? args.total_units * (unit / kIter)                               \
                                       : (args.total_units + 2 * kTileUnit / unit - 1) / (2 * kTileUnit / unit) * 5; \

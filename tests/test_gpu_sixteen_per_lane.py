@@ -1,5 +1,6 @@
-"""GPU parity of the kernels that give a lane 16 elements: flat buffers of more than 3 * 2^18
-elements, tables of more units than that, blocks of 2048.  Same bar as test_gpu_parity.py."""
+"""GPU parity of the kernels that give a lane 16 elements: flat buffers of more than 5 * 2^20
+elements (some formats from 2^19 on), tables of more than 3 * 2^18, blocks of 2048.  Same bar as
+test_gpu_parity.py."""
 import numpy as np
 import pytest
 
@@ -8,7 +9,7 @@ from test_gpu_parity import GpuSide, dev, gpu, run_teacher_forced  # noqa: F401
 
 pytestmark = pytest.mark.gpu
 
-LAST8 = 3 << 18                    # the largest flat buffer that runs 8 elements per lane
+LAST8 = 5 << 20                    # the largest flat buffer of any format that runs 8 elements per lane
 FORMATS = [(bm, bv, B) for B in (64, 128) for bm in (2, 3, 4) for bv in (2, 3, 4)]
 # whole chunks of 1024 only; a chunk short of one element, of all but one; ends in either half of a
 # chunk, on and next to a code word's and a block's end
@@ -18,11 +19,12 @@ SIZES = [LAST8, LAST8 + 1, LAST8 + 1023, LAST8 + 1024, LAST8 + 1025, LAST8 + 512
 
 @pytest.mark.parametrize("k,bm,bv,B", [(k, *f) for k, f in enumerate(FORMATS)])
 def test_formats_and_ragged_ends(so, gpu, k, bm, bv, B):  # noqa: F811
-    for j in range(2):
-        n = SIZES[(2 * k + j) % len(SIZES)]
+    for j in range(3):
+        # (the last one: 8 per lane with fp32 gradients, 16 with bf16 ones and a copy)
+        n = SIZES[(2 * k + j) % len(SIZES)] if j < 2 else (3 << 18) + (k * 401) % 1100
         opt = ("adamw", "adam_l2", "adabelief")[(k + j) % 3]
         ext = dict(grad_scale=0.5, bf16_copy=True) if (k + j) % 4 == 0 else {}
-        run_teacher_forced(so, gpu, n, bm, bv, B, bf16=(k + j) % 2 == 0, steps=2, seed0=10 * k, de=(k // 2 + j) % 2 == 1,
+        run_teacher_forced(so, gpu, n, bm, bv, B, bf16=(k + j) % 2 == 0, steps=2 if j < 2 else 3, seed0=10 * k, de=(k // 2 + j) % 2 == 1,
                            optimizer=opt, eps=1e-12 if opt == "adabelief" else 1e-8, **ext)
 
 
