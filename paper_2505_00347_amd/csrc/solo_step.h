@@ -1581,7 +1581,9 @@ template <int BM, int BV, int B, bool BF16, bool MDE>
 constexpr int table_unit() { return multi_chunked(BF16, MDE) ? kTileUnit : unit_elems(BM, BV, B); }
 
 // 8 elements per lane, for tables of few elements: UNIT / 512 wavefronts per map entry.
-template <int BM, int BV, int B, bool BF16, bool MDE>
+// (The plain step has a form of its own here too: the variants' g + l2 * p turns a parameter that is
+// infinite or NaN into a gradient that is, also with l2 = 0, and spoils the state of its block.)
+template <int BM, int BV, int B, bool BF16, bool MDE, bool EXT>
 __global__ __launch_bounds__(kWaves * 64, kMinWaves)
 void multi_chunk8_kernel(const MultiArgs ma)
 {
@@ -1601,9 +1603,9 @@ void multi_chunk8_kernel(const MultiArgs ma)
     const StepArgs a = tensor_args(ma, *r.e);
     uint32_t *const slab = lds_slab + wave * Lay::kSlab;
     if ((c + 1) * kIter <= a.n)
-        step_chunk8<BM, BV, B, BF16, MDE, false, true>(a, c, lane, slab, lds_de);
+        step_chunk8<BM, BV, B, BF16, MDE, false, EXT>(a, c, lane, slab, lds_de);
     else if (c * kIter < end_of_words(a.n))
-        step_chunk8<BM, BV, B, BF16, MDE, true, true>(a, c, lane, slab, lds_de);
+        step_chunk8<BM, BV, B, BF16, MDE, true, EXT>(a, c, lane, slab, lds_de);
 }
 
 // 16 elements per lane.  A map entry owns the 1024-element chunks of its tensor that begin inside
@@ -1684,6 +1686,8 @@ hipError_t launch_multi_impl(uint32_t bits_v, uint32_t block_size, bool bf16, co
 {
     const StepArgs &c = args.common;
     const bool ext = args.any_bf16_copy || c.grad_scale || c.belief || c.l2 != 0.0f;
+#define SOLO_KERNEL(KERNEL_, BV_, B_, BF_, EXT_)                                                        \
+    hipLaunchKernelGGL((KERNEL_<BM, BV_, B_, BF_, MDE, EXT_>), dim3((uint32_t)grid), dim3(kWaves * 64), 0, stream, args)
 #define SOLO_LAUNCH(BV_, B_, BF_)                                                                       \
     do {                                                                                                \
         constexpr uint64_t unit = table_unit<BM, BV_, B_, BF_, MDE>();                                  \
@@ -1693,15 +1697,10 @@ hipError_t launch_multi_impl(uint32_t bits_v, uint32_t block_size, bool bf16, co
                                       : (args.total_units + 2 * kTileUnit / unit - 1) / (2 * kTileUnit / unit) * 5; \
         const uint64_t grid = (slots + kWaves - 1) / kWaves;                                            \
         if (grid == 0 || grid > 0x7FFFFFFFull) return hipErrorInvalidValue;                             \
-        if (narrow)                                                                                     \
-            hipLaunchKernelGGL((multi_chunk8_kernel<BM, BV_, B_, BF_, MDE>), dim3((uint32_t)grid),      \
-                               dim3(kWaves * 64), 0, stream, args);                                     \
-        else if (ext)                                                                                   \
-            hipLaunchKernelGGL((multi_chunk16_kernel<BM, BV_, B_, BF_, MDE, true>), dim3((uint32_t)grid), \
-                               dim3(kWaves * 64), 0, stream, args);                                     \
-        else                                                                                            \
-            hipLaunchKernelGGL((multi_chunk16_kernel<BM, BV_, B_, BF_, MDE, false>), dim3((uint32_t)grid), \
-                               dim3(kWaves * 64), 0, stream, args);                                     \
+        if (narrow && ext) SOLO_KERNEL(multi_chunk8_kernel, BV_, B_, BF_, true);                        \
+        else if (narrow)   SOLO_KERNEL(multi_chunk8_kernel, BV_, B_, BF_, false);                       \
+        else if (ext)      SOLO_KERNEL(multi_chunk16_kernel, BV_, B_, BF_, true);                       \
+        else               SOLO_KERNEL(multi_chunk16_kernel, BV_, B_, BF_, false);                      \
     } while (0)
 #define SOLO_CASE(BV_, B_)                                                                              \
     if (bits_v == BV_ && block_size == B_) {                                                            \
@@ -1711,6 +1710,7 @@ hipError_t launch_multi_impl(uint32_t bits_v, uint32_t block_size, bool bf16, co
     SOLO_CASE(2, 64) SOLO_CASE(2, 128) SOLO_CASE(3, 64) SOLO_CASE(3, 128) SOLO_CASE(4, 64) SOLO_CASE(4, 128)
 #undef SOLO_CASE
 #undef SOLO_LAUNCH
+#undef SOLO_KERNEL
     return hipErrorInvalidValue;
 }
 

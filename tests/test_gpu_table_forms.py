@@ -1,0 +1,63 @@
+"""GPU tests of the forms a multi-tensor launch takes: every tensor is left as the flat step leaves it that
+starts at the tensor's own place in the xi stream, byte for byte."""
+import pytest
+
+from test_gpu_parity import gpu  # noqa: F401
+
+pytestmark = pytest.mark.gpu
+
+
+def bits(t):
+    import torch
+    return t.view(torch.int16 if t.element_size() == 2 else torch.int32)
+
+
+def table_against_flat(gpu, sizes, bm, bv, B, bf16=True, de=False, flags=0, mp=False, p=0.1, steps=2, spoil=None):  # noqa: F811
+    """Steps the tensors in one launch and one by one; returns the (param, state, copy) of the table's side.
+    spoil(params): changes the parameters first."""
+    import torch
+    off0 = 8 * 321
+    flags |= 1 | (2 if de else 0)
+
+    def config(off):
+        return gpu.make_config(bm, bv, B, 1 if bf16 else 0, flags=flags, quantile_p=p, index_offset=off)
+
+    cfg = config(off0)
+    gen = torch.Generator(device="cuda").manual_seed(7)
+    scale = torch.tensor([0.5], device="cuda") if mp else None
+    ps = [torch.randn(n, device="cuda", generator=gen) for n in sizes]
+    if spoil:
+        spoil(ps)
+    sides = [[(q.clone(), gpu.SoloState(n, cfg), torch.zeros(n, dtype=torch.bfloat16, device="cuda") if mp else None)
+              for q, n in zip(ps, sizes)] for _ in range(2)]
+    dtype = torch.bfloat16 if bf16 else torch.float32
+    gs = [torch.zeros(n, dtype=dtype, device="cuda") for n in sizes]
+    table = gpu.SoloMultiTable([(q, g, st, h) for (q, st, h), g in zip(sides[0], gs)], cfg)
+    for step in range(1, steps + 1):
+        for g in gs:
+            g.copy_((torch.randn(len(g), device="cuda", generator=gen) * 1e-3).to(dtype))
+        table.step(step, grad_scale=scale)
+        off = off0
+        for (q, st, h), g, n in zip(sides[1], gs, sizes):
+            gpu.solo_adamw_step_mp(q, h, g, scale, *st.buffers(), n, step, config(off))
+            off += -(-n // 2560) * 2560
+    torch.cuda.synchronize()
+    for n, (q, st, h), (q1, st1, h1) in zip(sizes, *sides):
+        assert torch.equal(bits(q), bits(q1)), n
+        assert h is None or torch.equal(bits(h), bits(h1)), n
+        for a, b in zip(st.buffers(), st1.buffers()):
+            assert torch.equal(bits(a), bits(b)), n
+    return sides[0]
+
+
+@pytest.mark.parametrize("bf16,B", [(True, 128), (False, 64), (True, 2048)])
+def test_a_parameter_that_is_not_finite_leaves_the_state_alone(gpu, bf16, B):  # noqa: F811
+    """Plain AdamW does not feed parameters back into the moments, however short the table."""
+    import torch
+
+    def spoil(ps):
+        ps[0][17], ps[0][5119], ps[1][0] = float("inf"), float("nan"), float("-inf")
+
+    for n in (10240, 400 * 2560):               # 8 and 16 elements per lane
+        for q, st, _ in table_against_flat(gpu, [n, 5120 + 77], 2, 3, B, bf16, spoil=spoil):
+            assert all(bool(torch.isfinite(x).all()) for x in (st.m_scale, st.v_scale, st.v_base))
