@@ -222,6 +222,9 @@ size_t solo_multi_table_bytes(uint32_t count, uint64_t units);
  * solo_adamw_step_multi takes back.  Checks every pointer's alignment. */
 #define SOLO_TABLE_BF16_COPY 1u   /* some tensor has a bf16 copy to write */
 #define SOLO_TABLE_SHORT_BLOCK 2u /* blocks of 2048: some tensor ends in a shorter block */
+#define SOLO_TABLE_PIECES_SHIFT 2 /* blocks of 64 and 128: table_flags >> 2 is the number of pieces of the
+                                     tensors (one wavefront each), which sizes the launch; 0 where the
+                                     units do, which is right for every table but larger than need be */
 int solo_multi_table_build(const solo_tensor *tensors, uint32_t count, const solo_config *cfg,
                            void *table_host, size_t table_bytes, uint32_t *table_flags);
 

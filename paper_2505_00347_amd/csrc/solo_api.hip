@@ -48,6 +48,7 @@ template <> hipError_t launch_multi_big<3, true>(uint32_t, bool, const MultiArgs
 template <> hipError_t launch_multi_big<4, true>(uint32_t, bool, const MultiArgs &, hipStream_t);
 
 constexpr uint32_t kLargeBlock = 2048;      // the large-block setting (one workgroup per block)
+constexpr uint64_t kFewPieces = 64;
 
 static bool bits_ok(uint32_t b) { return b >= 2 && b <= 4; }
 
@@ -309,7 +310,7 @@ int solo_multi_table_build(const solo_tensor *tensors, uint32_t count, const sol
                                              (cfg->flags & SOLO_FLAG_M_DYNAMIC_EXPONENT) != 0);
     solo::TensorEntry *entries = static_cast<solo::TensorEntry *>(table_host);
     uint32_t *map = reinterpret_cast<uint32_t *>(static_cast<char *>(table_host) + solo::multi_map_offset(count));
-    uint64_t unit0 = 0, xi_offset = cfg->index_offset;
+    uint64_t unit0 = 0, xi_offset = cfg->index_offset, first16 = 0, first8 = 0;
     uint32_t flags = 0;
     for (uint32_t k = 0; k < count; ++k) {
         const solo_tensor &t = tensors[k];
@@ -326,7 +327,8 @@ int solo_multi_table_build(const solo_tensor *tensors, uint32_t count, const sol
         e.v_words = t.v_codes; e.v_scale = t.v_scale; e.v_base = t.v_base;
         e.n = t.n; e.unit0 = unit0;
         e.index_offset = xi_offset;
-        e.reserved = 0;
+        e.first16 = (uint32_t)first16; e.first8 = (uint32_t)first8;
+        first16 += solo::pieces16(t.n); first8 += solo::pieces8(t.n);
         // full units first, then the 512-element iterations of the ragged end, one entry each
         // (chunked formats: one entry per 2560-element unit, the shorter last one included)
         // (blocks of 2048: one entry per full block, then one flagged entry for a shorter last block)
@@ -338,6 +340,10 @@ int solo_multi_table_build(const solo_tensor *tensors, uint32_t count, const sol
         unit0 += nf + nc;
         xi_offset += (t.n + solo::kTileUnit - 1) / solo::kTileUnit * (uint64_t)solo::kTileUnit;
     }
+    // the pieces go with the flags where they say more than the units (a launch that the units size
+    // has up to five wavefronts per piece, which a few pieces do not notice) and fit
+    if (!big && first16 >= solo::kFewPieces && first16 < (1ull << (32 - SOLO_TABLE_PIECES_SHIFT)))
+        flags |= (uint32_t)first16 << SOLO_TABLE_PIECES_SHIFT;
     *table_flags = flags;
     return SOLO_OK;
 }
@@ -357,6 +363,9 @@ int solo_adamw_step_multi(const void *table_device, uint32_t count, uint64_t uni
     ma.unit_map = reinterpret_cast<const uint32_t *>(static_cast<const char *>(table_device) +
                                                      solo::multi_map_offset(count));
     ma.total_units = units;
+    ma.pieces = table_flags >> SOLO_TABLE_PIECES_SHIFT;
+    ma.units_per_piece = ma.pieces ? (float)((double)units / (double)ma.pieces) : 1.0f;
+    ma.count = count;
     ma.any_bf16_copy = (table_flags & SOLO_TABLE_BF16_COPY) ? 1u : 0u;
     const bool bf16 = cfg->grad_dtype == SOLO_GRAD_BF16;
     const bool mde = (cfg->flags & SOLO_FLAG_M_DYNAMIC_EXPONENT) != 0;

@@ -113,12 +113,14 @@ struct TensorEntry {
     uint64_t n;             // elements of the tensor
     uint64_t unit0;         // index of the tensor's first unit among all units of the table
     uint64_t index_offset;  // global index of the tensor's element 0 in the xi stream
-    uint64_t reserved;
+    uint32_t first16;       // pieces (pieces16) of the tensors before this one
+    uint32_t first8;        // 512-element pieces of the tensors before this one
 };
 static_assert(sizeof(TensorEntry) == 96, "table layout");
 
-// An entry of the unit map: the tensor's index; for the ragged end of a tensor, which is cut into
-// its 512-element iterations with one entry (one wavefront) each, also the iteration and a flag.
+// An entry of the unit map: the tensor's index; for the ragged end of a tensor, which has one entry
+// per 512 elements, also the number of that entry and a flag.  (Blocks of 64 and 128 are cut into pieces,
+// see find_tensor(): there the map is a first guess only.)
 constexpr uint32_t kMapTensorMask = 0x00FFFFFFu, kMapRagged = 0x80000000u;
 constexpr int kMapChunkShift = 24;
 inline uint64_t multi_full_units(uint64_t n, uint64_t unit) { return n / unit; }
@@ -132,10 +134,13 @@ struct MultiArgs {
     const TensorEntry *entries;
     const uint32_t *unit_map;     // tensor index of every unit
     uint64_t total_units;
+    uint64_t pieces;              // blocks of 64 and 128: of all tensors (0: the caller does not know)
+    float units_per_piece;
+    uint32_t count;               // tensors
     uint32_t any_bf16_copy;       // some tensor of the table has a bf16 copy to write
 };
 
-// The layout of a multi-tensor table (what a map entry stands for).  fp32 gradients with the linear
+// The units of a multi-tensor table (what a map entry stands for).  fp32 gradients with the linear
 // codebook: one entry per 2560 elements, a tensor's shorter end included.  Every other format: one
 // entry per full unit of 5120 or 2560 elements, and one per 512-element iteration of a ragged end.
 constexpr bool multi_chunked(bool bf16, bool mde) { return !bf16 && !mde; }
@@ -147,6 +152,19 @@ constexpr int unit_elems(uint32_t bits_m, uint32_t bits_v, uint32_t block_size)
 // Elements up to the end of the last code word of n elements (80 = lcm of 16, 10 and 8 codes per
 // word): a word's unused fields are written as zeros like every other field.
 __host__ __device__ constexpr uint64_t end_of_words(uint64_t n) { return (n + 79) / 80 * 80; }
+
+// The pieces that n elements are cut into, one wavefront each: whole chunks of 1024 and, for what is
+// left behind them, up to three of 512; or 512 elements each.
+__host__ __device__ constexpr uint64_t rest_pieces(uint64_t n, uint64_t whole)
+{
+    return n == whole * kIter16 ? 0 : (end_of_words(n) - whole * kIter16 + kIter - 1) / kIter;
+}
+__host__ __device__ constexpr uint64_t pieces16(uint64_t n) { return n / kIter16 + rest_pieces(n, n / kIter16); }
+__host__ __device__ constexpr uint64_t pieces8(uint64_t n) { return n % kIter ? rest_pieces(n, 0) : n / kIter; }
+// A unit of a table holds at most so many pieces (5120 elements: five, 2560 or a shorter end: three).
+constexpr uint64_t kPiecesPerUnit = 5;
+// Workgroups of a launch: the grid counts its work-items in 32 bits.
+constexpr uint64_t kMaxGroups = 0xFFFFFFFFull / (kWaves * 64);
 
 // ---------------------------------------------------------------- cross-lane
 
@@ -536,8 +554,8 @@ constexpr uint64_t narrow_up_to(bool bf16, bool copy, uint32_t rank)
     if (!bf16) return 5ull << 20;
     return copy ? 3ull << 18 : 3ull << 20;
 }
-// Up to how many elements in its units a table does (there the ragged ends leave wavefronts idle).
-constexpr uint64_t narrow_table_up_to() { return 3ull << 18; }
+// Up to how many pieces (pieces16) a table does.
+constexpr uint64_t narrow_table_up_to() { return 3ull << 8; }
 
 // The lowest set bit of every G-bit field of a ballot, one field per group of lanes.  Every field
 // has a bit set (the lanes whose key equals the group's minimum), so ~h + 1 does not carry out of
@@ -1536,24 +1554,23 @@ void chunk16_kernel(const StepArgs a)
 
 // ---- many tensors in one launch.  Blocks never span tensors: each tensor is quantized on its own.
 
-// The elements [begin, begin + elems) of its tensor that a map entry stands for.
-template <int UNIT>
-struct UnitRange {
-    const TensorEntry *e;
-    uint64_t begin;
-    uint32_t elems;
-    __device__ __forceinline__ UnitRange(const MultiArgs &ma, uint64_t unit)
-    {
-        const uint32_t me = ma.unit_map[unit];                      // uniform: scalar loads
-        e = &ma.entries[me & kMapTensorMask];
-        const bool ragged = (me & kMapRagged) != 0;
-        begin = ragged ? e->n / UNIT * UNIT + (uint64_t)((me >> kMapChunkShift) & 0x7Fu) * kIter : (unit - e->unit0) * UNIT;
-        elems = ragged ? kIter : UNIT;
-    }
-    // first chunk of `size` elements that begins inside the range, and the first one behind it
-    __device__ __forceinline__ uint64_t first(uint32_t size) const { return (begin + size - 1) / size; }
-    __device__ __forceinline__ uint64_t last(uint32_t size) const { return (begin + elems + size - 1) / size; }
-};
+// The tensor whose pieces hold piece `s` of all tensors, first8 / first16 (FIRST) counting the pieces
+// in front of each: 64 tensors are looked at per step, one by every lane, so that up to 64 tensors
+// take one dependent load and up to 4096 two.  (A tensor without elements shares its count with the
+// one behind it, which is the one taken.)
+template <uint32_t TensorEntry::*FIRST>
+__device__ __forceinline__ const TensorEntry &find_tensor(const MultiArgs &ma, const uint32_t s, const uint32_t lane)
+{
+    uint32_t lo = 0, len = ma.count;
+    do {
+        const uint32_t stride = (len + 63u) / 64u, at = lane * stride;
+        const bool before = at < len && ma.entries[lo + at].*FIRST <= s;
+        const uint32_t j = (uint32_t)__builtin_popcountll(__builtin_amdgcn_ballot_w64(before)) - 1u;   // (tensor 0 has 0 in front)
+        lo += j * stride;
+        len = umin(stride, len - j * stride);
+    } while (len > 1u);
+    return ma.entries[lo];
+}
 
 // A pointer of an entry, read as one to global memory.  (A pointer that comes out of a kernel's own
 // arguments is known to be one; behind a pointer out of memory every access was a flat one, which
@@ -1577,30 +1594,30 @@ __device__ __forceinline__ StepArgs tensor_args(const MultiArgs &ma, const Tenso
     return a;
 }
 
-template <int BM, int BV, int B, bool BF16, bool MDE>
-constexpr int table_unit() { return multi_chunked(BF16, MDE) ? kTileUnit : unit_elems(BM, BV, B); }
+// Every tensor is cut into the pieces of a flat buffer of its size, one wavefront each, and stepped by
+// the same code.  (Cutting the units of the map instead - five wavefronts per 5120 elements, a ragged end
+// as part of them - left most wavefronts of a table of short tensors without work, and one wavefront
+// with three pieces one behind the other where a tensor ends; 1000 tensors of 600 elements,
+// 2-bit/3-bit bf16: 16.2 us, 7.9 now; 20,000 of them: 160 and 77; 53 tensors of 787,050 elements,
+// 3-bit/4-bit fp32 with a copy: 14.2 and 7.1.)
 
-// 8 elements per lane, for tables of few elements: UNIT / 512 wavefronts per map entry.
+// 8 elements per lane, for tables of few elements.
 // (The plain step has a form of its own here too: the variants' g + l2 * p turns a parameter that is
 // infinite or NaN into a gradient that is, also with l2 = 0, and spoils the state of its block.)
 template <int BM, int BV, int B, bool BF16, bool MDE, bool EXT>
 __global__ __launch_bounds__(kWaves * 64, kMinWaves)
 void multi_chunk8_kernel(const MultiArgs ma)
 {
-    constexpr int kUnit = table_unit<BM, BV, B, BF16, MDE>();
     using Lay = ChunkLayout8<BM, BV, B>;
     __shared__ __attribute__((aligned(64))) uint32_t lds_slab[kWaves * Lay::kSlab];
     __shared__ __attribute__((aligned(64))) uint32_t lds_de[de_words<BM, MDE>()];
     load_de_table<BM, MDE, de_words<BM, MDE>()>(lds_de);
     const uint32_t lane = threadIdx.x & 63u;
     const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    const uint64_t slot = (uint64_t)blockIdx.x * kWaves + wave;
-    const uint64_t unit = slot / (kUnit / kIter);
-    if (unit >= ma.total_units) return;
-    const UnitRange<kUnit> r(ma, unit);
-    const uint64_t c = r.first(kIter) + slot % (kUnit / kIter);
-    if (c >= r.last(kIter)) return;
-    const StepArgs a = tensor_args(ma, *r.e);
+    const uint32_t s = blockIdx.x * kWaves + wave;
+    const TensorEntry &e = find_tensor<&TensorEntry::first8>(ma, s, lane);
+    const uint64_t c = s - e.first8;
+    const StepArgs a = tensor_args(ma, e);
     uint32_t *const slab = lds_slab + wave * Lay::kSlab;
     if ((c + 1) * kIter <= a.n)
         step_chunk8<BM, BV, B, BF16, MDE, false, EXT>(a, c, lane, slab, lds_de);
@@ -1608,47 +1625,39 @@ void multi_chunk8_kernel(const MultiArgs ma)
         step_chunk8<BM, BV, B, BF16, MDE, true, EXT>(a, c, lane, slab, lds_de);
 }
 
-// 16 elements per lane.  A map entry owns the 1024-element chunks of its tensor that begin inside
-// its range: five wavefronts for an entry of 5120 elements, five for two entries of 2560 (two or
-// three chunks each; where two tensors meet it can be six, and the fifth wavefront takes two).
-// An entry of a ragged end owns one or none.  The chunk that a tensor does not fill, and such a
-// sixth chunk, run in their 512-element iterations, with bounds checks (a loop around the
-// 16-per-lane code spills registers).
+// find_tensor() with a first try: the tensor that the map names at the same fraction of the units.  In
+// a table of large tensors that is nearly always the one, and two scalar loads say so, where the
+// search takes two vector loads one behind the other for the 99 tensors of the GPT-2-125M shapes
+// (2-bit/2-bit, B 64: 269 us without the try, 249 with it).
+__device__ __forceinline__ const TensorEntry &find_tensor_of_chunk(const MultiArgs &ma, const uint32_t s, const uint32_t lane)
+{
+    const uint32_t unit = umin((uint32_t)((float)s * ma.units_per_piece), (uint32_t)ma.total_units - 1u);
+    const uint32_t k = ma.unit_map[unit] & kMapTensorMask;
+    const uint32_t next = k + 1u < ma.count ? ma.entries[k + 1u].first16 : 0xFFFFFFFFu;
+    if (ma.entries[k].first16 <= s && s < next) return ma.entries[k];
+    return find_tensor<&TensorEntry::first16>(ma, s, lane);
+}
+
+// 16 elements per lane, and 8 for what a tensor has left behind its whole chunks.
 template <int BM, int BV, int B, bool BF16, bool MDE, bool EXT>
 __global__ __launch_bounds__(kWaves * 64, kMinWaves16)
 void multi_chunk16_kernel(const MultiArgs ma)
 {
-    constexpr int kUnit = table_unit<BM, BV, B, BF16, MDE>();
     using Lay = ChunkLayout16<BM, BV, B>;
     __shared__ __attribute__((aligned(64))) uint32_t lds_slab[kWaves * Lay::kSlab];
     __shared__ __attribute__((aligned(64))) uint32_t lds_de[de_words<BM, MDE>()];
     load_de_table<BM, MDE, de_words<BM, MDE>()>(lds_de);
     const uint32_t lane = threadIdx.x & 63u;
     const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    const uint64_t slot = (uint64_t)blockIdx.x * kWaves + wave;
-    const uint32_t sub = (uint32_t)(slot % 5);
-    const uint64_t unit0 = slot / 5 * (2 * kTileUnit / kUnit);
-    if (unit0 >= ma.total_units) return;
-    UnitRange<kUnit> r(ma, unit0);
-    uint64_t c = r.first(kIter16) + sub;
-    bool two = false;                              // the fifth wavefront where two entries own six chunks
-    if (c >= r.last(kIter16)) {
-        if (kUnit == 2 * kTileUnit || unit0 + 1 >= ma.total_units) return;
-        const uint32_t here = (uint32_t)(r.last(kIter16) - r.first(kIter16));
-        r = UnitRange<kUnit>(ma, unit0 + 1);
-        c = r.first(kIter16) + (sub - here);
-        if (c >= r.last(kIter16)) return;
-        two = sub == 4 && c + 1 < r.last(kIter16);
-    }
-    const StepArgs a = tensor_args(ma, *r.e);
+    const uint32_t s = blockIdx.x * kWaves + wave;
+    const TensorEntry &e = find_tensor_of_chunk(ma, s, lane);
+    const uint64_t c = s - e.first16, whole = e.n / kIter16;
+    const StepArgs a = tensor_args(ma, e);
     uint32_t *const slab = lds_slab + wave * Lay::kSlab;
-    const bool whole = (c + 1) * kIter16 <= a.n;
-    if (whole) step_chunk16<BM, BV, B, BF16, MDE, EXT>(a, c, lane, slab, lds_de);
-    // the chunk that the tensor does not fill, and the sixth chunk of two entries
-    const uint64_t i0 = 2 * c + (whole ? 2 : 0), i1 = 2 * c + (two ? 4 : 2);
-#pragma unroll 1
-    for (uint64_t i = i0; i < i1 && i * kIter < end_of_words(a.n); ++i)
-        step_chunk8<BM, BV, B, BF16, MDE, true, EXT>(a, i, lane, slab, lds_de);
+    if (c < whole)
+        step_chunk16<BM, BV, B, BF16, MDE, EXT>(a, c, lane, slab, lds_de);
+    else if ((whole + c) * kIter < end_of_words(a.n))
+        step_chunk8<BM, BV, B, BF16, MDE, true, EXT>(a, whole + c, lane, slab, lds_de);
 }
 
 // Host-side launcher of one instantiation family (fixed bits_m and 1st-moment codebook);
@@ -1664,9 +1673,9 @@ hipError_t launch_one(const StepArgs &args_in, hipStream_t stream)
     if (args.n == 0) return hipSuccess;
     const bool narrow = args.n <= narrow_up_to(BF16, args.param_bf16 != nullptr, args.rank_full);
     const uint64_t whole = narrow ? 0 : args.n / kIter16;
-    args.rest = args.n == whole * kIter16 ? 0 : (end_of_words(args.n) - whole * kIter16 + kIter - 1) / kIter;
+    args.rest = rest_pieces(args.n, whole);
     const uint64_t groups = (whole + args.rest + kWaves - 1) / kWaves;
-    if (groups > 0x7FFFFFFFull) return hipErrorInvalidValue;
+    if (groups > kMaxGroups) return hipErrorInvalidValue;
     const bool ext = args.param_bf16 || args.grad_scale || args.belief || args.l2 != 0.0f;
 #define SOLO_LAUNCH(KERNEL_, EXT_)                                                                              \
     hipLaunchKernelGGL((KERNEL_<BM, BV, B, BF16, MDE, EXT_>), dim3((uint32_t)groups), dim3(kWaves * 64), 0, stream, args)
@@ -1686,17 +1695,16 @@ hipError_t launch_multi_impl(uint32_t bits_v, uint32_t block_size, bool bf16, co
 {
     const StepArgs &c = args.common;
     const bool ext = args.any_bf16_copy || c.grad_scale || c.belief || c.l2 != 0.0f;
+    // wavefronts; those behind the last piece find nothing to do (a tensor of 512-element pieces has
+    // at most twice as many as of 1024-element ones)
+    const uint64_t pieces = args.pieces ? args.pieces : args.total_units * kPiecesPerUnit;
+    const bool narrow = pieces <= narrow_table_up_to();
+    const uint64_t grid = ((narrow ? 2 * pieces : pieces) + kWaves - 1) / kWaves;
+    if (grid == 0 || grid > kMaxGroups || args.count == 0) return hipErrorInvalidValue;
 #define SOLO_KERNEL(KERNEL_, BV_, B_, BF_, EXT_)                                                        \
     hipLaunchKernelGGL((KERNEL_<BM, BV_, B_, BF_, MDE, EXT_>), dim3((uint32_t)grid), dim3(kWaves * 64), 0, stream, args)
 #define SOLO_LAUNCH(BV_, B_, BF_)                                                                       \
     do {                                                                                                \
-        constexpr uint64_t unit = table_unit<BM, BV_, B_, BF_, MDE>();                                  \
-        const bool narrow = args.total_units <= narrow_table_up_to() / unit;                            \
-        /* wavefronts: one per 512 elements of a unit, or five per 5120 elements */                     \
-        const uint64_t slots = narrow ? args.total_units * (unit / kIter)                               \
-                                      : (args.total_units + 2 * kTileUnit / unit - 1) / (2 * kTileUnit / unit) * 5; \
-        const uint64_t grid = (slots + kWaves - 1) / kWaves;                                            \
-        if (grid == 0 || grid > 0x7FFFFFFFull) return hipErrorInvalidValue;                             \
         if (narrow && ext) SOLO_KERNEL(multi_chunk8_kernel, BV_, B_, BF_, true);                        \
         else if (narrow)   SOLO_KERNEL(multi_chunk8_kernel, BV_, B_, BF_, false);                       \
         else if (ext)      SOLO_KERNEL(multi_chunk16_kernel, BV_, B_, BF_, true);                       \

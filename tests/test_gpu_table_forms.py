@@ -61,3 +61,40 @@ def test_a_parameter_that_is_not_finite_leaves_the_state_alone(gpu, bf16, B):  #
     for n in (10240, 400 * 2560):               # 8 and 16 elements per lane
         for q, st, _ in table_against_flat(gpu, [n, 5120 + 77], 2, 3, B, bf16, spoil=spoil):
             assert all(bool(torch.isfinite(x).all()) for x in (st.m_scale, st.v_scale, st.v_base))
+
+
+# ends of every kind: less than a word, a block, a 512-element piece, a chunk; one and two pieces behind
+# whole chunks; empty tensors between and behind
+ENDS = [600, 1, 0, 79, 512, 513, 1023, 1024, 1025, 1535, 1537, 2047, 2048, 2560, 5119, 5120, 5121, 7, 3000, 0, 0]
+
+
+@pytest.mark.parametrize("count,bm,bv,B,bf16,de,mp", [(1, 2, 3, 128, True, False, False), (2, 4, 2, 64, True, True, True),
+                                                       (63, 3, 3, 128, False, False, True), (64, 2, 2, 64, False, True, False),
+                                                       (65, 3, 4, 128, False, False, False), (400, 4, 4, 128, True, False, True),
+                                                       (4097, 2, 3, 64, True, False, False)])
+def test_many_short_tensors(gpu, count, bm, bv, B, bf16, de, mp):  # noqa: F811
+    """The search for the tensor of a wavefront (64 tensors at a step) and the pieces of tensors that are
+    mostly ends, in tables of few pieces and of many."""
+    table_against_flat(gpu, [ENDS[k % len(ENDS)] for k in range(count)], bm, bv, B, bf16, de, mp=mp)
+
+
+@pytest.mark.parametrize("bf16", (True, False))
+def test_a_launch_sized_by_the_units(gpu, bf16):  # noqa: F811
+    """A caller that hands back only the documented bits of the flags gets the same step."""
+    import torch
+    cfg = gpu.make_config(3, 2, 128, 1 if bf16 else 0)
+    sizes = [n for n in ENDS if n] * 40
+    dtype = torch.bfloat16 if bf16 else torch.float32
+    sides = []
+    for bits_kept in (~0, 3):
+        gen = torch.Generator(device="cuda").manual_seed(1)
+        items = [(torch.randn(n, device="cuda", generator=gen), torch.randn(n, device="cuda", generator=gen).to(dtype),
+                  gpu.SoloState(n, cfg)) for n in sizes]
+        table = gpu.SoloMultiTable(items, cfg)
+        assert table.flags >> 2 == sum(n // 1024 + -(-(-(-n // 80) * 80 - n // 1024 * 1024) // 512) * (n % 1024 > 0)
+                                       for n in sizes)
+        table.flags &= bits_kept
+        table.step(1)
+        table.step(2)
+        sides.append([x for p, _, st in items for x in (p, *st.buffers())])
+    assert all(torch.equal(bits(a), bits(b)) for a, b in zip(*sides))
