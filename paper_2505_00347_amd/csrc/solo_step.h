@@ -488,7 +488,8 @@ template <bool V> struct BoolTag { static constexpr bool value = V; };
 // accesses per lane and stream.  A wavefront's access then covers every other 16 bytes of its two
 // kilobytes, twice the requests of a coalesced one, but nothing has to be turned around through LDS:
 // the code for 8 elements per lane runs where a launch is all latency (the transposition and its
-// waits were 500 of the 6400-7200 cycles of a wavefront).  TAIL: element by element, bounds-checked.
+// waits were 500 of the 6400-7200 cycles of a wavefront).  TAIL: the lane that holds the buffer's end
+// goes element by element, bounds-checked, and those behind it not at all.
 struct RawPG { float4 p0, p1; uint4 g0, g1; };
 
 template <bool BF16, bool TAIL>
@@ -496,7 +497,7 @@ __device__ __forceinline__ RawPG load_pg(const StepArgs &a, const uint64_t e0)
 {
     RawPG r;
     r.g1 = make_uint4(0, 0, 0, 0);
-    if (!TAIL) {
+    if (!TAIL || e0 + 8 <= a.n) {
         const float4 *pp = reinterpret_cast<const float4 *>(a.param + e0);
         r.p0 = pp[0]; r.p1 = pp[1];
         if (BF16) {
@@ -880,7 +881,7 @@ __device__ __forceinline__ void ema_param(const StepArgs &a, const uint32_t tm_a
 template <bool EXT, bool TAIL>
 __device__ __forceinline__ void store_params8(const StepArgs &a, const uint64_t e0, const bool *ok, const float (&p)[8])
 {
-    if (!TAIL) {
+    if (!TAIL || ok[7]) {
         float4 *const pp = reinterpret_cast<float4 *>(a.param + e0);
         pp[0] = make_float4(p[0], p[1], p[2], p[3]);
         pp[1] = make_float4(p[4], p[5], p[6], p[7]);
@@ -1148,41 +1149,55 @@ __device__ __forceinline__ uint32_t quantile16(const float (&vh)[16], uint32_t *
 template <bool BF16>
 struct RawPG16 { float4 p[4]; uint4 g[BF16 ? 2 : 4]; };
 
-// TAIL: loaded per lane (its own 16 elements, those that exist).
-template <bool BF16, bool TAIL = false>
-__device__ __forceinline__ RawPG16<BF16> load_pg16(const StepArgs &a, uint64_t chunk_e0, uint32_t lane)
+// `here`: elements of the chunk that exist (uniform); absent ones read as zeros, and only the vector
+// that holds the end of the buffer is read element by element.
+template <bool BF16>
+__device__ __forceinline__ RawPG16<BF16> load_pg16(const StepArgs &a, uint64_t chunk_e0, uint32_t lane, const uint32_t here = kIter16)
 {
     RawPG16<BF16> r;
-    if (!TAIL) {
-        const float *pp = a.param + chunk_e0 + lane * 4u;
+    const float *pp = a.param + chunk_e0 + lane * 4u;
+    const uint16_t *hp = static_cast<const uint16_t *>(a.grad) + chunk_e0 + lane * 8u;     // bf16 gradients
+    const uint32_t *gp = static_cast<const uint32_t *>(a.grad) + chunk_e0 + lane * 4u;     // fp32 gradients
+    if (__builtin_expect(here == kIter16, 1)) {
 #pragma unroll
         for (int k = 0; k < 4; ++k) r.p[k] = stream_load_f4(pp + 256 * k);
-        if (BF16) {
-            const uint16_t *gp = static_cast<const uint16_t *>(a.grad) + chunk_e0 + lane * 8u;
 #pragma unroll
-            for (int k = 0; k < 2; ++k) r.g[k] = stream_load_u4(gp + 512 * k);
-        } else {
-            const float *gp = static_cast<const float *>(a.grad) + chunk_e0 + lane * 4u;
+        for (int k = 0; k < (BF16 ? 2 : 4); ++k) r.g[k] = BF16 ? stream_load_u4(hp + 512 * k) : stream_load_u4(gp + 256 * k);
+        return r;
+    }
 #pragma unroll
-            for (int k = 0; k < (BF16 ? 2 : 4); ++k) r.g[k] = stream_load_u4(gp + 256 * k);
+    for (int k = 0; k < 4; ++k) {
+        const uint32_t i = lane * 4u + 256u * k;
+        r.p[k] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+        if (!BF16) r.g[k] = make_uint4(0, 0, 0, 0);
+        if (i + 4u <= here) {
+            r.p[k] = stream_load_f4(pp + 256 * k);
+            if (!BF16) r.g[k] = stream_load_u4(gp + 256 * k);
+        } else if (i < here) {
+            r.p[k].x = pp[256 * k];
+            if (i + 1u < here) r.p[k].y = pp[256 * k + 1];
+            if (i + 2u < here) r.p[k].z = pp[256 * k + 2];
+            if (!BF16) {
+                r.g[k].x = gp[256 * k];
+                if (i + 1u < here) r.g[k].y = gp[256 * k + 1];
+                if (i + 2u < here) r.g[k].z = gp[256 * k + 2];
+            }
         }
-    } else {
-        const uint64_t e0 = chunk_e0 + lane * 16u;
-        float p[16]; uint32_t g[16];
+    }
+    if (BF16) {
 #pragma unroll
-        for (int j = 0; j < 16; ++j) {
-            const bool ok = e0 + j < a.n;
-            p[j] = ok ? a.param[e0 + j] : 0.0f;
-            if (BF16) g[j] = ok ? (uint32_t)static_cast<const uint16_t *>(a.grad)[e0 + j] : 0u;
-            else      g[j] = ok ? static_cast<const uint32_t *>(a.grad)[e0 + j] : 0u;
-        }
+        for (int k = 0; k < 2; ++k) {
+            const uint32_t i = lane * 8u + 512u * k;
+            r.g[k] = make_uint4(0, 0, 0, 0);
+            if (i + 8u <= here) {
+                r.g[k] = stream_load_u4(hp + 512 * k);
+            } else if (i < here) {
+                uint32_t w[4] = {0, 0, 0, 0};
 #pragma unroll
-        for (int k = 0; k < 4; ++k) r.p[k] = make_float4(p[4 * k], p[4 * k + 1], p[4 * k + 2], p[4 * k + 3]);
-#pragma unroll
-        for (int k = 0; k < (BF16 ? 2 : 4); ++k) {
-            if (BF16) r.g[k] = make_uint4(g[8 * k] | (g[8 * k + 1] << 16), g[8 * k + 2] | (g[8 * k + 3] << 16),
-                                          g[8 * k + 4] | (g[8 * k + 5] << 16), g[8 * k + 6] | (g[8 * k + 7] << 16));
-            else      r.g[k] = make_uint4(g[4 * k], g[4 * k + 1], g[4 * k + 2], g[4 * k + 3]);
+                for (int j = 0; j < 7; ++j)
+                    if (i + j < here) w[j / 2] |= (uint32_t)hp[512 * k + j] << (16 * (j & 1));
+                r.g[k] = make_uint4(w[0], w[1], w[2], w[3]);
+            }
         }
     }
     return r;
@@ -1200,37 +1215,29 @@ struct Stage16 {
           c2(stage + (lane + lane / 8u)), l2(stage + (2u * lane + lane / 4u)) {}
 };
 
-// A lane's 16 consecutive elements out of the coalesced layout they were loaded in (TAIL: loaded
-// per lane already).
-template <bool BF16, bool TAIL = false>
+// A lane's 16 consecutive elements out of the coalesced layout they were loaded in.
+template <bool BF16>
 __device__ __forceinline__ void lane_layout16(const RawPG16<BF16> &raw, const Stage16 &st,
                                               float (&p)[16], float (&g)[16])
 {
     float4 t[4];
     uint4 h[BF16 ? 2 : 4];
-    if (TAIL) {
 #pragma unroll
-        for (int c = 0; c < 4; ++c) t[c] = raw.p[c];
+    for (int k = 0; k < 4; ++k) st.c4[72 * k] = raw.p[k];
+    wave_lds_sync();                   // (also orders the level tables before their readers)
 #pragma unroll
-        for (int c = 0; c < (BF16 ? 2 : 4); ++c) h[c] = raw.g[c];
-    } else {
+    for (int c = 0; c < 4; ++c) t[c] = st.l4[c];
+    wave_lds_sync();
 #pragma unroll
-        for (int k = 0; k < 4; ++k) st.c4[72 * k] = raw.p[k];
-        wave_lds_sync();                   // (also orders the level tables before their readers)
+    for (int k = 0; k < (BF16 ? 2 : 4); ++k) {
+        const float4 x = make_float4(u2f(raw.g[k].x), u2f(raw.g[k].y), u2f(raw.g[k].z), u2f(raw.g[k].w));
+        if (BF16) st.c2[72 * k] = x; else st.c4[72 * k] = x;
+    }
+    wave_lds_sync();
 #pragma unroll
-        for (int c = 0; c < 4; ++c) t[c] = st.l4[c];
-        wave_lds_sync();
-#pragma unroll
-        for (int k = 0; k < (BF16 ? 2 : 4); ++k) {
-            const float4 x = make_float4(u2f(raw.g[k].x), u2f(raw.g[k].y), u2f(raw.g[k].z), u2f(raw.g[k].w));
-            if (BF16) st.c2[72 * k] = x; else st.c4[72 * k] = x;
-        }
-        wave_lds_sync();
-#pragma unroll
-        for (int c = 0; c < (BF16 ? 2 : 4); ++c) {
-            const float4 x = BF16 ? st.l2[c] : st.l4[c];
-            h[c] = make_uint4(f2u(x.x), f2u(x.y), f2u(x.z), f2u(x.w));
-        }
+    for (int c = 0; c < (BF16 ? 2 : 4); ++c) {
+        const float4 x = BF16 ? st.l2[c] : st.l4[c];
+        h[c] = make_uint4(f2u(x.x), f2u(x.y), f2u(x.z), f2u(x.w));
     }
 #pragma unroll
     for (int c = 0; c < 4; ++c) { p[4 * c] = t[c].x; p[4 * c + 1] = t[c].y; p[4 * c + 2] = t[c].z; p[4 * c + 3] = t[c].w; }
@@ -1247,22 +1254,11 @@ __device__ __forceinline__ void lane_layout16(const RawPG16<BF16> &raw, const St
 
 // The new parameters of a lane's 16 elements (and their bf16 copy, if asked for: 32 bytes per
 // lane, two vectors, first) back to the coalesced layout and streamed out; chunk_e0: first
-// element of the wavefront's 1024.
-template <bool EXT, bool TAIL = false>
+// element of the wavefront's 1024, of which `here` exist.
+template <bool EXT>
 __device__ __forceinline__ void store_params16(const StepArgs &a, const uint64_t chunk_e0, const uint32_t lane,
-                                               const float (&p)[16], const Stage16 &st)
+                                               const float (&p)[16], const Stage16 &st, const uint32_t here = kIter16)
 {
-    if (TAIL) {                                    // element-wise, those that exist
-        const uint64_t e0 = chunk_e0 + lane * 16u;
-#pragma unroll
-        for (int j = 0; j < 16; ++j) {
-            if (e0 + j < a.n) {
-                a.param[e0 + j] = p[j];
-                if (EXT && a.param_bf16) a.param_bf16[e0 + j] = (uint16_t)pack_bf16(p[j], 0.0f);
-            }
-        }
-        return;
-    }
     wave_lds_sync();
     if (EXT && a.param_bf16) {
 #pragma unroll
@@ -1274,15 +1270,41 @@ __device__ __forceinline__ void store_params16(const StepArgs &a, const uint64_t
         wave_lds_sync();
         uint16_t *hp = a.param_bf16 + chunk_e0 + lane * 8u;
 #pragma unroll
-        for (int k = 0; k < 2; ++k) stream_store_f4(reinterpret_cast<float *>(hp + 512 * k), st.c2[72 * k]);
+        for (int k = 0; k < 2; ++k) {
+            const uint32_t i = lane * 8u + 512u * k;
+            const float4 x = st.c2[72 * k];
+            if (here == kIter16 || i + 8u <= here) {
+                stream_store_f4(reinterpret_cast<float *>(hp + 512 * k), x);
+            } else if (i < here) {
+                const uint32_t w[4] = {f2u(x.x), f2u(x.y), f2u(x.z), f2u(x.w)};
+#pragma unroll
+                for (int j = 0; j < 7; ++j)
+                    if (i + j < here) hp[512 * k + j] = (uint16_t)(w[j / 2] >> (16 * (j & 1)));
+            }
+        }
         wave_lds_sync();
     }
 #pragma unroll
     for (int c = 0; c < 4; ++c) st.l4[c] = make_float4(p[4 * c], p[4 * c + 1], p[4 * c + 2], p[4 * c + 3]);
     wave_lds_sync();
     float *pp = a.param + chunk_e0 + lane * 4u;
+    if (__builtin_expect(here == kIter16, 1)) {
 #pragma unroll
-    for (int k = 0; k < 4; ++k) stream_store_f4(pp + 256 * k, st.c4[72 * k]);
+        for (int k = 0; k < 4; ++k) stream_store_f4(pp + 256 * k, st.c4[72 * k]);
+        return;
+    }
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        const uint32_t i = lane * 4u + 256u * k;
+        const float4 x = st.c4[72 * k];
+        if (here == kIter16 || i + 4u <= here) {
+            stream_store_f4(pp + 256 * k, x);
+        } else if (i < here) {
+            pp[256 * k] = x.x;
+            if (i + 1u < here) pp[256 * k + 1] = x.y;
+            if (i + 2u < here) pp[256 * k + 2] = x.z;
+        }
+    }
 }
 
 // Codes of a lane's 16 elements (two runs of 8: e0 is the first element, wm / sm / wv / sv the
@@ -1290,9 +1312,8 @@ __device__ __forceinline__ void store_params16(const StepArgs &a, const uint64_t
 // image of the code words.  3-bit codes share words between lanes: XOR turns this lane's old
 // fields into the new ones and leaves the neighbours' alone.  2- and 4-bit words belong to one lane
 // (2-bit: both runs lie in word wm[0]).
-template <int BM, int BV, bool MDE, bool TAIL = false>
+template <int BM, int BV, bool MDE>
 __device__ __forceinline__ void encode_into_image16(const StepArgs &a, const uint64_t e0, const float *mh, const float *vh,
-                                                    const bool *ok,
                                                     const BlockCodec &codec, const uint32_t de_base,
                                                     uint32_t *const img_m, uint32_t *const img_v,
                                                     const uint32_t (&wm)[2], const uint32_t (&sm)[2],
@@ -1303,7 +1324,7 @@ __device__ __forceinline__ void encode_into_image16(const StepArgs &a, const uin
 #pragma unroll
     for (int r = 0; r < 2; ++r) {
         uint32_t m8, v8;
-        encode_run<BM, BV, MDE, TAIL>(a, e0 + 8u * r, mh + 8 * r, vh + 8 * r, TAIL ? ok + 8 * r : nullptr, codec, de_base, m8, v8);
+        encode_run<BM, BV, MDE, false>(a, e0 + 8u * r, mh + 8 * r, vh + 8 * r, nullptr, codec, de_base, m8, v8);
         if (BM == 3) {
             const uint32_t xm = mc8[r] ^ m8;
             atomicXor(&img_m[wm[r]], (xm << (3u * sm[r])) & 0x3FFFFFFFu);
@@ -1330,8 +1351,7 @@ __device__ __forceinline__ void encode_into_image16(const StepArgs &a, const uin
 // The code words of the 1024 elements that a wavefront steps on its own (16 consecutive elements
 // per lane): staged in LDS, one or two words of each stream per lane, and written back by the lane
 // that staged them.  The first word may begin in the share before (ten-to-a-word codes).
-// TAIL: words behind the buffer are left alone.
-template <int BM, int BV, bool TAIL = false>
+template <int BM, int BV>
 struct ChunkWords16 {
     static constexpr int CM = 32 / BM, CV = 32 / BV;                 // codes per word
     static constexpr int KM = CM == 16 ? 1 : 2, KV = CV == 16 ? 1 : 2;   // words of a stream per lane (64 x K >= words of 1024 elements)
@@ -1341,26 +1361,27 @@ struct ChunkWords16 {
     uint32_t own_m[KM], own_v[KV];             // the staged words as they were loaded
     uint32_t wm[2], sm[2], wv[2], sv[2];       // word (of the image) and slot of the first code of the lane's two runs of 8
 
-    // ew0: first element of the wavefront's share.  Issues the loads.
-    __device__ __forceinline__ void load(const StepArgs &a, const uint64_t ew0, const uint32_t lane)
+    // ew0: first element of the wavefront's share, of which `here` exist (0: of the share in front of it).
+    // Issues the loads.  ALL_LANES: lanes without a word load the last one again, because a load
+    // under a condition is waited for inside it, with every load in front of it (blocks of 2048, 1 million
+    // elements, 2-bit/3-bit bf16: 9.6 us, 9.2 with it and the words in front of the parameters).
+    template <bool ALL_LANES>
+    __device__ __forceinline__ void load(const StepArgs &a, const uint64_t ew0, const uint32_t lane, const uint32_t here)
     {
         gm_lo = ew0 / CM; gv_lo = ew0 / CV;
         const uint32_t rm0 = (uint32_t)(ew0 - gm_lo * CM), rv0 = (uint32_t)(ew0 - gv_lo * CV);   // slot of the first element
-        nwm = (rm0 + kIter16 + CM - 1) / CM; nwv = (rv0 + kIter16 + CV - 1) / CV;
-        if (TAIL) {
-            const uint64_t m_left = (a.n + CM - 1) / CM, v_left = (a.n + CV - 1) / CV;    // words of the buffer
-            nwm = m_left <= gm_lo ? 0u : m_left - gm_lo < nwm ? (uint32_t)(m_left - gm_lo) : nwm;
-            nwv = v_left <= gv_lo ? 0u : v_left - gv_lo < nwv ? (uint32_t)(v_left - gv_lo) : nwv;
-        }
+        nwm = here ? (rm0 + here + CM - 1) / CM : 0; nwv = here ? (rv0 + here + CV - 1) / CV : 0;
+        const uint64_t fm = here ? gm_lo : (ew0 - kIter16) / CM, fv = here ? gv_lo : (ew0 - kIter16) / CV;
+        const uint32_t lm = here ? nwm - 1u : 0u, lv = here ? nwv - 1u : 0u;
 #pragma unroll
         for (int k = 0; k < KM; ++k) {
             own_m[k] = 0;
-            if (lane + 64u * k < nwm) own_m[k] = a.m_words[gm_lo + lane + 64u * k];
+            if (ALL_LANES || lane + 64u * k < nwm) own_m[k] = a.m_words[fm + (ALL_LANES ? umin(lane + 64u * k, lm) : lane + 64u * k)];
         }
 #pragma unroll
         for (int k = 0; k < KV; ++k) {
             own_v[k] = 0;
-            if (lane + 64u * k < nwv) own_v[k] = a.v_words[gv_lo + lane + 64u * k];
+            if (ALL_LANES || lane + 64u * k < nwv) own_v[k] = a.v_words[fv + (ALL_LANES ? umin(lane + 64u * k, lv) : lane + 64u * k)];
         }
 #pragma unroll
         for (int r = 0; r < 2; ++r) {
@@ -1394,6 +1415,16 @@ struct ChunkWords16 {
             const uint32_t vw0 = img_v[wv[BV == 2 ? 0 : r]], vw1 = (BV == 3) ? img_v[wv[r] + 1] : 0u;
             mc8[r] = extract8<BM>(mw0, mw1, BM == 2 ? 8u * r : sm[r]) & (uint32_t)((1ull << (8 * BM)) - 1ull);
             vc8[r] = extract8<BV>(vw0, vw1, BV == 2 ? 8u * r : sv[r]) & (uint32_t)((1ull << (8 * BV)) - 1ull);
+        }
+    }
+    // `here` < 1024: the fields behind the last element of the buffer stay zero
+    __device__ __forceinline__ void clear_behind(uint32_t *const img_m, uint32_t *const img_v, const uint64_t ew0,
+                                                 const uint32_t lane, const uint32_t here) const
+    {
+        if (lane == 0 && here != 0) {
+            const uint32_t um = (uint32_t)(ew0 + here - (gm_lo + nwm - 1u) * CM), uv = (uint32_t)(ew0 + here - (gv_lo + nwv - 1u) * CV);
+            img_m[nwm - 1u] &= (uint32_t)((1ull << (BM * um)) - 1ull);       // (fields in use of the last word)
+            img_v[nwv - 1u] &= (uint32_t)((1ull << (BV * uv)) - 1ull);
         }
     }
     __device__ __forceinline__ void write_back(const StepArgs &a, const uint32_t *const img_m, const uint32_t *const img_v,
@@ -1448,7 +1479,7 @@ __device__ __forceinline__ void step_chunk16(const StepArgs &a, const uint64_t c
 
     // ---- every load is issued before the first one is waited for
     ChunkWords16<BM, BV> words;
-    words.load(a, ew0, lane);
+    words.template load<false>(a, ew0, lane, kIter16);
     const uint64_t gb = chunk * NG + grp;
     const float dm_old = a.m_scale[gb], dv_old = a.v_scale[gb], al_old = a.v_base[gb];
     const RawPG16<BF16> raw = load_pg16<BF16>(a, ew0, lane);
@@ -1486,7 +1517,7 @@ __device__ __forceinline__ void step_chunk16(const StepArgs &a, const uint64_t c
     const uint32_t xp_bits = quantile16<G>(vh, col, a.rank_full, dv);
 
     const BlockCodec codec = block_codec<BV, G, L, MDE>(xp_bits, dm, dv, lane, lig, gshift);
-    encode_into_image16<BM, BV, MDE>(a, e0, mh, vh, nullptr, codec, de_base, img_m, img_v,
+    encode_into_image16<BM, BV, MDE>(a, e0, mh, vh, codec, de_base, img_m, img_v,
                                      words.wm, words.sm, words.wv, words.sv, mc8, vc8);
     if (lig == 0) { a.m_scale[gb] = dm; a.v_scale[gb] = dv; a.v_base[gb] = codec.alpha; }
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");

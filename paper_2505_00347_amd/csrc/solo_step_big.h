@@ -1,10 +1,9 @@
 // The fused SOLO AdamW step for blocks of 2048 elements (the large-block setting of the paper's
 // block-size comparison, Sec. 4.2), gfx950, wave64.
 //
-// A block of 2048 elements is held by one workgroup of two wavefronts, 1024 elements each, sixteen
-// consecutive elements per lane; the shorter last block of a buffer by one more workgroup of the
-// same launch (the first one, since its code, with bounds checks on every element, takes longest;
-// a launch of its own behind the full blocks made 1,000,003 elements take 15.9 us instead of 10.2).
+// A block of 2048 elements is held by one workgroup: of two wavefronts, 1024 elements each, sixteen
+// consecutive elements per lane, or, where a launch has few blocks, of four, eight per lane
+// (step_block_quad).  The shorter last block of a buffer runs in the same launch.
 // The element-wise part (decode by table look-up, both EMAs, the parameter, the encoders, the
 // 32-bit words of the code streams) is that of a 1024-element chunk of solo_step.h and runs
 // without any exchange between the wavefronts.  What a block of this size changes is the block
@@ -51,11 +50,15 @@ struct BigLayout {
     static constexpr int kOffTv = 272;                        // level tables, 64-byte aligned
     static constexpr int kOffTm = 288;
     static constexpr int kSlab = 304;
-    // exchange between the wavefronts: block maxima; ranges of two passes; counts of the guess; the
-    // keys that are left
-    static constexpr int kMax = 0, kPass = 4, kCounts = 14, kLeft = 18, kList = 20, kXch = kList + 2 * (int)kFewKeys;
 };
 static_assert(BigLayout::kWork >= 2048, "the histogram lies inside the work area");
+// Exchange between the W wavefronts of a block: block maxima; ranges of two passes; counts of the guess;
+// the keys that are left.
+template <int W>
+struct BigExchange {
+    static constexpr int kMaxM = 0, kMaxV = W, kPass = 2 * W, kCounts = kPass + 10, kLeft = kCounts + 2 * W, kList = kLeft + W;
+    static constexpr int kWords = kList + W * (int)kFewKeys;
+};
 static_assert(288 * 4 <= BigLayout::kStage, "the padded transposition (Stage16) fits a staging area");
 static_assert(ChunkWords16<3, 4>::kImage <= 132, "images");
 
@@ -85,6 +88,7 @@ __device__ __forceinline__ uint32_t wave_inclusive_sum(uint32_t x)
 // of that range which many of them may equal (kNoGuess: none known).
 struct Narrowed { uint32_t base, len, rank, count, guess; };
 constexpr uint32_t kNoGuess = 0xFFFFFFFFu;
+constexpr uint32_t kNoKey = 0xFFFFFFFFu;       // of an element that does not exist: outside every range
 
 // The bin of the histogram (512 bins of 4 counters each, in the halves `half` of its words) that holds
 // the rank-th key, by one wavefront: a lane sums the 32 words of its own 8 bins (128-bit reads in an
@@ -116,20 +120,28 @@ __device__ __forceinline__ uint32_t find_bin(const uint32_t *const h, const uint
 // one of the two wavefronts (they take turns) finds the bin of the rank and leaves the new range in
 // LDS, a second barrier (it costs less than both wavefronts summing the histogram for themselves).
 // FIRST: every key counts, those below the range in its first bin, and what only a non-finite input
-// can put above it in the last one.
+// can put above it in the last one; `absent`: but for those of elements that do not exist (kNoKey).
 template <int NK, bool FIRST>
 __device__ __forceinline__ void narrow(Narrowed &at, const uint32_t (&key)[NK], const uint32_t lane, const bool mine,
-                                       uint32_t *const h, const uint32_t half, uint32_t *const res)
+                                       uint32_t *const h, const uint32_t half, uint32_t *const res, const bool absent = false)
 {
     const uint32_t wide = 32u - (uint32_t)__builtin_clz(at.len - 1u);          // (len > 1)
     const uint32_t shift = FIRST ? 19u : wide > 9u ? wide - 9u : 0u, one = 1u << half;
     const uint32_t counter = 4u * (lane & 3u);
     char *const bytes = reinterpret_cast<char *>(h);
+    if (FIRST && __builtin_expect(absent, 0)) {
 #pragma unroll
-    for (int j = 0; j < NK; ++j) {
-        const uint32_t d = FIRST ? __builtin_elementwise_sub_sat(key[j], at.base) : key[j] - at.base;
-        const uint32_t bin = FIRST ? umin(d >> shift, 511u) : d >> shift;
-        if (FIRST || d < at.len) atomicAdd(reinterpret_cast<uint32_t *>(bytes + ((bin << 4) | counter)), one);
+        for (int j = 0; j < NK; ++j) {
+            const uint32_t bin = umin(__builtin_elementwise_sub_sat(key[j], at.base) >> shift, 511u);
+            if (key[j] != kNoKey) atomicAdd(reinterpret_cast<uint32_t *>(bytes + ((bin << 4) | counter)), one);
+        }
+    } else {
+#pragma unroll
+        for (int j = 0; j < NK; ++j) {
+            const uint32_t d = FIRST ? __builtin_elementwise_sub_sat(key[j], at.base) : key[j] - at.base;
+            const uint32_t bin = FIRST ? umin(d >> shift, 511u) : d >> shift;
+            if (FIRST || d < at.len) atomicAdd(reinterpret_cast<uint32_t *>(bytes + ((bin << 4) | counter)), one);
+        }
     }
     __syncthreads();
     if (mine) {
@@ -163,7 +175,7 @@ __device__ __forceinline__ void narrow(Narrowed &at, const uint32_t (&key)[NK], 
 // The keys of the range below the guess and equal to it are counted (by ballot: nothing that many
 // equal keys could slow down); the rank's side of it becomes the range.  Returns whether the guess
 // is the answer.
-template <int NK>
+template <int NK, int W>
 __device__ __forceinline__ bool try_guess(Narrowed &at, const uint32_t (&key)[NK], const uint32_t lane, const uint32_t wave,
                                           uint32_t *const counts)
 {
@@ -175,8 +187,11 @@ __device__ __forceinline__ bool try_guess(Narrowed &at, const uint32_t (&key)[NK
     }
     if (lane == 0) { counts[2 * wave] = below; counts[2 * wave + 1] = same; }
     __syncthreads();
-    below = (uint32_t)__builtin_amdgcn_readfirstlane((int)(counts[0] + counts[2]));
-    same = (uint32_t)__builtin_amdgcn_readfirstlane((int)(counts[1] + counts[3]));
+    below = 0; same = 0;
+#pragma unroll
+    for (int w = 0; w < W; ++w) { below += counts[2 * w]; same += counts[2 * w + 1]; }
+    below = (uint32_t)__builtin_amdgcn_readfirstlane((int)below);
+    same = (uint32_t)__builtin_amdgcn_readfirstlane((int)same);
     if (at.rank <= below) {
         at.len = at.guess - at.base;
         at.count = below;
@@ -190,33 +205,38 @@ __device__ __forceinline__ bool try_guess(Narrowed &at, const uint32_t (&key)[NK
     return false;
 }
 
-// The rank-th smallest (1-based, uniform over the workgroup) of the NK keys that each thread of the
-// workgroup holds, 2048 in all: bit patterns of non-negative floats, none above kmax.  The first
-// pass counts sixteenths of an octave below the maximum (2^28 consecutive patterns in 512 bins), the
-// next ones 512ths of the bin that holds the rank.  As soon as at most kFewKeys are left, both
-// wavefronts compare those with each other instead: after two passes on scattered values and on
-// the clusters of a trained state.  Elements without a gradient share the few decoded values:
-// then, after the first pass, one of the keys that are left is tried as it is.  A rank below the first pass's range (28
-// octaves under the maximum, or zeros) starts over from 0.
+// The rank-th smallest (1-based, uniform over the workgroup) of the `present` keys that the threads of
+// the workgroup hold, NK each (W wavefronts; kNoKey: no key): bit patterns of non-negative floats, none
+// above kmax.  The first pass counts sixteenths of an octave below the maximum (2^28 consecutive
+// patterns in 512 bins), the next ones 512ths of the bin that holds the rank.  As soon as at most
+// kFewKeys are left, every wavefront compares those with each other instead: after two passes on
+// scattered values and on the clusters of a trained state.  Elements without a gradient share the
+// few decoded values: then, after the first pass, one of the keys that are left is tried as it is.
+// A rank below the first pass's range (28 octaves under the maximum, or zeros) starts over from 0.
 // (Against four fixed passes over 8 + 8 + 8 + 7 bits, the first of which only told binades apart, on
 // 2^26 elements of 2-bit/3-bit codes: 163.6 -> 153.7 us, with nine of ten gradients at zero
 // 203 -> 140 us, all gradients alike 236 -> 155 us; 72 -> 65 vector instructions per parameter, of
 // which about 15 are the selection.)
-template <int NK>
+template <int NK, int W>
 __device__ __forceinline__ uint32_t select_rank(const uint32_t (&key)[NK], const uint32_t kmax, const uint32_t rank,
-                                                const uint32_t lane, const uint32_t wave,
+                                                const uint32_t present, const uint32_t lane, const uint32_t wave,
                                                 uint32_t *const work, uint32_t *const xch)
 {
+    using Xch = BigExchange<W>;
     constexpr uint32_t kReach = 1u << 28;
-    uint32_t *const res = xch + BigLayout::kPass;
-    Narrowed at = {kmax >= kReach ? kmax - (kReach - 1u) : 0u, kReach, rank, (uint32_t)kBigBlock, kNoGuess};
-    narrow<NK, true>(at, key, lane, wave == 0, work, 0, res);
-    if (at.guess != kNoGuess && try_guess<NK>(at, key, lane, wave, xch + BigLayout::kCounts)) return at.guess;
+    uint32_t *const res = xch + Xch::kPass;
+    Narrowed at = {0u, 1u << 31, rank, present, kNoGuess};
+    if (__builtin_expect(present > kFewKeys, 1)) {
+        at.base = kmax >= kReach ? kmax - (kReach - 1u) : 0u;
+        at.len = kReach;
+        narrow<NK, true>(at, key, lane, wave == 0, work, 0, res, present < (uint32_t)kBigBlock);
+        if (at.guess != kNoGuess && try_guess<NK, W>(at, key, lane, wave, xch + Xch::kCounts)) return at.guess;
+    }
 #pragma unroll 1
     for (uint32_t pass = 1; at.count > kFewKeys && at.len > 1u; ++pass) {
         if (pass >= 2) {                           // both halves have been used
             uint4 *const z = reinterpret_cast<uint4 *>(work);
-            for (uint32_t i = wave * 64u + lane; i < 512u; i += kBigWaves * 64) z[i] = make_uint4(0, 0, 0, 0);
+            for (uint32_t i = wave * 64u + lane; i < 512u; i += W * 64) z[i] = make_uint4(0, 0, 0, 0);
             __syncthreads();
         }
         narrow<NK, false>(at, key, lane, wave == (pass & 1u), work, pass == 1 ? 16u : 0u, res + 5 * (pass & 1u));
@@ -224,7 +244,7 @@ __device__ __forceinline__ uint32_t select_rank(const uint32_t (&key)[NK], const
     if (at.len == 1u) return at.base;
     // few keys: every wavefront packs its own into LDS, then each lane compares one with all of
     // them: the answer is the largest key with fewer than `rank` keys below it
-    uint32_t *const list = xch + BigLayout::kList + wave * kFewKeys;
+    uint32_t *const list = xch + Xch::kList + wave * kFewKeys;
     uint32_t mine = 0;
 #pragma unroll
     for (int j = 0; j < NK; ++j) {
@@ -234,20 +254,49 @@ __device__ __forceinline__ uint32_t select_rank(const uint32_t (&key)[NK], const
         if (in) list[to & (kFewKeys - 1u)] = key[j];
         mine += (uint32_t)__builtin_popcountll(who);
     }
-    if (lane == 0) xch[BigLayout::kLeft + wave] = mine;
+    if (lane == 0) xch[Xch::kLeft + wave] = mine;
     __syncthreads();
-    const uint32_t first = (uint32_t)__builtin_amdgcn_readfirstlane((int)xch[BigLayout::kLeft]);
-    const uint32_t my = xch[BigLayout::kList + (lane < first ? lane : kFewKeys + lane - first) % (2u * kFewKeys)];
+    uint32_t slot = lane, from = 0;                // the lane's key: `slot` of wavefront `from`
+#pragma unroll
+    for (int w = 0; w + 1 < W; ++w) {
+        const uint32_t theirs = (uint32_t)__builtin_amdgcn_readfirstlane((int)xch[Xch::kLeft + w]);
+        const bool behind = from == (uint32_t)w && slot >= theirs;
+        slot = behind ? slot - theirs : slot;
+        from = behind ? w + 1u : from;
+    }
+    const uint32_t my = xch[Xch::kList + from * kFewKeys + (slot & (kFewKeys - 1u))];
     uint32_t below = 0;
     for (uint32_t i = 0; i < at.count; ++i)
         below += (uint32_t)__builtin_amdgcn_readlane((int)my, (int)i) < my ? 1u : 0u;
     return wave_max(lane < at.count && below < at.rank ? my : 0u);
 }
 
-// The whole step for block `blk` of 2048 elements (TAIL: the last, shorter block of the buffer,
-// with bounds checks on every element), executed by the two wavefronts of the calling workgroup.
-// What is done once per lane and block (level tables, the two divisions, the base, the hash of a
-// group of eight) is spread over 16 elements.
+// Elements of block `blk` that exist, and the rank of the quantile among them.
+__device__ __forceinline__ uint32_t present_in(const uint64_t n, const uint64_t blk)
+{
+    const uint64_t left = n - blk * kBigBlock;
+    return left < (uint64_t)kBigBlock ? (uint32_t)left : (uint32_t)kBigBlock;
+}
+__device__ __forceinline__ uint32_t rank_among(const StepArgs &a, const uint32_t present)
+{
+    if (present == (uint32_t)kBigBlock) return a.rank_full;
+    const float x = __builtin_ceilf(a.quantile_p * (float)present);
+    const uint32_t rank = x < 1.0f ? 1u : (uint32_t)x;
+    return rank > present ? present : rank;
+}
+
+// The whole step for block `blk` of 2048 elements, executed by the two wavefronts of the calling
+// workgroup.  What is done once per lane and block (level tables, the two divisions, the base, the
+// hash of a group of eight) is spread over 16 elements.
+// TAIL: also the shorter last block of a buffer.  It takes the same way with a few corrections under
+// branches that are uniform for a wavefront: absent
+// elements are read as zeros with the codes of a zero 1st moment, get no key, and their fields of the last
+// code word are cleared again.  (Bounds checks on every element, instead, cost the full blocks of
+// the same kernel registers: with fp32 gradients and the variants 106 instead of 96, i.e. four
+// wavefronts per SIMD instead of five; 2-bit/3-bit AdaBelief, 42.7 million
+// elements: 114 us, 108 now.)
+// The variants run full blocks by this form, too: two copies of them would spill.  The plain step has a copy
+// for full blocks without the corrections (2-bit/3-bit bf16: 97 us by the one form, 93 with the copy).
 template <int BM, int BV, bool BF16, bool MDE, bool EXT, bool TAIL>
 __device__ __forceinline__ void step_block(const StepArgs &a, const uint64_t blk, const uint32_t lane,
                                            const uint32_t wave, uint32_t *const slab, uint32_t *const work,
@@ -255,25 +304,25 @@ __device__ __forceinline__ void step_block(const StepArgs &a, const uint64_t blk
 {
     constexpr int L = (1 << (BM - 1)) - 1;
     constexpr bool kDeTable = MDE && BM >= 3;
+    using Xch = BigExchange<kBigWaves>;
 
-    const uint32_t tid = wave * 64u + lane;
     const uint64_t ew0 = blk * kBigBlock + (uint64_t)wave * kIter16;  // first element of this wavefront
     const uint64_t e0 = ew0 + lane * 16u;                             // first element of this lane
+    const uint32_t present = TAIL ? present_in(a.n, blk) : (uint32_t)kBigBlock, before = wave * kIter16;
+    const uint32_t here = !TAIL ? (uint32_t)kIter16 : present <= before ? 0u : umin(present - before, (uint32_t)kIter16);  // of this wavefront
+    const uint32_t mine = here <= lane * 16u ? 0u : umin(here - lane * 16u, 16u);                                           // of this lane
     uint32_t *const img_m = slab + BigLayout::kOffImgM, *const img_v = slab + BigLayout::kOffImgV;
     float *const my_tv = reinterpret_cast<float *>(slab + BigLayout::kOffTv);
     float *const my_tm = reinterpret_cast<float *>(slab + BigLayout::kOffTm);
     const uint32_t tv_addr = lds_addr(my_tv), tm_addr = lds_addr(my_tm);
-    bool ok[16];                                   // the lane's elements that exist
-#pragma unroll
-    for (int j = 0; j < 16; ++j) ok[j] = !TAIL || e0 + j < a.n;
 
     // ---- loads: parameters and gradients, the wavefront's code words, the block's scalars
-    const RawPG16<BF16> raw = load_pg16<BF16, TAIL>(a, ew0, lane);
+    ChunkWords16<BM, BV> words;
+    words.template load<true>(a, ew0, lane, here);
+    const float dm_old = a.m_scale[blk], dv_old = a.v_scale[blk], al_old = a.v_base[blk];
+    const RawPG16<BF16> raw = load_pg16<BF16>(a, ew0, lane, here);
     const float gscale = (EXT && a.grad_scale) ? *a.grad_scale : 1.0f;
     const Stage16 st(reinterpret_cast<float4 *>(work + wave * BigLayout::kStage), lane);
-    ChunkWords16<BM, BV, TAIL> words;
-    words.load(a, ew0, lane);
-    const float dm_old = a.m_scale[blk], dv_old = a.v_scale[blk], al_old = a.v_base[blk];
     words.stage(img_m, img_v, lane);
 
     // ---- level tables of the block (every wavefront its own copy)
@@ -284,10 +333,18 @@ __device__ __forceinline__ void step_block(const StepArgs &a, const uint64_t blk
     wave_lds_sync();
     uint32_t mc8[2], vc8[2];
     words.codes(img_m, img_v, mc8, vc8);
+    if (__builtin_expect(here != kIter16, 0)) {                         // (code L is level 0 of either codebook)
+        constexpr uint32_t kZeroCodes = (uint32_t)((uint64_t)L * (((1ull << (8 * BM)) - 1ull) / ((1ull << BM) - 1ull)));
+#pragma unroll
+        for (int r = 0; r < 2; ++r) {
+            const uint32_t run = mine <= 8u * r ? 0u : umin(mine - 8u * r, 8u), keep = (uint32_t)((1ull << (BM * run)) - 1ull);
+            mc8[r] = (mc8[r] & keep) | (kZeroCodes & ~keep);
+        }
+    }
 
     // ---- coalesced layout -> 16 consecutive elements per lane
     float p[16], g[16];
-    lane_layout16<BF16, TAIL>(raw, st, p, g);
+    lane_layout16<BF16>(raw, st, p, g);
     if (EXT) {
 #pragma unroll
         for (int j = 0; j < 16; ++j) g[j] = __builtin_fmaf(a.l2, p[j], g[j] * gscale);
@@ -296,8 +353,16 @@ __device__ __forceinline__ void step_block(const StepArgs &a, const uint64_t blk
     // ---- dequantize (table look-up), EMA, parameter; new parameters streamed out
     float mh[16], vh[16];
     float m_absmax, v_max;
-    ema_param<16, BM, BV, EXT, TAIL, true>(a, tm_addr, tv_addr, mc8, vc8, ok, p, g, mh, vh, m_absmax, v_max);
-    store_params16<EXT, TAIL>(a, ew0, lane, p, st);
+    ema_param<16, BM, BV, EXT, false, true>(a, tm_addr, tv_addr, mc8, vc8, nullptr, p, g, mh, vh, m_absmax, v_max);
+    store_params16<EXT>(a, ew0, lane, p, st, here);
+    if (__builtin_expect(here != kIter16, 0)) {                         // (kNoKey is a NaN: its code is whatever clear_behind() removes)
+        v_max = 0.0f;
+#pragma unroll
+        for (int j = 0; j < 16; ++j) {
+            v_max = (uint32_t)j < mine ? __builtin_fmaxf(v_max, vh[j]) : v_max;
+            vh[j] = (uint32_t)j < mine ? vh[j] : u2f(kNoKey);
+        }
+    }
 
     // ---- the work area becomes the histograms of the selection: a wavefront clears its own staging
     // area (it is done with it; the other may still be using its own)
@@ -313,57 +378,152 @@ __device__ __forceinline__ void step_block(const StepArgs &a, const uint64_t blk
     // ---- block maxima over the two wavefronts
     {
         const uint32_t wm_max = wave_max(f2u(m_absmax)), wv_max = wave_max(f2u(v_max));
-        if (lane == 0) { xch[BigLayout::kMax + wave] = wm_max; xch[BigLayout::kMax + 2 + wave] = wv_max; }
+        if (lane == 0) { xch[Xch::kMaxM + wave] = wm_max; xch[Xch::kMaxV + wave] = wv_max; }
     }
     __syncthreads();
-    float dm = u2f(umax(xch[BigLayout::kMax], xch[BigLayout::kMax + 1]));
-    const uint32_t kmax = (uint32_t)__builtin_amdgcn_readfirstlane(
-        (int)umax(xch[BigLayout::kMax + 2], xch[BigLayout::kMax + 3]));
+    float dm = u2f(umax(xch[Xch::kMaxM], xch[Xch::kMaxM + 1]));
+    const uint32_t kmax = (uint32_t)__builtin_amdgcn_readfirstlane((int)umax(xch[Xch::kMaxV], xch[Xch::kMaxV + 1]));
     float dv = u2f(kmax);
     if (dm < kTiny) dm = 0.0f;
     if (dv < kTiny) dv = 0.0f;
 
     // ---- the r-th smallest v^ of the block
-    uint32_t rank = a.rank_full;
-    if (TAIL) {
-        const uint32_t nb = (uint32_t)(a.n - blk * kBigBlock);
-        const float x = __builtin_ceilf(a.quantile_p * (float)nb);
-        rank = x < 1.0f ? 1u : (uint32_t)x;
-        rank = rank > nb ? nb : rank;
-    }
     uint32_t key[16];
 #pragma unroll
-    for (int j = 0; j < 16; ++j) key[j] = TAIL && !ok[j] ? kmax : f2u(vh[j]);   // (absent: further maxima, which no rank reaches)
-    const uint32_t xp_bits = select_rank<16>(key, kmax, rank, lane, wave, work, xch);
+    for (int j = 0; j < 16; ++j) key[j] = f2u(vh[j]);
+    const uint32_t xp_bits = select_rank<16, kBigWaves>(key, kmax, rank_among(a, present), present, lane, wave, work, xch);
 
     // ---- encoder constants (every 16 lanes for themselves), codes, the wavefront's words
     const uint32_t lig = lane & 15u, gshift = lane & 16u;
     uint32_t de_base = 0;
     if (kDeTable) de_base = lds_addr(lds_de) - 16u * DeBuckets<BM>::kLo;
     const BlockCodec codec = block_codec<BV, 16, L, MDE>(xp_bits, dm, dv, lane, lig, gshift);
-    encode_into_image16<BM, BV, MDE, TAIL>(a, e0, mh, vh, ok, codec, de_base, img_m, img_v,
-                                           words.wm, words.sm, words.wv, words.sv, mc8, vc8);
+    encode_into_image16<BM, BV, MDE>(a, e0, mh, vh, codec, de_base, img_m, img_v,
+                                     words.wm, words.sm, words.wv, words.sv, mc8, vc8);
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    if (__builtin_expect(here != kIter16, 0)) {
+        words.clear_behind(img_m, img_v, ew0, lane, here);
+        wave_lds_sync();
+    }
+    words.write_back(a, img_m, img_v, lane);
+    if (wave == 0 && lane == 0) { a.m_scale[blk] = dm; a.v_scale[blk] = dv; a.v_base[blk] = codec.alpha; }
+}
+
+// The same by four wavefronts, 8 consecutive elements per lane, where a launch is all latency: half
+// as long a chain in every lane, and parameters and gradients that are not turned around through
+// LDS.  Full and short blocks alike, with bounds checks.  (1000 elements, 2-bit/3-bit bf16: 8.8 us by
+// the two wavefronts with bounds checks on every element, 5.7 by this form; 1,000,003: 9.7 and 7.9.)
+constexpr int kQuadWaves = kBigBlock / kIter;
+struct QuadLayout {
+    static constexpr int kOffImgM = 0;                        // per wavefront: its words of each code stream
+    static constexpr int kOffImgV = ChunkWords8<3, 4, true>::kImage;
+    static constexpr int kOffTv = 144;                        // level tables, 64-byte aligned
+    static constexpr int kOffTm = 160;
+    static constexpr int kSlab = 176;
+};
+static_assert(2 * ChunkWords8<3, 4, true>::kImage <= QuadLayout::kOffTv, "images");
+
+template <int BM, int BV, bool BF16, bool MDE, bool EXT>
+__device__ __forceinline__ void step_block_quad(const StepArgs &a, const uint64_t blk, const uint32_t lane,
+                                                const uint32_t wave, uint32_t *const slab, uint32_t *const work,
+                                                uint32_t *const xch, const uint32_t *const lds_de)
+{
+    constexpr int L = (1 << (BM - 1)) - 1;
+    constexpr bool kDeTable = MDE && BM >= 3;
+    using Xch = BigExchange<kQuadWaves>;
+
+    const uint64_t ew0 = blk * kBigBlock + (uint64_t)wave * kIter;    // first element of this wavefront
+    const uint64_t e0 = ew0 + lane * 8u;                              // first element of this lane
+    const uint32_t present = present_in(a.n, blk);
+    uint32_t *const img_m = slab + QuadLayout::kOffImgM, *const img_v = slab + QuadLayout::kOffImgV;
+    float *const my_tv = reinterpret_cast<float *>(slab + QuadLayout::kOffTv);
+    float *const my_tm = reinterpret_cast<float *>(slab + QuadLayout::kOffTm);
+    const uint32_t tv_addr = lds_addr(my_tv), tm_addr = lds_addr(my_tm);
+    bool ok[8];                                    // the lane's elements that exist
+#pragma unroll
+    for (int j = 0; j < 8; ++j) ok[j] = e0 + j < a.n;
+
+    // ---- every load is issued before the first one is waited for; the histogram is cleared meanwhile
+    ChunkWords8<BM, BV, true> words;
+    words.load(a, ew0, lane);
+    const float dm_old = a.m_scale[blk], dv_old = a.v_scale[blk], al_old = a.v_base[blk];
+    const RawPG raw = load_pg<BF16, true>(a, e0);
+    const float gscale = (EXT && a.grad_scale) ? *a.grad_scale : 1.0f;
+    {
+        uint4 *const z = reinterpret_cast<uint4 *>(work);
+#pragma unroll
+        for (uint32_t i = 0; i < 512u / (64u * kQuadWaves); ++i) z[wave * 64u + lane + 64u * kQuadWaves * i] = make_uint4(0, 0, 0, 0);
+    }
+    words.stage(img_m, img_v, lane);
+    {
+        const float de_level = MDE ? DeLevels<BM>::level(lane) : 0.0f;
+        fill_level_tables<BM, BV, MDE, 64>(my_tv, my_tm, lane, dm_old, dv_old, al_old, &de_level);
+    }
+    wave_lds_sync();
+    uint32_t mc8, vc8;
+    words.codes(img_m, img_v, mc8, vc8);
+
+    // ---- dequantize (table look-up), EMA, parameter
+    float p[8], g[8];
+    unpack_pg<BF16>(raw, p, g);
+    if (EXT) {
+#pragma unroll
+        for (int j = 0; j < 8; ++j) g[j] = __builtin_fmaf(a.l2, p[j], g[j] * gscale);
+    }
+    float mh[8], vh[8];
+    float m_absmax, v_max;
+    ema_param<8, BM, BV, EXT, true, true>(a, tm_addr, tv_addr, &mc8, &vc8, ok, p, g, mh, vh, m_absmax, v_max);
+    store_params8<EXT, true>(a, e0, ok, p);
+
+    // ---- block maxima over the four wavefronts
+    {
+        const uint32_t wm_max = wave_max(f2u(m_absmax)), wv_max = wave_max(f2u(v_max));
+        if (lane == 0) { xch[Xch::kMaxM + wave] = wm_max; xch[Xch::kMaxV + wave] = wv_max; }
+    }
+    __syncthreads();
+    float dm = u2f(umax(umax(xch[Xch::kMaxM], xch[Xch::kMaxM + 1]), umax(xch[Xch::kMaxM + 2], xch[Xch::kMaxM + 3])));
+    const uint32_t kmax = (uint32_t)__builtin_amdgcn_readfirstlane(
+        (int)umax(umax(xch[Xch::kMaxV], xch[Xch::kMaxV + 1]), umax(xch[Xch::kMaxV + 2], xch[Xch::kMaxV + 3])));
+    float dv = u2f(kmax);
+    if (dm < kTiny) dm = 0.0f;
+    if (dv < kTiny) dv = 0.0f;
+
+    // ---- the r-th smallest v^ of the block
+    uint32_t key[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) key[j] = ok[j] ? f2u(vh[j]) : kNoKey;
+    const uint32_t xp_bits = select_rank<8, kQuadWaves>(key, kmax, rank_among(a, present), present, lane, wave, work, xch);
+
+    // ---- encoder constants (every 16 lanes for themselves), codes, the wavefront's words
+    const uint32_t lig = lane & 15u, gshift = lane & 16u;
+    uint32_t de_base = 0;
+    if (kDeTable) de_base = lds_addr(lds_de) - 16u * DeBuckets<BM>::kLo;
+    const BlockCodec codec = block_codec<BV, 16, L, MDE>(xp_bits, dm, dv, lane, lig, gshift);
+    uint32_t m8, v8;
+    encode_run<BM, BV, MDE, true>(a, e0, mh, vh, ok, codec, de_base, m8, v8);
+    xor_into_image8<BM, BV>(img_m, img_v, words.wm, words.sm, words.wv, words.sv, mc8 ^ m8, vc8 ^ v8);
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     __builtin_amdgcn_wave_barrier();
     words.write_back(a, img_m, img_v, lane);
-    if (tid == 0) { a.m_scale[blk] = dm; a.v_scale[blk] = dv; a.v_base[blk] = codec.alpha; }
+    if (wave == 0 && lane == 0) { a.m_scale[blk] = dm; a.v_scale[blk] = dv; a.v_base[blk] = codec.alpha; }
 }
 
-// (Registers: the plain step with bf16 gradients fits five wavefronts per SIMD without spilling,
-// except with two ten-to-a-word streams; LDS allows five for every format.)
-template <int BM, int BV, bool BF16, bool EXT>
-constexpr int big_waves() { return (BF16 && !EXT && !(BM == 3 && BV == 3)) ? kMinWaves : kMinWaves - 1; }
+// (Five wavefronts per SIMD: 77-97 registers, and LDS allows six.)
 
-#define SOLO_BIG_LDS                                                                                   \
+#define SOLO_BIG_LDS(WAVES_, WORK_, SLAB_)                                                             \
     constexpr int kDeWords = de_words<BM, MDE>();                                                      \
-    __shared__ __attribute__((aligned(64))) uint32_t lds_work[BigLayout::kWork];                       \
-    __shared__ __attribute__((aligned(64))) uint32_t lds_slab[kBigWaves * BigLayout::kSlab];           \
-    __shared__ __attribute__((aligned(64))) uint32_t lds_xch[BigLayout::kXch];                         \
-    __shared__ __attribute__((aligned(64))) uint32_t lds_de[kDeWords]
+    __shared__ __attribute__((aligned(64))) uint32_t lds_work[WORK_];                                  \
+    __shared__ __attribute__((aligned(64))) uint32_t lds_slab[WAVES_ * SLAB_];                         \
+    __shared__ __attribute__((aligned(64))) uint32_t lds_xch[BigExchange<WAVES_>::kWords];             \
+    __shared__ __attribute__((aligned(64))) uint32_t lds_de[kDeWords];                                 \
+    load_de_table<BM, MDE, kDeWords>(lds_de);                                                          \
+    const uint32_t lane = threadIdx.x & 63u;                                                           \
+    const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));           \
+    uint32_t *const slab = lds_slab + wave * SLAB_
 
-// The kernel's arguments, loaded behind this point.  The bounds-checked code needs far more scalar
-// registers than there are; arguments loaded in front of the branch to it would be spilled for the
-// full blocks, too (86 vector instructions per 16 elements).
+// The kernel's arguments, loaded behind this point: loaded in front of the branch between the two forms of a
+// block, the union of what they need of them is spilled for the full blocks, too.
 template <typename T>
 __device__ __forceinline__ T arguments_here()
 {
@@ -378,16 +538,15 @@ __device__ __forceinline__ T arguments_here()
 // One workgroup of two wavefronts per block; the shorter last block, if there is one, is block 0 of
 // the grid.
 template <int BM, int BV, bool BF16, bool MDE, bool EXT>
-__global__ __launch_bounds__(kBigWaves * 64, (big_waves<BM, BV, BF16, EXT>()))
+__global__ __launch_bounds__(kBigWaves * 64, kMinWaves)
 void big_kernel(const StepArgs args)
 {
-    SOLO_BIG_LDS;
-    load_de_table<BM, MDE, kDeWords>(lds_de);
-    const uint32_t lane = threadIdx.x & 63u;
-    const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    uint32_t *const slab = lds_slab + wave * BigLayout::kSlab;
+    SOLO_BIG_LDS(kBigWaves, BigLayout::kWork, BigLayout::kSlab);
     const uint32_t ragged = (uint32_t)args.rest;
-    if (blockIdx.x < ragged) {
+    if (EXT) {                                     // (see step_block)
+        const uint64_t blk = blockIdx.x < ragged ? args.n / kBigBlock : blockIdx.x - ragged;
+        step_block<BM, BV, BF16, MDE, EXT, true>(args, blk, lane, wave, slab, lds_work, lds_xch, lds_de);
+    } else if (blockIdx.x < ragged) {
         const StepArgs a = arguments_here<StepArgs>();
         step_block<BM, BV, BF16, MDE, EXT, true>(a, a.n / kBigBlock, lane, wave, slab, lds_work, lds_xch, lds_de);
     } else {
@@ -396,30 +555,55 @@ void big_kernel(const StepArgs args)
     }
 }
 
+// Four wavefronts per block.
+template <int BM, int BV, bool BF16, bool MDE, bool EXT>
+__global__ __launch_bounds__(kQuadWaves * 64, kMinWaves)
+void big_quad_kernel(const StepArgs a)
+{
+    SOLO_BIG_LDS(kQuadWaves, 2048, QuadLayout::kSlab);
+    step_block_quad<BM, BV, BF16, MDE, EXT>(a, blockIdx.x, lane, wave, slab, lds_work, lds_xch, lds_de);
+}
+
 // The step over many tensors in one launch, blocks of 2048 elements.  The map of the table holds
 // one entry per block of every tensor (the tensor's index; a shorter last block is flagged).
 // Blocks never span tensors.
 template <int BM, int BV, bool BF16, bool MDE, bool EXT>
-__global__ __launch_bounds__(kBigWaves * 64, (big_waves<BM, BV, BF16, EXT>()))
+__global__ __launch_bounds__(kBigWaves * 64, kMinWaves)
 void multi_big_kernel(const MultiArgs args)
 {
-    SOLO_BIG_LDS;
-    load_de_table<BM, MDE, kDeWords>(lds_de);
     const uint32_t me = args.unit_map[blockIdx.x];              // uniform: scalar loads
-    const uint32_t lane = threadIdx.x & 63u;
-    const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    uint32_t *const slab = lds_slab + wave * BigLayout::kSlab;
+    SOLO_BIG_LDS(kBigWaves, BigLayout::kWork, BigLayout::kSlab);
     const MultiArgs ma = arguments_here<MultiArgs>();
     const TensorEntry &e = ma.entries[me & kMapTensorMask];
     const uint64_t blk = blockIdx.x - e.unit0;
-    if (me & kMapRagged) {
-        StepArgs a = tensor_args(ma, e);
-        step_block<BM, BV, BF16, MDE, EXT, true>(a, blk, lane, wave, slab, lds_work, lds_xch, lds_de);
-    } else {
+    if (EXT || (me & kMapRagged))
+        step_block<BM, BV, BF16, MDE, EXT, true>(tensor_args(ma, e), blk, lane, wave, slab, lds_work, lds_xch, lds_de);
+    else
         step_block<BM, BV, BF16, MDE, EXT, false>(tensor_args(ma, e), blk, lane, wave, slab, lds_work, lds_xch, lds_de);
-    }
+}
+
+template <int BM, int BV, bool BF16, bool MDE, bool EXT>
+__global__ __launch_bounds__(kQuadWaves * 64, kMinWaves)
+void multi_big_quad_kernel(const MultiArgs ma)
+{
+    const TensorEntry &e = ma.entries[ma.unit_map[blockIdx.x] & kMapTensorMask];
+    SOLO_BIG_LDS(kQuadWaves, 2048, QuadLayout::kSlab);
+    step_block_quad<BM, BV, BF16, MDE, EXT>(tensor_args(ma, e), blockIdx.x - e.unit0, lane, wave, slab, lds_work, lds_xch, lds_de);
 }
 #undef SOLO_BIG_LDS
+
+// Up to how many blocks a launch gives four wavefronts to each: up to four workgroups on a CU the time is the
+// chain of one block, behind that the two-wavefront form has the fewer instructions.  Measured on MI355X,
+// us per launch, four | two wavefronts per block:
+//   blocks                             1            128          488          1000           2000           5000
+//   2-bit/3-bit bf16                   5.51 | 6.69  6.36 | 7.43  7.83 | 8.93  10.38 | 10.48  16.75 | 15.05  34.4 | 27.7
+//   2-bit/3-bit AdaBelief fp32         5.86 | 7.50  6.79 | 8.24  8.24 | 9.81  10.95 | 11.34  17.94 | 16.23  36.2 | 30.4
+//   4-bit/2-bit DE fp32                6.05 | 7.27  7.02 | 8.19  8.43 | 9.96  11.33 | 11.50  18.09 | 17.01  35.4 | 32.0
+//   2-bit/2-bit bf16, p 0.3            5.66 | 7.08  6.82 | 8.10  8.26 | 9.80  11.07 | 11.57  17.66 | 16.82  34.4 | 31.3
+//   4000 tensors of 1000 elements (a block each): 27 | 42, so a table of which at least three in four
+//   blocks are the only one of their tensor takes four at any size.
+constexpr uint64_t kQuadUpTo = 1024;
+constexpr bool quad_table(uint64_t blocks, uint64_t tensors) { return blocks <= kQuadUpTo || 4 * blocks <= 5 * tensors; }
 
 template <int BM, bool MDE>
 hipError_t launch_multi_big(uint32_t bits_v, bool bf16, const MultiArgs &args, hipStream_t stream);
@@ -427,12 +611,19 @@ hipError_t launch_multi_big(uint32_t bits_v, bool bf16, const MultiArgs &args, h
 template <int BM, bool MDE>
 hipError_t launch_multi_big_impl(uint32_t bits_v, bool bf16, const MultiArgs &args, hipStream_t stream)
 {
-    if (args.total_units == 0 || args.total_units > 0x7FFFFFFFull) return hipErrorInvalidValue;
+    if (args.total_units == 0 || args.count == 0) return hipErrorInvalidValue;
+    const bool quad = quad_table(args.total_units, args.count);
+    const uint32_t threads = (quad ? kQuadWaves : kBigWaves) * 64;
+    if (args.total_units > 0xFFFFFFFFull / threads) return hipErrorInvalidValue;
     const StepArgs &c = args.common;
     const bool ext = args.any_bf16_copy || c.grad_scale || c.belief || c.l2 != 0.0f;
+#define SOLO_KERNEL(KERNEL_, BV_, BF_, EXT_)                                                        \
+    hipLaunchKernelGGL((KERNEL_<BM, BV_, BF_, MDE, EXT_>), dim3((uint32_t)args.total_units), dim3(threads), 0, stream, args)
 #define SOLO_LAUNCH(BV_, BF_, EXT_)                                                                 \
-    hipLaunchKernelGGL((multi_big_kernel<BM, BV_, BF_, MDE, EXT_>), dim3((uint32_t)args.total_units), \
-                       dim3(kBigWaves * 64), 0, stream, args)
+    do {                                                                                            \
+        if (quad) SOLO_KERNEL(multi_big_quad_kernel, BV_, BF_, EXT_);                               \
+        else      SOLO_KERNEL(multi_big_kernel, BV_, BF_, EXT_);                                    \
+    } while (0)
 #define SOLO_CASE(BV_)                                                                              \
     if (bits_v == BV_) {                                                                            \
         if (bf16) { if (ext) SOLO_LAUNCH(BV_, true, true); else SOLO_LAUNCH(BV_, true, false); }    \
@@ -442,6 +633,7 @@ hipError_t launch_multi_big_impl(uint32_t bits_v, bool bf16, const MultiArgs &ar
     SOLO_CASE(2) SOLO_CASE(3) SOLO_CASE(4)
 #undef SOLO_CASE
 #undef SOLO_LAUNCH
+#undef SOLO_KERNEL
     return hipErrorInvalidValue;
 }
 
@@ -453,12 +645,18 @@ hipError_t launch_big_impl(uint32_t bits_v, bool bf16, const StepArgs &args_in, 
 {
     StepArgs args = args_in;
     const uint64_t blocks = (args.n + kBigBlock - 1) / kBigBlock;
-    if (blocks == 0 || blocks > 0x7FFFFFFFull) return hipErrorInvalidValue;
+    const bool quad = blocks <= kQuadUpTo;
+    const uint32_t threads = (quad ? kQuadWaves : kBigWaves) * 64;
+    if (blocks == 0 || blocks > 0xFFFFFFFFull / threads) return hipErrorInvalidValue;
     args.rest = args.n % kBigBlock ? 1 : 0;
     const bool ext = args.param_bf16 || args.grad_scale || args.belief || args.l2 != 0.0f;
+#define SOLO_KERNEL(KERNEL_, BV_, BF_, EXT_)                                                        \
+    hipLaunchKernelGGL((KERNEL_<BM, BV_, BF_, MDE, EXT_>), dim3((uint32_t)blocks), dim3(threads), 0, stream, args)
 #define SOLO_LAUNCH(BV_, BF_, EXT_)                                                                 \
-    hipLaunchKernelGGL((big_kernel<BM, BV_, BF_, MDE, EXT_>), dim3((uint32_t)blocks),               \
-                       dim3(kBigWaves * 64), 0, stream, args)
+    do {                                                                                            \
+        if (quad) SOLO_KERNEL(big_quad_kernel, BV_, BF_, EXT_);                                     \
+        else      SOLO_KERNEL(big_kernel, BV_, BF_, EXT_);                                          \
+    } while (0)
 #define SOLO_CASE(BV_)                                                                              \
     if (bits_v == BV_) {                                                                            \
         if (bf16) { if (ext) SOLO_LAUNCH(BV_, true, true); else SOLO_LAUNCH(BV_, true, false); }    \
@@ -468,6 +666,7 @@ hipError_t launch_big_impl(uint32_t bits_v, bool bf16, const StepArgs &args_in, 
     SOLO_CASE(2) SOLO_CASE(3) SOLO_CASE(4)
 #undef SOLO_CASE
 #undef SOLO_LAUNCH
+#undef SOLO_KERNEL
     return hipErrorInvalidValue;
 }
 
