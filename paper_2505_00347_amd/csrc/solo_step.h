@@ -984,6 +984,38 @@ struct ChunkWords8 {
     }
 };
 
+// The DE bucket table of a workgroup, copied from constant memory.  Every thread asks for its words
+// first (the constructor) and puts them into LDS, with a barrier, when the loads of its elements are
+// under way (ready(), which every wavefront of the workgroup calls once): with the whole copy in
+// front of those loads its latency stood in front of every 4096 elements (842 million elements,
+// 3-bit/3-bit bf16: 1820 us, 1783 now; 2^24, 4-bit/2-bit: 39.3 and 37.6).
+template <int BM, bool MDE>
+struct DeTable {
+    static constexpr bool kUsed = MDE && BM >= 3;
+    static constexpr int kWords = de_words<BM, MDE>(), kPer = (kWords + kWaves * 64 - 1) / (kWaves * 64);
+    uint32_t *const lds;
+    uint32_t word[kPer];
+    __device__ __forceinline__ explicit DeTable(uint32_t *const l) : lds(l)
+    {
+#pragma unroll
+        for (int i = 0; i < kPer; ++i) {
+            const uint32_t w = threadIdx.x + (uint32_t)(i * kWaves * 64);
+            word[i] = 0;
+            if (kUsed && w < (uint32_t)kWords) word[i] = (&DeBuckets<BM>::tab.w[0][0])[w];
+        }
+    }
+    __device__ __forceinline__ void ready() const
+    {
+        if (!kUsed) return;
+#pragma unroll
+        for (int i = 0; i < kPer; ++i) {
+            const uint32_t w = threadIdx.x + (uint32_t)(i * kWaves * 64);
+            if (w < (uint32_t)kWords) lds[w] = word[i];
+        }
+        __syncthreads();
+    }
+};
+
 // LDS of a wavefront that steps one 512-element chunk (32-bit words; offsets are compile-time
 // constants, so the parts are reached with instruction offsets from very few address registers).
 template <int BM, int BV, int B>
@@ -999,13 +1031,13 @@ struct ChunkLayout8 {
 };
 
 // The whole step for the 512 elements from 512 * chunk on (TAIL: clipped to a.n, with bounds checks
-// on every element), by the calling wavefront on its own.  `slab` is its LDS, `lds_de` the
+// on every element), by the calling wavefront on its own.  `slab` is its LDS, `de` the
 // workgroup's DE bucket table.
 // EXT: the code that also serves the variants of the step (gradient scale, coupled decay,
 // AdaBelief, bf16 weight copy); the plain AdamW step runs the one without them.
 template <int BM, int BV, int B, bool BF16, bool MDE, bool TAIL, bool EXT>
 __device__ __forceinline__ void step_chunk8(const StepArgs &a, const uint64_t chunk, const uint32_t lane,
-                                            uint32_t *const slab, const uint32_t *const lds_de)
+                                            uint32_t *const slab, const DeTable<BM, MDE> &de)
 {
     constexpr int G = B / 8;                       // lanes per block
     constexpr int NG = 64 / G;                     // blocks of the chunk
@@ -1043,6 +1075,7 @@ __device__ __forceinline__ void step_chunk8(const StepArgs &a, const uint64_t ch
     if (blk_ok) { dm_old = a.m_scale[gb]; dv_old = a.v_scale[gb]; al_old = a.v_base[gb]; }
     const RawPG raw = load_pg<BF16, TAIL>(a, e0);
     const float gscale = (EXT && a.grad_scale) ? *a.grad_scale : 1.0f;      // uniform: the gradient is transformed first
+    de.ready();
     words.stage(img_m, img_v, lane);
 
     // ---- level tables of this lane's block: entries lig, lig + G, ...
@@ -1051,7 +1084,7 @@ __device__ __forceinline__ void step_chunk8(const StepArgs &a, const uint64_t ch
     if (MDE) {
 #pragma unroll
         for (int r = 0; r < (MT + G - 1) / G; ++r) de_level[r] = DeLevels<BM>::level(lig + r * G);
-        if (kDeTable) de_base = lds_addr(lds_de) - 16u * DeBuckets<BM>::kLo;
+        if (kDeTable) de_base = lds_addr(de.lds) - 16u * DeBuckets<BM>::kLo;
     }
     fill_level_tables<BM, BV, MDE, G>(my_tv, my_tm, lig, dm_old, dv_old, al_old, de_level);
     wave_lds_sync();
@@ -1457,7 +1490,7 @@ struct ChunkLayout16 {
 // by the calling wavefront on its own, 16 consecutive elements per lane.
 template <int BM, int BV, int B, bool BF16, bool MDE, bool EXT>
 __device__ __forceinline__ void step_chunk16(const StepArgs &a, const uint64_t chunk, const uint32_t lane,
-                                             uint32_t *const slab, const uint32_t *const lds_de)
+                                             uint32_t *const slab, const DeTable<BM, MDE> &de)
 {
     constexpr int G = B / 16;                      // lanes per block
     constexpr int NG = 64 / G;                     // blocks of the chunk
@@ -1485,6 +1518,7 @@ __device__ __forceinline__ void step_chunk16(const StepArgs &a, const uint64_t c
     const RawPG16<BF16> raw = load_pg16<BF16>(a, ew0, lane);
     const float gscale = (EXT && a.grad_scale) ? *a.grad_scale : 1.0f;
     const Stage16 st(reinterpret_cast<float4 *>(slab + Lay::kOffCol), lane);
+    de.ready();
 
     words.stage(img_m, img_v, lane);
     float de_level[(16 + G - 1) / G];
@@ -1492,7 +1526,7 @@ __device__ __forceinline__ void step_chunk16(const StepArgs &a, const uint64_t c
     if (MDE) {
 #pragma unroll
         for (int r = 0; r < (MT + G - 1) / G; ++r) de_level[r] = DeLevels<BM>::level(lig + r * G);
-        if (kDeTable) de_base = lds_addr(lds_de) - 16u * DeBuckets<BM>::kLo;
+        if (kDeTable) de_base = lds_addr(de.lds) - 16u * DeBuckets<BM>::kLo;
     }
     fill_level_tables<BM, BV, MDE, G>(my_tv, my_tm, lig, dm_old, dv_old, al_old, de_level);
     wave_lds_sync();
@@ -1525,18 +1559,6 @@ __device__ __forceinline__ void step_chunk16(const StepArgs &a, const uint64_t c
     words.write_back(a, img_m, img_v, lane);
 }
 
-// The DE bucket table of a workgroup: copied from constant memory once, before any wavefront
-// of the workgroup can leave.
-template <int BM, bool MDE, int WORDS>
-__device__ __forceinline__ void load_de_table(uint32_t *lds_de)
-{
-    if (MDE && BM >= 3) {
-        const uint32_t *src = &DeBuckets<BM>::tab.w[0][0];
-        for (uint32_t w = threadIdx.x; w < (uint32_t)WORDS; w += blockDim.x) lds_de[w] = src[w];
-        __syncthreads();
-    }
-}
-
 // The step over one flat buffer, 8 elements per lane: one wavefront per 512 elements, the last
 // ones (a.rest: up to the end of the last code word) with bounds checks where the buffer ends.
 template <int BM, int BV, int B, bool BF16, bool MDE, bool EXT>
@@ -1546,7 +1568,7 @@ void chunk8_kernel(const StepArgs a)
     using Lay = ChunkLayout8<BM, BV, B>;
     __shared__ __attribute__((aligned(64))) uint32_t lds_slab[kWaves * Lay::kSlab];
     __shared__ __attribute__((aligned(64))) uint32_t lds_de[de_words<BM, MDE>()];
-    load_de_table<BM, MDE, de_words<BM, MDE>()>(lds_de);
+    const DeTable<BM, MDE> de(lds_de);
     const uint32_t lane = threadIdx.x & 63u;
     // the wavefront index is uniform: keeping it (and every address derived from the chunk) in
     // scalar registers frees vector registers
@@ -1554,9 +1576,11 @@ void chunk8_kernel(const StepArgs a)
     const uint64_t c = (uint64_t)blockIdx.x * kWaves + wave;
     uint32_t *const slab = lds_slab + wave * Lay::kSlab;
     if ((c + 1) * kIter <= a.n)
-        step_chunk8<BM, BV, B, BF16, MDE, false, EXT>(a, c, lane, slab, lds_de);
+        step_chunk8<BM, BV, B, BF16, MDE, false, EXT>(a, c, lane, slab, de);
     else if (c < a.rest)
-        step_chunk8<BM, BV, B, BF16, MDE, true, EXT>(a, c, lane, slab, lds_de);
+        step_chunk8<BM, BV, B, BF16, MDE, true, EXT>(a, c, lane, slab, de);
+    else
+        de.ready();
 }
 
 // The step over one flat buffer, 16 elements per lane: one wavefront per 1024 elements.  The first
@@ -1570,16 +1594,18 @@ void chunk16_kernel(const StepArgs a)
     static_assert(Lay::kSlab >= ChunkLayout8<BM, BV, B>::kSlab, "one slab serves both forms");
     __shared__ __attribute__((aligned(64))) uint32_t lds_slab[kWaves * Lay::kSlab];
     __shared__ __attribute__((aligned(64))) uint32_t lds_de[de_words<BM, MDE>()];
-    load_de_table<BM, MDE, de_words<BM, MDE>()>(lds_de);
+    const DeTable<BM, MDE> de(lds_de);
     const uint32_t lane = threadIdx.x & 63u;
     const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const uint64_t c = (uint64_t)blockIdx.x * kWaves + wave;
     uint32_t *const slab = lds_slab + wave * Lay::kSlab;
     if (c >= a.rest) {
         if (c - a.rest < a.n / kIter16)
-            step_chunk16<BM, BV, B, BF16, MDE, EXT>(a, c - a.rest, lane, slab, lds_de);
+            step_chunk16<BM, BV, B, BF16, MDE, EXT>(a, c - a.rest, lane, slab, de);
+        else
+            de.ready();
     } else {
-        step_chunk8<BM, BV, B, BF16, MDE, true, EXT>(a, a.n / kIter16 * (kIter16 / kIter) + c, lane, slab, lds_de);
+        step_chunk8<BM, BV, B, BF16, MDE, true, EXT>(a, a.n / kIter16 * (kIter16 / kIter) + c, lane, slab, de);
     }
 }
 
@@ -1642,7 +1668,7 @@ void multi_chunk8_kernel(const MultiArgs ma)
     using Lay = ChunkLayout8<BM, BV, B>;
     __shared__ __attribute__((aligned(64))) uint32_t lds_slab[kWaves * Lay::kSlab];
     __shared__ __attribute__((aligned(64))) uint32_t lds_de[de_words<BM, MDE>()];
-    load_de_table<BM, MDE, de_words<BM, MDE>()>(lds_de);
+    const DeTable<BM, MDE> de(lds_de);
     const uint32_t lane = threadIdx.x & 63u;
     const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const uint32_t s = blockIdx.x * kWaves + wave;
@@ -1651,9 +1677,11 @@ void multi_chunk8_kernel(const MultiArgs ma)
     const StepArgs a = tensor_args(ma, e);
     uint32_t *const slab = lds_slab + wave * Lay::kSlab;
     if ((c + 1) * kIter <= a.n)
-        step_chunk8<BM, BV, B, BF16, MDE, false, EXT>(a, c, lane, slab, lds_de);
+        step_chunk8<BM, BV, B, BF16, MDE, false, EXT>(a, c, lane, slab, de);
     else if (c * kIter < end_of_words(a.n))
-        step_chunk8<BM, BV, B, BF16, MDE, true, EXT>(a, c, lane, slab, lds_de);
+        step_chunk8<BM, BV, B, BF16, MDE, true, EXT>(a, c, lane, slab, de);
+    else
+        de.ready();
 }
 
 // find_tensor() with a first try: the tensor that the map names at the same fraction of the units.  In
@@ -1677,7 +1705,7 @@ void multi_chunk16_kernel(const MultiArgs ma)
     using Lay = ChunkLayout16<BM, BV, B>;
     __shared__ __attribute__((aligned(64))) uint32_t lds_slab[kWaves * Lay::kSlab];
     __shared__ __attribute__((aligned(64))) uint32_t lds_de[de_words<BM, MDE>()];
-    load_de_table<BM, MDE, de_words<BM, MDE>()>(lds_de);
+    const DeTable<BM, MDE> de(lds_de);
     const uint32_t lane = threadIdx.x & 63u;
     const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const uint32_t s = blockIdx.x * kWaves + wave;
@@ -1686,9 +1714,11 @@ void multi_chunk16_kernel(const MultiArgs ma)
     const StepArgs a = tensor_args(ma, e);
     uint32_t *const slab = lds_slab + wave * Lay::kSlab;
     if (c < whole)
-        step_chunk16<BM, BV, B, BF16, MDE, EXT>(a, c, lane, slab, lds_de);
+        step_chunk16<BM, BV, B, BF16, MDE, EXT>(a, c, lane, slab, de);
     else if ((whole + c) * kIter < end_of_words(a.n))
-        step_chunk8<BM, BV, B, BF16, MDE, true, EXT>(a, whole + c, lane, slab, lds_de);
+        step_chunk8<BM, BV, B, BF16, MDE, true, EXT>(a, whole + c, lane, slab, de);
+    else
+        de.ready();
 }
 
 // Host-side launcher of one instantiation family (fixed bits_m and 1st-moment codebook);

@@ -271,6 +271,17 @@ __device__ __forceinline__ uint32_t select_rank(const uint32_t (&key)[NK], const
     return wave_max(lane < at.count && below < at.rank ? my : 0u);
 }
 
+// The DE bucket table of a workgroup: copied from constant memory first.
+template <int BM, bool MDE, int WORDS>
+__device__ __forceinline__ void load_de_table(uint32_t *lds_de)
+{
+    if (MDE && BM >= 3) {
+        const uint32_t *src = &DeBuckets<BM>::tab.w[0][0];
+        for (uint32_t w = threadIdx.x; w < (uint32_t)WORDS; w += blockDim.x) lds_de[w] = src[w];
+        __syncthreads();
+    }
+}
+
 // Elements of block `blk` that exist, and the rank of the quantile among them.
 __device__ __forceinline__ uint32_t present_in(const uint64_t n, const uint64_t blk)
 {
