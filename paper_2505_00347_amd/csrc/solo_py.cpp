@@ -5,7 +5,8 @@
 // beside an MI355X (launch included), so the caller was what bounded it: 3.5 us through this module,
 // and the call of 4096 elements went from 7.8 to 4.5 us.
 // Nothing is kept between calls but the entry points of libsolo and torch's two functions that name
-// the current stream: every pointer is asked for on every call.
+// the current stream: every pointer is asked for on every call.  What only ctypes can pass (its own
+// integer objects, anything with _as_parameter_) goes to the binding's calls through ctypes.
 #define PY_SSIZE_T_CLEAN
 #include <Python.h>
 #include <stdint.h>
@@ -18,9 +19,11 @@ decltype(&solo_adamw_step_mp) g_step = nullptr;
 decltype(&solo_adamw_step_multi) g_multi = nullptr;
 PyObject *g_config_type = nullptr;      // the ctypes mirror of solo_config
 PyObject *g_argument_error = nullptr;   // ctypes.ArgumentError
+PyObject *g_ctypes_object = nullptr;    // base class of ctypes' integers and pointers
+PyObject *g_ctypes_step = nullptr, *g_ctypes_multi = nullptr;    // the same calls through ctypes
 PyObject *g_slow_stream = nullptr;      // Python: the current stream's handle, initialising torch's GPU side if need be
 PyObject *g_get_device = nullptr, *g_raw_stream = nullptr;   // torch's own, or null where it has none
-PyObject *g_data_ptr = nullptr, *g_cuda_stream = nullptr;    // interned names
+PyObject *g_data_ptr = nullptr, *g_cuda_stream = nullptr, *g_as_parameter = nullptr;    // interned names
 bool g_gpu_ready = false;               // g_slow_stream has succeeded in this process
 
 bool refuse(const char *what, PyObject *got)
@@ -29,10 +32,15 @@ bool refuse(const char *what, PyObject *got)
     return false;
 }
 
-// An integer argument, as ctypes passes one: wrapped to the width of its C type.
+// An integer argument, as ctypes passes one: wrapped to the width of its C type.  False without an
+// exception: one for ctypes.
 bool integer(PyObject *o, uint64_t &out)
 {
-    if (!PyLong_Check(o)) return refuse("an int", o);
+    if (!PyLong_Check(o)) {
+        const int is = PyObject_IsInstance(o, g_ctypes_object);
+        if (is < 0) return false;
+        return is || PyObject_HasAttr(o, g_as_parameter) ? false : refuse("an int", o);
+    }
     out = PyLong_AsUnsignedLongLongMask(o);
     return !(out == (uint64_t)-1 && PyErr_Occurred());
 }
@@ -48,7 +56,7 @@ bool pointer(PyObject *o, T *&out)
         } else {
             PyObject *r = PyObject_CallMethodNoArgs(o, g_data_ptr);
             if (!r) return false;
-            const bool ok = integer(r, v);
+            const bool ok = r == Py_None || integer(r, v);
             Py_DECREF(r);
             if (!ok) return false;
         }
@@ -79,7 +87,7 @@ bool stream_of(PyObject *o, void *&out)
         r = PyObject_GetAttr(o, g_cuda_stream);
     }
     if (!r) return false;
-    const bool ok = integer(r, v);
+    const bool ok = r == Py_None || integer(r, v);      // (None: the default stream)
     Py_DECREF(r);
     out = reinterpret_cast<void *>(v);
     return ok;
@@ -109,6 +117,11 @@ bool count_args(Py_ssize_t got, Py_ssize_t want)
     return false;
 }
 
+PyObject *by_ctypes(PyObject *call, PyObject *const *a, Py_ssize_t count)
+{
+    return PyErr_Occurred() ? nullptr : PyObject_Vectorcall(call, a, (size_t)count, nullptr);
+}
+
 // step(param, param_bf16, grad, grad_scale, m_codes, m_scale, v_codes, v_scale, v_base, n, step, cfg, stream)
 PyObject *step(PyObject *, PyObject *const *a, Py_ssize_t count)
 {
@@ -120,11 +133,12 @@ PyObject *step(PyObject *, PyObject *const *a, Py_ssize_t count)
     uint64_t n, t;
     void *stream = nullptr;
     Config cfg;
-    if (!count_args(count, 13) || !pointer(a[0], param) || !pointer(a[1], param_bf16) || !pointer(a[2], grad) ||
+    if (!count_args(count, 13)) return nullptr;
+    if (!pointer(a[0], param) || !pointer(a[1], param_bf16) || !pointer(a[2], grad) ||
         !pointer(a[3], grad_scale) || !pointer(a[4], m_codes) || !pointer(a[5], m_scale) || !pointer(a[6], v_codes) ||
-        !pointer(a[7], v_scale) || !pointer(a[8], v_base) || !integer(a[9], n) || !integer(a[10], t) || !cfg.get(a[11]))
-        return nullptr;
-    if (n != 0 && !stream_of(a[12], stream)) return nullptr;
+        !pointer(a[7], v_scale) || !pointer(a[8], v_base) || !integer(a[9], n) || !integer(a[10], t) || !cfg.get(a[11]) ||
+        (n != 0 && !stream_of(a[12], stream)))
+        return by_ctypes(g_ctypes_step, a, count);
     int rc;
     Py_BEGIN_ALLOW_THREADS
     rc = g_step(param, param_bf16, grad, grad_scale, m_codes, m_scale, v_codes, v_scale, v_base, n, t, cfg.ptr(), stream);
@@ -140,10 +154,11 @@ PyObject *multi(PyObject *, PyObject *const *a, Py_ssize_t count)
     uint64_t tensors, units, flags, t;
     void *stream = nullptr;
     Config cfg;
-    if (!count_args(count, 8) || !pointer(a[0], table) || !integer(a[1], tensors) || !integer(a[2], units) ||
-        !integer(a[3], flags) || !pointer(a[4], grad_scale) || !integer(a[5], t) || !cfg.get(a[6]))
-        return nullptr;
-    if (units != 0 && !stream_of(a[7], stream)) return nullptr;
+    if (!count_args(count, 8)) return nullptr;
+    if (!pointer(a[0], table) || !integer(a[1], tensors) || !integer(a[2], units) ||
+        !integer(a[3], flags) || !pointer(a[4], grad_scale) || !integer(a[5], t) || !cfg.get(a[6]) ||
+        (units != 0 && !stream_of(a[7], stream)))
+        return by_ctypes(g_ctypes_multi, a, count);
     int rc;
     Py_BEGIN_ALLOW_THREADS
     rc = g_multi(table, (uint32_t)tensors, units, (uint32_t)flags, grad_scale, t, cfg.ptr(), stream);
@@ -151,23 +166,31 @@ PyObject *multi(PyObject *, PyObject *const *a, Py_ssize_t count)
     return PyLong_FromLong(rc);
 }
 
-// bind(address of solo_adamw_step_mp, of solo_adamw_step_multi, config type, ArgumentError, slow stream,
-//      torch's current device, torch's raw stream of a device): the last two may be None
+// bind(address of solo_adamw_step_mp, of solo_adamw_step_multi, config type, its size, ArgumentError, ctypes' base
+//      class, the step through ctypes, the multi-tensor step through ctypes, slow stream, torch's current
+//      device, torch's raw stream of a device): the last two may be None
 PyObject *bind(PyObject *, PyObject *args)
 {
     unsigned long long s, m;
-    PyObject *type, *error, *slow, *device, *raw;
-    if (!PyArg_ParseTuple(args, "KKOOOOO", &s, &m, &type, &error, &slow, &device, &raw)) return nullptr;
+    Py_ssize_t size;
+    PyObject *type, *error, *object, *step_c, *multi_c, *slow, *device, *raw;
+    if (!PyArg_ParseTuple(args, "KKOnOOOOOOO", &s, &m, &type, &size, &error, &object, &step_c, &multi_c, &slow, &device, &raw))
+        return nullptr;
+    if (size != (Py_ssize_t)sizeof(solo_config)) {
+        PyErr_Format(PyExc_ImportError, "built for a solo_config of %zu bytes, not %zd", sizeof(solo_config), size);
+        return nullptr;
+    }
     g_step = reinterpret_cast<decltype(g_step)>((uintptr_t)s);
     g_multi = reinterpret_cast<decltype(g_multi)>((uintptr_t)m);
-    Py_INCREF(type); Py_INCREF(error); Py_INCREF(slow);
-    Py_XSETREF(g_config_type, type);
-    Py_XSETREF(g_argument_error, error);
-    Py_XSETREF(g_slow_stream, slow);
     const bool fast = device != Py_None && raw != Py_None;
-    if (fast) { Py_INCREF(device); Py_INCREF(raw); }
-    Py_XSETREF(g_get_device, fast ? device : nullptr);
-    Py_XSETREF(g_raw_stream, fast ? raw : nullptr);
+    struct { PyObject **to, *from; } kept[] = {
+        {&g_config_type, type}, {&g_argument_error, error}, {&g_ctypes_object, object}, {&g_ctypes_step, step_c},
+        {&g_ctypes_multi, multi_c}, {&g_slow_stream, slow}, {&g_get_device, fast ? device : nullptr},
+        {&g_raw_stream, fast ? raw : nullptr}};
+    for (auto &k : kept) {
+        Py_XINCREF(k.from);
+        Py_XSETREF(*k.to, k.from);
+    }
     g_gpu_ready = false;
     Py_RETURN_NONE;
 }
@@ -194,6 +217,7 @@ PyMODINIT_FUNC PyInit__solo_native()
 {
     g_data_ptr = PyUnicode_InternFromString("data_ptr");
     g_cuda_stream = PyUnicode_InternFromString("cuda_stream");
-    if (!g_data_ptr || !g_cuda_stream) return nullptr;
+    g_as_parameter = PyUnicode_InternFromString("_as_parameter_");
+    if (!g_data_ptr || !g_cuda_stream || !g_as_parameter) return nullptr;
     return PyModule_Create(&module);
 }

@@ -4,14 +4,17 @@ Every function has the name and meaning of the C entry point it calls; all of th
 optimizer step runs in the HIP kernels of the library.  Tensors are torch tensors
 on an AMD GPU (torch is used for device memory and streams only); a tensor is
 passed as its device pointer, the stream as the current torch stream's handle.
-The calls of a step are marshalled by a small native module (csrc/solo_py.cpp), the
-others through ctypes.  The module fails loudly when the library has not been built:
-there is no fallback path.
+The calls of a step are marshalled by a small native module (csrc/solo_py.cpp) where
+one has been built for this interpreter, the others through ctypes; arguments that only
+ctypes knows how to pass (its own integer objects) take its way in a step, too.  The module
+fails loudly when the library has not been built: there is no fallback path for it.
 """
 import ctypes as C
+import functools
 import importlib.util
 import os
 import sysconfig
+import threading
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "lib", "libsolo.so")
@@ -57,60 +60,83 @@ class SoloError(RuntimeError):
 
 
 _lib = None
-_native = None
+_step = _multi = None            # the calls of a step: native, or through ctypes
+_loading = threading.RLock()
 
 
 def lib():
     """Load libsolo.so (built by ``python -m paper_2505_00347_amd.build``)."""
-    global _lib, _native
-    if _lib is None:
-        for path in (LIB_PATH, NATIVE_PATH):
-            if not os.path.exists(path):
-                raise ImportError(f"{path} is missing: build it with "
+    global _lib, _step, _multi
+    if _lib is not None:
+        return _lib
+    with _loading:
+        if _lib is None:
+            if not os.path.exists(LIB_PATH):
+                raise ImportError(f"{LIB_PATH} is missing: build it with "
                                   "`python -m paper_2505_00347_amd.build` (needs hipcc)")
-        # torch first: the wheel brings a HIP runtime of its own and exports it to the process.
-        # Loaded after it, libsolo binds to that runtime, the one the tensors and streams of the
-        # callers belong to; loaded before it, libsolo would bind to the system's copy, and every
-        # launch on a torch stream would fail.
-        import torch  # noqa: F401
-        L = C.CDLL(LIB_PATH)
-        vp, u32, u64, cfgp = C.c_void_p, C.c_uint32, C.c_uint64, C.POINTER(solo_config)
-        L.solo_code_words.restype = C.c_size_t; L.solo_code_words.argtypes = [u64, u32]
-        L.solo_num_blocks.restype = C.c_size_t; L.solo_num_blocks.argtypes = [u64, u32]
-        L.solo_state_bytes.restype = C.c_size_t; L.solo_state_bytes.argtypes = [u64, cfgp]
-        L.solo_beta1_default.restype = C.c_float; L.solo_beta1_default.argtypes = [u32, C.c_int]
-        L.solo_beta1_bound.restype = C.c_float
-        L.solo_beta1_bound.argtypes = [C.c_float, C.c_float, C.c_float]
-        L.solo_strerror.restype = C.c_char_p; L.solo_strerror.argtypes = [C.c_int]
-        L.solo_state_init.restype = C.c_int
-        L.solo_state_init.argtypes = [vp, vp, vp, vp, vp, u64, cfgp, vp]
-        L.solo_adamw_step.restype = C.c_int
-        L.solo_adamw_step.argtypes = [vp, vp, vp, vp, vp, vp, vp, u64, u64, cfgp, vp]
-        L.solo_adamw_step_mp.restype = C.c_int
-        L.solo_adamw_step_mp.argtypes = [vp, vp, vp, vp, vp, vp, vp, vp, vp, u64, u64, cfgp, vp]
-        tp = C.POINTER(solo_tensor)
-        L.solo_multi_units.restype = C.c_uint64; L.solo_multi_units.argtypes = [tp, u32, cfgp]
-        L.solo_multi_table_bytes.restype = C.c_size_t; L.solo_multi_table_bytes.argtypes = [u32, u64]
-        L.solo_multi_table_build.restype = C.c_int
-        L.solo_multi_table_build.argtypes = [tp, u32, cfgp, vp, C.c_size_t, C.POINTER(C.c_uint32)]
-        L.solo_adamw_step_multi.restype = C.c_int
-        L.solo_adamw_step_multi.argtypes = [vp, u32, u64, u32, vp, u64, cfgp, vp]
-        spec = importlib.util.spec_from_file_location("_solo_native", NATIVE_PATH)
-        native = importlib.util.module_from_spec(spec)
-        spec.loader.exec_module(native)
-        native.bind(C.cast(L.solo_adamw_step_mp, vp).value, C.cast(L.solo_adamw_step_multi, vp).value,
-                    solo_config, C.ArgumentError, _stream_of_now,
-                    getattr(torch._C, "_cuda_getDevice", None), getattr(torch._C, "_cuda_getCurrentRawStream", None))
-        os.register_at_fork(after_in_child=native.forked)
-        _lib, _native = L, native
+            # torch first: the wheel brings a HIP runtime of its own and exports it to the process.
+            # Loaded after it, libsolo binds to that runtime, the one the tensors and streams of the
+            # callers belong to; loaded before it, libsolo would bind to the system's copy, and every
+            # launch on a torch stream would fail.
+            import torch  # noqa: F401
+            L = _declared(C.CDLL(LIB_PATH))
+            step, multi = functools.partial(_step_by_ctypes, L), functools.partial(_multi_by_ctypes, L)
+            if os.path.exists(NATIVE_PATH):
+                native = _native_calls(L, step, multi)
+                step, multi = native.step, native.multi
+            _step, _multi = step, multi
+            _lib = L                 # last: a thread that finds it set finds the others set
     return _lib
 
 
-def _step_calls():
-    """The native module (see csrc/solo_py.cpp)."""
-    if _native is None:
-        lib()
-    return _native
+def _declared(L):
+    vp, u32, u64, cfgp = C.c_void_p, C.c_uint32, C.c_uint64, C.POINTER(solo_config)
+    L.solo_code_words.restype = C.c_size_t; L.solo_code_words.argtypes = [u64, u32]
+    L.solo_num_blocks.restype = C.c_size_t; L.solo_num_blocks.argtypes = [u64, u32]
+    L.solo_state_bytes.restype = C.c_size_t; L.solo_state_bytes.argtypes = [u64, cfgp]
+    L.solo_beta1_default.restype = C.c_float; L.solo_beta1_default.argtypes = [u32, C.c_int]
+    L.solo_beta1_bound.restype = C.c_float
+    L.solo_beta1_bound.argtypes = [C.c_float, C.c_float, C.c_float]
+    L.solo_strerror.restype = C.c_char_p; L.solo_strerror.argtypes = [C.c_int]
+    L.solo_state_init.restype = C.c_int
+    L.solo_state_init.argtypes = [vp, vp, vp, vp, vp, u64, cfgp, vp]
+    L.solo_adamw_step.restype = C.c_int
+    L.solo_adamw_step.argtypes = [vp, vp, vp, vp, vp, vp, vp, u64, u64, cfgp, vp]
+    L.solo_adamw_step_mp.restype = C.c_int
+    L.solo_adamw_step_mp.argtypes = [vp, vp, vp, vp, vp, vp, vp, vp, vp, u64, u64, cfgp, vp]
+    tp = C.POINTER(solo_tensor)
+    L.solo_multi_units.restype = C.c_uint64; L.solo_multi_units.argtypes = [tp, u32, cfgp]
+    L.solo_multi_table_bytes.restype = C.c_size_t; L.solo_multi_table_bytes.argtypes = [u32, u64]
+    L.solo_multi_table_build.restype = C.c_int
+    L.solo_multi_table_build.argtypes = [tp, u32, cfgp, vp, C.c_size_t, C.POINTER(C.c_uint32)]
+    L.solo_adamw_step_multi.restype = C.c_int
+    L.solo_adamw_step_multi.argtypes = [vp, u32, u64, u32, vp, u64, cfgp, vp]
+    return L
+
+
+def _native_calls(L, step, multi):
+    """The native module (csrc/solo_py.cpp), which hands what it does not take to `step` and `multi`."""
+    import torch
+    spec = importlib.util.spec_from_file_location("_solo_native", NATIVE_PATH)
+    native = importlib.util.module_from_spec(spec)
+    spec.loader.exec_module(native)
+    address = lambda f: C.cast(f, C.c_void_p).value
+    native.bind(address(L.solo_adamw_step_mp), address(L.solo_adamw_step_multi), solo_config, C.sizeof(solo_config),
+                C.ArgumentError, C._SimpleCData, step, multi, _stream_of_now,
+                getattr(torch._C, "_cuda_getDevice", None), getattr(torch._C, "_cuda_getCurrentRawStream", None))
+    os.register_at_fork(after_in_child=native.forked)
+    return native
+
+
+def _step_by_ctypes(L, param, param_bf16, grad, grad_scale, m_codes, m_scale, v_codes, v_scale, v_base, n, step, cfg, stream):
+    return L.solo_adamw_step_mp(_ptr(param), _ptr(param_bf16), _ptr(grad), _ptr(grad_scale), _ptr(m_codes), _ptr(m_scale),
+                                _ptr(v_codes), _ptr(v_scale), _ptr(v_base), n, step, C.byref(cfg),
+                                _stream(stream) if n else None)
+
+
+def _multi_by_ctypes(L, table_device, count, units, table_flags, grad_scale, step, cfg, stream):
+    return L.solo_adamw_step_multi(_ptr(table_device), count, units, table_flags, _ptr(grad_scale), step, C.byref(cfg),
+                                   _stream(stream) if units else None)
 
 
 def _stream_of_now():
@@ -150,7 +176,9 @@ def solo_state_init(m_codes, m_scale, v_codes, v_scale, v_base, n, cfg, stream=N
 def solo_adamw_step(param, grad, m_codes, m_scale, v_codes, v_scale, v_base, n, step, cfg,
                     stream=None, check=True):
     # (solo_adamw_step of the library is this call with both extras NULL)
-    rc = _step_calls().step(param, None, grad, None, m_codes, m_scale, v_codes, v_scale, v_base, n, step, cfg, stream)
+    if _step is None:
+        lib()
+    rc = _step(param, None, grad, None, m_codes, m_scale, v_codes, v_scale, v_base, n, step, cfg, stream)
     if check and rc != SOLO_OK:
         raise SoloError(rc)
     return rc
@@ -159,8 +187,9 @@ def solo_adamw_step(param, grad, m_codes, m_scale, v_codes, v_scale, v_base, n, 
 def solo_adamw_step_mp(param, param_bf16, grad, grad_scale, m_codes, m_scale, v_codes, v_scale,
                        v_base, n, step, cfg, stream=None, check=True):
     """param_bf16 (bf16 tensor) and grad_scale (one-element float32 device tensor) may be None."""
-    rc = _step_calls().step(param, param_bf16, grad, grad_scale, m_codes, m_scale, v_codes, v_scale, v_base,
-                            n, step, cfg, stream)
+    if _step is None:
+        lib()
+    rc = _step(param, param_bf16, grad, grad_scale, m_codes, m_scale, v_codes, v_scale, v_base, n, step, cfg, stream)
     if check and rc != SOLO_OK:
         raise SoloError(rc)
     return rc
@@ -181,7 +210,9 @@ def solo_multi_table_build(tensors, count, cfg, table_host, table_bytes, check=T
 
 def solo_adamw_step_multi(table_device, count, units, table_flags, grad_scale, step, cfg, stream=None,
                           check=True):
-    rc = _step_calls().multi(table_device, count, units, table_flags, grad_scale, step, cfg, stream)
+    if _multi is None:
+        lib()
+    rc = _multi(table_device, count, units, table_flags, grad_scale, step, cfg, stream)
     if check and rc != SOLO_OK:
         raise SoloError(rc)
     return rc
