@@ -2,9 +2,13 @@
 
 Usage: python -m paper_2505_00347_amd.build [--force]
 The library is built in-tree (paper_2505_00347_amd/lib/libsolo.so); object
-files go to paper_2505_00347_amd/_build/.
+files go to paper_2505_00347_amd/_build/.  The native step calls of the Python
+binding (lib/_solo_native...so) are built beside it for the interpreter that runs
+this, with g++ and that interpreter's headers; without those the binding makes the
+same calls through ctypes.
 """
 import os
+import shutil
 import subprocess
 import sys
 import sysconfig
@@ -36,20 +40,36 @@ def _compile(src):
     return obj
 
 
+def _link(command, output):
+    """Runs `command -o <output>`; the file appears under its name when the command has succeeded."""
+    subprocess.check_call([*command, "-o", output + ".new"])
+    os.replace(output + ".new", output)
+
+
+def _native_compiler():
+    """The command that compiles the native step calls, or None where there is no compiler or no Python.h."""
+    include = sysconfig.get_paths()["include"]
+    if shutil.which("g++") is None or not os.path.exists(os.path.join(include, "Python.h")):
+        return None
+    return ["g++", "-O2", "-std=c++17", "-shared", "-fPIC", "-Wall", "-fvisibility=hidden", "-I" + include]
+
+
 def build(force=True, verbose=False):
     os.makedirs(OBJ, exist_ok=True)
     os.makedirs(LIBDIR, exist_ok=True)
     deps = [os.path.join(CSRC, f) for f in os.listdir(CSRC)] + [
         os.path.join(HERE, "..", "include", "solo.h")]
-    if not force and os.path.exists(LIB) and os.path.exists(NATIVE) and all(
-            os.path.getmtime(LIB) >= os.path.getmtime(d) for d in deps):
+    native = _native_compiler()
+    outputs = [LIB] + ([NATIVE] if native else [])
+    if not force and all(os.path.exists(o) and os.path.getmtime(o) >= os.path.getmtime(d) for o in outputs for d in deps):
         return LIB
     with ThreadPoolExecutor(len(SOURCES)) as ex:
         objs = list(ex.map(_compile, SOURCES))
-    subprocess.check_call([HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB, *objs])
-    # the step calls of the Python binding (host code only)
-    subprocess.check_call(["g++", "-O2", "-std=c++17", "-shared", "-fPIC", "-Wall", "-fvisibility=hidden",
-                           "-I" + sysconfig.get_paths()["include"], os.path.join(CSRC, "solo_py.cpp"), "-o", NATIVE])
+    _link([HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", *objs], LIB)
+    if native:
+        _link([*native, os.path.join(CSRC, "solo_py.cpp")], NATIVE)
+    elif os.path.exists(NATIVE):
+        os.remove(NATIVE)                # of an earlier build: its view of the library may be another
     # stand-alone memory-ceiling probe (read / write / copy / step-shaped streams)
     subprocess.check_call([HIPCC, "-O3", "--offload-arch=gfx950", "-std=c++17",
                            "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
