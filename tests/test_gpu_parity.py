@@ -28,10 +28,15 @@ class GpuSide:
     def __init__(self, solo, n, cfg, grad_scale=None, bf16_copy=False, multi=False):
         import torch
         self.solo, self.n, self.cfg = solo, n, cfg
-        # multi: the buffer goes through solo_adamw_step_multi as a table of one tensor, which runs
-        # the streaming kernels on its full units whatever the size (a flat buffer of a test's
-        # size runs one wavefront per 512 elements)
+        # multi: the buffer goes through solo_adamw_step_multi in a table with a second tensor, large
+        # enough that the launch runs the kernels with 16 elements per lane (a flat buffer of a
+        # test's size, or a table of it alone, runs those with 8)
         self.multi = multi
+        if multi:
+            k = 1025 * 2048
+            self.second = (torch.zeros(k, device="cuda"),
+                           torch.zeros(k, dtype=torch.bfloat16 if cfg.grad_dtype == solo.SOLO_GRAD_BF16 else torch.float32, device="cuda"),
+                           solo.SoloState(k, cfg))
         self.state = solo.SoloState(n, cfg)
         self.p = None
         self.grad_scale = None if grad_scale is None else torch.tensor([grad_scale], dtype=torch.float32,
@@ -47,7 +52,7 @@ class GpuSide:
 
     def step(self, g_dev, step):
         if self.multi:
-            table = self.solo.SoloMultiTable([(self.p, g_dev, self.state, self.p_bf16)], self.cfg)
+            table = self.solo.SoloMultiTable([(self.p, g_dev, self.state, self.p_bf16), self.second], self.cfg)
             table.step(step, grad_scale=self.grad_scale)
             return
         self.state.step(self.p, g_dev, step, param_bf16=self.p_bf16, grad_scale=self.grad_scale)
@@ -203,11 +208,10 @@ def test_all_formats(so, gpu, bm, bv):
 @pytest.mark.parametrize("bm", (2, 3, 4))
 @pytest.mark.parametrize("bv", (2, 3, 4))
 def test_streaming_kernels_all_formats(so, gpu, bm, bv):
-    """The kernels that own a whole super-tile per wavefront (8 or 16 elements per lane, chosen by
-    the format) serve flat buffers only from 2^25 elements on; through a table of one tensor they
-    run at any size.  Every format, both block sizes, both codebooks with bf16 gradients, the
-    dynamic-exponent codebook with fp32 gradients, plain and with every extra: several super-tiles
-    and a ragged end."""
+    """The kernels with 16 elements per lane serve flat buffers only from 2^19 to 5 * 2^20 elements on; in
+    a table with a large second tensor they run at any size.  Every format, both block sizes, both
+    codebooks with bf16 gradients, the dynamic-exponent codebook with fp32 gradients, plain and with
+    every extra: several chunks and a ragged end."""
     n = 3 * TILE + 2 * 2560 + 1283
     for B in (128, 64):
         for de, bf16 in ((False, True), (True, True), (True, False)):
@@ -224,13 +228,10 @@ WIDE_FORMATS = [(bm, bv, 128, de) for de in (False, True)
 
 @pytest.mark.parametrize("bm,bv,B,de", WIDE_FORMATS)
 def test_wide_path_formats(so, gpu, bm, bv, B, de):
-    """The formats whose full super-tiles run 16 elements per lane (8 lanes per 128-element
-    block, 4 per 64-element block): both gradient types, the plain step and the one with every
-    extra, four full tiles and a ragged end (which runs the 8-elements-per-lane code on the same
-    state).  A flat buffer reaches these kernels only from 2^25 elements on, so the buffer goes in
-    as a table of one tensor, whose full units run them at any size (fp32 gradients with the linear
-    codebook have no such kernels in use: their flat and multi-tensor launches run one wavefront
-    per 512 elements, which the flat call here covers)."""
+    """16 elements per lane (8 lanes per 128-element block, 4 per 64-element block) in a table with a
+    large second tensor: both gradient types (fp32 gradients with the linear codebook as a flat
+    buffer, 8 elements per lane), the plain step and the one with every extra, whole chunks and a
+    ragged end (which runs the 8-elements-per-lane code on the same state)."""
     n = 4 * TILE + 3000
     for bf16 in (True, False):
         multi = bf16 or de
@@ -247,7 +248,7 @@ def test_wide_path_formats(so, gpu, bm, bv, B, de):
                                              (3, 3, 64, False, False), (4, 4, 128, False, False)])
 def test_step_variants(so, gpu, optimizer, bm, bv, B, bf16, de):
     """Coupled decay, AdaBelief, a gradient scale read from device memory and the bf16 weight
-    copy, together, over several super-tiles and a ragged tail."""
+    copy, together, over several chunks and a ragged tail."""
     n = 5 * TILE + 1234
     kw = dict(optimizer=optimizer, grad_scale=1.0 / 1024, wd=0.1, de=de, bf16_copy=True,
               eps=1e-12 if optimizer == "adabelief" else 1e-8, std=1.024)
@@ -292,7 +293,7 @@ def test_quantile_settings_and_nearest_rounding(so, gpu):
         run_teacher_forced(so, gpu, n, 2, 3, 64, steps=3, p=p, seed0=int(p * 100) + 1)
     run_teacher_forced(so, gpu, n, 3, 3, 128, steps=4, stochastic=0, seed0=77)
     run_free(so, gpu, n, 2, 4, 128, steps=6, stochastic=0, seed0=78)
-    # the same on the streaming kernels (a table of one tensor): 16 and 8 elements per lane
+    # the same with 16 elements per lane (a table with a large second tensor)
     for p in (0.0, 0.05, 0.3, 0.5, 0.95):
         run_teacher_forced(so, gpu, n, 2, 3, 128, bf16=True, steps=3, p=p, seed0=int(p * 100) + 2, multi=True, std=1e-4)
         run_teacher_forced(so, gpu, n, 4, 4, 64, bf16=True, steps=3, p=p, seed0=int(p * 100) + 3, multi=True, de=True)
@@ -302,7 +303,7 @@ def test_quantile_settings_and_nearest_rounding(so, gpu):
 def test_index_offset_and_seed(so, gpu):
     run_teacher_forced(so, gpu, 6000, 2, 3, 128, steps=3, off=8 * (1 << 33) + 2560 * 7, seed=123456789)
     run_teacher_forced(so, gpu, 6000, 4, 4, 64, steps=3, off=8, seed=0)
-    # the streaming kernels (a table of one tensor), with an offset whose group index crosses 2^32 inside the buffer
+    # 16 elements per lane (a table with a large second tensor), with an offset whose group index crosses 2^32 inside the buffer
     run_teacher_forced(so, gpu, 3 * TILE + 100, 2, 3, 128, bf16=True, steps=3, off=8 * ((1 << 32) - 700), seed=987654321,
                        multi=True, std=1e-4)
     run_teacher_forced(so, gpu, 3 * TILE + 100, 2, 3, 2048, bf16=True, steps=3, off=8 * ((1 << 32) - 700), seed=5,
@@ -315,7 +316,7 @@ def test_hyperparameter_ranges(so, gpu):
     run_teacher_forced(so, gpu, 5000, 3, 3, 64, steps=3, std=30.0)            # large gradients
     run_teacher_forced(so, gpu, 5000, 3, 3, 64, steps=3, std=1e-9, bf16=True)  # tiny gradients
     for kw in (dict(beta1=0.0, beta2=0.0, lr=1e-2, wd=0.0, eps=1e-6), dict(beta1=0.1, beta2=0.98, lr=3e-4, wd=0.1),
-               dict(std=30.0), dict(std=1e-9)):                                # the same on the streaming kernels
+               dict(std=30.0), dict(std=1e-9)):                                # the same with 16 elements per lane
         run_teacher_forced(so, gpu, 2 * TILE + 5000, 2, 3, 128, bf16=True, steps=3, multi=True, **kw)
 
 
@@ -344,7 +345,7 @@ def test_nearly_constant_blocks(so, gpu, eps):
               off=265625140904, kind="student_t3", std=5.4e-5)
     run_teacher_forced(so, gpu, 13899, 2, 3, 128, bf16=True, steps=3, seed0=358133, **kw)
     run_teacher_forced(so, gpu, 3 * TILE + 100, 4, 4, 64, bf16=False, steps=2, seed0=11, **kw)
-    run_teacher_forced(so, gpu, 3 * TILE + 100, 2, 3, 128, bf16=True, steps=3, seed0=358134, multi=True, **kw)   # streaming kernels
+    run_teacher_forced(so, gpu, 3 * TILE + 100, 2, 3, 128, bf16=True, steps=3, seed0=358134, multi=True, **kw)   # 16 elements per lane
     run_teacher_forced(so, gpu, 3 * TILE + 100, 4, 4, 64, bf16=False, steps=2, seed0=12, multi=True, **kw)
 
 
@@ -353,9 +354,9 @@ def test_nearly_constant_blocks(so, gpu, eps):
                                               (2, 2, 64, True, True)])
 @pytest.mark.parametrize("multi", (False, True))
 def test_degenerate_blocks(so, gpu, bm, bv, B, bf16, de, multi):
-    """Constant, zero and sparse blocks, an all-zero step, rows that stay idle.  multi: as a table
-    of one tensor, two super-tiles longer, so that the streaming kernels (or, with fp32 gradients
-    and the linear codebook, the multi-tensor form of the one-wavefront-per-512 kernels) see them."""
+    """Constant, zero and sparse blocks, an all-zero step, rows that stay idle.  multi: in a
+    table with a large second tensor, two tiles longer, so that the kernels with 16 elements per lane
+    see them."""
     from paper_2505_00347_amd import synth
     n = 24 * B + 11 + (2 * TILE if multi else 0)
     oc, gc = make_cfgs(so, gpu, bm, bv, B, bf16, de=de)
@@ -563,7 +564,7 @@ def test_trained_state_with_clustered_second_moments(so, gpu, B, bm, bv, multi):
     from parity_common import DeviceView
     n = 40 * 2048 + 1283
     oc, gc = make_cfgs(so, gpu, bm, bv, B, True)
-    side = GpuSide(gpu, n, gc, multi=multi)              # multi: a table of one tensor (the streaming kernels for B = 128)
+    side = GpuSide(gpu, n, gc, multi=multi)              # multi: a table with a large second tensor (16 elements per lane for B = 128)
     side.p = dev(synth.make_params(n))
     grads = [grads_for("normal_outliers", n, 1e-4, 5000 + k, True) for k in range(8)]
     for step in range(1, 301):
@@ -592,7 +593,7 @@ def test_non_finite_gradients_stay_inside_their_blocks(so, gpu, B, n, bm, bv):
     """A NaN or an infinity in the gradient spoils its own block and nothing else: the step
     completes, and every block without such an entry equals the oracle's result for the same
     gradients with the bad entries removed.
-    (The last case is large enough for the streaming kernels; the others run one wavefront per
+    (The last case is large enough for 16 elements per lane; the others run one wavefront per
     512 elements, or one workgroup per block of 2048.)"""
     import torch
     from paper_2505_00347_amd import synth
@@ -736,7 +737,7 @@ def random_cases(so, gpu, seed, blocks, cases):
         if rng.integers(0, 2):
             kw.update(grad_scale=float(rng.choice([1.0, 0.5, 1.0 / 1024])), bf16_copy=True)
         try:
-            # every other case as a table of one tensor (the streaming kernels on its full units)
+            # every other case in a table with a large second tensor (16 elements per lane)
             run_teacher_forced(so, gpu, n, bm, bv, B, bf16=bf16, steps=3, kind=kind, std=std,
                                seed0=int(rng.integers(0, 10 ** 6)), multi=c % 2 == 1, **kw)
         except AssertionError as e:
@@ -765,7 +766,7 @@ def test_full_size_7b_workload_sampled_tiles(so, gpu, name, variant):
     one call): the metric's format, and the paper's own 4/2-bit format (dynamic-exponent m)
     through solo_adamw_step_mp with the bf16 weight copy and a gradient scale.  The oracle cannot
     run 6.7e9 elements in seconds, so the third step is checked on sampled 5120-element
-    super-tiles (first, last full, the ragged tail, tensor boundaries and random ones; with blocks
+    slices (first, last full, the ragged tail, tensor boundaries and random ones; with blocks
     of 2048 elements, slices of five blocks): inputs of
     those slices are copied out before the step, the oracle runs on each slice with the slice's
     global offset, and every output byte of the slice is compared.  Properties that hold at any

@@ -411,9 +411,8 @@ def test_config5_sparse_embedding_rows(so, gpu, launch):
     receive no gradient, the case Sec. 3.2.2 raises for the adaptive base: their v^ = beta2 v~
     sit on at most eight distinct values per block (every extraction round of the quantile is
     a tie), blocks go to and come from the zero state, x_p = 0 blocks clamp the base.  Ten
-    teacher-forced and ten free-running steps, every element.  The flat buffer (8.4 M elements)
-    runs one wavefront per 512 elements; as a table of one tensor it runs the streaming kernel
-    of the metric's format, 16 elements per lane."""
+    teacher-forced and ten free-running steps, every element.  The buffer (8.4 M elements) runs
+    16 elements per lane, flat and as a table."""
     from paper_2505_00347_amd import synth
     from test_gpu_parity import GpuSide
     solo = gpu

@@ -1,6 +1,8 @@
 """GPU parity of the kernels that give a lane 16 elements: flat buffers of more than 5 * 2^20
-elements (some formats from 2^19 on), tables of more than 3 * 2^18, blocks of 2048.  Same bar as
-test_gpu_parity.py."""
+elements (some formats from 2^19 on), tables of more than 3 * 2^8 pieces.  Same bar as
+test_gpu_parity.py.  (Every instantiation of them is compared with the 8-per-lane kernels in
+test_gpu_both_forms.py; blocks of 2048 give a lane 16 elements from 1025 of them on, see
+test_gpu_short_blocks.py.)"""
 import numpy as np
 import pytest
 
