@@ -13,7 +13,7 @@
 // base, the hash, packing) is spread over twice as many elements with 16 per lane, so that form
 // needs an eighth fewer instructions and is the faster one as soon as there is work for several
 // rounds of wavefronts on every SIMD; a buffer that is shorter than that takes the latency of one
-// wavefront, and 8 elements per lane have the shorter one (narrow_up_to()).  The ragged end of a
+// wavefront, and 8 elements per lane have the shorter one (narrow_buffer()).  The ragged end of a
 // buffer always runs the 8-per-lane form with bounds checks.  chunk8_kernel and chunk16_kernel run
 // over a flat buffer, multi_chunk8_kernel and multi_chunk16_kernel over the tensors of a
 // caller-built table.
@@ -488,16 +488,17 @@ template <bool V> struct BoolTag { static constexpr bool value = V; };
 // accesses per lane and stream.  A wavefront's access then covers every other 16 bytes of its two
 // kilobytes, twice the requests of a coalesced one, but nothing has to be turned around through LDS:
 // the code for 8 elements per lane runs where a launch is all latency (the transposition and its
-// waits were 500 of the 6400-7200 cycles of a wavefront).  TAIL: the lane that holds the buffer's end
-// goes element by element, bounds-checked, and those behind it not at all.
+// waits were 500 of the 6400-7200 cycles of a wavefront).  TAIL: unless `whole` says that
+// all of them exist, element by element, bounds-checked.  (A caller asks for a wavefront, whose loads
+// are then all under way at once, or, with a long chain behind them, for every lane.)
 struct RawPG { float4 p0, p1; uint4 g0, g1; };
 
 template <bool BF16, bool TAIL>
-__device__ __forceinline__ RawPG load_pg(const StepArgs &a, const uint64_t e0)
+__device__ __forceinline__ RawPG load_pg(const StepArgs &a, const uint64_t e0, const bool whole)
 {
     RawPG r;
     r.g1 = make_uint4(0, 0, 0, 0);
-    if (!TAIL || e0 + 8 <= a.n) {
+    if (!TAIL || whole) {
         const float4 *pp = reinterpret_cast<const float4 *>(a.param + e0);
         r.p0 = pp[0]; r.p1 = pp[1];
         if (BF16) {
@@ -537,23 +538,36 @@ constexpr int m_table_stride() { return BM == 2 ? 4 : BM == 3 ? 8 : 16; }   // a
 template <int BM, bool MDE>
 constexpr int de_words() { return MDE && BM >= 3 ? 4 * DeBuckets<BM>::N : 16; }
 
-// Up to how many elements a flat buffer runs 8 elements per lane, for a quantile of rank `rank` in a
-// full block; `copy`: a bf16 copy of the parameters is written.  Measured on MI355X over six
-// states in turn, us per launch, 8 | 16 per lane:
-//                                    2^19          2^20          2^21          2^22            2^23
-//   2-bit/3-bit bf16                 5.48 | 6.45   6.65 | 6.75   8.98 | 9.04   13.34 | 13.34   22.94 | 21.36
-//   4-bit/2-bit DE bf16, copy        5.85 | 6.70   7.59 | 6.99   10.70 | 9.75  16.27 | 15.90   29.16 | 26.04
-//   4-bit/4-bit fp32                 5.08 | 5.87   6.53 | 6.24   9.37 | 9.84   14.08 | 14.93   26.85 | 24.64
-//   3-bit/3-bit DE fp32, B 64        5.18 | 6.85   6.82 | 7.21   9.20 | 10.66  13.81 | 15.15   25.69 | 25.49
-//   2-bit/3-bit bf16, rank 39        7.63 | 7.79   9.24 | 8.13   11.83 | 10.74 17.99 | 15.59   29.51 | 24.42
-//   3-bit/4-bit fp32, B 64, rank 20  5.80 | 6.63   7.10 | 7.01   10.07 | 10.78 15.46 | 15.91   27.09 | 26.17
-// The form with 8 saves layout transpositions, most of them with fp32 gradients; its rounds of the
-// selection cost twice the instructions, which a large rank makes the larger part.
-constexpr uint64_t narrow_up_to(bool bf16, bool copy, uint32_t rank)
+// Whether a flat buffer runs 8 elements per lane, for a quantile of rank `rank` in a full block;
+// `copy`: a bf16 copy of the parameters is written.  Measured on MI355X (1024 SIMDs) over six states in
+// turn, us per launch, 8 | 16 per lane:
+//   elements / 2^18                2             3             4             6             8             12            16            20            24            28
+//   4-bit/4-bit fp32               5.05 | 5.79   6.06 | 5.99   6.57 | 6.16   7.91 | 8.67   9.41 | 9.74   11.6 | 12.2   14.2 | 14.7   16.9 | 17.0   20.0 | 19.7   23.7 | 21.9
+//   3-bit/3-bit fp32               5.74 | 6.51   6.52 | 6.64   7.42 | 6.87   8.44 | 9.43   9.59 | 10.5   12.0 | 13.0   14.6 | 15.1   16.7 | 17.1   19.7 | 20.3   22.0 | 22.2
+//   3-bit/4-bit fp32, B 64         4.73 | 5.98   5.93 | 6.13   6.37 | 6.38   7.80 | 9.00   9.14 | 9.95   11.4 | 12.6   13.7 | 14.9   16.8 | 17.1   19.6 | 20.1   22.8 | 21.9
+//     rank 20                      5.84 | 6.61   6.64 | 6.76   7.15 | 7.02   8.67 | 9.71   10.1 | 10.7   12.6 | 13.6   15.6 | 16.0   18.1 | 18.0   21.1 | 21.1   23.7 | 23.2
+//   4-bit/4-bit fp32, copy         5.54 | 5.99   6.36 | 6.20   7.13 | 6.52   8.75 | 9.64   10.1 | 10.5   12.5 | 13.8   15.7 | 16.5   19.4 | 18.9   23.2 | 22.1   26.7 | 24.7
+//   4-bit/4-bit fp32, rank 39      7.15 | 7.17   7.85 | 7.33   8.66 | 7.52   10.2 | 10.1   11.9 | 11.3   15.1 | 14.2
+//   2-bit/3-bit bf16               5.52 | 6.24   5.90 | 6.41   6.77 | 6.59   7.92 | 8.34   9.09 | 9.14   11.7 | 11.7   13.7 | 13.5   15.9 | 15.4   18.7 | 18.1   20.7 | 19.8
+//   3-bit/3-bit DE bf16            5.82 | 6.66   6.26 | 6.79   7.28 | 6.92   8.33 | 8.97   9.45 | 9.95   12.1 | 12.5   14.3 | 14.3   16.5 | 16.6   19.6 | 19.3   21.5 | 21.5
+//   2-bit/2-bit bf16, B 64, rank 20 5.33 | 6.26  5.98 | 6.40   6.81 | 6.59   8.24 | 8.37   9.60 | 9.08   12.2 | 12.1
+//   2-bit/3-bit bf16, copy         5.69 | 6.30   6.24 | 6.52   7.19 | 6.63   8.56 | 8.46   9.99 | 9.78   12.7 | 12.3
+//   4-bit/2-bit DE bf16, copy      5.74 | 6.59   6.62 | 6.79   7.48 | 6.93   9.10 | 8.68   10.7 | 9.91   13.5 | 13.3
+//   2-bit/3-bit bf16, rank 39      7.62 | 7.43   7.93 | 7.67   9.25 | 7.81   10.5 | 9.52   12.1 | 10.7   15.6 | 13.5
+// A launch is a number of rounds of wavefronts per SIMD.  2^20 elements are one round with 16 per lane
+// and two of half as large wavefronts with 8; a little more is two rounds against three shorter ones.
+// 16 is up to 7 % ahead at that one size over states that come out of the last-level cache, as here, but
+// behind by as much where the state is still in the L2 (one state again and again, 3-bit/3-bit fp32
+// 5.93 | 6.45, 4-bit/4-bit 5.53 | 5.55), so no line is drawn there.  Further up the fewer
+// instructions of 16 decide: with bf16 gradients, where 8 saves the fewer layout transpositions, from
+// 3 * 2^20 elements on, with fp32 ones from 6 * 2^20 (the formats cross between 5 and 8); earlier with a copy,
+// which 8 writes in half-covered requests, and with a large rank, whose rounds cost 8 twice the
+// instructions.  (No line is within 3 % of a size for every format.)
+constexpr bool narrow_buffer(uint64_t n, bool bf16, bool copy, uint32_t rank)
 {
-    if (rank > 24) return 1ull << 19;
-    if (!bf16) return 5ull << 20;
-    return copy ? 3ull << 18 : 3ull << 20;
+    if (rank > 24) return n <= 1ull << 19;
+    if (!bf16) return n <= (copy ? 4ull << 20 : 6ull << 20);
+    return n <= (copy ? 5ull << 18 : rank > 16 ? 3ull << 19 : 3ull << 20);
 }
 // Up to how many pieces (pieces16) a table does.
 constexpr uint64_t narrow_table_up_to() { return 3ull << 8; }
@@ -879,9 +893,9 @@ __device__ __forceinline__ void ema_param(const StepArgs &a, const uint32_t tm_a
 
 // The new parameters of a lane's 8 elements and their bf16 copy, if asked for.
 template <bool EXT, bool TAIL>
-__device__ __forceinline__ void store_params8(const StepArgs &a, const uint64_t e0, const bool *ok, const float (&p)[8])
+__device__ __forceinline__ void store_params8(const StepArgs &a, const uint64_t e0, const bool whole, const bool *ok, const float (&p)[8])
 {
-    if (!TAIL || ok[7]) {
+    if (!TAIL || whole) {
         float4 *const pp = reinterpret_cast<float4 *>(a.param + e0);
         pp[0] = make_float4(p[0], p[1], p[2], p[3]);
         pp[1] = make_float4(p[4], p[5], p[6], p[7]);
@@ -1073,7 +1087,8 @@ __device__ __forceinline__ void step_chunk8(const StepArgs &a, const uint64_t ch
     words.load(a, ew0, lane);
     float dm_old = 0.0f, dv_old = 0.0f, al_old = 1.0f;
     if (blk_ok) { dm_old = a.m_scale[gb]; dv_old = a.v_scale[gb]; al_old = a.v_base[gb]; }
-    const RawPG raw = load_pg<BF16, TAIL>(a, e0);
+    const bool whole = !TAIL || __builtin_expect(ew0 + kIter <= a.n, 0);
+    const RawPG raw = load_pg<BF16, TAIL>(a, e0, whole);
     const float gscale = (EXT && a.grad_scale) ? *a.grad_scale : 1.0f;      // uniform: the gradient is transformed first
     de.ready();
     words.stage(img_m, img_v, lane);
@@ -1101,7 +1116,7 @@ __device__ __forceinline__ void step_chunk8(const StepArgs &a, const uint64_t ch
     float mh[8], vh[8];
     float m_absmax, v_max;                     // (v_max of full chunks: the last sorted key below)
     ema_param<8, BM, BV, EXT, TAIL, TAIL>(a, tm_addr, tv_addr, &mc8, &vc8, ok, p, g, mh, vh, m_absmax, v_max);
-    store_params8<EXT, TAIL>(a, e0, ok, p);
+    store_params8<EXT, TAIL>(a, e0, whole, ok, p);
 
     // ---- the lane's v^ sorted (non-negative floats order like their bit patterns); block maxima
     uint32_t key[8];
@@ -1732,9 +1747,9 @@ hipError_t launch_one(const StepArgs &args_in, hipStream_t stream)
 {
     StepArgs args = args_in;                   // the tiling belongs to the instantiation
     if (args.n == 0) return hipSuccess;
-    const bool narrow = args.n <= narrow_up_to(BF16, args.param_bf16 != nullptr, args.rank_full);
+    const bool narrow = narrow_buffer(args.n, BF16, args.param_bf16 != nullptr, args.rank_full);
     const uint64_t whole = narrow ? 0 : args.n / kIter16;
-    args.rest = rest_pieces(args.n, whole);
+    args.rest = narrow ? pieces8(args.n) : rest_pieces(args.n, whole);
     const uint64_t groups = (whole + args.rest + kWaves - 1) / kWaves;
     if (groups > kMaxGroups) return hipErrorInvalidValue;
     const bool ext = args.param_bf16 || args.grad_scale || args.belief || args.l2 != 0.0f;

@@ -459,7 +459,7 @@ __device__ __forceinline__ void step_block_quad(const StepArgs &a, const uint64_
     ChunkWords8<BM, BV, true> words;
     words.load(a, ew0, lane);
     const float dm_old = a.m_scale[blk], dv_old = a.v_scale[blk], al_old = a.v_base[blk];
-    const RawPG raw = load_pg<BF16, true>(a, e0);
+    const RawPG raw = load_pg<BF16, true>(a, e0, ok[7]);
     const float gscale = (EXT && a.grad_scale) ? *a.grad_scale : 1.0f;
     {
         uint4 *const z = reinterpret_cast<uint4 *>(work);
@@ -485,7 +485,7 @@ __device__ __forceinline__ void step_block_quad(const StepArgs &a, const uint64_
     float mh[8], vh[8];
     float m_absmax, v_max;
     ema_param<8, BM, BV, EXT, true, true>(a, tm_addr, tv_addr, &mc8, &vc8, ok, p, g, mh, vh, m_absmax, v_max);
-    store_params8<EXT, true>(a, e0, ok, p);
+    store_params8<EXT, true>(a, e0, ok[7], ok, p);
 
     // ---- block maxima over the four wavefronts
     {

@@ -33,7 +33,7 @@ def gradients(n, B, gen, dtype):
 @pytest.mark.parametrize("k,bm,bv,B", [(k, *f) for k, f in enumerate(FORMATS)])
 def test_flat(gpu, k, bm, bv, B, bf16, de, ext):  # noqa: F811
     import torch
-    large = ((3 << 18) if ext else (3 << 20)) if bf16 else 5 << 20        # the 8-per-lane kernels' largest buffer
+    large = ((5 << 18) if ext else (3 << 20)) if bf16 else 6 << 20        # the 8-per-lane kernels' largest buffer
     dtype = torch.bfloat16 if bf16 else torch.float32
     for j, (p, above) in enumerate(((0.1, large), (0.45, 1 << 19))):      # (ranks above 24 have a line of their own)
         n = above + 2048 + ENDS[(2 * k + j) % len(ENDS)]

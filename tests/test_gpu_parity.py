@@ -208,7 +208,7 @@ def test_all_formats(so, gpu, bm, bv):
 @pytest.mark.parametrize("bm", (2, 3, 4))
 @pytest.mark.parametrize("bv", (2, 3, 4))
 def test_streaming_kernels_all_formats(so, gpu, bm, bv):
-    """The kernels with 16 elements per lane serve flat buffers only from 2^19 to 5 * 2^20 elements on; in
+    """The kernels with 16 elements per lane serve flat buffers only from 2^19 to 6 * 2^20 elements on; in
     a table with a large second tensor they run at any size.  Every format, both block sizes, both
     codebooks with bf16 gradients, the dynamic-exponent codebook with fp32 gradients, plain and with
     every extra: several chunks and a ragged end."""

@@ -1,4 +1,4 @@
-"""GPU parity of the kernels that give a lane 16 elements: flat buffers of more than 5 * 2^20
+"""GPU parity of the kernels that give a lane 16 elements: flat buffers of more than 6 * 2^20
 elements (some formats from 2^19 on), tables of more than 3 * 2^8 pieces.  Same bar as
 test_gpu_parity.py.  (Every instantiation of them is compared with the 8-per-lane kernels in
 test_gpu_both_forms.py; blocks of 2048 give a lane 16 elements from 1025 of them on, see
@@ -11,7 +11,7 @@ from test_gpu_parity import GpuSide, dev, gpu, run_teacher_forced  # noqa: F401
 
 pytestmark = pytest.mark.gpu
 
-LAST8 = 5 << 20                    # the largest flat buffer of any format that runs 8 elements per lane
+LAST8 = 6 << 20                    # the largest flat buffer of any format that runs 8 elements per lane
 FORMATS = [(bm, bv, B) for B in (64, 128) for bm in (2, 3, 4) for bv in (2, 3, 4)]
 # whole chunks of 1024 only; a chunk short of one element, of all but one; ends in either half of a
 # chunk, on and next to a code word's and a block's end
@@ -23,7 +23,7 @@ SIZES = [LAST8, LAST8 + 1, LAST8 + 1023, LAST8 + 1024, LAST8 + 1025, LAST8 + 512
 def test_formats_and_ragged_ends(so, gpu, k, bm, bv, B):  # noqa: F811
     for j in range(3):
         # (the last one: 8 per lane with fp32 gradients, 16 with bf16 ones and a copy)
-        n = SIZES[(2 * k + j) % len(SIZES)] if j < 2 else (3 << 18) + (k * 401) % 1100
+        n = SIZES[(2 * k + j) % len(SIZES)] if j < 2 else (5 << 18) + 1 + (k * 401) % 1100
         opt = ("adamw", "adam_l2", "adabelief")[(k + j) % 3]
         ext = dict(grad_scale=0.5, bf16_copy=True) if (k + j) % 4 == 0 else {}
         run_teacher_forced(so, gpu, n, bm, bv, B, bf16=(k + j) % 2 == 0, steps=2 if j < 2 else 3, seed0=10 * k, de=(k // 2 + j) % 2 == 1,
