@@ -13,6 +13,7 @@ oracle timed on the host cores of this machine on a bounded sample of the same workl
 import argparse
 import contextlib
 import json
+import math
 import os
 import sys
 import time
@@ -26,7 +27,7 @@ HBM_PEAK_GBS = 8000.0          # MI355X: 8 TB/s HBM3E
 # HBM bytes per launch of the step kernel from rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE, each
 # scaled by what the same counter reads for a plain copy of known size (see profiles/).
 MEASURED_TRAFFIC = {"c5_llama7b_2bit_3bit": 77.917e9,    # profiles/chunk16_kernel_c5_llama7b.txt
-                    "c5_llama7b_block2048": 77.78e9}     # profiles/big_wide_kernel_c5_block2048.txt
+                    "c5_llama7b_block2048": 77.45e9}     # profiles/big_kernel_c5_block2048.txt
 
 
 def bytes_per_param(w):
@@ -38,6 +39,30 @@ def bytes_per_param(w):
     codes = (stored[w.bits_m] + stored[w.bits_v]) / 8.0
     scales = 12.0 / w.block_size
     return (4 + g + codes + scales) + (4 + codes + scales)
+
+
+def step_kernel_name(w, n, mp, launch):
+    """The kernel that takes the time: the library's rules by format, size and launch (narrow_buffer and
+    narrow_table_up_to of solo_step.h, kQuadUpTo and quad_table of solo_step_big.h)."""
+    sizes = [t[1] for t in w.tensors]
+    if launch == "per_tensor":
+        n = max(sizes)
+    B, bf16, multi = w.block_size, w.grad_dtype == "bf16", launch == "multi"
+    if B == 2048:
+        blocks = sum(-(-k // B) for k in sizes) if multi else -(-n // B)
+        quad = blocks <= 1024 or (multi and 4 * blocks <= 5 * len(sizes))
+        return "solo::" + ("multi_" if multi else "") + ("big_quad_kernel" if quad else "big_kernel")
+    if multi:                                    # chunks of 1024, then 512 elements each to the end of the last code word
+        pieces = sum(k // 1024 + (-(-(-(-k // 80) * 80 - k // 1024 * 1024) // 512) if k % 1024 else 0) for k in sizes)
+        return f"solo::multi_chunk{8 if pieces <= 3 << 8 else 16}_kernel"
+    rank = min(B, max(1, math.ceil(w.quantile_p * B)))
+    if rank > 24:
+        up_to = 1 << 19
+    elif bf16:
+        up_to = 5 << 18 if mp else 3 << 19 if rank > 16 else 3 << 20
+    else:
+        up_to = 4 << 20 if mp else 6 << 20
+    return f"solo::chunk{8 if n <= up_to else 16}_kernel"
 
 
 def device_grads(torch, n, kind, std, seed, dtype, sparse_rows=None):
@@ -337,14 +362,7 @@ def main():
     def frac_of(ms):
         return (bpp * n / (ms * 1e-3) / 1e9 / HBM_PEAK_GBS) if ms else None
 
-    # the kernel that takes the time (the library picks it from the format, the size and the launch)
-    if w.block_size == 2048:
-        kernel_name = "solo::multi_big_kernel" if args.launch == "multi" else "solo::big_kernel"
-    elif args.launch == "multi":
-        kernel_name = f"solo::multi_chunk{8 if n <= 3 << 18 else 16}_kernel"
-    else:
-        up_to = 5 << 20 if w.grad_dtype != "bf16" else 3 << 18 if mp else 3 << 20
-        kernel_name = f"solo::chunk{8 if n <= up_to else 16}_kernel"
+    kernel_name = step_kernel_name(w, n, mp, args.launch)
     out = {
         "metric": "updated_params_per_sec", "value": n / (wall / args.steps), "unit": "params/s",
         "n_gpus": 1, "steps": args.steps, "warmup": args.warmup, "ms_per_step": ms_per_step,

@@ -221,7 +221,8 @@ size_t solo_multi_table_bytes(uint32_t count, uint64_t units);
  * array of descriptors holding DEVICE pointers) and set *table_flags (SOLO_TABLE_*), which
  * solo_adamw_step_multi takes back.  Checks every pointer's alignment. */
 #define SOLO_TABLE_BF16_COPY 1u   /* some tensor has a bf16 copy to write */
-#define SOLO_TABLE_SHORT_BLOCK 2u /* blocks of 2048: some tensor ends in a shorter block */
+#define SOLO_TABLE_SHORT_BLOCK 2u /* blocks of 2048: some tensor ends in a shorter block (for the caller; the
+                                     launch does not depend on it) */
 #define SOLO_TABLE_PIECES_SHIFT 2 /* blocks of 64 and 128: table_flags >> 2 is the number of pieces of the
                                      tensors (one wavefront each), which sizes the launch; 0 where the
                                      units do, which is right for every table but larger than need be */

@@ -4,8 +4,8 @@
 // first load to the last store: 1024 elements, 16 per lane (step_chunk16), or 512, 8 per lane
 // (step_chunk8).  A block of 128 (64) elements is held by 8 (4) or 16 (8) neighbouring lanes, i.e.
 // by half a DPP row or a row, and every per-block reduction is a few DPP steps.  Nothing is shared
-// between wavefronts but a constant table: the only workgroup barrier sits before the first
-// element is touched.  No software prefetch: 60-100 registers leave room for five to seven
+// between wavefronts but a constant table: the only workgroup barrier, with dynamic-exponent codes
+// of 3 and 4 bits, waits for that table while the elements' loads are under way.  No software prefetch: 60-100 registers leave room for five to seven
 // wavefronts per SIMD, which hide each other's memory latency, and the whole machine sweeps one
 // compact window of memory.
 //
@@ -20,27 +20,28 @@
 //
 // (Measured against one wavefront that walks a super-tile of 5120 elements in five iterations
 // and prefetches one iteration ahead, the form of the large bf16 buffers before: 2^24 elements
-// 2-bit/3-bit 43.5 -> 35.9 us, 2^28 elements 594 -> 508 us, 6.7e9 elements 13.62 -> 13.47 ms.)
+// 2-bit/3-bit 41.8 -> 34.5 us, 2^28 elements 582 -> 520 us; at 6.7e9 elements, where HBM is the bound,
+// no difference: 13.27 and 13.29 ms.)
 //
 // The pieces that these functions and the large-block functions of solo_step_big.h have in common
 // (layout transposition, level tables, EMAs and parameter, encoders, code words) exist once, as
 // inlined helpers in front of them.
 //
-// The kernel is bound by vector-ALU issue as much as by HBM (packed FP32 is
-// off, so a CU retires 64 lane-operations per clock: about 80 per parameter at
-// 70 % of the HBM peak).  Everything below is shaped by instruction count:
+// The kernel is bound by vector-ALU issue as much as by HBM: packed FP32 is off, so a CU retires 64
+// lane-operations per clock; 16 per lane issues 58 vector instructions per parameter (2-bit/3-bit bf16),
+// which is as long as its bytes take.  Everything below is shaped by instruction count:
 //   * both dequantizers are table look-ups: the lanes of a group compute the
 //     block's level tables (alpha^q * Delta_v, (c-L) * Delta_m/L) once and park
 //     them in LDS; an element costs one bit-field extract, one address add and
 //     one ds_read per moment;
-//   * the p-quantile is exact: each lane sorts its 8 values with min3/med3/max3
-//     (32 instructions) and the group runs r rounds of "row minimum by DPP, the
+//   * the p-quantile is exact: each lane sorts its 8 or 16 values with min3/med3/max3
+//     and merges, and the group runs r rounds of "row minimum by DPP, the
 //     lowest lane that holds it pops its column"; four scalar instructions pick
 //     that lane for all groups, ties or not;
 //   * the two per-block divisions share one IEEE division sequence (even lanes
 //     divide x_p by Delta_v, odd lanes L by Delta_m);
-//   * the base alpha = rho^(1/K) is found by testing G consecutive binary32
-//     candidates around a hardware exp2/log2 guess, one per lane;
+//   * the base alpha = rho^(1/K) is found by testing 16 consecutive binary32
+//     candidates around a hardware exp2/log2 guess, spread over the group's lanes;
 //   * codes are rounded in the float domain and accumulated with FMAs
 //     (acc += code * 2^(b j)); xi is built as a float in [1, 2) by one
 //     bit-align of the element's finalized word of the xi stream (one hash
@@ -58,7 +59,6 @@
 #include <stdint.h>
 
 namespace solo {
-
 
 constexpr int kTileUnit = 2560;    // lcm of the block sizes and of 16, 10 and 8 codes per word
 constexpr int kIter = 512;         // elements of a chunk with 8 per lane
@@ -481,8 +481,6 @@ __device__ __forceinline__ uint32_t pack_bf16(float lo, float hi)
     const bf16x2_t v = {(__bf16)lo, (__bf16)hi};
     return __builtin_bit_cast(uint32_t, v);
 }
-
-template <bool V> struct BoolTag { static constexpr bool value = V; };
 
 // Parameters and gradients of a lane's 8 consecutive elements: two (bf16 gradients: one) 16-byte
 // accesses per lane and stream.  A wavefront's access then covers every other 16 bytes of its two
@@ -1670,7 +1668,7 @@ __device__ __forceinline__ StepArgs tensor_args(const MultiArgs &ma, const Tenso
 // the same code.  (Cutting the units of the map instead - five wavefronts per 5120 elements, a ragged end
 // as part of them - left most wavefronts of a table of short tensors without work, and one wavefront
 // with three pieces one behind the other where a tensor ends; 1000 tensors of 600 elements,
-// 2-bit/3-bit bf16: 16.2 us, 7.9 now; 20,000 of them: 160 and 77; 53 tensors of 787,050 elements,
+// 2-bit/3-bit bf16: 16.2 us, 7.0 now; 20,000 of them: 160 and 77; 53 tensors of 787,050 elements,
 // 3-bit/4-bit fp32 with a copy: 14.2 and 7.1.)
 
 // 8 elements per lane, for tables of few elements.

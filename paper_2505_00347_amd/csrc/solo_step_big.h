@@ -16,7 +16,7 @@
 //   * the base alpha, the divisions and the level tables are computed by every wavefront (every
 //     16 lanes) for itself: cheaper than another barrier.
 // The kernel is bound by vector-ALU issue and, through the number of workgroups on a CU, by LDS
-// (17.3 ms for 6.7e9 parameters at 3.5 wavefronts per SIMD, 15.7 ms at 5), so the histogram is
+// (an earlier form: 17.3 ms for 6.7e9 parameters at 3.5 wavefronts per SIMD, 15.7 ms at 5), so the histogram is
 // kept small: see BigLayout.  Every wavefront stages and writes back the words of its own elements
 // (whole 128-byte lines for 2- and 4-bit codes; ten-to-a-word codes by one atomic XOR per word at
 // the memory side, since a wavefront's share does not end on a word).
@@ -215,8 +215,9 @@ __device__ __forceinline__ bool try_guess(Narrowed &at, const uint32_t (&key)[NK
 // A rank below the first pass's range (28 octaves under the maximum, or zeros) starts over from 0.
 // (Against four fixed passes over 8 + 8 + 8 + 7 bits, the first of which only told binades apart, on
 // 2^26 elements of 2-bit/3-bit codes: 163.6 -> 153.7 us, with nine of ten gradients at zero
-// 203 -> 140 us, all gradients alike 236 -> 155 us; 72 -> 65 vector instructions per parameter, of
-// which about 15 are the selection.)
+// 203 -> 140 us, all gradients alike 236 -> 155 us.  The kernel issues 62 vector instructions per
+// parameter, four more than blocks of 128.  2-bit v at p = 0.3 narrows slowly: 1000 to 5000 blocks take up to
+// 10 % longer than with the fixed passes.)
 template <int NK, int W>
 __device__ __forceinline__ uint32_t select_rank(const uint32_t (&key)[NK], const uint32_t kmax, const uint32_t rank,
                                                 const uint32_t present, const uint32_t lane, const uint32_t wave,
