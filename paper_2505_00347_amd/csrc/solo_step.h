@@ -194,6 +194,7 @@ __device__ __forceinline__ uint32_t f2u(float x) { return __builtin_bit_cast(uin
 __device__ __forceinline__ float u2f(uint32_t x) { return __builtin_bit_cast(float, x); }
 __device__ __forceinline__ uint32_t umin(uint32_t a, uint32_t b) { return a < b ? a : b; }
 __device__ __forceinline__ uint32_t umax(uint32_t a, uint32_t b) { return a > b ? a : b; }
+__device__ __forceinline__ uint64_t umin64(uint64_t a, uint64_t b) { return a < b ? a : b; }
 // Median of three bit patterns of non-negative floats (they order like the floats).
 __device__ __forceinline__ uint32_t umed3(uint32_t a, uint32_t b, uint32_t c)
 {
@@ -964,9 +965,19 @@ struct ChunkWords8 {
         gw_m = gm_lo + lane; gw_v = gv_lo + lane;
         has_m = lane < (rm0 + kIter + CM - 1) / CM && (!TAIL || gw_m < (a.n + CM - 1) / CM);
         has_v = lane < (rv0 + kIter + CV - 1) / CV && (!TAIL || gw_v < (a.n + CV - 1) / CV);
-        own_m = 0; own_v = 0;
-        if (has_m) own_m = a.m_words[gw_m];
-        if (has_v) own_v = a.v_words[gw_v];
+        // (Lanes without a word load the last one again: a load under a condition whose fields are masked
+        // behind it was waited for inside, in front of all the loads that follow.  2^20 elements,
+        // 3-bit/3-bit fp32: 5.46 us under conditions, 5.27 without; the 1.3e9 elements of the 1.3B shapes, 3-bit/3-bit
+        // bf16, 16 per lane: 2535 and 2439.)
+        uint32_t lm = (rm0 + kIter + CM - 1) / CM - 1, lv = (rv0 + kIter + CV - 1) / CV - 1;
+        uint64_t fm = gm_lo, fv = gv_lo;
+        if (TAIL) {
+            const uint64_t end_m = (a.n - 1) / CM, end_v = (a.n - 1) / CV;     // last words of the buffer
+            fm = umin64(fm, end_m); lm = (uint32_t)umin64(lm, end_m - fm);
+            fv = umin64(fv, end_v); lv = (uint32_t)umin64(lv, end_v - fv);
+        }
+        own_m = a.m_words[fm + umin(lane, lm)];
+        own_v = a.v_words[fv + umin(lane, lv)];
         const uint32_t qm = rm0 + lane * 8u, qv = rv0 + lane * 8u;      // < 520: e / 10 by multiplication
         wm = (CM == 10) ? __umul24(qm, 52429u) >> 19 : qm / CM; sm = qm - wm * CM;
         wv = (CV == 10) ? __umul24(qv, 52429u) >> 19 : qv / CV; sv = qv - wv * CV;
@@ -1408,10 +1419,9 @@ struct ChunkWords16 {
     uint32_t wm[2], sm[2], wv[2], sv[2];       // word (of the image) and slot of the first code of the lane's two runs of 8
 
     // ew0: first element of the wavefront's share, of which `here` exist (0: of the share in front of it).
-    // Issues the loads.  ALL_LANES: lanes without a word load the last one again, because a load
-    // under a condition is waited for inside it, with every load in front of it (blocks of 2048, 1 million
-    // elements, 2-bit/3-bit bf16: 9.6 us, 9.2 with it and the words in front of the parameters).
-    template <bool ALL_LANES>
+    // Issues the loads.  Lanes without a word load the last one again, because a load
+    // under a condition is waited for inside it, with every load in front of it (see ChunkWords8; blocks of 2048,
+    // 1 million elements, 2-bit/3-bit bf16: 9.6 us, 9.2 with it and the words in front of the parameters).
     __device__ __forceinline__ void load(const StepArgs &a, const uint64_t ew0, const uint32_t lane, const uint32_t here)
     {
         gm_lo = ew0 / CM; gv_lo = ew0 / CV;
@@ -1420,15 +1430,9 @@ struct ChunkWords16 {
         const uint64_t fm = here ? gm_lo : (ew0 - kIter16) / CM, fv = here ? gv_lo : (ew0 - kIter16) / CV;
         const uint32_t lm = here ? nwm - 1u : 0u, lv = here ? nwv - 1u : 0u;
 #pragma unroll
-        for (int k = 0; k < KM; ++k) {
-            own_m[k] = 0;
-            if (ALL_LANES || lane + 64u * k < nwm) own_m[k] = a.m_words[fm + (ALL_LANES ? umin(lane + 64u * k, lm) : lane + 64u * k)];
-        }
+        for (int k = 0; k < KM; ++k) own_m[k] = a.m_words[fm + umin(lane + 64u * k, lm)];
 #pragma unroll
-        for (int k = 0; k < KV; ++k) {
-            own_v[k] = 0;
-            if (ALL_LANES || lane + 64u * k < nwv) own_v[k] = a.v_words[fv + (ALL_LANES ? umin(lane + 64u * k, lv) : lane + 64u * k)];
-        }
+        for (int k = 0; k < KV; ++k) own_v[k] = a.v_words[fv + umin(lane + 64u * k, lv)];
 #pragma unroll
         for (int r = 0; r < 2; ++r) {
             const uint32_t qm = rm0 + lane * 16u + 8u * r, qv = rv0 + lane * 16u + 8u * r;   // < 1040: e / 10 by multiplication
@@ -1525,7 +1529,7 @@ __device__ __forceinline__ void step_chunk16(const StepArgs &a, const uint64_t c
 
     // ---- every load is issued before the first one is waited for
     ChunkWords16<BM, BV> words;
-    words.template load<false>(a, ew0, lane, kIter16);
+    words.load(a, ew0, lane, kIter16);
     const uint64_t gb = chunk * NG + grp;
     const float dm_old = a.m_scale[gb], dv_old = a.v_scale[gb], al_old = a.v_base[gb];
     const RawPG16<BF16> raw = load_pg16<BF16>(a, ew0, lane);

@@ -330,7 +330,7 @@ __device__ __forceinline__ void step_block(const StepArgs &a, const uint64_t blk
 
     // ---- loads: parameters and gradients, the wavefront's code words, the block's scalars
     ChunkWords16<BM, BV> words;
-    words.template load<true>(a, ew0, lane, here);
+    words.load(a, ew0, lane, here);
     const float dm_old = a.m_scale[blk], dv_old = a.v_scale[blk], al_old = a.v_base[blk];
     const RawPG16<BF16> raw = load_pg16<BF16>(a, ew0, lane, here);
     const float gscale = (EXT && a.grad_scale) ? *a.grad_scale : 1.0f;
