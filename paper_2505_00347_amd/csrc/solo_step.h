@@ -171,7 +171,7 @@ constexpr uint64_t kMaxGroups = 0xFFFFFFFFull / (kWaves * 64);
 template <int CTRL>
 __device__ __forceinline__ uint32_t dpp(uint32_t x)
 {
-    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, CTRL, 0xF, 0xF, false);
+    return (uint32_t)__builtin_amdgcn_mov_dpp((int)x, CTRL, 0xF, 0xF, true);   // (every lane has a source: no old value to set up)
 }
 
 // Butterfly over the G (4, 8 or 16) lanes that hold one block: lane^1 and lane^2
@@ -199,6 +199,12 @@ __device__ __forceinline__ uint64_t umin64(uint64_t a, uint64_t b) { return a < 
 __device__ __forceinline__ uint32_t umed3(uint32_t a, uint32_t b, uint32_t c)
 {
     return f2u(__builtin_amdgcn_fmed3f(u2f(a), u2f(b), u2f(c)));
+}
+
+// (x & mask) | base as one two-cycle instruction (v_and_or_b32 takes four).
+__device__ __forceinline__ uint32_t and_or(uint32_t x, uint32_t mask, uint32_t base)
+{
+    return __builtin_amdgcn_bitop3_b32(x, mask, base, 0xEA);
 }
 
 // The bits of a wave-wide ballot that belong to this lane's group, shifted down.
@@ -463,15 +469,15 @@ __device__ __forceinline__ uint4 stream_load_u4(const void *p)
 // (Written as assembly because no builtin sets sc1.  The s_nop covers the two wait states that a
 // store of more than 64 bits needs before its data registers may be overwritten: the compiler
 // keeps that distance for its own stores but does not look inside an asm block.)
-__device__ __forceinline__ void stream_store_u4(void *p, u32x4_t v)
+// `base`: uniform over the wavefront; `at`: bytes behind it, per lane; OFFSET: of the instruction.  (One
+// 32-bit register per lane addresses all stores of a chunk, instead of a 64-bit address for each.)
+template <int OFFSET>
+__device__ __forceinline__ void stream_store_f4(void *const base, const uint32_t at, float4 x)
 {
-    asm volatile("global_store_dwordx4 %0, %1, off sc1 nt\n\ts_nop 1" ::"v"(p), "v"(v) : "memory");
-}
-__device__ __forceinline__ void stream_store_f4(float *p, float4 x)
-{
+    static_assert(OFFSET >= 0 && OFFSET < 4096, "offset of a global access");
     const u32x4_t v = {__builtin_bit_cast(uint32_t, x.x), __builtin_bit_cast(uint32_t, x.y),
                        __builtin_bit_cast(uint32_t, x.z), __builtin_bit_cast(uint32_t, x.w)};
-    stream_store_u4(p, v);
+    asm volatile("global_store_dwordx4 %0, %1, %2 offset:%3 sc1 nt\n\ts_nop 1" ::"v"(at), "v"(v), "s"(base), "n"(OFFSET) : "memory");
 }
 
 // Two binary32 values rounded to bfloat16 (nearest, ties to even: the hardware conversion),
@@ -520,6 +526,20 @@ __device__ __forceinline__ RawPG load_pg(const StepArgs &a, const uint64_t e0, c
         else      { r.g0 = make_uint4(g[0], g[1], g[2], g[3]); r.g1 = make_uint4(g[4], g[5], g[6], g[7]); }
     }
     return r;
+}
+
+// A launch constant in a vector register.  With eight wavefronts per SIMD, MI355X issues an fp32 add,
+// multiplication or fused multiply-add, an and / or / xor / bitop3, a right shift and an integer add of a
+// wavefront in 2.3-2.7 cycles, but in 4.4 where an operand is a scalar register (everything else, min, max,
+// conversions, left shifts and DPP among it, takes 4.3 in any case, the transcendental functions 8.3).
+// The moments of an element had six such operands: with them in vector registers, and the two table addresses
+// by bitop3, the 1024 elements of a wavefront take 3414 instead of 3616 cycles of issue (2-bit/3-bit bf16).
+template <typename T>                     // (a template: the host compiler does not know the constraint)
+__device__ __forceinline__ T in_vector(const T x)
+{
+    T v;
+    asm("v_mov_b32 %0, %1" : "=v"(v) : "s"(x));
+    return v;
 }
 
 // Wave-level ordering point for LDS traffic between lanes of one wavefront (LDS executes a
@@ -723,23 +743,43 @@ __device__ __forceinline__ BlockCodec block_codec(uint32_t xp_bits, float dm, fl
     return c;
 }
 
-// Encodes a lane's run of 8 consecutive elements starting at global element index e (a multiple
-// of 8): returns the packed 1st- and 2nd-moment codes (element j in bits [b j, b j + b)).
+// The xi stream of a wavefront's share: its first group of eight (`group0`, 64 bits, uniform) and what the
+// groups of a lane need of the upper half of their number.
+struct XiGroups {
+    uint32_t low, high;        // group0's low word; key2 times its high word
+    bool wraps;                // the low word wraps inside the share (of at most 128 groups)
+    __device__ __forceinline__ XiGroups(const StepArgs &a, const uint64_t first_element)
+    {
+        const uint64_t group0 = (a.index_offset + first_element) >> 3;
+        low = (uint32_t)group0;
+        high = (uint32_t)(group0 >> 32) * a.key2;
+        wraps = low > 0xFFFFFFFFu - 128u;
+    }
+    // the hash's input for group group0 + k
+    __device__ __forceinline__ uint32_t word(const StepArgs &a, const uint32_t k) const
+    {
+        const uint32_t x = low + k;
+        uint32_t h = high;
+        if (__builtin_expect(wraps, 0)) h += x < k ? a.key2 : 0u;
+        return (x ^ a.key0) + h;
+    }
+};
+
+// Encodes a lane's run of 8 consecutive elements, the group `xi_word` (XiGroups::word) of the xi stream: returns the packed 1st- and 2nd-moment codes (element j in bits [b j, b j + b)).
 // xi: one hashed start and stride per 8 elements, every element's word finalized on its own;
 // 1.5 + xi - 2^-24 is built as a float in [1,2) by one bit-align of the finalized word.
 // Codes are rounded in the float domain, four to an
 // accumulator (element j weighs 2^(b (j mod 4))): m: code - L = rint(m^ * L/Delta_m) in [-L, L];
 // v: code + 1 = floor(log_alpha(v^/Delta_v) + 1.5 + xi).  `ok` (TAIL only): the elements that exist.
 template <int BM, int BV, bool MDE, bool TAIL>
-__device__ __forceinline__ void encode_run(const StepArgs &a, uint64_t e, const float *mh, const float *vh,
+__device__ __forceinline__ void encode_run(const StepArgs &a, const uint32_t xi_word, const float *mh, const float *vh,
                                            const bool *ok, const BlockCodec &c, uint32_t de_base,
                                            uint32_t &m8, uint32_t &v8)
 {
     constexpr int L = (1 << (BM - 1)) - 1;
     constexpr int K = (1 << BV) - 1;
     constexpr bool kDeTable = MDE && BM >= 3;
-    const uint64_t gidx = (a.index_offset + e) >> 3;
-    uint32_t X = mix32(((uint32_t)gidx ^ a.key0) + (uint32_t)(gidx >> 32) * a.key2);
+    uint32_t X = mix32(xi_word);
     uint32_t Y = mix32(X ^ a.key1) | 1u;
     if (!a.stochastic) { X = kXiZeroWord; Y = 0u; }     // xi = 0: the float is 1.5
     uint32_t xj = X;                                    // X + j Y, walked up from j = 0
@@ -859,31 +899,34 @@ __device__ __forceinline__ void ema_param(const StepArgs &a, const uint32_t tm_a
         for (int j = 0; j < N; ++j) {
             const uint32_t om = (j == 0) ? (mc8[0] << 2) : (mc8[0] >> (BM * j - 2));
             const uint32_t ov = (j == 0) ? (vc8[0] << 2) : (vc8[0] >> (BV * j - 2));
-            mt[j] = lds_f32(tm_addr | (om & MIDX));
-            vt[j] = lds_f32(tv_addr | (ov & VIDX));
+            mt[j] = lds_f32(and_or(om, MIDX, tm_addr));
+            vt[j] = lds_f32(and_or(ov, VIDX, tv_addr));
         }
     }
+    const float beta1 = in_vector(a.beta1), omb1 = in_vector(a.omb1), beta2 = in_vector(a.beta2), omb2 = in_vector(a.omb2);
+    const float denom_scale = in_vector(a.denom_scale), denom_eps = in_vector(a.denom_eps), decay = in_vector(a.decay);
     m_absmax = 0.0f;
     v_max = 0.0f;
-    const float kb = a.belief ? 1.0f : 0.0f;
+    float kb = 0.0f, eps_state = 0.0f;
+    if (EXT) { kb = in_vector(a.belief ? 1.0f : 0.0f); eps_state = in_vector(a.eps_state); }
 #pragma unroll
     for (int j = 0; j < N; ++j) {
         if (N != 8) {
             const int r = j / 8, jj = j % 8;
             const uint32_t om = (jj == 0) ? (mc8[r] << 2) : (mc8[r] >> (BM * jj - 2));
             const uint32_t ov = (jj == 0) ? (vc8[r] << 2) : (vc8[r] >> (BV * jj - 2));
-            mt[j] = lds_f32(tm_addr | (om & MIDX));
-            vt[j] = lds_f32(tv_addr | (ov & VIDX));
+            mt[j] = lds_f32(and_or(om, MIDX, tm_addr));
+            vt[j] = lds_f32(and_or(ov, VIDX, tv_addr));
         }
-        mh[j] = __builtin_fmaf(a.beta1, mt[j], a.omb1 * g[j]);
+        mh[j] = __builtin_fmaf(beta1, mt[j], omb1 * g[j]);
         if (EXT) {
             const float d = __builtin_fmaf(-kb, mh[j], g[j]);
-            vh[j] = __builtin_fmaf(a.beta2, vt[j], a.omb2 * (d * d)) + a.eps_state;
+            vh[j] = __builtin_fmaf(beta2, vt[j], omb2 * (d * d)) + eps_state;
         } else {
-            vh[j] = __builtin_fmaf(a.beta2, vt[j], a.omb2 * (g[j] * g[j]));
+            vh[j] = __builtin_fmaf(beta2, vt[j], omb2 * (g[j] * g[j]));
         }
-        const float denom = __builtin_fmaf(__builtin_amdgcn_sqrtf(vh[j]), a.denom_scale, a.denom_eps);
-        p[j] = __builtin_fmaf(p[j], a.decay, -(mh[j] * __builtin_amdgcn_rcpf(denom)));
+        const float denom = __builtin_fmaf(__builtin_amdgcn_sqrtf(vh[j]), denom_scale, denom_eps);
+        p[j] = __builtin_fmaf(p[j], decay, -(mh[j] * __builtin_amdgcn_rcpf(denom)));
         if (TAIL && !ok[j]) { mh[j] = 0.0f; vh[j] = 0.0f; }
         m_absmax = __builtin_fmaxf(m_absmax, __builtin_fabsf(mh[j]));
         if (VMAX) v_max = __builtin_fmaxf(v_max, vh[j]);
@@ -1157,7 +1200,7 @@ __device__ __forceinline__ void step_chunk8(const StepArgs &a, const uint64_t ch
     // ---- the block's encoder constants, then this lane's 8 codes of each moment
     const BlockCodec codec = block_codec<BV, G, L, MDE>(xp_bits, dm, dv, lane, lig, gshift);
     uint32_t m8, v8;
-    encode_run<BM, BV, MDE, TAIL>(a, e0, mh, vh, ok, codec, de_base, m8, v8);
+    encode_run<BM, BV, MDE, TAIL>(a, XiGroups(a, ew0).word(a, lane), mh, vh, ok, codec, de_base, m8, v8);
     xor_into_image8<BM, BV>(img_m, img_v, words.wm, words.sm, words.wv, words.sv, mc8 ^ m8, vc8 ^ v8);
     if (lig == 0 && blk_ok) { a.m_scale[gb] = dm; a.v_scale[gb] = dv; a.v_base[gb] = codec.alpha; }
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
@@ -1309,6 +1352,21 @@ __device__ __forceinline__ void lane_layout16(const RawPG16<BF16> &raw, const St
     }
 }
 
+// Half K of the 1024 bf16 copies of a chunk: the lane's 8 of them at byte `at`.
+template <int K>
+__device__ __forceinline__ void store_halves(uint16_t *const hp, const uint32_t at, const float4 x, const bool all, const uint32_t here)
+{
+    const uint32_t i = at / 2u + 512u * K;
+    if (all || i + 8u <= here) {
+        stream_store_f4<1024 * K>(hp, at, x);
+    } else if (i < here) {
+        const uint32_t w[4] = {f2u(x.x), f2u(x.y), f2u(x.z), f2u(x.w)};
+#pragma unroll
+        for (int j = 0; j < 7; ++j)
+            if (i + j < here) hp[i + j] = (uint16_t)(w[j / 2] >> (16 * (j & 1)));
+    }
+}
+
 // The new parameters of a lane's 16 elements (and their bf16 copy, if asked for: 32 bytes per
 // lane, two vectors, first) back to the coalesced layout and streamed out; chunk_e0: first
 // element of the wavefront's 1024, of which `here` exist.
@@ -1317,6 +1375,8 @@ __device__ __forceinline__ void store_params16(const StepArgs &a, const uint64_t
                                                const float (&p)[16], const Stage16 &st, const uint32_t here = kIter16)
 {
     wave_lds_sync();
+    const bool all = __builtin_expect(here == kIter16, 1);
+    const uint32_t at = lane * 16u;
     if (EXT && a.param_bf16) {
 #pragma unroll
         for (int c = 0; c < 2; ++c) {
@@ -1325,52 +1385,43 @@ __device__ __forceinline__ void store_params16(const StepArgs &a, const uint64_t
             st.l2[c] = make_float4(u2f(h0), u2f(h1), u2f(h2), u2f(h3));
         }
         wave_lds_sync();
-        uint16_t *hp = a.param_bf16 + chunk_e0 + lane * 8u;
-#pragma unroll
-        for (int k = 0; k < 2; ++k) {
-            const uint32_t i = lane * 8u + 512u * k;
-            const float4 x = st.c2[72 * k];
-            if (here == kIter16 || i + 8u <= here) {
-                stream_store_f4(reinterpret_cast<float *>(hp + 512 * k), x);
-            } else if (i < here) {
-                const uint32_t w[4] = {f2u(x.x), f2u(x.y), f2u(x.z), f2u(x.w)};
-#pragma unroll
-                for (int j = 0; j < 7; ++j)
-                    if (i + j < here) hp[512 * k + j] = (uint16_t)(w[j / 2] >> (16 * (j & 1)));
-            }
-        }
+        uint16_t *const hp = a.param_bf16 + chunk_e0;
+        store_halves<0>(hp, at, st.c2[0], all, here);
+        store_halves<1>(hp, at, st.c2[72], all, here);
         wave_lds_sync();
     }
 #pragma unroll
     for (int c = 0; c < 4; ++c) st.l4[c] = make_float4(p[4 * c], p[4 * c + 1], p[4 * c + 2], p[4 * c + 3]);
     wave_lds_sync();
-    float *pp = a.param + chunk_e0 + lane * 4u;
-    if (__builtin_expect(here == kIter16, 1)) {
-#pragma unroll
-        for (int k = 0; k < 4; ++k) stream_store_f4(pp + 256 * k, st.c4[72 * k]);
+    float *const pp = a.param + chunk_e0;
+    if (all) {
+        stream_store_f4<0>(pp, at, st.c4[0]);
+        stream_store_f4<1024>(pp, at, st.c4[72]);
+        stream_store_f4<2048>(pp, at, st.c4[144]);
+        stream_store_f4<3072>(pp, at, st.c4[216]);
         return;
     }
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
         const uint32_t i = lane * 4u + 256u * k;
         const float4 x = st.c4[72 * k];
-        if (here == kIter16 || i + 4u <= here) {
-            stream_store_f4(pp + 256 * k, x);
+        if (i + 4u <= here) {
+            *reinterpret_cast<float4 *>(pp + i) = x;
         } else if (i < here) {
-            pp[256 * k] = x.x;
-            if (i + 1u < here) pp[256 * k + 1] = x.y;
-            if (i + 2u < here) pp[256 * k + 2] = x.z;
+            pp[i] = x.x;
+            if (i + 1u < here) pp[i + 1u] = x.y;
+            if (i + 2u < here) pp[i + 2u] = x.z;
         }
     }
 }
 
-// Codes of a lane's 16 elements (two runs of 8: e0 is the first element, wm / sm / wv / sv the
+// Codes of a lane's 16 elements (two runs of 8; ew0 is the wavefront's first element, wm / sm / wv / sv the
 // word and slot of each run's first code in the image, mc8 / vc8 the old codes) into the LDS
 // image of the code words.  3-bit codes share words between lanes: XOR turns this lane's old
 // fields into the new ones and leaves the neighbours' alone.  2- and 4-bit words belong to one lane
 // (2-bit: both runs lie in word wm[0]).
 template <int BM, int BV, bool MDE>
-__device__ __forceinline__ void encode_into_image16(const StepArgs &a, const uint64_t e0, const float *mh, const float *vh,
+__device__ __forceinline__ void encode_into_image16(const StepArgs &a, const uint64_t ew0, const uint32_t lane, const float *mh, const float *vh,
                                                     const BlockCodec &codec, const uint32_t de_base,
                                                     uint32_t *const img_m, uint32_t *const img_v,
                                                     const uint32_t (&wm)[2], const uint32_t (&sm)[2],
@@ -1378,10 +1429,11 @@ __device__ __forceinline__ void encode_into_image16(const StepArgs &a, const uin
                                                     const uint32_t (&mc8)[2], const uint32_t (&vc8)[2])
 {
     uint32_t m_word = 0, v_word = 0;
+    const XiGroups xi(a, ew0);
 #pragma unroll
     for (int r = 0; r < 2; ++r) {
         uint32_t m8, v8;
-        encode_run<BM, BV, MDE, false>(a, e0 + 8u * r, mh + 8 * r, vh + 8 * r, nullptr, codec, de_base, m8, v8);
+        encode_run<BM, BV, MDE, false>(a, xi.word(a, 2u * lane + r), mh + 8 * r, vh + 8 * r, nullptr, codec, de_base, m8, v8);
         if (BM == 3) {
             const uint32_t xm = mc8[r] ^ m8;
             atomicXor(&img_m[wm[r]], (xm << (3u * sm[r])) & 0x3FFFFFFFu);
@@ -1519,7 +1571,7 @@ __device__ __forceinline__ void step_chunk16(const StepArgs &a, const uint64_t c
     // A runaway column address (possible only with non-finite input) stays inside the slab.
     static_assert(Lay::kSlab >= 64 * kColStride16 + 140, "column slack");
 
-    const uint64_t ew0 = chunk * kIter16, e0 = ew0 + lane * 16u;
+    const uint64_t ew0 = chunk * kIter16;
     const uint32_t lig = lane & (G - 1), grp = lane / G, gshift = lane & 31u & ~(uint32_t)(G - 1);
     uint32_t *const img_m = slab + Lay::kOffImgM, *const img_v = slab + Lay::kOffImgV;
     uint32_t *const col = slab + Lay::kOffCol + lane * kColStride16;
@@ -1530,8 +1582,8 @@ __device__ __forceinline__ void step_chunk16(const StepArgs &a, const uint64_t c
     // ---- every load is issued before the first one is waited for
     ChunkWords16<BM, BV> words;
     words.load(a, ew0, lane, kIter16);
-    const uint64_t gb = chunk * NG + grp;
-    const float dm_old = a.m_scale[gb], dv_old = a.v_scale[gb], al_old = a.v_base[gb];
+    float *const m_scale = a.m_scale + chunk * NG, *const v_scale = a.v_scale + chunk * NG, *const v_base = a.v_base + chunk * NG;
+    const float dm_old = m_scale[grp], dv_old = v_scale[grp], al_old = v_base[grp];
     const RawPG16<BF16> raw = load_pg16<BF16>(a, ew0, lane);
     const float gscale = (EXT && a.grad_scale) ? *a.grad_scale : 1.0f;
     const Stage16 st(reinterpret_cast<float4 *>(slab + Lay::kOffCol), lane);
@@ -1568,9 +1620,9 @@ __device__ __forceinline__ void step_chunk16(const StepArgs &a, const uint64_t c
     const uint32_t xp_bits = quantile16<G>(vh, col, a.rank_full, dv);
 
     const BlockCodec codec = block_codec<BV, G, L, MDE>(xp_bits, dm, dv, lane, lig, gshift);
-    encode_into_image16<BM, BV, MDE>(a, e0, mh, vh, codec, de_base, img_m, img_v,
+    encode_into_image16<BM, BV, MDE>(a, ew0, lane, mh, vh, codec, de_base, img_m, img_v,
                                      words.wm, words.sm, words.wv, words.sv, mc8, vc8);
-    if (lig == 0) { a.m_scale[gb] = dm; a.v_scale[gb] = dv; a.v_base[gb] = codec.alpha; }
+    if (lig == 0) { m_scale[grp] = dm; v_scale[grp] = dv; v_base[grp] = codec.alpha; }
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     __builtin_amdgcn_wave_barrier();
     words.write_back(a, img_m, img_v, lane);
@@ -1650,12 +1702,19 @@ __device__ __forceinline__ const TensorEntry &find_tensor(const MultiArgs &ma, c
 // arguments is known to be one; behind a pointer out of memory every access was a flat one, which
 // also occupies the LDS path and its counter: 203 million elements in nine tensors, 2-bit/2-bit DE with
 // a bf16 copy, 436 -> 430 us, 4-bit/4-bit AdaBelief 443 -> 429, 2-bit/3-bit fp32 B 64 418 -> 407,
-// blocks of 2048 2-bit/3-bit 469 -> 454.)
+// blocks of 2048 2-bit/3-bit 469 -> 454.)  Like every field of an entry it is the same for the whole wavefront;
+// where the entry is read by vector loads (behind a store or a barrier) the compiler has to be told.
+__device__ __forceinline__ uint64_t uniform64(const uint64_t x)
+{
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)x);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(x >> 32));
+    return lo | (uint64_t)hi << 32;
+}
 template <typename T>
 __device__ __forceinline__ T *global_field(T *const &field)
 {
     typedef __attribute__((address_space(1))) T global_t;
-    return (T *)*reinterpret_cast<global_t *const *>(&field);
+    return (T *)(global_t *)uniform64((uint64_t)field);
 }
 
 __device__ __forceinline__ StepArgs tensor_args(const MultiArgs &ma, const TensorEntry &e)
@@ -1664,7 +1723,7 @@ __device__ __forceinline__ StepArgs tensor_args(const MultiArgs &ma, const Tenso
     a.param = global_field(e.param); a.param_bf16 = global_field(e.param_bf16); a.grad = global_field(e.grad);
     a.m_words = global_field(e.m_words); a.m_scale = global_field(e.m_scale);
     a.v_words = global_field(e.v_words); a.v_scale = global_field(e.v_scale); a.v_base = global_field(e.v_base);
-    a.n = e.n; a.index_offset = e.index_offset;
+    a.n = uniform64(e.n); a.index_offset = uniform64(e.index_offset);
     return a;
 }
 

@@ -319,7 +319,6 @@ __device__ __forceinline__ void step_block(const StepArgs &a, const uint64_t blk
     using Xch = BigExchange<kBigWaves>;
 
     const uint64_t ew0 = blk * kBigBlock + (uint64_t)wave * kIter16;  // first element of this wavefront
-    const uint64_t e0 = ew0 + lane * 16u;                             // first element of this lane
     const uint32_t present = TAIL ? present_in(a.n, blk) : (uint32_t)kBigBlock, before = wave * kIter16;
     const uint32_t here = !TAIL ? (uint32_t)kIter16 : present <= before ? 0u : umin(present - before, (uint32_t)kIter16);  // of this wavefront
     const uint32_t mine = here <= lane * 16u ? 0u : umin(here - lane * 16u, 16u);                                           // of this lane
@@ -410,7 +409,7 @@ __device__ __forceinline__ void step_block(const StepArgs &a, const uint64_t blk
     uint32_t de_base = 0;
     if (kDeTable) de_base = lds_addr(lds_de) - 16u * DeBuckets<BM>::kLo;
     const BlockCodec codec = block_codec<BV, 16, L, MDE>(xp_bits, dm, dv, lane, lig, gshift);
-    encode_into_image16<BM, BV, MDE>(a, e0, mh, vh, codec, de_base, img_m, img_v,
+    encode_into_image16<BM, BV, MDE>(a, ew0, lane, mh, vh, codec, de_base, img_m, img_v,
                                      words.wm, words.sm, words.wv, words.sv, mc8, vc8);
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     __builtin_amdgcn_wave_barrier();
@@ -513,7 +512,7 @@ __device__ __forceinline__ void step_block_quad(const StepArgs &a, const uint64_
     if (kDeTable) de_base = lds_addr(lds_de) - 16u * DeBuckets<BM>::kLo;
     const BlockCodec codec = block_codec<BV, 16, L, MDE>(xp_bits, dm, dv, lane, lig, gshift);
     uint32_t m8, v8;
-    encode_run<BM, BV, MDE, true>(a, e0, mh, vh, ok, codec, de_base, m8, v8);
+    encode_run<BM, BV, MDE, true>(a, XiGroups(a, ew0).word(a, lane), mh, vh, ok, codec, de_base, m8, v8);
     xor_into_image8<BM, BV>(img_m, img_v, words.wm, words.sm, words.wv, words.sv, mc8 ^ m8, vc8 ^ v8);
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     __builtin_amdgcn_wave_barrier();
