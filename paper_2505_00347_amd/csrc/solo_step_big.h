@@ -512,7 +512,9 @@ __device__ __forceinline__ void step_block_quad(const StepArgs &a, const uint64_
     if (kDeTable) de_base = lds_addr(lds_de) - 16u * DeBuckets<BM>::kLo;
     const BlockCodec codec = block_codec<BV, 16, L, MDE>(xp_bits, dm, dv, lane, lig, gshift);
     uint32_t m8, v8;
-    encode_run<BM, BV, MDE, true>(a, XiGroups(a, ew0).word(a, lane), mh, vh, ok, codec, de_base, m8, v8);
+    uint32_t xi_word[1];
+    XiGroups(a, ew0).words<1>(a, lane, xi_word);
+    encode_run<BM, BV, MDE, true>(a, xi_word[0], mh, vh, ok, codec, de_base, m8, v8);
     xor_into_image8<BM, BV>(img_m, img_v, words.wm, words.sm, words.wv, words.sv, mc8 ^ m8, vc8 ^ v8);
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     __builtin_amdgcn_wave_barrier();
