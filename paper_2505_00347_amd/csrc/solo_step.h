@@ -66,7 +66,7 @@ constexpr int kIter16 = 1024;      // elements of a chunk with 16 per lane
 constexpr int kWaves = 4;          // wavefronts per workgroup
 constexpr int kMinWaves = 5;       // wavefronts per SIMD that the register allocator must leave room for, 8 elements per lane
 constexpr int kMinWaves16 = 4;     // and 16 per lane (81-96 registers, i.e. five, in most formats; forcing five spills in the others and gains nothing)
-constexpr int kColStride16 = 18;   // words per lane of the sorted columns (16 keys, +inf, pad; written 8 bytes at a time)
+constexpr int kColStride16 = 18;   // words per lane of the sorted columns (16 keys, two +inf; written 8 bytes at a time)
 constexpr float kTiny = 0x1p-100f; // block maxima below this are stored as 0
 constexpr float kRhoMin = 0x1p-64f;
 constexpr uint32_t kInfBits = 0x7F800000u;
@@ -214,9 +214,11 @@ __device__ __forceinline__ uint32_t group_bits(uint64_t ballot, uint32_t lane, u
     return (half >> gshift) & gmask;
 }
 
+// (The larger key is what the exclusive or of all three leaves: two cycles instead of the four of a second comparison,
+// whose shorter chain makes no difference where a launch is all latency.)
 __device__ __forceinline__ void cswap(uint32_t &a, uint32_t &b)
 {
-    const uint32_t lo = umin(a, b), hi = umax(a, b);
+    const uint32_t lo = umin(a, b), hi = __builtin_amdgcn_bitop3_b32(a, b, lo, 0x96);
     a = lo; b = hi;
 }
 
@@ -605,32 +607,73 @@ __device__ __forceinline__ uint64_t lowest_holders(uint64_t h)
     return h & (~h + kOnes);
 }
 
-// The r-th smallest key of every group of G lanes (full blocks).  Each lane has parked its sorted
-// column at col_addr (the +inf sentinel behind it) and passes its two smallest keys.  A round:
-// group minimum of the heads by DPP; the lowest lane that holds it pops its column, so exactly one
-// key leaves a group per round and the r-th minimum is the order statistic, multiplicities
-// included.  The pop is written out (the popping lanes run under their own exec mask), so a round
-// is straight-line code with the loop's back edge as its only branch.  A lane keeps the key behind
-// its head in a register: a pop moves it up and fetches the one after it, whose LDS latency then
-// lies outside the chain of rounds.  (All 64 lanes of the wavefront are active here.)
+// The rank-th smallest key of every group of G = 4 or 8 lanes (full blocks).  Each lane has parked its
+// sorted column at `haddr` (+inf behind it) and passes its four smallest keys.  A round:
+// group minimum of the heads by DPP; the lowest lane that holds it (lowest_holders()) pops its column, so
+// exactly one key leaves a group per round and the last minimum is the order statistic, multiplicities
+// included.  While more than G + 1 keys are asked for, a round pops two at once: the lane whose second
+// key is the smallest drops both.  In front of that key there are at most its own first one and
+// one of every other lane, so both are among the first G + 1.  (Rank 13 of 128: 10 rounds instead of 12; 39: 23 instead of
+// 38.)  The keys behind the head are fetched a round ahead, so that their LDS latency lies outside the chain.
+// One block of assembly, because a fetch is under way across the back edges: the registers it lands in are
+// the block's own until its last wait.  The popping lanes run under their own exec mask; all 64 lanes are
+// active in front of the block and behind it.  (A DPP operand needs two instructions between
+// the vector instruction that writes it and the one that reads it.)
 template <int G>
-__device__ __forceinline__ uint32_t extract_rth(uint32_t head, uint32_t behind, uint32_t haddr, uint32_t rank)
+__device__ __forceinline__ uint32_t extract_rth(uint32_t head, uint32_t behind, uint32_t next, uint32_t next2,
+                                                uint32_t haddr, uint32_t rank)
 {
-    for (uint32_t k = 1; k < rank; ++k) {
-        const uint32_t mn = group_reduce<G>(head, UMin());
-        const uint64_t pop = lowest_holders<G>(__builtin_amdgcn_ballot_w64(head == mn));
-        asm volatile("s_mov_b64 exec, %[pop]\n\t"
-                     "s_waitcnt lgkmcnt(0)\n\t"
-                     "v_mov_b32_e32 %[head], %[behind]\n\t"
-                     "ds_read_b32 %[behind], %[haddr] offset:8\n\t"
-                     "v_add_u32_e32 %[haddr], 4, %[haddr]\n\t"
-                     "s_mov_b64 exec, -1"
-                     : [head] "+v"(head), [behind] "+v"(behind), [haddr] "+v"(haddr)
-                     : [pop] "s"(pop)
-                     : "memory");
-    }
-    // the last fetch may still be in flight: its register is free only once it has landed
-    asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(behind) : : "memory");
+    static_assert(G == 4 || G == 8, "group of 4 or 8 lanes");
+    uint32_t mn, left = (uint32_t)__builtin_amdgcn_readfirstlane((int)rank);
+#define SOLO_DPP(D_, S_, CTRL_) "v_min_u32_dpp " D_ ", " S_ ", " S_ " " CTRL_ " row_mask:0xf bank_mask:0xf\n\t"
+#define SOLO_MIN4(X_) SOLO_DPP("%[mn]", X_, "quad_perm:[1,0,3,2]") "s_nop 1\n\t" SOLO_DPP("%[mn]", "%[mn]", "quad_perm:[2,3,0,1]")
+#define SOLO_MIN8(X_) SOLO_MIN4(X_) "s_nop 1\n\t" SOLO_DPP("%[mn]", "%[mn]", "row_half_mirror")
+    // exec: of every group's lanes that hold the minimum the lowest (the literals: kOnes - 1 in two halves)
+#define SOLO_HOLDERS(X_, LOW_, HIGH_) "v_cmp_eq_u32_e32 vcc, " X_ ", %[mn]\n\t"                        \
+        "s_sub_u32 exec_lo, " LOW_ ", vcc_lo\n\ts_subb_u32 exec_hi, " HIGH_ ", vcc_hi\n\ts_and_b64 exec, exec, vcc\n\t"
+#define SOLO_EXTRACT(MIN_, LOW_, HIGH_)                                                                   \
+    asm volatile("s_sub_u32 %[left], %[left], %[more]\n\t"          /* ranks behind the first G + 1 */    \
+                 "s_cmp_lt_i32 %[left], 1\n\t"                                                           \
+                 "s_cbranch_scc1 .Lone%=\n"                                                             \
+                 ".Lpair%=:\n\t"                                                                        \
+                 MIN_("%[behind]") SOLO_HOLDERS("%[behind]", LOW_, HIGH_)                               \
+                 "s_waitcnt lgkmcnt(0)\n\t"                                                             \
+                 "v_mov_b32_e32 %[head], %[next]\n\t"                                                   \
+                 "v_mov_b32_e32 %[behind], %[next2]\n\t"                                                \
+                 "ds_read_b32 %[next], %[haddr] offset:16\n\t"                                          \
+                 "ds_read_b32 %[next2], %[haddr] offset:20\n\t"                                         \
+                 "v_add_u32_e32 %[haddr], 8, %[haddr]\n\t"                                              \
+                 "s_mov_b64 exec, -1\n\t"                                                               \
+                 "s_sub_u32 %[left], %[left], 2\n\t"                                                    \
+                 "s_cmp_gt_i32 %[left], 0\n\t"                                                          \
+                 "s_cbranch_scc1 .Lpair%=\n"                                                            \
+                 ".Lone%=:\n\t"                                                                         \
+                 "s_add_u32 %[left], %[left], %[more]\n\t"                                              \
+                 "s_sub_u32 %[left], %[left], 2\n\t"                /* rounds after the first, borrow: none at all */ \
+                 "s_cbranch_scc1 .Ldone%=\n"                                                            \
+                 ".Lround%=:\n\t"                                                                       \
+                 MIN_("%[head]") SOLO_HOLDERS("%[head]", LOW_, HIGH_)                                   \
+                 "s_waitcnt lgkmcnt(0)\n\t"                                                             \
+                 "v_mov_b32_e32 %[head], %[behind]\n\t"                                                 \
+                 "ds_read_b32 %[behind], %[haddr] offset:8\n\t"                                         \
+                 "v_add_u32_e32 %[haddr], 4, %[haddr]\n\t"                                              \
+                 "s_mov_b64 exec, -1\n\t"                                                               \
+                 "s_sub_u32 %[left], %[left], 1\n\t"                                                    \
+                 "s_cbranch_scc0 .Lround%=\n"                                                           \
+                 ".Ldone%=:\n\t"                                                                        \
+                 "s_waitcnt lgkmcnt(0)\n\t"                                                             \
+                 "s_nop 1"                                                                              \
+                 : [head] "+v"(head), [behind] "+v"(behind), [next] "+v"(next), [next2] "+v"(next2),    \
+                   [haddr] "+v"(haddr), [left] "+s"(left), [mn] "=&v"(mn)                               \
+                 : [more] "n"(G + 1)                                                                    \
+                 : "vcc", "scc", "memory")
+    if (G == 8) SOLO_EXTRACT(SOLO_MIN8, "0x1010100", "0x1010101");
+    else        SOLO_EXTRACT(SOLO_MIN4, "0x11111110", "0x11111111");
+#undef SOLO_EXTRACT
+#undef SOLO_HOLDERS
+#undef SOLO_MIN8
+#undef SOLO_MIN4
+#undef SOLO_DPP
     return group_reduce<G>(head, UMin());
 }
 
@@ -1241,15 +1284,23 @@ __device__ __forceinline__ void step_chunk8(const StepArgs &a, const uint64_t ch
     words.write_back(a, img_m, img_v, lane);
 }
 
-// Sixteen keys: two eight-sorts and Batcher's odd-even merge of the halves (25 exchanges).
-__device__ __forceinline__ void sort16(uint32_t (&k)[16])
+// Sixteen keys, two sorted halves: the eight smallest in order (the smaller of a and b's mirror image are a
+// bitonic sequence).
+__device__ __forceinline__ void lower_half(const uint32_t (&a)[8], const uint32_t (&b)[8], uint32_t (&k)[8])
 {
-    uint32_t lo[8], hi[8];
 #pragma unroll
-    for (int i = 0; i < 8; ++i) { lo[i] = k[i]; hi[i] = k[i + 8]; }
-    sort8(lo); sort8(hi);
+    for (int i = 0; i < 8; ++i) k[i] = umin(a[i], b[7 - i]);
 #pragma unroll
-    for (int i = 0; i < 8; ++i) { k[i] = lo[i]; k[i + 8] = hi[i]; }
+    for (int w = 4; w >= 1; w /= 2)
+#pragma unroll
+        for (int i = 0; i < 8; ++i) if ((i & w) == 0) cswap(k[i], k[i + w]);
+}
+
+// The merge of all sixteen: Batcher's odd-even merge of the halves (25 exchanges).
+__device__ __forceinline__ void merge16(const uint32_t (&a)[8], const uint32_t (&b)[8], uint32_t (&k)[16])
+{
+#pragma unroll
+    for (int i = 0; i < 8; ++i) { k[i] = a[i]; k[i + 8] = b[i]; }
 #pragma unroll
     for (int i = 0; i < 8; ++i) cswap(k[i], k[i + 8]);
 #pragma unroll
@@ -1260,21 +1311,48 @@ __device__ __forceinline__ void sort16(uint32_t (&k)[16])
     for (int i = 1; i < 15; i += 2) cswap(k[i], k[i + 1]);
 }
 
+// Up to which rank the eight smallest of a lane's 16 values are enough but for one wavefront in a hundred
+// (G lanes; the ranks in front of it fall on the lanes at random: at rank 13 of 128 one in a thousand, at 7 of 64 none).
+template <int G>
+constexpr uint32_t low_rank() { return G == 8 ? 16u : 10u; }
+
 // The largest (dv, values below kTiny as 0) and the rank-th smallest (returned) v^ of every group of G
 // lanes that hold 16 of them each.  `col`: the lane's column in LDS.
+// Small ranks: the columns hold the eight smallest of every lane only, which takes a sixth off the sorting.  What is
+// selected from those is the answer unless some lane's eighth is smaller than it, as leaving keys out can only
+// raise it; then everything is done again with full columns.  (With pairs popped at once (extract_rth()) and exclusive
+// ors in the exchanges, against full columns and one key a round, us: 2^26 elements 2-bit/3-bit bf16 133.6 -> 120.0, at
+// p = 0.3, whose columns are full, 148.5 -> 127.7, 2-bit/2-bit B 64 at p = 0.3 132.5 -> 124.1; the 7B shapes 12843 -> 12586.)
 template <int G>
 __device__ __forceinline__ uint32_t quantile16(const float (&vh)[16], uint32_t *const col, const uint32_t rank, float &dv)
 {
-    uint32_t key[16];                              // (non-negative floats order like their bit patterns)
+    uint32_t a[8], b[8];                           // (non-negative floats order like their bit patterns)
 #pragma unroll
-    for (int j = 0; j < 16; ++j) key[j] = f2u(vh[j]);
-    sort16(key);
-    dv = u2f(group_reduce<G>(key[15], UMax()));
+    for (int j = 0; j < 8; ++j) { a[j] = f2u(vh[j]); b[j] = f2u(vh[8 + j]); }
+    sort8(a);
+    sort8(b);
+    dv = u2f(group_reduce<G>(umax(a[7], b[7]), UMax()));
     if (dv < kTiny) dv = 0.0f;
-    col[16] = kInfBits;
+    uint32_t xp;
+    if (__builtin_expect(rank <= low_rank<G>(), 1)) {
+        uint32_t k[8];
+        lower_half(a, b, k);
 #pragma unroll
-    for (int c = 0; c < 8; ++c) *reinterpret_cast<uint2 *>(col + 2 * c) = make_uint2(key[2 * c], key[2 * c + 1]);
-    return extract_rth<G>(key[0], key[1], lds_addr(col), rank);
+        for (int c = 0; c < 4; ++c) *reinterpret_cast<uint2 *>(col + 2 * c) = make_uint2(k[2 * c], k[2 * c + 1]);
+        *reinterpret_cast<uint2 *>(col + 8) = *reinterpret_cast<uint2 *>(col + 10) = make_uint2(kInfBits, kInfBits);
+        xp = extract_rth<G>(k[0], k[1], k[2], k[3], lds_addr(col), rank);
+        if (__builtin_expect(__builtin_amdgcn_ballot_w64(k[7] < xp) == 0, 1)) return xp;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) { a[j] = f2u(vh[j]); b[j] = f2u(vh[8 + j]); }
+        sort8(a);
+        sort8(b);
+    }
+    uint32_t k[16];
+    merge16(a, b, k);
+#pragma unroll
+    for (int c = 0; c < 8; ++c) *reinterpret_cast<uint2 *>(col + 2 * c) = make_uint2(k[2 * c], k[2 * c + 1]);
+    *reinterpret_cast<uint2 *>(col + 16) = make_uint2(kInfBits, kInfBits);
+    return extract_rth<G>(k[0], k[1], k[2], k[3], lds_addr(col), rank);
 }
 
 // Parameters and gradients of one lane and one 1024-element chunk, in the
