@@ -94,7 +94,7 @@ constexpr uint32_t kNoKey = 0xFFFFFFFFu;       // of an element that does not ex
 // the rank-th key, by one wavefront: a lane sums the 32 words of its own 8 bins (128-bit reads in an
 // order that starts neighbouring lanes in different banks), a prefix sum over the wavefront names
 // the lane whose bins hold the rank, and that lane's words are read once more, one per lane, for a
-// second prefix sum that names the bin.  Returns the bin, its rank and its count.
+// second prefix sum that names the bin.  Returns the bin, its rank and its count (0: the histogram holds fewer keys).
 __device__ __forceinline__ uint32_t find_bin(const uint32_t *const h, const uint32_t half, uint32_t &rank, uint32_t &count,
                                              const uint32_t lane)
 {
@@ -106,6 +106,7 @@ __device__ __forceinline__ uint32_t find_bin(const uint32_t *const h, const uint
         acc += (c4.x + c4.y) + (c4.z + c4.w);
     }
     const uint32_t s = (acc >> half) & 0xFFFFu, incl = wave_inclusive_sum(s);
+    if (rank > (uint32_t)__builtin_amdgcn_readlane((int)incl, 63)) { count = 0; return 0; }
     const uint32_t sel = (uint32_t)__builtin_ctzll(__builtin_amdgcn_ballot_w64(rank <= incl) | (1ull << 63));
     rank -= (uint32_t)__builtin_amdgcn_readlane((int)(incl - s), (int)sel);
     const uint32_t in_row = wave_inclusive_sum((h[32u * sel + (lane & 31u)] >> half) & 0xFFFFu);   // (lanes 0-31 matter)
@@ -116,33 +117,39 @@ __device__ __forceinline__ uint32_t find_bin(const uint32_t *const h, const uint
     return 8u * sel + bin;
 }
 
+// Counts a key in the histogram where `at16`, sixteen times its bin and some bits below, lies inside of it.  (All lanes
+// are active.  Written out because the compiler branches around an atomic under a condition.)
+__device__ __forceinline__ void count_key(const uint32_t at16, const uint32_t counters, const uint32_t one)
+{
+    asm volatile("v_cmp_gt_u32_e32 vcc, 0x2000, %0\n\ts_mov_b64 exec, vcc\n\tds_add_u32 %1, %2\n\ts_mov_b64 exec, -1"
+                 : : "v"(at16), "v"(counters + (at16 & 0x1FF0u)), "v"(one) : "vcc", "memory");
+}
+
 // One pass of the selection: the keys in the range are counted by (key - base) >> shift, one barrier,
 // one of the two wavefronts (they take turns) finds the bin of the rank and leaves the new range in
 // LDS, a second barrier (it costs less than both wavefronts summing the histogram for themselves).
-// FIRST: every key counts, those below the range in its first bin, and what only a non-finite input
-// can put above it in the last one; `absent`: but for those of elements that do not exist (kNoKey).
+// FIRST: 512 bins of 2^shift patterns from at.base on; keys below it count in the first bin, keys behind the last
+// one (and kNoKey) not at all: at.count = 0 says that the rank lies there, and at.rank stays.
 template <int NK, bool FIRST>
 __device__ __forceinline__ void narrow(Narrowed &at, const uint32_t (&key)[NK], const uint32_t lane, const bool mine,
-                                       uint32_t *const h, const uint32_t half, uint32_t *const res, const bool absent = false)
+                                       uint32_t *const h, const uint32_t half, uint32_t *const res, const uint32_t first_shift = 0)
 {
     const uint32_t wide = 32u - (uint32_t)__builtin_clz(at.len - 1u);          // (len > 1)
-    const uint32_t shift = FIRST ? 19u : wide > 9u ? wide - 9u : 0u, one = 1u << half;
-    const uint32_t counter = 4u * (lane & 3u);
-    char *const bytes = reinterpret_cast<char *>(h);
-    if (FIRST && __builtin_expect(absent, 0)) {
+    const uint32_t shift = FIRST ? first_shift : wide > 9u ? wide - 9u : 0u, one = 1u << half;
+    const uint32_t counters = lds_addr(h) + 4u * (lane & 3u);
+    if (FIRST) {
+        const uint32_t base = in_vector(at.base), by = in_vector(shift - 4u);
 #pragma unroll
-        for (int j = 0; j < NK; ++j) {
-            const uint32_t bin = umin(__builtin_elementwise_sub_sat(key[j], at.base) >> shift, 511u);
-            if (key[j] != kNoKey) atomicAdd(reinterpret_cast<uint32_t *>(bytes + ((bin << 4) | counter)), one);
-        }
+        for (int j = 0; j < NK; ++j) count_key(__builtin_elementwise_sub_sat(key[j], base) >> by, counters, one);
     } else {
+        char *const bytes = reinterpret_cast<char *>(h);
 #pragma unroll
         for (int j = 0; j < NK; ++j) {
-            const uint32_t d = FIRST ? __builtin_elementwise_sub_sat(key[j], at.base) : key[j] - at.base;
-            const uint32_t bin = FIRST ? umin(d >> shift, 511u) : d >> shift;
-            if (FIRST || d < at.len) atomicAdd(reinterpret_cast<uint32_t *>(bytes + ((bin << 4) | counter)), one);
+            const uint32_t d = key[j] - at.base;
+            if (d < at.len) atomicAdd(reinterpret_cast<uint32_t *>(bytes + ((d >> shift) << 4 | 4u * (lane & 3u))), one);
         }
     }
+    asm volatile("s_waitcnt lgkmcnt(0)" : : : "memory");        // (the compiler does not know of count_key's)
     __syncthreads();
     if (mine) {
         uint32_t rank = at.rank, count;
@@ -151,7 +158,7 @@ __device__ __forceinline__ void narrow(Narrowed &at, const uint32_t (&key)[NK], 
         if (FIRST && bin == 0) {                   // everything below the first bin's end
             base = 0;
         } else {
-            const uint32_t begin = bin << shift, left = at.len - begin;
+            const uint32_t begin = bin << shift, left = FIRST ? 1u << shift : at.len - begin;
             base += begin;
             len = left < (1u << shift) ? left : 1u << shift;
         }
@@ -165,10 +172,12 @@ __device__ __forceinline__ void narrow(Narrowed &at, const uint32_t (&key)[NK], 
         if (lane == 0) { res[0] = base; res[1] = len; res[2] = rank; res[3] = count; if (FIRST) res[4] = guess; }
     }
     __syncthreads();
+    const uint32_t count = (uint32_t)__builtin_amdgcn_readfirstlane((int)res[3]);
+    at.count = count;
+    if (FIRST && count == 0) return;
     at.base = (uint32_t)__builtin_amdgcn_readfirstlane((int)res[0]);
     at.len = (uint32_t)__builtin_amdgcn_readfirstlane((int)res[1]);
     at.rank = (uint32_t)__builtin_amdgcn_readfirstlane((int)res[2]);
-    at.count = (uint32_t)__builtin_amdgcn_readfirstlane((int)res[3]);
     if (FIRST) at.guess = (uint32_t)__builtin_amdgcn_readfirstlane((int)res[4]);
 }
 
@@ -205,42 +214,65 @@ __device__ __forceinline__ bool try_guess(Narrowed &at, const uint32_t (&key)[NK
     return false;
 }
 
+// The largest v^ of the block, out of the exchange (behind a barrier).
+template <int W>
+__device__ __forceinline__ uint32_t largest_key(const uint32_t *const xch)
+{
+    uint32_t k = 0;
+#pragma unroll
+    for (int w = 0; w < W; ++w) k = umax(k, xch[BigExchange<W>::kMaxV + w]);
+    return (uint32_t)__builtin_amdgcn_readfirstlane((int)k);
+}
+
 // The rank-th smallest (1-based, uniform over the workgroup) of the `present` keys that the threads of
-// the workgroup hold, NK each (W wavefronts; kNoKey: no key): bit patterns of non-negative floats, none
-// above kmax.  The first pass counts sixteenths of an octave below the maximum (2^28 consecutive
-// patterns in 512 bins), the next ones 512ths of the bin that holds the rank.  As soon as at most
-// kFewKeys are left, every wavefront compares those with each other instead: after two passes on
-// scattered values and on the clusters of a trained state.  Elements without a gradient share the
+// the workgroup hold, NK each (W wavefronts; kNoKey: no key): bit patterns of non-negative floats.
+// `floor`: a bound below all keys that the old state gives (0: none), beta2 times its smallest level.  Of a
+// state that has been trained for a while the elements with the last code, a little more than the quantile's share,
+// lie right above it, moved up by (1 - beta2) g^2.  So the first pass counts the quarter of an octave above the
+// floor in 512 bins; seven of eight keys are above it and cost no LDS access.  Where the rank lies higher, or without
+// a floor, a pass over sixteenths of an octave below the maximum follows (2^28 consecutive
+// patterns in 512 bins); the next ones count 512ths of the bin that holds the rank.  As soon as at most
+// kFewKeys are left, every wavefront compares those with each other instead: mostly after one pass on a trained state,
+// after two on scattered values.  Elements without a gradient share the
 // few decoded values: then, after the first pass, one of the keys that are left is tried as it is.
 // A rank below the first pass's range (28 octaves under the maximum, or zeros) starts over from 0.
-// (Against four fixed passes over 8 + 8 + 8 + 7 bits, the first of which only told binades apart, on
-// 2^26 elements of 2-bit/3-bit codes: 163.6 -> 153.7 us, with nine of ten gradients at zero
-// 203 -> 140 us, all gradients alike 236 -> 155 us.  The kernel issues 62 vector instructions per
-// parameter, four more than blocks of 128.  2-bit v at p = 0.3 narrows slowly: 1000 to 5000 blocks take up to
-// 10 % longer than with the fixed passes.)
-template <int NK, int W>
-__device__ __forceinline__ uint32_t select_rank(const uint32_t (&key)[NK], const uint32_t kmax, const uint32_t rank,
+// BARRIER: whether the exchange's maxima still need one.
+template <int NK, int W, bool BARRIER>
+__device__ __forceinline__ uint32_t select_rank(const uint32_t (&key)[NK], const uint32_t floor, const uint32_t rank,
                                                 const uint32_t present, const uint32_t lane, const uint32_t wave,
                                                 uint32_t *const work, uint32_t *const xch)
 {
     using Xch = BigExchange<W>;
-    constexpr uint32_t kReach = 1u << 28;
+    constexpr uint32_t kReach = 1u << 28, kFine = 12u, kCoarse = 19u, kBelow = 8u << kFine;   // (a few bins of room for rounding)
     uint32_t *const res = xch + Xch::kPass;
     Narrowed at = {0u, 1u << 31, rank, present, kNoGuess};
+    bool lower_only = true;                        // of the histogram's words, only the lower halves have been used
     if (__builtin_expect(present > kFewKeys, 1)) {
-        at.base = kmax >= kReach ? kmax - (kReach - 1u) : 0u;
-        at.len = kReach;
-        narrow<NK, true>(at, key, lane, wave == 0, work, 0, res, present < (uint32_t)kBigBlock);
+        uint32_t shift = kFine;
+        at.base = floor - umin(floor, kBelow);
+        if (BARRIER && floor == 0) __syncthreads();
+        for (;;) {
+            if (floor == 0 || shift == kCoarse) {
+                const uint32_t kmax = largest_key<W>(xch);
+                at.base = umax(floor == 0 ? 0u : at.base + (512u << kFine), kmax >= kReach ? kmax - (kReach - 1u) : 0u);
+                shift = kCoarse;
+            }
+            narrow<NK, true>(at, key, lane, wave == 0, work, lower_only ? 0u : 16u, res, shift);
+            if (at.count != 0 || shift == kCoarse) break;          // (no key left: only what is not finite)
+            shift = kCoarse;
+            lower_only = false;
+        }
         if (at.guess != kNoGuess && try_guess<NK, W>(at, key, lane, wave, xch + Xch::kCounts)) return at.guess;
     }
 #pragma unroll 1
-    for (uint32_t pass = 1; at.count > kFewKeys && at.len > 1u; ++pass) {
-        if (pass >= 2) {                           // both halves have been used
+    for (uint32_t turn = 1; at.count > kFewKeys && at.len > 1u; ++turn) {
+        if (!lower_only) {                         // both halves have been used
             uint4 *const z = reinterpret_cast<uint4 *>(work);
             for (uint32_t i = wave * 64u + lane; i < 512u; i += W * 64) z[i] = make_uint4(0, 0, 0, 0);
             __syncthreads();
         }
-        narrow<NK, false>(at, key, lane, wave == (pass & 1u), work, pass == 1 ? 16u : 0u, res + 5 * (pass & 1u));
+        narrow<NK, false>(at, key, lane, wave == (turn & 1u), work, lower_only ? 16u : 0u, res + 5 * (turn & 1u));
+        lower_only = false;
     }
     if (at.len == 1u) return at.base;
     // few keys: every wavefront packs its own into LDS, then each lane compares one with all of
@@ -251,6 +283,7 @@ __device__ __forceinline__ uint32_t select_rank(const uint32_t (&key)[NK], const
     for (int j = 0; j < NK; ++j) {
         const bool in = key[j] - at.base < at.len;
         const uint64_t who = __builtin_amdgcn_ballot_w64(in);
+        if (who == 0) continue;
         const uint32_t to = __builtin_amdgcn_mbcnt_hi((uint32_t)(who >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)who, mine));
         if (in) list[to & (kFewKeys - 1u)] = key[j];
         mine += (uint32_t)__builtin_popcountll(who);
@@ -270,6 +303,15 @@ __device__ __forceinline__ uint32_t select_rank(const uint32_t (&key)[NK], const
     for (uint32_t i = 0; i < at.count; ++i)
         below += (uint32_t)__builtin_amdgcn_readlane((int)my, (int)i) < my ? 1u : 0u;
     return wave_max(lane < at.count && below < at.rank ? my : 0u);
+}
+
+// What the old state's smallest level becomes without a gradient, in the steps of ema_param(): no key is
+// smaller (but by rounding, where the base is next to 1).  0 for a block without a state.
+template <int BV, bool EXT>
+__device__ __forceinline__ uint32_t key_floor(const StepArgs &a, const float *const my_tv)
+{
+    const float low = my_tv[(1 << BV) - 1], key = a.beta2 * low;
+    return (uint32_t)__builtin_amdgcn_readfirstlane((int)(low > 0.0f ? f2u(EXT ? key + a.eps_state : key) : 0u));
 }
 
 // The DE bucket table of a workgroup: copied from constant memory first.
@@ -353,6 +395,8 @@ __device__ __forceinline__ void step_block(const StepArgs &a, const uint64_t blk
         }
     }
 
+    const uint32_t floor = key_floor<BV, EXT>(a, my_tv);
+
     // ---- coalesced layout -> 16 consecutive elements per lane
     float p[16], g[16];
     lane_layout16<BF16>(raw, st, p, g);
@@ -392,17 +436,15 @@ __device__ __forceinline__ void step_block(const StepArgs &a, const uint64_t blk
         if (lane == 0) { xch[Xch::kMaxM + wave] = wm_max; xch[Xch::kMaxV + wave] = wv_max; }
     }
     __syncthreads();
-    float dm = u2f(umax(xch[Xch::kMaxM], xch[Xch::kMaxM + 1]));
-    const uint32_t kmax = (uint32_t)__builtin_amdgcn_readfirstlane((int)umax(xch[Xch::kMaxV], xch[Xch::kMaxV + 1]));
-    float dv = u2f(kmax);
-    if (dm < kTiny) dm = 0.0f;
-    if (dv < kTiny) dv = 0.0f;
 
     // ---- the r-th smallest v^ of the block
     uint32_t key[16];
 #pragma unroll
     for (int j = 0; j < 16; ++j) key[j] = f2u(vh[j]);
-    const uint32_t xp_bits = select_rank<16, kBigWaves>(key, kmax, rank_among(a, present), present, lane, wave, work, xch);
+    const uint32_t xp_bits = select_rank<16, kBigWaves, false>(key, floor, rank_among(a, present), present, lane, wave, work, xch);
+    float dm = u2f(umax(xch[Xch::kMaxM], xch[Xch::kMaxM + 1])), dv = u2f(largest_key<kBigWaves>(xch));
+    if (dm < kTiny) dm = 0.0f;
+    if (dv < kTiny) dv = 0.0f;
 
     // ---- encoder constants (every 16 lanes for themselves), codes, the wavefront's words
     const uint32_t lig = lane & 15u, gshift = lane & 16u;
@@ -474,6 +516,8 @@ __device__ __forceinline__ void step_block_quad(const StepArgs &a, const uint64_
     wave_lds_sync();
     uint32_t mc8, vc8;
     words.codes(img_m, img_v, mc8, vc8);
+    const uint32_t floor = key_floor<BV, EXT>(a, my_tv);
+    __syncthreads();                               // (the histogram is cleared)
 
     // ---- dequantize (table look-up), EMA, parameter
     float p[8], g[8];
@@ -487,24 +531,21 @@ __device__ __forceinline__ void step_block_quad(const StepArgs &a, const uint64_
     ema_param<8, BM, BV, EXT, true, true>(a, tm_addr, tv_addr, &mc8, &vc8, ok, p, g, mh, vh, m_absmax, v_max);
     store_params8<EXT, true>(a, e0, ok[7], ok, p);
 
-    // ---- block maxima over the four wavefronts
+    // ---- block maxima over the four wavefronts (read behind the selection's barriers)
     {
         const uint32_t wm_max = wave_max(f2u(m_absmax)), wv_max = wave_max(f2u(v_max));
         if (lane == 0) { xch[Xch::kMaxM + wave] = wm_max; xch[Xch::kMaxV + wave] = wv_max; }
     }
-    __syncthreads();
-    float dm = u2f(umax(umax(xch[Xch::kMaxM], xch[Xch::kMaxM + 1]), umax(xch[Xch::kMaxM + 2], xch[Xch::kMaxM + 3])));
-    const uint32_t kmax = (uint32_t)__builtin_amdgcn_readfirstlane(
-        (int)umax(umax(xch[Xch::kMaxV], xch[Xch::kMaxV + 1]), umax(xch[Xch::kMaxV + 2], xch[Xch::kMaxV + 3])));
-    float dv = u2f(kmax);
-    if (dm < kTiny) dm = 0.0f;
-    if (dv < kTiny) dv = 0.0f;
 
     // ---- the r-th smallest v^ of the block
     uint32_t key[8];
 #pragma unroll
     for (int j = 0; j < 8; ++j) key[j] = ok[j] ? f2u(vh[j]) : kNoKey;
-    const uint32_t xp_bits = select_rank<8, kQuadWaves>(key, kmax, rank_among(a, present), present, lane, wave, work, xch);
+    const uint32_t xp_bits = select_rank<8, kQuadWaves, true>(key, floor, rank_among(a, present), present, lane, wave, work, xch);
+    float dm = u2f(umax(umax(xch[Xch::kMaxM], xch[Xch::kMaxM + 1]), umax(xch[Xch::kMaxM + 2], xch[Xch::kMaxM + 3])));
+    float dv = u2f(largest_key<kQuadWaves>(xch));
+    if (dm < kTiny) dm = 0.0f;
+    if (dv < kTiny) dv = 0.0f;
 
     // ---- encoder constants (every 16 lanes for themselves), codes, the wavefront's words
     const uint32_t lig = lane & 15u, gshift = lane & 16u;
