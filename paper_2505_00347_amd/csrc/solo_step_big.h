@@ -306,12 +306,14 @@ __device__ __forceinline__ uint32_t select_rank(const uint32_t (&key)[NK], const
 }
 
 // What the old state's smallest level becomes without a gradient, in the steps of ema_param(): no key is
-// smaller (but by rounding, where the base is next to 1).  0 for a block without a state.
+// smaller (but by rounding, where the base is next to 1).  0 for a block without a state, and for a beta2 so small
+// that the gradients carry the quantile out of the first pass's quarter octave: 2^25 elements, 2-bit/3-bit bf16, with | without
+// the floor, us: beta2 0.9 70 | 83, 0.85 85 | 87, 0.8 92 | 77, 0.5 80 | 74.
 template <int BV, bool EXT>
 __device__ __forceinline__ uint32_t key_floor(const StepArgs &a, const float *const my_tv)
 {
     const float low = my_tv[(1 << BV) - 1], key = a.beta2 * low;
-    return (uint32_t)__builtin_amdgcn_readfirstlane((int)(low > 0.0f ? f2u(EXT ? key + a.eps_state : key) : 0u));
+    return (uint32_t)__builtin_amdgcn_readfirstlane((int)(low > 0.0f && a.beta2 >= 0.85f ? f2u(EXT ? key + a.eps_state : key) : 0u));
 }
 
 // The DE bucket table of a workgroup: copied from constant memory first.
