@@ -59,9 +59,9 @@ def step_kernel_name(w, n, mp, launch):
     if rank > 24:
         up_to = 1 << 19
     elif bf16:
-        up_to = 5 << 18 if mp else 3 << 19 if rank > 16 else 3 << 20
+        up_to = 5 << 18 if mp else 3 << 19
     else:
-        up_to = 4 << 20 if mp else 6 << 20
+        up_to = 9 << 19
     return f"solo::chunk{8 if n <= up_to else 16}_kernel"
 
 

@@ -563,33 +563,33 @@ constexpr int de_words() { return MDE && BM >= 3 ? 4 * DeBuckets<BM>::N : 16; }
 // Whether a flat buffer runs 8 elements per lane, for a quantile of rank `rank` in a full block;
 // `copy`: a bf16 copy of the parameters is written.  Measured on MI355X (1024 SIMDs) over six states in
 // turn, us per launch, 8 | 16 per lane:
-//   elements / 2^18                2             3             4             6             8             12            16            20            24            28
-//   4-bit/4-bit fp32               5.05 | 5.79   6.06 | 5.99   6.57 | 6.16   7.91 | 8.67   9.41 | 9.74   11.6 | 12.2   14.2 | 14.7   16.9 | 17.0   20.0 | 19.7   23.7 | 21.9
-//   3-bit/3-bit fp32               5.74 | 6.51   6.52 | 6.64   7.42 | 6.87   8.44 | 9.43   9.59 | 10.5   12.0 | 13.0   14.6 | 15.1   16.7 | 17.1   19.7 | 20.3   22.0 | 22.2
-//   3-bit/4-bit fp32, B 64         4.73 | 5.98   5.93 | 6.13   6.37 | 6.38   7.80 | 9.00   9.14 | 9.95   11.4 | 12.6   13.7 | 14.9   16.8 | 17.1   19.6 | 20.1   22.8 | 21.9
-//     rank 20                      5.84 | 6.61   6.64 | 6.76   7.15 | 7.02   8.67 | 9.71   10.1 | 10.7   12.6 | 13.6   15.6 | 16.0   18.1 | 18.0   21.1 | 21.1   23.7 | 23.2
-//   4-bit/4-bit fp32, copy         5.54 | 5.99   6.36 | 6.20   7.13 | 6.52   8.75 | 9.64   10.1 | 10.5   12.5 | 13.8   15.7 | 16.5   19.4 | 18.9   23.2 | 22.1   26.7 | 24.7
-//   4-bit/4-bit fp32, rank 39      7.15 | 7.17   7.85 | 7.33   8.66 | 7.52   10.2 | 10.1   11.9 | 11.3   15.1 | 14.2
-//   2-bit/3-bit bf16               5.52 | 6.24   5.90 | 6.41   6.77 | 6.59   7.92 | 8.34   9.09 | 9.14   11.7 | 11.7   13.7 | 13.5   15.9 | 15.4   18.7 | 18.1   20.7 | 19.8
-//   3-bit/3-bit DE bf16            5.82 | 6.66   6.26 | 6.79   7.28 | 6.92   8.33 | 8.97   9.45 | 9.95   12.1 | 12.5   14.3 | 14.3   16.5 | 16.6   19.6 | 19.3   21.5 | 21.5
-//   2-bit/2-bit bf16, B 64, rank 20 5.33 | 6.26  5.98 | 6.40   6.81 | 6.59   8.24 | 8.37   9.60 | 9.08   12.2 | 12.1
-//   2-bit/3-bit bf16, copy         5.69 | 6.30   6.24 | 6.52   7.19 | 6.63   8.56 | 8.46   9.99 | 9.78   12.7 | 12.3
-//   4-bit/2-bit DE bf16, copy      5.74 | 6.59   6.62 | 6.79   7.48 | 6.93   9.10 | 8.68   10.7 | 9.91   13.5 | 13.3
-//   2-bit/3-bit bf16, rank 39      7.62 | 7.43   7.93 | 7.67   9.25 | 7.81   10.5 | 9.52   12.1 | 10.7   15.6 | 13.5
+//   elements / 2^18                 2             3             4             5             6             8             12            16            20
+//   4-bit/4-bit fp32                4.33 | 5.57   5.77 | 5.82   6.23 | 6.03   7.25 | 7.68   7.62 | 8.30   9.03 | 9.41   11.0 | 11.8   13.9 | 14.0   16.1 | 16.2
+//   3-bit/3-bit fp32                4.47 | 5.82   5.88 | 5.99   6.25 | 6.21   7.25 | 7.78   7.59 | 8.26   8.88 | 9.01   11.3 | 11.3   13.5 | 13.3   16.1 | 15.8
+//   3-bit/4-bit fp32, B 64          4.13 | 5.60   5.56 | 5.78   5.95 | 5.95   6.96 | 7.55   7.30 | 8.23   8.70 | 9.16   10.8 | 11.5   13.4 | 13.8   15.9 | 16.3
+//   4-bit/4-bit fp32, AdaBelief     4.50 | 5.64   5.92 | 5.91   6.34 | 6.12   7.33 | 7.80   7.64 | 8.39   9.24 | 9.46   11.4 | 11.9   13.4 | 14.2   17.0 | 16.2
+//   4-bit/4-bit fp32, copy          4.69 | 5.77   6.13 | 6.03   6.61 | 6.24   7.73 | 8.04   8.17 | 9.00   9.77 | 10.1   12.1 | 13.2   15.8 | 15.8   18.9 | 18.2
+//   4-bit/4-bit fp32, rank 39       5.93 | 6.39   7.42 | 6.53   7.84 | 6.71   9.29 | 8.45   9.66 | 9.10   11.4 | 10.3   14.5 | 12.8   17.2 | 15.2   20.5 | 17.5
+//   2-bit/3-bit bf16                4.47 | 5.57   5.28 | 5.77   5.92 | 5.95   6.94 | 7.09   7.20 | 7.29   8.46 | 8.06   10.7 | 10.6   12.9 | 12.6   14.6 | 14.3
+//   3-bit/3-bit DE bf16             4.71 | 6.37   5.58 | 6.49   6.21 | 6.64   7.20 | 7.75   7.46 | 7.97   8.87 | 8.47   11.2 | 11.1   13.5 | 13.2   15.6 | 15.0
+//   2-bit/2-bit bf16, B 64, rank 20 4.90 | 5.88   5.83 | 6.03   6.49 | 6.21   7.51 | 7.49   7.88 | 7.77   9.18 | 8.27   11.7 | 11.2   14.0 | 13.4   16.0 | 15.1
+//   2-bit/3-bit bf16, copy          4.70 | 6.02   5.71 | 6.14   6.46 | 6.35   7.43 | 7.53   7.79 | 7.85   9.44 | 8.66   11.7 | 11.6   13.7 | 14.2   17.2 | 16.5
+//   4-bit/2-bit DE bf16, copy       5.31 | 6.51   6.45 | 6.63   7.26 | 6.83   8.36 | 8.25   8.74 | 8.52   10.6 | 9.54   13.0 | 12.7   15.7 | 15.3   18.8 | 17.5
+//   2-bit/3-bit bf16, rank 39       5.99 | 6.40   6.95 | 6.57   7.61 | 6.75   8.96 | 7.94   9.30 | 8.21   10.9 | 8.86   13.9 | 11.7   17.1 | 13.8   19.1 | 15.7
 // A launch is a number of rounds of wavefronts per SIMD.  2^20 elements are one round with 16 per lane
 // and two of half as large wavefronts with 8; a little more is two rounds against three shorter ones.
-// 16 is up to 7 % ahead at that one size over states that come out of the last-level cache, as here, but
-// behind by as much where the state is still in the L2 (one state again and again, 3-bit/3-bit fp32
-// 5.93 | 6.45, 4-bit/4-bit 5.53 | 5.55), so no line is drawn there.  Further up the fewer
-// instructions of 16 decide: with bf16 gradients, where 8 saves the fewer layout transpositions, from
-// 3 * 2^20 elements on, with fp32 ones from 6 * 2^20 (the formats cross between 5 and 8); earlier with a copy,
-// which 8 writes in half-covered requests, and with a large rank, whose rounds cost 8 twice the
+// 16 is up to 6 % ahead at that one size over states that come out of the last-level cache, as here, but
+// behind by 10 % where the state is still in the L2 (one state again and again, 4-bit/4-bit fp32 5.23 | 5.76,
+// 2-bit/3-bit bf16 5.36 | 5.93), so no line is drawn there.  Further up the fewer
+// instructions of 16 decide: with bf16 gradients, where 8 saves the fewer layout transpositions, behind
+// 3 * 2^19 elements (with a copy, which 8 writes in half-covered requests, 5 * 2^18), with fp32 ones behind
+// 9 * 2^19 (one state again and again, at 5 * 2^20: 15.2 | 14.2, AdaBelief 15.7 | 14.5, B 64 14.9 | 13.7); earlier with a large rank, whose rounds cost 8 twice the
 // instructions.  (No line is within 3 % of a size for every format.)
 constexpr bool narrow_buffer(uint64_t n, bool bf16, bool copy, uint32_t rank)
 {
     if (rank > 24) return n <= 1ull << 19;
-    if (!bf16) return n <= (copy ? 4ull << 20 : 6ull << 20);
-    return n <= (copy ? 5ull << 18 : rank > 16 ? 3ull << 19 : 3ull << 20);
+    if (!bf16) return n <= 9ull << 19;
+    return n <= (copy ? 5ull << 18 : 3ull << 19);
 }
 // Up to how many pieces (pieces16) a table does.
 constexpr uint64_t narrow_table_up_to() { return 3ull << 8; }
