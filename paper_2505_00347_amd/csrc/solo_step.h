@@ -1129,30 +1129,35 @@ struct ChunkWords8 {
 // under way (ready(), which every wavefront of the workgroup calls once): with the whole copy in
 // front of those loads its latency stood in front of every 4096 elements (842 million elements,
 // 3-bit/3-bit bf16: 1820 us, 1783 now; 2^24, 4-bit/2-bit: 39.3 and 37.6).
-template <int BM, bool MDE>
+// THREADS: of the workgroup.
+template <int BM, bool MDE, int THREADS = kWaves * 64>
 struct DeTable {
     static constexpr bool kUsed = MDE && BM >= 3;
-    static constexpr int kWords = de_words<BM, MDE>(), kPer = (kWords + kWaves * 64 - 1) / (kWaves * 64);
+    static constexpr int kWords = de_words<BM, MDE>(), kPer = (kWords + THREADS - 1) / THREADS;
     uint32_t *const lds;
     uint32_t word[kPer];
     __device__ __forceinline__ explicit DeTable(uint32_t *const l) : lds(l)
     {
 #pragma unroll
         for (int i = 0; i < kPer; ++i) {
-            const uint32_t w = threadIdx.x + (uint32_t)(i * kWaves * 64);
+            const uint32_t w = threadIdx.x + (uint32_t)(i * THREADS);
             word[i] = 0;
             if (kUsed && w < (uint32_t)kWords) word[i] = (&DeBuckets<BM>::tab.w[0][0])[w];
         }
     }
-    __device__ __forceinline__ void ready() const
+    __device__ __forceinline__ void store() const       // (ready() without its barrier)
     {
         if (!kUsed) return;
 #pragma unroll
         for (int i = 0; i < kPer; ++i) {
-            const uint32_t w = threadIdx.x + (uint32_t)(i * kWaves * 64);
+            const uint32_t w = threadIdx.x + (uint32_t)(i * THREADS);
             if (w < (uint32_t)kWords) lds[w] = word[i];
         }
-        __syncthreads();
+    }
+    __device__ __forceinline__ void ready() const
+    {
+        store();
+        if (kUsed) __syncthreads();
     }
 };
 

@@ -316,17 +316,6 @@ __device__ __forceinline__ uint32_t key_floor(const StepArgs &a, const float *co
     return (uint32_t)__builtin_amdgcn_readfirstlane((int)(low > 0.0f && a.beta2 >= 0.85f ? f2u(EXT ? key + a.eps_state : key) : 0u));
 }
 
-// The DE bucket table of a workgroup: copied from constant memory first.
-template <int BM, bool MDE, int WORDS>
-__device__ __forceinline__ void load_de_table(uint32_t *lds_de)
-{
-    if (MDE && BM >= 3) {
-        const uint32_t *src = &DeBuckets<BM>::tab.w[0][0];
-        for (uint32_t w = threadIdx.x; w < (uint32_t)WORDS; w += blockDim.x) lds_de[w] = src[w];
-        __syncthreads();
-    }
-}
-
 // Elements of block `blk` that exist, and the rank of the quantile among them.
 __device__ __forceinline__ uint32_t present_in(const uint64_t n, const uint64_t blk)
 {
@@ -356,7 +345,7 @@ __device__ __forceinline__ uint32_t rank_among(const StepArgs &a, const uint32_t
 template <int BM, int BV, bool BF16, bool MDE, bool EXT, bool TAIL>
 __device__ __forceinline__ void step_block(const StepArgs &a, const uint64_t blk, const uint32_t lane,
                                            const uint32_t wave, uint32_t *const slab, uint32_t *const work,
-                                           uint32_t *const xch, const uint32_t *const lds_de)
+                                           uint32_t *const xch, const DeTable<BM, MDE, kBigWaves * 64> &de)
 {
     constexpr int L = (1 << (BM - 1)) - 1;
     constexpr bool kDeTable = MDE && BM >= 3;
@@ -378,6 +367,7 @@ __device__ __forceinline__ void step_block(const StepArgs &a, const uint64_t blk
     const RawPG16<BF16> raw = load_pg16<BF16>(a, ew0, lane, here);
     const float gscale = (EXT && a.grad_scale) ? *a.grad_scale : 1.0f;
     const Stage16 st(reinterpret_cast<float4 *>(work + wave * BigLayout::kStage), lane);
+    de.store();                                    // (read behind the barrier of the maxima)
     words.stage(img_m, img_v, lane);
 
     // ---- level tables of the block (every wavefront its own copy)
@@ -451,7 +441,7 @@ __device__ __forceinline__ void step_block(const StepArgs &a, const uint64_t blk
     // ---- encoder constants (every 16 lanes for themselves), codes, the wavefront's words
     const uint32_t lig = lane & 15u, gshift = lane & 16u;
     uint32_t de_base = 0;
-    if (kDeTable) de_base = lds_addr(lds_de) - 16u * DeBuckets<BM>::kLo;
+    if (kDeTable) de_base = lds_addr(de.lds) - 16u * DeBuckets<BM>::kLo;
     const BlockCodec codec = block_codec<BV, 16, L, MDE>(xp_bits, dm, dv, lane, lig, gshift);
     encode_into_image16<BM, BV, MDE>(a, ew0, lane, mh, vh, codec, de_base, img_m, img_v,
                                      words.wm, words.sm, words.wv, words.sv, mc8, vc8);
@@ -467,7 +457,7 @@ __device__ __forceinline__ void step_block(const StepArgs &a, const uint64_t blk
 
 // The same by four wavefronts, 8 consecutive elements per lane, where a launch is all latency: half
 // as long a chain in every lane, and parameters and gradients that are not turned around through
-// LDS.  Full and short blocks alike, with bounds checks.  (1000 elements, 2-bit/3-bit bf16: 8.8 us by
+// LDS.  TAIL: the shorter last block, with bounds checks.  (1000 elements, 2-bit/3-bit bf16: 8.8 us by
 // the two wavefronts with bounds checks on every element, 5.7 by this form; 1,000,003: 9.7 and 7.9.)
 constexpr int kQuadWaves = kBigBlock / kIter;
 struct QuadLayout {
@@ -479,10 +469,10 @@ struct QuadLayout {
 };
 static_assert(2 * ChunkWords8<3, 4, true>::kImage <= QuadLayout::kOffTv, "images");
 
-template <int BM, int BV, bool BF16, bool MDE, bool EXT>
+template <int BM, int BV, bool BF16, bool MDE, bool EXT, bool TAIL>
 __device__ __forceinline__ void step_block_quad(const StepArgs &a, const uint64_t blk, const uint32_t lane,
                                                 const uint32_t wave, uint32_t *const slab, uint32_t *const work,
-                                                uint32_t *const xch, const uint32_t *const lds_de)
+                                                uint32_t *const xch, const DeTable<BM, MDE, kQuadWaves * 64> &de)
 {
     constexpr int L = (1 << (BM - 1)) - 1;
     constexpr bool kDeTable = MDE && BM >= 3;
@@ -490,26 +480,27 @@ __device__ __forceinline__ void step_block_quad(const StepArgs &a, const uint64_
 
     const uint64_t ew0 = blk * kBigBlock + (uint64_t)wave * kIter;    // first element of this wavefront
     const uint64_t e0 = ew0 + lane * 8u;                              // first element of this lane
-    const uint32_t present = present_in(a.n, blk);
+    const uint32_t present = TAIL ? present_in(a.n, blk) : (uint32_t)kBigBlock;
     uint32_t *const img_m = slab + QuadLayout::kOffImgM, *const img_v = slab + QuadLayout::kOffImgV;
     float *const my_tv = reinterpret_cast<float *>(slab + QuadLayout::kOffTv);
     float *const my_tm = reinterpret_cast<float *>(slab + QuadLayout::kOffTm);
     const uint32_t tv_addr = lds_addr(my_tv), tm_addr = lds_addr(my_tm);
     bool ok[8];                                    // the lane's elements that exist
 #pragma unroll
-    for (int j = 0; j < 8; ++j) ok[j] = e0 + j < a.n;
+    for (int j = 0; j < 8; ++j) ok[j] = !TAIL || e0 + j < a.n;
 
     // ---- every load is issued before the first one is waited for; the histogram is cleared meanwhile
-    ChunkWords8<BM, BV, true> words;
+    ChunkWords8<BM, BV, TAIL> words;
     words.load(a, ew0, lane);
     const float dm_old = a.m_scale[blk], dv_old = a.v_scale[blk], al_old = a.v_base[blk];
-    const RawPG raw = load_pg<BF16, true>(a, e0, ok[7]);
+    const RawPG raw = load_pg<BF16, TAIL>(a, e0, ok[7]);
     const float gscale = (EXT && a.grad_scale) ? *a.grad_scale : 1.0f;
     {
         uint4 *const z = reinterpret_cast<uint4 *>(work);
 #pragma unroll
         for (uint32_t i = 0; i < 512u / (64u * kQuadWaves); ++i) z[wave * 64u + lane + 64u * kQuadWaves * i] = make_uint4(0, 0, 0, 0);
     }
+    de.store();
     words.stage(img_m, img_v, lane);
     {
         const float de_level = MDE ? DeLevels<BM>::level(lane) : 0.0f;
@@ -519,7 +510,7 @@ __device__ __forceinline__ void step_block_quad(const StepArgs &a, const uint64_
     uint32_t mc8, vc8;
     words.codes(img_m, img_v, mc8, vc8);
     const uint32_t floor = key_floor<BV, EXT>(a, my_tv);
-    __syncthreads();                               // (the histogram is cleared)
+    __syncthreads();                               // (the histogram is cleared, the DE table is there)
 
     // ---- dequantize (table look-up), EMA, parameter
     float p[8], g[8];
@@ -530,8 +521,8 @@ __device__ __forceinline__ void step_block_quad(const StepArgs &a, const uint64_
     }
     float mh[8], vh[8];
     float m_absmax, v_max;
-    ema_param<8, BM, BV, EXT, true, true>(a, tm_addr, tv_addr, &mc8, &vc8, ok, p, g, mh, vh, m_absmax, v_max);
-    store_params8<EXT, true>(a, e0, ok[7], ok, p);
+    ema_param<8, BM, BV, EXT, TAIL, true>(a, tm_addr, tv_addr, &mc8, &vc8, ok, p, g, mh, vh, m_absmax, v_max);
+    store_params8<EXT, TAIL>(a, e0, ok[7], ok, p);
 
     // ---- block maxima over the four wavefronts (read behind the selection's barriers)
     {
@@ -552,12 +543,12 @@ __device__ __forceinline__ void step_block_quad(const StepArgs &a, const uint64_
     // ---- encoder constants (every 16 lanes for themselves), codes, the wavefront's words
     const uint32_t lig = lane & 15u, gshift = lane & 16u;
     uint32_t de_base = 0;
-    if (kDeTable) de_base = lds_addr(lds_de) - 16u * DeBuckets<BM>::kLo;
+    if (kDeTable) de_base = lds_addr(de.lds) - 16u * DeBuckets<BM>::kLo;
     const BlockCodec codec = block_codec<BV, 16, L, MDE>(xp_bits, dm, dv, lane, lig, gshift);
     uint32_t m8, v8;
     uint32_t xi_word[1];
     XiGroups(a, ew0).words<1>(a, lane, xi_word);
-    encode_run<BM, BV, MDE, true>(a, xi_word[0], mh, vh, ok, codec, de_base, m8, v8);
+    encode_run<BM, BV, MDE, TAIL>(a, xi_word[0], mh, vh, ok, codec, de_base, m8, v8);
     xor_into_image8<BM, BV>(img_m, img_v, words.wm, words.sm, words.wv, words.sv, mc8 ^ m8, vc8 ^ v8);
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     __builtin_amdgcn_wave_barrier();
@@ -573,7 +564,7 @@ __device__ __forceinline__ void step_block_quad(const StepArgs &a, const uint64_
     __shared__ __attribute__((aligned(64))) uint32_t lds_slab[WAVES_ * SLAB_];                         \
     __shared__ __attribute__((aligned(64))) uint32_t lds_xch[BigExchange<WAVES_>::kWords];             \
     __shared__ __attribute__((aligned(64))) uint32_t lds_de[kDeWords];                                 \
-    load_de_table<BM, MDE, kDeWords>(lds_de);                                                          \
+    const DeTable<BM, MDE, WAVES_ * 64> de(lds_de);                                                    \
     const uint32_t lane = threadIdx.x & 63u;                                                           \
     const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));           \
     uint32_t *const slab = lds_slab + wave * SLAB_
@@ -601,23 +592,29 @@ void big_kernel(const StepArgs args)
     const uint32_t ragged = (uint32_t)args.rest;
     if (EXT) {                                     // (see step_block)
         const uint64_t blk = blockIdx.x < ragged ? args.n / kBigBlock : blockIdx.x - ragged;
-        step_block<BM, BV, BF16, MDE, EXT, true>(args, blk, lane, wave, slab, lds_work, lds_xch, lds_de);
+        step_block<BM, BV, BF16, MDE, EXT, true>(args, blk, lane, wave, slab, lds_work, lds_xch, de);
     } else if (blockIdx.x < ragged) {
         const StepArgs a = arguments_here<StepArgs>();
-        step_block<BM, BV, BF16, MDE, EXT, true>(a, a.n / kBigBlock, lane, wave, slab, lds_work, lds_xch, lds_de);
+        step_block<BM, BV, BF16, MDE, EXT, true>(a, a.n / kBigBlock, lane, wave, slab, lds_work, lds_xch, de);
     } else {
         const StepArgs a = arguments_here<StepArgs>();
-        step_block<BM, BV, BF16, MDE, EXT, false>(a, blockIdx.x - ragged, lane, wave, slab, lds_work, lds_xch, lds_de);
+        step_block<BM, BV, BF16, MDE, EXT, false>(a, blockIdx.x - ragged, lane, wave, slab, lds_work, lds_xch, de);
     }
 }
 
 // Four wavefronts per block.
 template <int BM, int BV, bool BF16, bool MDE, bool EXT>
 __global__ __launch_bounds__(kQuadWaves * 64, kMinWaves)
-void big_quad_kernel(const StepArgs a)
+void big_quad_kernel(const StepArgs args)
 {
     SOLO_BIG_LDS(kQuadWaves, 2048, QuadLayout::kSlab);
-    step_block_quad<BM, BV, BF16, MDE, EXT>(a, blockIdx.x, lane, wave, slab, lds_work, lds_xch, lds_de);
+    if (blockIdx.x < args.n / kBigBlock) {
+        const StepArgs a = arguments_here<StepArgs>();
+        step_block_quad<BM, BV, BF16, MDE, EXT, false>(a, blockIdx.x, lane, wave, slab, lds_work, lds_xch, de);
+    } else {
+        const StepArgs a = arguments_here<StepArgs>();
+        step_block_quad<BM, BV, BF16, MDE, EXT, true>(a, blockIdx.x, lane, wave, slab, lds_work, lds_xch, de);
+    }
 }
 
 // The step over many tensors in one launch, blocks of 2048 elements.  The map of the table holds
@@ -633,9 +630,9 @@ void multi_big_kernel(const MultiArgs args)
     const TensorEntry &e = ma.entries[me & kMapTensorMask];
     const uint64_t blk = blockIdx.x - e.unit0;
     if (EXT || (me & kMapRagged))
-        step_block<BM, BV, BF16, MDE, EXT, true>(tensor_args(ma, e), blk, lane, wave, slab, lds_work, lds_xch, lds_de);
+        step_block<BM, BV, BF16, MDE, EXT, true>(tensor_args(ma, e), blk, lane, wave, slab, lds_work, lds_xch, de);
     else
-        step_block<BM, BV, BF16, MDE, EXT, false>(tensor_args(ma, e), blk, lane, wave, slab, lds_work, lds_xch, lds_de);
+        step_block<BM, BV, BF16, MDE, EXT, false>(tensor_args(ma, e), blk, lane, wave, slab, lds_work, lds_xch, de);
 }
 
 template <int BM, int BV, bool BF16, bool MDE, bool EXT>
@@ -644,7 +641,7 @@ void multi_big_quad_kernel(const MultiArgs ma)
 {
     const TensorEntry &e = ma.entries[ma.unit_map[blockIdx.x] & kMapTensorMask];
     SOLO_BIG_LDS(kQuadWaves, 2048, QuadLayout::kSlab);
-    step_block_quad<BM, BV, BF16, MDE, EXT>(tensor_args(ma, e), blockIdx.x - e.unit0, lane, wave, slab, lds_work, lds_xch, lds_de);
+    step_block_quad<BM, BV, BF16, MDE, EXT, true>(tensor_args(ma, e), blockIdx.x - e.unit0, lane, wave, slab, lds_work, lds_xch, de);
 }
 #undef SOLO_BIG_LDS
 
