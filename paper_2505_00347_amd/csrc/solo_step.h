@@ -65,7 +65,7 @@ constexpr int kIter = 512;         // elements of a chunk with 8 per lane
 constexpr int kIter16 = 1024;      // elements of a chunk with 16 per lane
 constexpr int kWaves = 4;          // wavefronts per workgroup
 constexpr int kMinWaves = 5;       // wavefronts per SIMD that the register allocator must leave room for, 8 elements per lane
-constexpr int kMinWaves16 = 4;     // and 16 per lane (81-96 registers, i.e. five, in most formats; forcing five spills in the others and gains nothing)
+constexpr int kMinWaves16 = 4;     // and 16 per lane (70-80 registers, i.e. six, in most formats)
 constexpr int kColStride16 = 18;   // words per lane of the sorted columns (16 keys, two +inf; written 8 bytes at a time)
 constexpr float kTiny = 0x1p-100f; // block maxima below this are stored as 0
 constexpr float kRhoMin = 0x1p-64f;
@@ -337,17 +337,35 @@ __device__ __forceinline__ uint32_t search_base(float rho, bool need, uint32_t l
     return ab;
 }
 
-// Eight consecutive BITS-wide codes starting at slot `slot` of word w0 (the
-// run may continue in w1 for 3-bit codes, ten to a word).
-template <int BITS>
-__device__ __forceinline__ uint32_t extract8(uint32_t w0, uint32_t w1, uint32_t slot)
+// A value that the compiler does not connect with what it has computed from `x` before: cheap arithmetic is then
+// done again instead of being kept in registers.
+__device__ __forceinline__ uint32_t fresh(uint32_t x)
 {
-    if (BITS == 3) {
-        const uint64_t both = (uint64_t)w0 | ((uint64_t)w1 << 30);
-        return (uint32_t)(both >> (3u * slot)) & 0xFFFFFFu;
-    }
-    return w0 >> (BITS * slot);   // 2-bit: slot 0 or 8; 4-bit: slot 0
+    asm("" : "+v"(x));
+    return x;
 }
+
+// A run of eight 3-bit codes that starts at slot `s` (0-9) of a word: `shift` = 3 s; the run may continue in the
+// word behind it.
+struct Run3 {
+    uint32_t word, shift;
+    // q: code index of the run's first code from the first staged word on (< 1040)
+    __device__ __forceinline__ explicit Run3(const uint32_t q)
+    {
+        word = __umul24(q, 52429u) >> 19;          // q / 10
+        shift = 3u * q - 30u * word;
+    }
+    __device__ __forceinline__ uint32_t codes(const uint32_t *const img) const
+    {
+        return (img[word] >> shift | img[word + 1] << (30u - shift)) & 0xFFFFFFu;
+    }
+    // changes codes by exclusive or: what lanes that share a word own of it stays
+    __device__ __forceinline__ void change(uint32_t *const img, const uint32_t x) const
+    {
+        atomicXor(&img[word], (x << shift) & 0x3FFFFFFFu);
+        atomicXor(&img[word + 1], x >> (30u - shift));
+    }
+};
 
 // Signed dynamic-exponent (DE) levels of the 1st moment (App. A of the paper): the first bit
 // is the sign, the other b-1 bits spend E leading zeros on the exponent 10^-E, one indicator
@@ -921,6 +939,9 @@ __device__ __forceinline__ void fill_level_tables(float *const my_tv, float *con
     constexpr int L = (1 << (BM - 1)) - 1;
     constexpr int VT = 1 << BV;
     constexpr int MT = MDE ? 2 * L + 2 : 2 * L + 1;
+    // (The scales are here: a load whose value is used under the condition below only would be moved behind it, and
+    // its latency with it.)
+    asm volatile("" : : "v"(dm_old), "v"(dv_old), "v"(al_old));
     const float s_m = (L == 1) ? dm_old : dm_old / (float)L;
     const float P1 = al_old, P2 = P1 * P1, P4 = P2 * P2, P8 = P4 * P4;
 #pragma unroll
@@ -1029,98 +1050,77 @@ __device__ __forceinline__ void store_params8(const StepArgs &a, const uint64_t 
     }
 }
 
-// A lane's run of 8 new codes into the LDS image of the code words (wm / sm, wv / sv: word and
-// slot of the run's first code; xm, xv: old codes XOR new codes): the XOR turns this lane's old
-// fields into the new ones and leaves the neighbours' fields of a shared word alone.
-template <int BM, int BV>
-__device__ __forceinline__ void xor_into_image8(uint32_t *const img_m, uint32_t *const img_v, const uint32_t wm,
-                                                const uint32_t sm, const uint32_t wv, const uint32_t sv,
-                                                const uint32_t xm, const uint32_t xv)
-{
-    const uint32_t xm0 = (BM == 3) ? (xm << (3u * sm)) & 0x3FFFFFFFu : xm << (BM * sm);
-    const uint32_t xm1 = (BM == 3) ? (uint32_t)(((uint64_t)xm << (3u * sm)) >> 30) : 0u;
-    const uint32_t xv0 = (BV == 3) ? (xv << (3u * sv)) & 0x3FFFFFFFu : xv << (BV * sv);
-    const uint32_t xv1 = (BV == 3) ? (uint32_t)(((uint64_t)xv << (3u * sv)) >> 30) : 0u;
-    atomicXor(&img_m[wm], xm0);
-    if (BM == 3) atomicXor(&img_m[wm + 1], xm1);
-    atomicXor(&img_v[wv], xv0);
-    if (BV == 3) atomicXor(&img_v[wv + 1], xv1);
-}
-
-// A lane writes back the code word it staged (`own`: as it was loaded; `fin`: as it is in the
-// image now).  Two- and four-bit words are whole words of whole lines and are stored plainly.
-// Ten-to-a-word codes do not end on a line (or even on a word) at the end of a wavefront's share:
+// A lane writes back what has changed of a word of 3-bit codes.  Ten-to-a-word codes do not end on a
+// line (or even on a word) at the end of a wavefront's share:
 // their words take this wavefront's changes by atomic XOR (the fields that two wavefronts own in
 // a shared word are disjoint), which is carried out at the memory side and leaves no partly
 // written line behind in the L2 of this die.
-template <int BITS>
-__device__ __forceinline__ void write_back_word(uint32_t *const word, const uint32_t fin, const uint32_t own)
+__device__ __forceinline__ void write_back_word(uint32_t *const word, const uint32_t changed)
 {
-    if (BITS != 3) *word = fin;
-    else if (fin != own) atomicXor(word, fin ^ own);
+    if (changed) atomicXor(word, changed);
 }
 
-// The code words of the 512 elements that a wavefront steps on its own (8 consecutive elements per
-// lane): staged in LDS, at most one word of each stream per lane, and written back by the lane
-// that staged them.  The first word may begin in the share before (ten-to-a-word codes).
+// The codes of the 512 elements that a wavefront steps on its own (8 consecutive elements per lane).  Eight 2- or
+// 4-bit codes are a half or a whole word of the stream: the lane loads and stores it.  Words of 3-bit codes are
+// staged in LDS, at most one of a stream per lane; once all codes have been read the image is cleared and collects what
+// changes of the words, and the lane that staged a word writes that back.  The first word may begin in the share before.
 // TAIL: words behind the buffer are left alone.
-template <int BM, int BV, bool TAIL>
-struct ChunkWords8 {
-    static constexpr int CM = 32 / BM, CV = 32 / BV;   // codes per word
-    static constexpr int kImage = 68;                  // words of a stream's image (<= 64, + 1)
-    static_assert(kIter / 8 <= 64, "one staged word per lane and code stream");
-    uint64_t gw_m, gw_v;                       // the words this lane stages
-    bool has_m, has_v;
-    uint32_t own_m, own_v;                     // as they were loaded
-    uint32_t wm, sm, wv, sv;                   // word (of the image) and slot of the lane's first code
+template <int BITS, bool TAIL>
+struct LaneCodes8 {
+    static constexpr int C = 32 / BITS;                // codes per word
+    static constexpr int kImage = BITS == 3 ? 68 : 0;  // words of the image (<= 64, + 1)
+    uint32_t *word;                            // the first word of the share (uniform)
+    bool has;                                  // this lane has a word, or half a one, to write
+    uint32_t own;                              // as it was loaded (3-bit: until it is staged)
+    uint32_t first;                            // 3-bit: slot of the first element in the first word
 
-    // ew0: first element of the wavefront's share.  Issues the loads.
-    __device__ __forceinline__ void load(const StepArgs &a, const uint64_t ew0, const uint32_t lane)
+    // ew0: first element of the wavefront's share.  Issues the load.
+    __device__ __forceinline__ void load(uint32_t *const words, const uint64_t n, const uint64_t ew0, const uint32_t lane)
     {
-        const uint64_t gm_lo = ew0 / CM, gv_lo = ew0 / CV;
-        const uint32_t rm0 = (uint32_t)(ew0 - gm_lo * CM), rv0 = (uint32_t)(ew0 - gv_lo * CV);   // slot of the first element
-        gw_m = gm_lo + lane; gw_v = gv_lo + lane;
-        has_m = lane < (rm0 + kIter + CM - 1) / CM && (!TAIL || gw_m < (a.n + CM - 1) / CM);
-        has_v = lane < (rv0 + kIter + CV - 1) / CV && (!TAIL || gw_v < (a.n + CV - 1) / CV);
+        const uint64_t lo = ew0 / C;
+        word = words + lo;
+        first = (uint32_t)(ew0 - lo * C);
         // (Lanes without a word load the last one again: a load under a condition whose fields are masked
         // behind it was waited for inside, in front of all the loads that follow.  2^20 elements,
         // 3-bit/3-bit fp32: 5.46 us under conditions, 5.27 without; the 1.3e9 elements of the 1.3B shapes, 3-bit/3-bit
         // bf16, 16 per lane: 2535 and 2439.)
-        uint32_t lm = (rm0 + kIter + CM - 1) / CM - 1, lv = (rv0 + kIter + CV - 1) / CV - 1;
-        uint64_t fm = gm_lo, fv = gv_lo;
+        const uint32_t at = BITS == 2 ? lane / 2u : lane;
+        uint32_t last = (first + kIter + C - 1) / C - 1;
+        uint64_t from = lo;
+        has = at <= last;
         if (TAIL) {
-            const uint64_t end_m = (a.n - 1) / CM, end_v = (a.n - 1) / CV;     // last words of the buffer
-            fm = umin64(fm, end_m); lm = (uint32_t)umin64(lm, end_m - fm);
-            fv = umin64(fv, end_v); lv = (uint32_t)umin64(lv, end_v - fv);
+            const uint64_t end = (n - 1) / C;              // last word of the buffer
+            has = has && lo + at <= end;
+            from = umin64(from, end); last = (uint32_t)umin64(last, end - from);
         }
-        own_m = a.m_words[fm + umin(lane, lm)];
-        own_v = a.v_words[fv + umin(lane, lv)];
-        const uint32_t qm = rm0 + lane * 8u, qv = rv0 + lane * 8u;      // < 520: e / 10 by multiplication
-        wm = (CM == 10) ? __umul24(qm, 52429u) >> 19 : qm / CM; sm = qm - wm * CM;
-        wv = (CV == 10) ? __umul24(qv, 52429u) >> 19 : qv / CV; sv = qv - wv * CV;
+        if (BITS == 2) own = reinterpret_cast<const uint16_t *>(words + from)[umin(lane, 2u * last + 1u)];
+        else own = words[from + umin(at, last)];
     }
-    __device__ __forceinline__ void stage(uint32_t *const img_m, uint32_t *const img_v, const uint32_t lane)
+    __device__ __forceinline__ void stage(uint32_t *const img, const uint32_t lane)
     {
-        if (BM == 3) own_m &= 0x3FFFFFFFu;
-        if (BV == 3) own_v &= 0x3FFFFFFFu;
-        img_m[lane] = own_m;
-        img_v[lane] = own_v;
-        // (a 3-bit run that ends with its word reads the word behind it without using it)
-        if (lane == 0) { img_m[64] = 0; img_v[64] = 0; }
+        if (BITS != 3) return;
+        img[lane] = own & 0x3FFFFFFFu;
+        if (lane == 0) img[64] = 0;                // (a run that ends with its word reads the word behind it without using it)
     }
-    __device__ __forceinline__ void codes(const uint32_t *const img_m, const uint32_t *const img_v,
-                                          uint32_t &mc8, uint32_t &vc8) const
+    __device__ __forceinline__ uint32_t codes(uint32_t *const img, const uint32_t lane) const
     {
-        const uint32_t mw0 = img_m[wm], mw1 = (BM == 3) ? img_m[wm + 1] : 0u;
-        const uint32_t vw0 = img_v[wv], vw1 = (BV == 3) ? img_v[wv + 1] : 0u;
-        mc8 = extract8<BM>(mw0, mw1, sm) & (uint32_t)((1ull << (8 * BM)) - 1ull);
-        vc8 = extract8<BV>(vw0, vw1, sv) & (uint32_t)((1ull << (8 * BV)) - 1ull);
+        if (BITS != 3) return own;
+        const uint32_t c = Run3(first + lane * 8u).codes(img);
+        wave_lds_sync();
+        img[lane] = 0;
+        return c;
     }
-    __device__ __forceinline__ void write_back(const StepArgs &a, const uint32_t *const img_m, const uint32_t *const img_v,
-                                               const uint32_t lane) const
+    // the lane's new codes (`old`: what codes() gave), in front of write_back()
+    __device__ __forceinline__ void change(uint32_t *const img, const uint32_t lane, const uint32_t old, const uint32_t now) const
     {
-        if (has_m) write_back_word<BM>(&a.m_words[gw_m], img_m[lane], own_m);
-        if (has_v) write_back_word<BV>(&a.v_words[gw_v], img_v[lane], own_v);
+        if (BITS == 3) Run3(first + fresh(lane) * 8u).change(img, old ^ now);
+    }
+    __device__ __forceinline__ void write_back(const uint32_t *const img, const uint32_t lane, const uint32_t now) const
+    {
+        if (TAIL || BITS == 3) { if (!has) return; }
+        if (BITS == 2) reinterpret_cast<uint16_t *>(word)[lane] = (uint16_t)now;
+        else if (BITS == 4) word[lane] = now;
+        else write_back_word(&word[lane], img[lane]);
     }
 };
 
@@ -1169,8 +1169,8 @@ struct ChunkLayout8 {
     static constexpr int VT = 1 << BV;
     static constexpr int MTS = m_table_stride<BM>();
     static constexpr int kOffImgM = 0;
-    static constexpr int kOffImgV = kOffImgM + ChunkWords8<BM, BV, false>::kImage;
-    static constexpr int kOffTv = ((kOffImgV + ChunkWords8<BM, BV, false>::kImage + 15) / 16) * 16;   // 64-byte aligned
+    static constexpr int kOffImgV = kOffImgM + LaneCodes8<BM, false>::kImage;
+    static constexpr int kOffTv = ((kOffImgV + LaneCodes8<BV, false>::kImage + 15) / 16) * 16;   // 64-byte aligned
     static constexpr int kOffTm = kOffTv + ((NG * VT + 15) / 16) * 16;
     static constexpr int kSlab = kOffTm + ((NG * MTS + 15) / 16) * 16;
 };
@@ -1214,15 +1214,18 @@ __device__ __forceinline__ void step_chunk8(const StepArgs &a, const uint64_t ch
     }
 
     // ---- every load is issued before the first one is waited for
-    ChunkWords8<BM, BV, TAIL> words;
-    words.load(a, ew0, lane);
+    LaneCodes8<BM, TAIL> mw;
+    LaneCodes8<BV, TAIL> vw;
+    mw.load(a.m_words, a.n, ew0, lane);
+    vw.load(a.v_words, a.n, ew0, lane);
     float dm_old = 0.0f, dv_old = 0.0f, al_old = 1.0f;
     if (blk_ok) { dm_old = a.m_scale[gb]; dv_old = a.v_scale[gb]; al_old = a.v_base[gb]; }
     const bool whole = !TAIL || __builtin_expect(ew0 + kIter <= a.n, 0);
     const RawPG raw = load_pg<BF16, TAIL>(a, e0, whole);
     const float gscale = (EXT && a.grad_scale) ? *a.grad_scale : 1.0f;      // uniform: the gradient is transformed first
     de.ready();
-    words.stage(img_m, img_v, lane);
+    mw.stage(img_m, lane);
+    vw.stage(img_v, lane);
 
     // ---- level tables of this lane's block: entries lig, lig + G, ...
     float de_level[(16 + G - 1) / G];                  // DE codebook: the levels of the entries this lane fills
@@ -1234,8 +1237,7 @@ __device__ __forceinline__ void step_chunk8(const StepArgs &a, const uint64_t ch
     }
     fill_level_tables<BM, BV, MDE, G>(my_tv, my_tm, lig, dm_old, dv_old, al_old, de_level);
     wave_lds_sync();
-    uint32_t mc8, vc8;
-    words.codes(img_m, img_v, mc8, vc8);
+    const uint32_t mc8 = mw.codes(img_m, lane), vc8 = vw.codes(img_v, lane);
 
     // ---- dequantize (table look-up), EMA, parameter
     float p[8], g[8];
@@ -1282,11 +1284,13 @@ __device__ __forceinline__ void step_chunk8(const StepArgs &a, const uint64_t ch
     uint32_t xi_word[1];
     XiGroups(a, ew0).words<1>(a, lane, xi_word);
     encode_run<BM, BV, MDE, TAIL>(a, xi_word[0], mh, vh, ok, codec, de_base, m8, v8);
-    xor_into_image8<BM, BV>(img_m, img_v, words.wm, words.sm, words.wv, words.sv, mc8 ^ m8, vc8 ^ v8);
+    mw.change(img_m, lane, mc8, m8);
+    vw.change(img_v, lane, vc8, v8);
     if (lig == 0 && blk_ok) { a.m_scale[gb] = dm; a.v_scale[gb] = dv; a.v_base[gb] = codec.alpha; }
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     __builtin_amdgcn_wave_barrier();
-    words.write_back(a, img_m, img_v, lane);
+    mw.write_back(img_m, lane, m8);
+    vw.write_back(img_v, lane, v8);
 }
 
 // Sixteen keys, two sorted halves: the eight smallest in order (the smaller of a and b's mirror image are a
@@ -1531,145 +1535,130 @@ __device__ __forceinline__ void store_params16(const StepArgs &a, const uint64_t
     }
 }
 
-// Codes of a lane's 16 elements (two runs of 8; ew0 is the wavefront's first element, wm / sm / wv / sv the
-// word and slot of each run's first code in the image, mc8 / vc8 the old codes) into the LDS
-// image of the code words.  3-bit codes share words between lanes: XOR turns this lane's old
-// fields into the new ones and leaves the neighbours' alone.  2- and 4-bit words belong to one lane
-// (2-bit: both runs lie in word wm[0]).
+// The codes of the 1024 elements that a wavefront steps on its own (16 consecutive elements per lane).  Sixteen
+// 2- or 4-bit codes are one or two words of the stream: the lane loads and stores them.  Words of 3-bit codes are
+// staged in LDS, two of a stream per lane, as those of LaneCodes8.  STAGED: they are, and so are 4-bit ones of
+// dynamic-exponent moments, whose rounding has no register to spare (4-bit/2-bit with a copy 85 instead of 75, five wavefronts
+// per SIMD instead of six: 2^26 elements 152 us, 157 without staging).
+template <int BITS, bool STAGED>
+struct LaneCodes16 {
+    static constexpr int C = 32 / BITS;                // codes per word
+    static constexpr int K = BITS == 2 ? 1 : 2;        // words of the stream per lane (64 K >= words of 1024 elements)
+    static constexpr int kImage = STAGED ? 132 : 0;    // words of the image (<= 128, + 4)
+    static_assert(BITS == 4 || STAGED == (BITS == 3), "2-bit words are a lane's own, 3-bit ones are not");
+    uint32_t *word;                            // the first word of the share (uniform)
+    uint32_t nw;                               // words touched (<= 128)
+    uint32_t own[K];                           // the words as they were loaded (3-bit: until they are staged)
+    uint32_t first;                            // 3-bit: slot of the first element in the first word
+
+    // which of the share's words a lane holds as own[k]
+    static __device__ __forceinline__ uint32_t at(const uint32_t lane, const int k) { return BITS == 4 && !STAGED ? 2u * lane + k : lane + 64u * k; }
+
+    // ew0: first element of the wavefront's share, of which `here` exist (0: none; FULL: all).
+    // Issues the loads.  Lanes without a word load the last one again, because a load
+    // under a condition is waited for inside it, with every load in front of it (see LaneCodes8; blocks of 2048,
+    // 1 million elements, 2-bit/3-bit bf16: 9.6 us, 9.2 with it and the words in front of the parameters).
+    template <bool FULL>
+    __device__ __forceinline__ void load(uint32_t *const words, const uint64_t ew0, const uint32_t lane, const uint32_t here)
+    {
+        const uint64_t lo = ew0 / C;
+        word = words + lo;
+        first = (uint32_t)(ew0 - lo * C);
+        nw = here ? (first + here + C - 1) / C : 0;
+        if (FULL && BITS == 4 && !STAGED) {
+            const uint2 two = *reinterpret_cast<const uint2 *>(word + 2u * lane);
+            own[0] = two.x; own[K - 1] = two.y;
+            return;
+        }
+        const uint64_t from = here ? lo : (ew0 - kIter16) / C;
+        const uint32_t last = here ? nw - 1u : 0u;
+#pragma unroll
+        for (int k = 0; k < K; ++k) own[k] = words[from + umin(at(lane, k), last)];
+    }
+    __device__ __forceinline__ void stage(uint32_t *const img, const uint32_t lane)
+    {
+        if (!STAGED) return;
+#pragma unroll
+        for (int k = 0; k < K; ++k) img[lane + 64u * k] = BITS == 3 ? own[k] & 0x3FFFFFFFu : own[k];
+        if (BITS == 3 && lane < 4) img[64 * K + lane] = 0;
+    }
+    // the lane's old codes, eight to a run (2-bit: the upper half of the register is not clear)
+    __device__ __forceinline__ void codes(uint32_t *const img, const uint32_t lane, uint32_t (&c8)[2]) const
+    {
+#pragma unroll
+        for (int r = 0; r < 2; ++r)
+            c8[r] = BITS == 3 ? Run3(first + lane * 16u + 8u * r).codes(img) : BITS == 2 ? own[0] >> (16 * r) : STAGED ? img[2u * lane + r] : own[r % K];
+        if (BITS != 3) return;
+        wave_lds_sync();
+#pragma unroll
+        for (int k = 0; k < K; ++k) img[lane + 64u * k] = 0;
+    }
+    // the lane's new codes of run r (`old`: what codes() gave), in front of write_back()
+    __device__ __forceinline__ void change(uint32_t *const img, const uint32_t lane, const int r, const uint32_t old, const uint32_t now) const
+    {
+        if (BITS == 3) Run3(first + fresh(lane) * 16u + 8u * r).change(img, old ^ now);
+        else if (STAGED) img[2u * lane + r] = now;
+    }
+    template <bool FULL>
+    __device__ __forceinline__ void write_back(const uint32_t *const img, const uint32_t lane, const uint32_t (&now)[2]) const
+    {
+        if (FULL && BITS == 4 && !STAGED) {
+            *reinterpret_cast<uint2 *>(word + 2u * lane) = make_uint2(now[0], now[1]);
+            return;
+        }
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            const uint32_t i = at(lane, k);
+            if ((FULL && BITS != 3) || i < nw) {
+                if (BITS == 3) write_back_word(&word[i], img[i]);
+                else word[i] = BITS == 2 ? now[0] | now[1] << 16 : STAGED ? img[i] : now[k];
+            }
+        }
+    }
+};
+
+template <int BM, bool MDE> using MomentCodes16 = LaneCodes16<BM, BM == 3 || (BM == 4 && MDE)>;
+template <int BV> using VarianceCodes16 = LaneCodes16<BV, BV == 3>;
+
+// New codes of a lane's 16 elements, two runs of 8; ew0 is the wavefront's first element, mc8 / vc8 the old codes.
+// `mine`: how many of them exist (fields behind the last element of the buffer become zero).
 template <int BM, int BV, bool MDE>
-__device__ __forceinline__ void encode_into_image16(const StepArgs &a, const uint64_t ew0, const uint32_t lane, const float *mh, const float *vh,
-                                                    const BlockCodec &codec, const uint32_t de_base,
-                                                    uint32_t *const img_m, uint32_t *const img_v,
-                                                    const uint32_t (&wm)[2], const uint32_t (&sm)[2],
-                                                    const uint32_t (&wv)[2], const uint32_t (&sv)[2],
-                                                    const uint32_t (&mc8)[2], const uint32_t (&vc8)[2])
+__device__ __forceinline__ void encode16(const StepArgs &a, const uint64_t ew0, const uint32_t lane, const float *mh, const float *vh,
+                                         const BlockCodec &codec, const uint32_t de_base, const MomentCodes16<BM, MDE> &mw,
+                                         const VarianceCodes16<BV> &vw, uint32_t *const img_m, uint32_t *const img_v,
+                                         const uint32_t (&mc8)[2], const uint32_t (&vc8)[2], uint32_t (&m8)[2], uint32_t (&v8)[2],
+                                         const bool all = true, const uint32_t mine = 16)
 {
-    uint32_t m_word = 0, v_word = 0;
     uint32_t xi_word[2];
     XiGroups(a, ew0).words<2>(a, 2u * lane, xi_word);
 #pragma unroll
     for (int r = 0; r < 2; ++r) {
-        uint32_t m8, v8;
-        encode_run<BM, BV, MDE, false>(a, xi_word[r], mh + 8 * r, vh + 8 * r, nullptr, codec, de_base, m8, v8);
-        if (BM == 3) {
-            const uint32_t xm = mc8[r] ^ m8;
-            atomicXor(&img_m[wm[r]], (xm << (3u * sm[r])) & 0x3FFFFFFFu);
-            atomicXor(&img_m[wm[r] + 1], (uint32_t)(((uint64_t)xm << (3u * sm[r])) >> 30));
-        } else if (BM == 4) {
-            img_m[wm[r]] = m8;
-        } else {
-            m_word |= m8 << (16 * r);
-            if (r == 1) img_m[wm[0]] = m_word;
+        encode_run<BM, BV, MDE, false>(a, xi_word[r], mh + 8 * r, vh + 8 * r, nullptr, codec, de_base, m8[r], v8[r]);
+        if (__builtin_expect(!all, 0)) {
+            const uint32_t run = mine <= 8u * r ? 0u : umin(mine - 8u * r, 8u);
+            m8[r] &= (uint32_t)((1ull << (BM * run)) - 1ull);
+            v8[r] &= (uint32_t)((1ull << (BV * run)) - 1ull);
         }
-        if (BV == 3) {
-            const uint32_t xv = vc8[r] ^ v8;
-            atomicXor(&img_v[wv[r]], (xv << (3u * sv[r])) & 0x3FFFFFFFu);
-            atomicXor(&img_v[wv[r] + 1], (uint32_t)(((uint64_t)xv << (3u * sv[r])) >> 30));
-        } else if (BV == 4) {
-            img_v[wv[r]] = v8;
-        } else {
-            v_word |= v8 << (16 * r);
-            if (r == 1) img_v[wv[0]] = v_word;
-        }
+        mw.change(img_m, lane, r, mc8[r], m8[r]);
+        vw.change(img_v, lane, r, vc8[r], v8[r]);
     }
 }
 
-// The code words of the 1024 elements that a wavefront steps on its own (16 consecutive elements
-// per lane): staged in LDS, one or two words of each stream per lane, and written back by the lane
-// that staged them.  The first word may begin in the share before (ten-to-a-word codes).
-template <int BM, int BV>
-struct ChunkWords16 {
-    static constexpr int CM = 32 / BM, CV = 32 / BV;                 // codes per word
-    static constexpr int KM = CM == 16 ? 1 : 2, KV = CV == 16 ? 1 : 2;   // words of a stream per lane (64 x K >= words of 1024 elements)
-    static constexpr int kImage = 132;                               // words of a stream's image (<= 128, + 4)
-    uint64_t gm_lo, gv_lo;                     // first word of each stream
-    uint32_t nwm, nwv;                         // words touched (<= 128)
-    uint32_t own_m[KM], own_v[KV];             // the staged words as they were loaded
-    uint32_t wm[2], sm[2], wv[2], sv[2];       // word (of the image) and slot of the first code of the lane's two runs of 8
-
-    // ew0: first element of the wavefront's share, of which `here` exist (0: of the share in front of it).
-    // Issues the loads.  Lanes without a word load the last one again, because a load
-    // under a condition is waited for inside it, with every load in front of it (see ChunkWords8; blocks of 2048,
-    // 1 million elements, 2-bit/3-bit bf16: 9.6 us, 9.2 with it and the words in front of the parameters).
-    __device__ __forceinline__ void load(const StepArgs &a, const uint64_t ew0, const uint32_t lane, const uint32_t here)
-    {
-        gm_lo = ew0 / CM; gv_lo = ew0 / CV;
-        const uint32_t rm0 = (uint32_t)(ew0 - gm_lo * CM), rv0 = (uint32_t)(ew0 - gv_lo * CV);   // slot of the first element
-        nwm = here ? (rm0 + here + CM - 1) / CM : 0; nwv = here ? (rv0 + here + CV - 1) / CV : 0;
-        const uint64_t fm = here ? gm_lo : (ew0 - kIter16) / CM, fv = here ? gv_lo : (ew0 - kIter16) / CV;
-        const uint32_t lm = here ? nwm - 1u : 0u, lv = here ? nwv - 1u : 0u;
-#pragma unroll
-        for (int k = 0; k < KM; ++k) own_m[k] = a.m_words[fm + umin(lane + 64u * k, lm)];
-#pragma unroll
-        for (int k = 0; k < KV; ++k) own_v[k] = a.v_words[fv + umin(lane + 64u * k, lv)];
-#pragma unroll
-        for (int r = 0; r < 2; ++r) {
-            const uint32_t qm = rm0 + lane * 16u + 8u * r, qv = rv0 + lane * 16u + 8u * r;   // < 1040: e / 10 by multiplication
-            wm[r] = (CM == 10) ? __umul24(qm, 52429u) >> 19 : qm / CM; sm[r] = qm - wm[r] * CM;
-            wv[r] = (CV == 10) ? __umul24(qv, 52429u) >> 19 : qv / CV; sv[r] = qv - wv[r] * CV;
-        }
-    }
-    __device__ __forceinline__ void stage(uint32_t *const img_m, uint32_t *const img_v, const uint32_t lane)
-    {
-#pragma unroll
-        for (int k = 0; k < KM; ++k) {
-            if (BM == 3) own_m[k] &= 0x3FFFFFFFu;
-            img_m[lane + 64u * k] = own_m[k];
-        }
-#pragma unroll
-        for (int k = 0; k < KV; ++k) {
-            if (BV == 3) own_v[k] &= 0x3FFFFFFFu;
-            img_v[lane + 64u * k] = own_v[k];
-        }
-        if (lane < 4) { img_m[64 * KM + lane] = 0; img_v[64 * KV + lane] = 0; }
-    }
-    // the lane's old codes, eight to a run, out of the staged words
-    __device__ __forceinline__ void codes(const uint32_t *const img_m, const uint32_t *const img_v,
-                                          uint32_t (&mc8)[2], uint32_t (&vc8)[2]) const
-    {
-#pragma unroll
-        for (int r = 0; r < 2; ++r) {
-            // (2-bit codes: both runs of the lane lie in one word)
-            const uint32_t mw0 = img_m[wm[BM == 2 ? 0 : r]], mw1 = (BM == 3) ? img_m[wm[r] + 1] : 0u;
-            const uint32_t vw0 = img_v[wv[BV == 2 ? 0 : r]], vw1 = (BV == 3) ? img_v[wv[r] + 1] : 0u;
-            mc8[r] = extract8<BM>(mw0, mw1, BM == 2 ? 8u * r : sm[r]) & (uint32_t)((1ull << (8 * BM)) - 1ull);
-            vc8[r] = extract8<BV>(vw0, vw1, BV == 2 ? 8u * r : sv[r]) & (uint32_t)((1ull << (8 * BV)) - 1ull);
-        }
-    }
-    // `here` < 1024: the fields behind the last element of the buffer stay zero
-    __device__ __forceinline__ void clear_behind(uint32_t *const img_m, uint32_t *const img_v, const uint64_t ew0,
-                                                 const uint32_t lane, const uint32_t here) const
-    {
-        if (lane == 0 && here != 0) {
-            const uint32_t um = (uint32_t)(ew0 + here - (gm_lo + nwm - 1u) * CM), uv = (uint32_t)(ew0 + here - (gv_lo + nwv - 1u) * CV);
-            img_m[nwm - 1u] &= (uint32_t)((1ull << (BM * um)) - 1ull);       // (fields in use of the last word)
-            img_v[nwv - 1u] &= (uint32_t)((1ull << (BV * uv)) - 1ull);
-        }
-    }
-    __device__ __forceinline__ void write_back(const StepArgs &a, const uint32_t *const img_m, const uint32_t *const img_v,
-                                               const uint32_t lane) const
-    {
-#pragma unroll
-        for (int k = 0; k < KM; ++k)
-            if (lane + 64u * k < nwm) write_back_word<BM>(&a.m_words[gm_lo + lane + 64u * k], img_m[lane + 64u * k], own_m[k]);
-#pragma unroll
-        for (int k = 0; k < KV; ++k)
-            if (lane + 64u * k < nwv) write_back_word<BV>(&a.v_words[gv_lo + lane + 64u * k], img_v[lane + 64u * k], own_v[k]);
-    }
-};
-
 // LDS of a wavefront that steps one 1024-element chunk on its own (32-bit words).
-template <int BM, int BV, int B>
+template <int BM, int BV, int B, bool MDE>
 struct ChunkLayout16 {
     static constexpr int NG = kIter16 / B;
     static constexpr int VT = 1 << BV;
     static constexpr int MTS = m_table_stride<BM>();
     static constexpr int kOffCol = 0;                          // staging of the transpositions, then the sorted columns
     static constexpr int kOffImgM = 64 * kColStride16;
-    static constexpr int kOffImgV = kOffImgM + ChunkWords16<BM, BV>::kImage;
-    static constexpr int kOffTv = ((kOffImgV + ChunkWords16<BM, BV>::kImage + 15) / 16) * 16;      // 64-byte aligned
+    static constexpr int kOffImgV = kOffImgM + MomentCodes16<BM, MDE>::kImage;
+    static constexpr int kOffTv = ((kOffImgV + VarianceCodes16<BV>::kImage + 15) / 16) * 16;      // 64-byte aligned
     static constexpr int kOffTm = kOffTv + ((NG * VT + 15) / 16) * 16;
-    static constexpr int kSlab = kOffTm + ((NG * MTS + 15) / 16) * 16;
+    static constexpr int kEnd = kOffTm + ((NG * MTS + 15) / 16) * 16;
+    // (a runaway column address, possible only with non-finite input, stays inside the slab)
+    static constexpr int kColumns = (64 * kColStride16 + 140 + 15) / 16 * 16;
+    static constexpr int kSlab = kEnd > kColumns ? kEnd : kColumns;
 };
 
 // The whole step for the 1024 elements from 1024 * chunk on (whole blocks, all of them present),
@@ -1683,10 +1672,8 @@ __device__ __forceinline__ void step_chunk16(const StepArgs &a, const uint64_t c
     constexpr int L = (1 << (BM - 1)) - 1;
     constexpr int VT = 1 << BV;
     constexpr int MT = MDE ? 2 * L + 2 : 2 * L + 1;
-    using Lay = ChunkLayout16<BM, BV, B>;
+    using Lay = ChunkLayout16<BM, BV, B, MDE>;
     constexpr bool kDeTable = MDE && BM >= 3;
-    // A runaway column address (possible only with non-finite input) stays inside the slab.
-    static_assert(Lay::kSlab >= 64 * kColStride16 + 140, "column slack");
 
     const uint64_t ew0 = chunk * kIter16;
     const uint32_t lig = lane & (G - 1), grp = lane / G, gshift = lane & 31u & ~(uint32_t)(G - 1);
@@ -1697,8 +1684,10 @@ __device__ __forceinline__ void step_chunk16(const StepArgs &a, const uint64_t c
     const uint32_t tv_addr = lds_addr(my_tv), tm_addr = lds_addr(my_tm);
 
     // ---- every load is issued before the first one is waited for
-    ChunkWords16<BM, BV> words;
-    words.load(a, ew0, lane, kIter16);
+    MomentCodes16<BM, MDE> mw;
+    VarianceCodes16<BV> vw;
+    mw.template load<true>(a.m_words, ew0, lane, kIter16);
+    vw.template load<true>(a.v_words, ew0, lane, kIter16);
     float *const m_scale = a.m_scale + chunk * NG, *const v_scale = a.v_scale + chunk * NG, *const v_base = a.v_base + chunk * NG;
     const float dm_old = m_scale[grp], dv_old = v_scale[grp], al_old = v_base[grp];
     const RawPG16<BF16> raw = load_pg16<BF16>(a, ew0, lane);
@@ -1706,7 +1695,8 @@ __device__ __forceinline__ void step_chunk16(const StepArgs &a, const uint64_t c
     const Stage16 st(reinterpret_cast<float4 *>(slab + Lay::kOffCol), lane);
     de.ready();
 
-    words.stage(img_m, img_v, lane);
+    mw.stage(img_m, lane);
+    vw.stage(img_v, lane);
     float de_level[(16 + G - 1) / G];
     uint32_t de_base = 0;
     if (MDE) {
@@ -1717,7 +1707,8 @@ __device__ __forceinline__ void step_chunk16(const StepArgs &a, const uint64_t c
     fill_level_tables<BM, BV, MDE, G>(my_tv, my_tm, lig, dm_old, dv_old, al_old, de_level);
     wave_lds_sync();
     uint32_t mc8[2], vc8[2];
-    words.codes(img_m, img_v, mc8, vc8);
+    mw.codes(img_m, lane, mc8);
+    vw.codes(img_v, lane, vc8);
 
     float p[16], g[16];
     lane_layout16<BF16>(raw, st, p, g);
@@ -1737,12 +1728,13 @@ __device__ __forceinline__ void step_chunk16(const StepArgs &a, const uint64_t c
     const uint32_t xp_bits = quantile16<G>(vh, col, a.rank_full, dv);
 
     const BlockCodec codec = block_codec<BV, G, L, MDE>(xp_bits, dm, dv, lane, lig, gshift);
-    encode_into_image16<BM, BV, MDE>(a, ew0, lane, mh, vh, codec, de_base, img_m, img_v,
-                                     words.wm, words.sm, words.wv, words.sv, mc8, vc8);
+    uint32_t m8[2], v8[2];
+    encode16<BM, BV, MDE>(a, ew0, lane, mh, vh, codec, de_base, mw, vw, img_m, img_v, mc8, vc8, m8, v8);
     if (lig == 0) { m_scale[grp] = dm; v_scale[grp] = dv; v_base[grp] = codec.alpha; }
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     __builtin_amdgcn_wave_barrier();
-    words.write_back(a, img_m, img_v, lane);
+    mw.template write_back<true>(img_m, lane, m8);
+    vw.template write_back<true>(img_v, lane, v8);
 }
 
 // The step over one flat buffer, 8 elements per lane: one wavefront per 512 elements, the last
@@ -1776,7 +1768,7 @@ template <int BM, int BV, int B, bool BF16, bool MDE, bool EXT>
 __global__ __launch_bounds__(kWaves * 64, kMinWaves16)
 void chunk16_kernel(const StepArgs a)
 {
-    using Lay = ChunkLayout16<BM, BV, B>;
+    using Lay = ChunkLayout16<BM, BV, B, MDE>;
     static_assert(Lay::kSlab >= ChunkLayout8<BM, BV, B>::kSlab, "one slab serves both forms");
     __shared__ __attribute__((aligned(64))) uint32_t lds_slab[kWaves * Lay::kSlab];
     __shared__ __attribute__((aligned(64))) uint32_t lds_de[de_words<BM, MDE>()];
@@ -1895,7 +1887,7 @@ template <int BM, int BV, int B, bool BF16, bool MDE, bool EXT>
 __global__ __launch_bounds__(kWaves * 64, kMinWaves16)
 void multi_chunk16_kernel(const MultiArgs ma)
 {
-    using Lay = ChunkLayout16<BM, BV, B>;
+    using Lay = ChunkLayout16<BM, BV, B, MDE>;
     __shared__ __attribute__((aligned(64))) uint32_t lds_slab[kWaves * Lay::kSlab];
     __shared__ __attribute__((aligned(64))) uint32_t lds_de[de_words<BM, MDE>()];
     const DeTable<BM, MDE> de(lds_de);

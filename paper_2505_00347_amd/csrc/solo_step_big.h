@@ -60,7 +60,7 @@ struct BigExchange {
     static constexpr int kWords = kList + W * (int)kFewKeys;
 };
 static_assert(288 * 4 <= BigLayout::kStage, "the padded transposition (Stage16) fits a staging area");
-static_assert(ChunkWords16<3, 4>::kImage <= 132, "images");
+static_assert(VarianceCodes16<3>::kImage <= 132, "images");
 
 // Maximum over the 64 lanes of a wavefront (uniform result).
 __device__ __forceinline__ uint32_t wave_max(uint32_t x)
@@ -361,14 +361,17 @@ __device__ __forceinline__ void step_block(const StepArgs &a, const uint64_t blk
     const uint32_t tv_addr = lds_addr(my_tv), tm_addr = lds_addr(my_tm);
 
     // ---- loads: parameters and gradients, the wavefront's code words, the block's scalars
-    ChunkWords16<BM, BV> words;
-    words.load(a, ew0, lane, here);
+    MomentCodes16<BM, MDE> mw;
+    VarianceCodes16<BV> vw;
+    mw.template load<!TAIL>(a.m_words, ew0, lane, here);
+    vw.template load<!TAIL>(a.v_words, ew0, lane, here);
     const float dm_old = a.m_scale[blk], dv_old = a.v_scale[blk], al_old = a.v_base[blk];
     const RawPG16<BF16> raw = load_pg16<BF16>(a, ew0, lane, here);
     const float gscale = (EXT && a.grad_scale) ? *a.grad_scale : 1.0f;
     const Stage16 st(reinterpret_cast<float4 *>(work + wave * BigLayout::kStage), lane);
     de.store();                                    // (read behind the barrier of the maxima)
-    words.stage(img_m, img_v, lane);
+    mw.stage(img_m, lane);
+    vw.stage(img_v, lane);
 
     // ---- level tables of the block (every wavefront its own copy)
     {
@@ -377,13 +380,15 @@ __device__ __forceinline__ void step_block(const StepArgs &a, const uint64_t blk
     }
     wave_lds_sync();
     uint32_t mc8[2], vc8[2];
-    words.codes(img_m, img_v, mc8, vc8);
+    mw.codes(img_m, lane, mc8);
+    vw.codes(img_v, lane, vc8);
+    uint32_t decode8[2] = {mc8[0], mc8[1]};
     if (__builtin_expect(here != kIter16, 0)) {                         // (code L is level 0 of either codebook)
         constexpr uint32_t kZeroCodes = (uint32_t)((uint64_t)L * (((1ull << (8 * BM)) - 1ull) / ((1ull << BM) - 1ull)));
 #pragma unroll
         for (int r = 0; r < 2; ++r) {
             const uint32_t run = mine <= 8u * r ? 0u : umin(mine - 8u * r, 8u), keep = (uint32_t)((1ull << (BM * run)) - 1ull);
-            mc8[r] = (mc8[r] & keep) | (kZeroCodes & ~keep);
+            decode8[r] = (mc8[r] & keep) | (kZeroCodes & ~keep);
         }
     }
 
@@ -400,9 +405,9 @@ __device__ __forceinline__ void step_block(const StepArgs &a, const uint64_t blk
     // ---- dequantize (table look-up), EMA, parameter; new parameters streamed out
     float mh[16], vh[16];
     float m_absmax, v_max;
-    ema_param<16, BM, BV, EXT, false, true>(a, tm_addr, tv_addr, mc8, vc8, nullptr, p, g, mh, vh, m_absmax, v_max);
+    ema_param<16, BM, BV, EXT, false, true>(a, tm_addr, tv_addr, decode8, vc8, nullptr, p, g, mh, vh, m_absmax, v_max);
     store_params16<EXT>(a, ew0, lane, p, st, here);
-    if (__builtin_expect(here != kIter16, 0)) {                         // (kNoKey is a NaN: its code is whatever clear_behind() removes)
+    if (__builtin_expect(here != kIter16, 0)) {                         // (kNoKey is a NaN: its code is whatever encode16() removes)
         v_max = 0.0f;
 #pragma unroll
         for (int j = 0; j < 16; ++j) {
@@ -443,15 +448,13 @@ __device__ __forceinline__ void step_block(const StepArgs &a, const uint64_t blk
     uint32_t de_base = 0;
     if (kDeTable) de_base = lds_addr(de.lds) - 16u * DeBuckets<BM>::kLo;
     const BlockCodec codec = block_codec<BV, 16, L, MDE>(xp_bits, dm, dv, lane, lig, gshift);
-    encode_into_image16<BM, BV, MDE>(a, ew0, lane, mh, vh, codec, de_base, img_m, img_v,
-                                     words.wm, words.sm, words.wv, words.sv, mc8, vc8);
+    uint32_t m8[2], v8[2];
+    encode16<BM, BV, MDE>(a, ew0, lane, mh, vh, codec, de_base, mw, vw, img_m, img_v, mc8, vc8, m8, v8,
+                          here == kIter16, mine);
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     __builtin_amdgcn_wave_barrier();
-    if (__builtin_expect(here != kIter16, 0)) {
-        words.clear_behind(img_m, img_v, ew0, lane, here);
-        wave_lds_sync();
-    }
-    words.write_back(a, img_m, img_v, lane);
+    mw.template write_back<!TAIL>(img_m, lane, m8);
+    vw.template write_back<!TAIL>(img_v, lane, v8);
     if (wave == 0 && lane == 0) { a.m_scale[blk] = dm; a.v_scale[blk] = dv; a.v_base[blk] = codec.alpha; }
 }
 
@@ -462,12 +465,12 @@ __device__ __forceinline__ void step_block(const StepArgs &a, const uint64_t blk
 constexpr int kQuadWaves = kBigBlock / kIter;
 struct QuadLayout {
     static constexpr int kOffImgM = 0;                        // per wavefront: its words of each code stream
-    static constexpr int kOffImgV = ChunkWords8<3, 4, true>::kImage;
+    static constexpr int kOffImgV = LaneCodes8<3, true>::kImage;
     static constexpr int kOffTv = 144;                        // level tables, 64-byte aligned
     static constexpr int kOffTm = 160;
     static constexpr int kSlab = 176;
 };
-static_assert(2 * ChunkWords8<3, 4, true>::kImage <= QuadLayout::kOffTv, "images");
+static_assert(2 * LaneCodes8<3, true>::kImage <= QuadLayout::kOffTv, "images");
 
 template <int BM, int BV, bool BF16, bool MDE, bool EXT, bool TAIL>
 __device__ __forceinline__ void step_block_quad(const StepArgs &a, const uint64_t blk, const uint32_t lane,
@@ -490,8 +493,10 @@ __device__ __forceinline__ void step_block_quad(const StepArgs &a, const uint64_
     for (int j = 0; j < 8; ++j) ok[j] = !TAIL || e0 + j < a.n;
 
     // ---- every load is issued before the first one is waited for; the histogram is cleared meanwhile
-    ChunkWords8<BM, BV, TAIL> words;
-    words.load(a, ew0, lane);
+    LaneCodes8<BM, TAIL> mw;
+    LaneCodes8<BV, TAIL> vw;
+    mw.load(a.m_words, a.n, ew0, lane);
+    vw.load(a.v_words, a.n, ew0, lane);
     const float dm_old = a.m_scale[blk], dv_old = a.v_scale[blk], al_old = a.v_base[blk];
     const RawPG raw = load_pg<BF16, TAIL>(a, e0, ok[7]);
     const float gscale = (EXT && a.grad_scale) ? *a.grad_scale : 1.0f;
@@ -501,14 +506,14 @@ __device__ __forceinline__ void step_block_quad(const StepArgs &a, const uint64_
         for (uint32_t i = 0; i < 512u / (64u * kQuadWaves); ++i) z[wave * 64u + lane + 64u * kQuadWaves * i] = make_uint4(0, 0, 0, 0);
     }
     de.store();
-    words.stage(img_m, img_v, lane);
+    mw.stage(img_m, lane);
+    vw.stage(img_v, lane);
     {
         const float de_level = MDE ? DeLevels<BM>::level(lane) : 0.0f;
         fill_level_tables<BM, BV, MDE, 64>(my_tv, my_tm, lane, dm_old, dv_old, al_old, &de_level);
     }
     wave_lds_sync();
-    uint32_t mc8, vc8;
-    words.codes(img_m, img_v, mc8, vc8);
+    const uint32_t mc8 = mw.codes(img_m, lane), vc8 = vw.codes(img_v, lane);
     const uint32_t floor = key_floor<BV, EXT>(a, my_tv);
     __syncthreads();                               // (the histogram is cleared, the DE table is there)
 
@@ -549,10 +554,12 @@ __device__ __forceinline__ void step_block_quad(const StepArgs &a, const uint64_
     uint32_t xi_word[1];
     XiGroups(a, ew0).words<1>(a, lane, xi_word);
     encode_run<BM, BV, MDE, TAIL>(a, xi_word[0], mh, vh, ok, codec, de_base, m8, v8);
-    xor_into_image8<BM, BV>(img_m, img_v, words.wm, words.sm, words.wv, words.sv, mc8 ^ m8, vc8 ^ v8);
+    mw.change(img_m, lane, mc8, m8);
+    vw.change(img_v, lane, vc8, v8);
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     __builtin_amdgcn_wave_barrier();
-    words.write_back(a, img_m, img_v, lane);
+    mw.write_back(img_m, lane, m8);
+    vw.write_back(img_v, lane, v8);
     if (wave == 0 && lane == 0) { a.m_scale[blk] = dm; a.v_scale[blk] = dv; a.v_base[blk] = codec.alpha; }
 }
 
