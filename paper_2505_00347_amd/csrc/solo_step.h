@@ -5,7 +5,7 @@
 // (step_chunk8).  A block of 128 (64) elements is held by 8 (4) or 16 (8) neighbouring lanes, i.e.
 // by half a DPP row or a row, and every per-block reduction is a few DPP steps.  Nothing is shared
 // between wavefronts but a constant table: the only workgroup barrier, with dynamic-exponent codes
-// of 3 and 4 bits, waits for that table while the elements' loads are under way.  No software prefetch: 60-100 registers leave room for five to seven
+// of 3 and 4 bits, waits for that table while the elements' loads are under way.  No software prefetch: 60-90 registers leave room for five to seven
 // wavefronts per SIMD, which hide each other's memory latency, and the whole machine sweeps one
 // compact window of memory.
 //
@@ -27,23 +27,27 @@
 // (layout transposition, level tables, EMAs and parameter, encoders, code words) exist once, as
 // inlined helpers in front of them.
 //
-// The kernel is bound by vector-ALU issue as much as by HBM: packed FP32 is off, so a CU retires 64
-// lane-operations per clock; 16 per lane issues 58 vector instructions per parameter (2-bit/3-bit bf16),
-// which is as long as its bytes take.  Everything below is shaped by instruction count:
+// Large launches are bound by HBM, those of 10^6 to 10^8 elements by HBM, the last-level cache and vector issue alike,
+// shorter ones by the latency of a wavefront, where every instruction counts.  What one costs (cycles of issue of a wavefront,
+// measured with eight per SIMD): an fp32 add, multiplication or fused multiply-add, and / or / xor / bitop3, a right
+// shift and an integer add 2.3-2.7, with a scalar register as an operand 4.4, a transcendental function 8.3, everything else
+// 4.3.  (Packed FP32 is off.)  Everything below is shaped by that:
 //   * both dequantizers are table look-ups: the lanes of a group compute the
 //     block's level tables (alpha^q * Delta_v, (c-L) * Delta_m/L) once and park
-//     them in LDS; an element costs one bit-field extract, one address add and
-//     one ds_read per moment;
+//     them in LDS; an element costs one shift, one bitop3 and
+//     one ds_read per moment; the launch's constants are in vector registers;
 //   * the p-quantile is exact: each lane sorts its 8 or 16 values with min3/med3/max3
-//     and merges, and the group runs r rounds of "row minimum by DPP, the
+//     and merges, and the group runs rounds of "row minimum by DPP, the
 //     lowest lane that holds it pops its column"; four scalar instructions pick
-//     that lane for all groups, ties or not;
+//     that lane for all groups, ties or not; 16 per lane keeps the eight smallest of a lane for small ranks and
+//     pops two of them at a time while the rank allows it;
 //   * the two per-block divisions share one IEEE division sequence (even lanes
 //     divide x_p by Delta_v, odd lanes L by Delta_m);
 //   * the base alpha = rho^(1/K) is found by testing 16 consecutive binary32
 //     candidates around a hardware exp2/log2 guess, spread over the group's lanes;
-//   * codes are rounded in the float domain and accumulated with FMAs
-//     (acc += code * 2^(b j)); xi is built as a float in [1, 2) by one
+//   * 1st-moment codes are rounded by adding 1.5 * 2^23 and accumulated by shift and add; two 2nd-moment
+//     codes share a conversion to binary16 that rounds down, a minimum and a dot product;
+//   * xi is built as a float by one
 //     bit-align of the element's finalized word of the xi stream (one hash
 //     per 8 elements gives a start and a stride, every word is then mixed
 //     on its own).
@@ -65,7 +69,7 @@ constexpr int kIter = 512;         // elements of a chunk with 8 per lane
 constexpr int kIter16 = 1024;      // elements of a chunk with 16 per lane
 constexpr int kWaves = 4;          // wavefronts per workgroup
 constexpr int kMinWaves = 5;       // wavefronts per SIMD that the register allocator must leave room for, 8 elements per lane
-constexpr int kMinWaves16 = 4;     // and 16 per lane (70-80 registers, i.e. six, in most formats)
+constexpr int kMinWaves16 = 4;     // and 16 per lane (70-80 registers, i.e. six, in most formats; forcing six spills in the others)
 constexpr int kColStride16 = 18;   // words per lane of the sorted columns (16 keys, two +inf; written 8 bytes at a time)
 constexpr float kTiny = 0x1p-100f; // block maxima below this are stored as 0
 constexpr float kRhoMin = 0x1p-64f;
@@ -601,12 +605,13 @@ constexpr int de_words() { return MDE && BM >= 3 ? 4 * DeBuckets<BM>::N : 16; }
 // 2-bit/3-bit bf16 5.36 | 5.93), so no line is drawn there.  Further up the fewer
 // instructions of 16 decide: with bf16 gradients, where 8 saves the fewer layout transpositions, behind
 // 3 * 2^19 elements (with a copy, which 8 writes in half-covered requests, 5 * 2^18), with fp32 ones behind
-// 9 * 2^19 (one state again and again, at 5 * 2^20: 15.2 | 14.2, AdaBelief 15.7 | 14.5, B 64 14.9 | 13.7); earlier with a large rank, whose rounds cost 8 twice the
+// 5 * 2^20 (a tie there over states in turn; 24 * 2^18: 19.2 | 18.5, 18.2 | 18.1, 18.9 | 19.4, AdaBelief 19.6 | 18.8; one state
+// again and again 8 falls behind earlier, 15.2 | 14.2 at 5 * 2^20); earlier with a large rank, whose rounds cost 8 twice the
 // instructions.  (No line is within 3 % of a size for every format.)
 constexpr bool narrow_buffer(uint64_t n, bool bf16, bool copy, uint32_t rank)
 {
     if (rank > 24) return n <= 1ull << 19;
-    if (!bf16) return n <= 9ull << 19;
+    if (!bf16) return n <= 5ull << 20;
     return n <= (copy ? 5ull << 18 : 3ull << 19);
 }
 // Up to how many pieces (pieces16) a table does.

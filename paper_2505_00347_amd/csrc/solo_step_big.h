@@ -11,13 +11,14 @@
 //   * Delta_m' and Delta_v' are maxima over the wavefronts: DPP inside a row, four lane reads
 //     across the rows, a few words of LDS and one barrier across the wavefronts;
 //   * the p-quantile is the rank-205 element of 2048 values (p = 0.1), far too deep for rounds
-//     of "extract the minimum".  It is found by histograms over ever narrower ranges of the bit
-//     patterns and, once a few keys are left, by comparing those (select_rank);
+//     of "extract the minimum".  It is found by histograms, first over what lies right above a bound that the
+//     old state gives, then over ever narrower ranges of the bit
+//     patterns, and, once a few keys are left, by comparing those (select_rank);
 //   * the base alpha, the divisions and the level tables are computed by every wavefront (every
 //     16 lanes) for itself: cheaper than another barrier.
-// The kernel is bound by vector-ALU issue and, through the number of workgroups on a CU, by LDS
+// The number of workgroups on a CU is bound by LDS
 // (an earlier form: 17.3 ms for 6.7e9 parameters at 3.5 wavefronts per SIMD, 15.7 ms at 5), so the histogram is
-// kept small: see BigLayout.  Every wavefront stages and writes back the words of its own elements
+// kept small: see BigLayout.  (What the selection costs: a layer of the 7B shapes, 2-bit/3-bit, 377 us, 330 without any.)  Every wavefront stages and writes back the words of its own elements
 // (whole 128-byte lines for 2- and 4-bit codes; ten-to-a-word codes by one atomic XOR per word at
 // the memory side, since a wavefront's share does not end on a word).
 #pragma once
@@ -235,7 +236,11 @@ __device__ __forceinline__ uint32_t largest_key(const uint32_t *const xch)
 // kFewKeys are left, every wavefront compares those with each other instead: mostly after one pass on a trained state,
 // after two on scattered values.  Elements without a gradient share the
 // few decoded values: then, after the first pass, one of the keys that are left is tried as it is.
-// A rank below the first pass's range (28 octaves under the maximum, or zeros) starts over from 0.
+// A rank below that pass's range (28 octaves under the maximum, or zeros) starts over from 0.
+// (Against a first pass over the 28 octaves, in turn, us: a layer of the 7B shapes 444 -> 377, as a table 472 -> 399, 2^26
+// elements 4-bit/2-bit DE fp32 with a copy 203 -> 182, 4.2 million 15.96 -> 14.77; 2^25 elements over four formats, quantiles from
+// 0.05 to 0.5 and idle rows 1.07 to 1.30 times as fast, without a state 1.03.  Before that, four fixed passes over
+// 8 + 8 + 8 + 7 bits took 6 % longer than the 28 octaves on scattered values, 45 % with nine of ten gradients at zero.)
 // BARRIER: whether the exchange's maxima still need one.
 template <int NK, int W, bool BARRIER>
 __device__ __forceinline__ uint32_t select_rank(const uint32_t (&key)[NK], const uint32_t floor, const uint32_t rank,
@@ -461,7 +466,7 @@ __device__ __forceinline__ void step_block(const StepArgs &a, const uint64_t blk
 // The same by four wavefronts, 8 consecutive elements per lane, where a launch is all latency: half
 // as long a chain in every lane, and parameters and gradients that are not turned around through
 // LDS.  TAIL: the shorter last block, with bounds checks.  (1000 elements, 2-bit/3-bit bf16: 8.8 us by
-// the two wavefronts with bounds checks on every element, 5.7 by this form; 1,000,003: 9.7 and 7.9.)
+// the two wavefronts with bounds checks on every element, 5.4 by this form; 1,000,003: 9.7 and 7.1.)
 constexpr int kQuadWaves = kBigBlock / kIter;
 struct QuadLayout {
     static constexpr int kOffImgM = 0;                        // per wavefront: its words of each code stream
