@@ -116,6 +116,7 @@ static void step_scalars(StepArgs &a, const solo_config *cfg, uint64_t step)
     a.decay = coupled ? 1.0f : (float)(1.0 - (double)cfg->lr * (double)cfg->weight_decay);
     a.l2 = coupled ? cfg->weight_decay : 0.0f;
     a.belief = belief ? 1u : 0u;
+    a.settled = 1.0 - (double)cfg->beta2 <= 0.1001 * bc2 ? 1u : 0u;    // (0.9 as binary32 included)
     a.eps_state = belief ? cfg->eps : 0.0f;
     // p <- p * decay - m^ / (sqrt(v^) * denom_scale + denom_eps): the step size lr / bc1 is folded
     // into the denominator; a step size too small to divide by (|.| < 2^-100) means no update

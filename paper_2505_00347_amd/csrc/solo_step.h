@@ -101,6 +101,7 @@ struct StepArgs {
     float l2;               // Adam with coupled decay: weight_decay, g <- g + l2 * p; otherwise 0
     float eps_state;        // AdaBelief: eps, added to the 2nd EMA itself at every step
     uint32_t belief;        // AdaBelief: the 2nd EMA follows (g - m^)^2 instead of g^2
+    uint32_t settled;       // the newest gradient is a small part of the 2nd EMA (blocks of 2048: key_floor())
 };
 
 // One tensor of a multi-tensor launch, as the kernel reads it from the caller's table

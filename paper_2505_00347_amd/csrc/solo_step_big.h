@@ -311,14 +311,16 @@ __device__ __forceinline__ uint32_t select_rank(const uint32_t (&key)[NK], const
 }
 
 // What the old state's smallest level becomes without a gradient, in the steps of ema_param(): no key is
-// smaller (but by rounding, where the base is next to 1).  0 for a block without a state, and for a beta2 so small
-// that the gradients carry the quantile out of the first pass's quarter octave: 2^25 elements, 2-bit/3-bit bf16, with | without
-// the floor, us: beta2 0.9 70 | 83, 0.85 85 | 87, 0.8 92 | 77, 0.5 80 | 74.
+// smaller (but by rounding, where the base is next to 1).  0 for a block without a state, and where the newest gradient is so
+// large a part of the 2nd EMA, (1 - beta2) / (1 - beta2^t), that it carries the quantile out of the first pass's
+// quarter octave: in the first steps and with a small beta2.  2^25 elements, 2-bit/3-bit bf16, late steps, with | without
+// the floor, us: beta2 0.9 70 | 83, 0.85 85 | 87, 0.8 92 | 77, 0.5 80 | 74; beta2 0.999, steps 7-9 of a fresh state
+// 82 | 73, 10-12 73 | 74, 13-16 65 | 74.  So the line lies at 0.1.
 template <int BV, bool EXT>
 __device__ __forceinline__ uint32_t key_floor(const StepArgs &a, const float *const my_tv)
 {
     const float low = my_tv[(1 << BV) - 1], key = a.beta2 * low;
-    return (uint32_t)__builtin_amdgcn_readfirstlane((int)(low > 0.0f && a.beta2 >= 0.85f ? f2u(EXT ? key + a.eps_state : key) : 0u));
+    return (uint32_t)__builtin_amdgcn_readfirstlane((int)(low > 0.0f && a.settled ? f2u(EXT ? key + a.eps_state : key) : 0u));
 }
 
 // Elements of block `blk` that exist, and the rank of the quantile among them.
@@ -658,14 +660,15 @@ void multi_big_quad_kernel(const MultiArgs ma)
 #undef SOLO_BIG_LDS
 
 // Up to how many blocks a launch gives four wavefronts to each: up to four workgroups on a CU the time is the
-// chain of one block, behind that the two-wavefront form has the fewer instructions.  Measured on MI355X,
+// chain of one block, behind that the two-wavefront form has the fewer instructions and reads whole lines.  Measured on MI355X,
 // us per launch, four | two wavefronts per block:
-//   blocks                             1            128          488          1000           2000           5000
-//   2-bit/3-bit bf16                   5.51 | 6.69  6.36 | 7.43  7.83 | 8.93  10.38 | 10.48  16.75 | 15.05  34.4 | 27.7
-//   2-bit/3-bit AdaBelief fp32         5.86 | 7.50  6.79 | 8.24  8.24 | 9.81  10.95 | 11.34  17.94 | 16.23  36.2 | 30.4
-//   4-bit/2-bit DE fp32                6.05 | 7.27  7.02 | 8.19  8.43 | 9.96  11.33 | 11.50  18.09 | 17.01  35.4 | 32.0
-//   2-bit/2-bit bf16, p 0.3            5.66 | 7.08  6.82 | 8.10  8.26 | 9.80  11.07 | 11.57  17.66 | 16.82  34.4 | 31.3
-//   4000 tensors of 1000 elements (a block each): 27 | 42, so a table of which at least three in four
+//   blocks                             1            128          488          1000           1500           2000           5000
+//   2-bit/3-bit bf16                   4.61 | 5.98  5.46 | 6.74  6.55 | 8.15  9.26 | 9.03    11.91 | 12.59  14.03 | 14.03  25.2 | 25.0
+//   2-bit/3-bit AdaBelief fp32         4.87 | 7.08  5.56 | 7.76  6.71 | 9.17  10.10 | 10.36  12.60 | 14.28  15.03 | 16.11  27.6 | 29.0
+//   4-bit/2-bit DE fp32                5.04 | 6.81  6.26 | 7.65  7.26 | 8.98  10.66 | 10.71  13.04 | 14.40  15.53 | 16.29  28.4 | 29.0
+//   2-bit/2-bit bf16, p 0.3            5.08 | 6.81  6.15 | 7.63  7.23 | 8.96  9.94 | 9.91    12.61 | 13.37  15.08 | 15.23  25.8 | 26.9
+//   (three states in turn.  From 1000 blocks on the two are close: four lead by up to 12 % at 1500 blocks, two by 3 % at 1000.)
+//   4000 tensors of 1000 elements (a block each): 27 | 42 with earlier kernels, so a table of which at least three in four
 //   blocks are the only one of their tensor takes four at any size.
 constexpr uint64_t kQuadUpTo = 1024;
 constexpr bool quad_table(uint64_t blocks, uint64_t tensors) { return blocks <= kQuadUpTo || 4 * blocks <= 5 * tensors; }

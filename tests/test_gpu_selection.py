@@ -1,10 +1,13 @@
 """The selection of the kernels with 16 elements per lane where a lane holds more of a block's smallest values than the
 shortened columns keep, around the ranks at which its forms change, against the kernels with 8 per lane
-(compared with the oracle elsewhere): the same inputs leave the same bytes."""
+(compared with the oracle elsewhere): the same inputs leave the same bytes.  And the selection in blocks of 2048 from the bound
+that the old state gives, against the oracle."""
+import numpy as np
 import pytest
 
+from parity_common import compare_step, flip_budget, make_cfgs
 from test_gpu_both_forms import PIECE
-from test_gpu_parity import gpu  # noqa: F401
+from test_gpu_parity import GpuSide, dev, gpu  # noqa: F401
 from test_gpu_table_forms import bits
 
 pytestmark = pytest.mark.gpu
@@ -43,3 +46,27 @@ def test_crowded_lanes(gpu, B, rank):  # noqa: F811
     torch.cuda.synchronize()
     for x, y in zip((sides[0][0], *sides[0][1]), (sides[1][0], *sides[1][1])):
         assert torch.equal(bits(x), bits(y))
+
+
+@pytest.mark.parametrize("p", (0.05, 0.1, 0.3, 0.97))
+@pytest.mark.parametrize("blocks,opt", [(5, "adamw"), (5, "adabelief"), (1027, "adamw")])
+def test_bound_of_the_old_state(so, gpu, blocks, opt, p):  # noqa: F811
+    """Late step numbers on a state (the bound is used then): quantiles right above the bound, beyond the first pass's
+    quarter octave (gradients that jump), on it (idle blocks), and blocks that have no state yet."""
+    from paper_2505_00347_amd import synth
+    n = blocks * 2048 + 77
+    oc, gc = make_cfgs(so, gpu, 2, 3, 2048, False, p=p, optimizer=opt, eps=1e-12 if opt == "adabelief" else 1e-8)
+    rng = np.random.default_rng(blocks)
+    kind = np.arange(n) // 2048 % 5
+    prm, st = synth.make_params(n), so.State(n, oc)
+    side = GpuSide(gpu, n, gc)
+    flips = 0
+    for k, step in enumerate((1, 8, 60, 1000, 1001)):
+        x = rng.standard_normal(n).astype(np.float32) * np.float32(1e-3)
+        g = np.where(kind == 1, x * (k == 0), np.where(kind == 2, x * 1000.0 ** (k % 2), np.where(kind == 3, x * (k >= 3), x))).astype(np.float32)
+        side.load(prm, st)
+        side.step(dev(g), step)
+        before = prm.astype(np.float64)
+        margin = so.step_packed(prm, g, st, step, oc, want_margin=True, threads=8)
+        flips += compare_step(so, oc, n, prm, st, margin, side.fetch(), 1e-6, 2e-6 * oc.lr, p_before=before)
+    assert flips <= flip_budget(5 * n)
