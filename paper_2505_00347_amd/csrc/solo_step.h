@@ -560,12 +560,14 @@ __device__ __forceinline__ RawPG load_pg(const StepArgs &a, const uint64_t e0, c
 // conversions, left shifts and DPP among it, takes 4.3 in any case, the transcendental functions 8.3).
 // The moments of an element had six such operands: with them in vector registers, and the two table addresses
 // by bitop3, the 1024 elements of a wavefront take 3414 instead of 3616 cycles of issue (2-bit/3-bit bf16).
-template <typename T>                     // (a template: the host compiler does not know the constraint)
-__device__ __forceinline__ T in_vector(const T x)
+// (The block of assembly is empty and only hides that the value is the constant: the move in front of it is the
+// compiler's own, which keeps the two wait states behind a vector instruction that writes the scalar register, a lane
+// read that reloads a spilled one for instance.  Those it does not keep for a move inside the block.)
+template <typename T>
+__device__ __forceinline__ T in_vector(T x)
 {
-    T v;
-    asm("v_mov_b32 %0, %1" : "=v"(v) : "s"(x));
-    return v;
+    asm("" : "+v"(x));
+    return x;
 }
 
 // Wave-level ordering point for LDS traffic between lanes of one wavefront (LDS executes a
