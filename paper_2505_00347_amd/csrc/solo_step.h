@@ -492,9 +492,10 @@ __device__ __forceinline__ uint4 stream_load_u4(const void *p)
 // Streaming stores are non-temporal and written through at device scope (sc1): the data leaves
 // the L2 at once instead of waiting for an eviction, which drains the write stream more evenly
 // (0.5-1 % on the whole step over a plain non-temporal store).
-// (Written as assembly because no builtin sets sc1.  The s_nop covers the two wait states that a
-// store of more than 64 bits needs before its data registers may be overwritten: the compiler
-// keeps that distance for its own stores but does not look inside an asm block.)
+// (Written as assembly because no builtin sets sc1.  The compiler keeps the distances that its own stores need but does not
+// look inside an asm block: the s_nop in front is the five wait states between a vector instruction that
+// writes a scalar register, a lane read for instance, and an access of memory that reads it as its base; the one behind is the
+// two that a store of more than 64 bits needs before its data registers may be overwritten.)
 // `base`: uniform over the wavefront; `at`: bytes behind it, per lane; OFFSET: of the instruction.  (One
 // 32-bit register per lane addresses all stores of a chunk, instead of a 64-bit address for each.)
 template <int OFFSET>
@@ -503,7 +504,7 @@ __device__ __forceinline__ void stream_store_f4(void *const base, const uint32_t
     static_assert(OFFSET >= 0 && OFFSET < 4096, "offset of a global access");
     const u32x4_t v = {__builtin_bit_cast(uint32_t, x.x), __builtin_bit_cast(uint32_t, x.y),
                        __builtin_bit_cast(uint32_t, x.z), __builtin_bit_cast(uint32_t, x.w)};
-    asm volatile("global_store_dwordx4 %0, %1, %2 offset:%3 sc1 nt\n\ts_nop 1" ::"v"(at), "v"(v), "s"(base), "n"(OFFSET) : "memory");
+    asm volatile("s_nop 4\n\tglobal_store_dwordx4 %0, %1, %2 offset:%3 sc1 nt\n\ts_nop 1" ::"v"(at), "v"(v), "s"(base), "n"(OFFSET) : "memory");
 }
 
 // Two binary32 values rounded to bfloat16 (nearest, ties to even: the hardware conversion),

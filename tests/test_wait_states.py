@@ -1,6 +1,6 @@
 """Wait states that MI355X asks for and that the compiler keeps for its own instructions but not around those inside an
-asm block: two between a vector instruction that writes a scalar register (a lane read reloads a spilled one) and a vector
-instruction that reads it.  Looked for in the device code of the built library, and in small kernels
+asm block: behind a vector instruction that writes a scalar register (a lane read reloads a spilled one), two in front of
+a vector instruction that reads it, five in front of an access of memory that does.  Looked for in the device code of the built library, and in small kernels
 in which nothing stands between the two."""
 import os
 import re
@@ -12,7 +12,7 @@ import pytest
 from paper_2505_00347_amd import build as libbuild
 
 OBJDUMP = "/opt/rocm/llvm/bin/llvm-objdump"
-VECTOR_READ = 2
+VECTOR_READ, MEMORY_READ = 2, 5
 WRITES = re.compile(r"\tv_(?:read(?:first)?lane_b32 (s\d+|vcc_lo|vcc_hi),|cmp_\w+ (s\[\d+:\d+\]),)")
 SCALARS = re.compile(r"\bs\[(\d+):(\d+)\]|\bs(\d+)\b|\b(vcc_lo|vcc_hi)\b")
 
@@ -37,8 +37,8 @@ def too_close(listing):
         if not wrote:
             continue
         left, passed = scalars(wrote.group(1) or wrote.group(2)), 0
-        for after in lines[k + 1:k + 8]:
-            if passed >= VECTOR_READ or not left:
+        for after in lines[k + 1:k + 12]:
+            if passed >= MEMORY_READ or not left:
                 break
             if not after.startswith("\t"):
                 continue
@@ -47,9 +47,11 @@ def too_close(listing):
             if name == "s_nop":
                 passed += int(operands, 0) + 1
                 continue
-            if name.startswith("v_") and left & scalars(sources):
+            memory = name.startswith(("global_", "flat_", "scratch_", "buffer_"))
+            need = MEMORY_READ if memory else VECTOR_READ if name.startswith("v_") else 0
+            if passed < need and left & scalars(operands if memory else sources):
                 found.append((kernel, line.strip(), after.strip(), passed))
-            if not name.startswith(("ds_", "global_", "scratch_", "buffer_")):
+            if not memory and not name.startswith("ds_"):
                 left -= scalars(results)
             passed += 1
     return found
@@ -76,6 +78,9 @@ def test_the_scan_sees_what_it_looks_for():
     assert [x[3] for x in too_close(write + nop % 0 + move)] == [1]
     assert not too_close(write + nop % 1 + move)
     assert not too_close(write + "\ts_add_u32 s9, s9, s8\n" + move)
+    store = "\tglobal_store_dwordx4 v0, v[2:5], s[8:9] offset:1024\n"
+    assert [x[3] for x in too_close(write + nop % 3 + store)] == [4]
+    assert not too_close(write + nop % 4 + store)
     assert len(too_close("\tv_cmp_gt_u32_e64 s[8:9], v1, v2\n" + move)) == 1
 
 
@@ -101,6 +106,11 @@ __global__ void constant_in_vector(float *out, const float *in)
     const float x = u2f((uint32_t)__builtin_amdgcn_readfirstlane((int)f2u(in[threadIdx.x])));
     out[threadIdx.x] = in_vector(x);
 }
+__global__ void streamed(float *const *out)
+{
+    float *const base = (float *)uniform64((uint64_t)out[threadIdx.x]);
+    stream_store_f4<0>(base, threadIdx.x * 16u, make_float4(1.0f, 2.0f, 3.0f, 4.0f));
+}
 """
 
 
@@ -113,7 +123,7 @@ def compiled(text, tmp_path):
     return listing.read_text()
 
 
-def test_constant_in_vector(tmp_path):
+def test_helpers_behind_a_lane_read(tmp_path):
     listing = compiled(PROBE, tmp_path)
-    assert "v_readfirstlane_b32" in listing
+    assert listing.count("\tv_readfirstlane_b32") >= 3 and "global_store_dwordx4" in listing
     assert not too_close(listing)
