@@ -61,7 +61,7 @@ def step_kernel_name(w, n, mp, launch):
     elif bf16:
         up_to = 5 << 18 if mp else 3 << 19
     else:
-        up_to = 5 << 20
+        up_to = 11 << 19
     return f"solo::chunk{8 if n <= up_to else 16}_kernel"
 
 

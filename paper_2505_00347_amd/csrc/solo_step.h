@@ -606,16 +606,42 @@ constexpr int de_words() { return MDE && BM >= 3 ? 4 * DeBuckets<BM>::N : 16; }
 // and two of half as large wavefronts with 8; a little more is two rounds against three shorter ones.
 // 16 is up to 6 % ahead at that one size over states that come out of the last-level cache, as here, but
 // behind by 10 % where the state is still in the L2 (one state again and again, 4-bit/4-bit fp32 5.23 | 5.76,
-// 2-bit/3-bit bf16 5.36 | 5.93), so no line is drawn there.  Further up the fewer
-// instructions of 16 decide: with bf16 gradients, where 8 saves the fewer layout transpositions, behind
-// 3 * 2^19 elements (with a copy, which 8 writes in half-covered requests, 5 * 2^18), with fp32 ones behind
-// 5 * 2^20 (a tie there over states in turn; 24 * 2^18: 19.2 | 18.5, 18.2 | 18.1, 18.9 | 19.4, AdaBelief 19.6 | 18.8; one state
-// again and again 8 falls behind earlier, 15.2 | 14.2 at 5 * 2^20); earlier with a large rank, whose rounds cost 8 twice the
-// instructions.  (No line is within 3 % of a size for every format.)
+// 2-bit/3-bit bf16 5.36 | 5.93), so no line is drawn there.  Further up it depends on where the buffers lie: out of HBM the
+// whole lines and non-temporal accesses of 16 decide, out of the last-level cache the layout transpositions that 8 saves, and
+// again and again on the same buffers the instructions of 16, which are fewer.  Time of 8 over time of 16, geometric mean over
+// four to ten formats and variants:
+//   elements / 2^18         5     6     6.5   8     8.25  10    12    14    16
+//   bf16, 1.3 GB in turn    1.00  1.00  1.07  1.11  1.04  1.06  1.11  1.09  1.14
+//     three in turn         0.86  0.90  1.01  1.10  1.04  1.03  1.09  0.99  1.04
+//     one again and again   0.85  0.86  0.96  0.97  0.93  0.94  1.02  0.95  1.02
+//   bf16, rank 18-24, 1.3 GB 1.04 1.04  1.12  1.16  1.09  1.10  1.15
+//     three in turn         0.91  0.95  1.05  1.16  1.09  1.08  1.14
+//     one again and again   0.90  0.92  1.01  1.02  0.98  0.99  1.07
+//   bf16, copy, 1.3 GB      1.08  1.10  1.20  1.21  1.12  1.10
+//     three in turn         0.90  0.96  1.07  1.16  1.10  1.06
+//     one again and again   0.89  0.92  1.01  1.04  0.99  0.97
+//   fp32, elements / 2^18   14    16    17    18    19    20    20.5  21    22    23    24    25    26    28    32
+//     1.3 GB in turn        1.07  1.17  1.06  1.08  1.10  1.11  1.06  1.06  1.08  1.10  1.11  1.07  1.10  1.10  1.10
+//     six states in turn    0.94  0.97  0.92  0.95  0.98  1.01  0.96  0.96  0.99  1.00  1.02  0.99  1.03  1.05  1.10
+//     three in turn         0.98  0.99  0.92  0.93  0.95  0.97  0.92  0.91  0.93  0.95  0.95  0.93  0.94  0.93  0.94
+//     one again and again   0.93  1.00  0.94  0.98  1.04  1.08  1.01  1.01  1.04  1.06  1.07  1.01  1.04  1.03  1.02
+//     mean of the four      0.98  1.03  0.96  0.99  1.02  1.04  0.98  0.98  1.01  1.02  1.04  1.00  1.02  1.02  1.04
+//   fp32, copy              14    16    17    18    19    20    20.5  21    22    23    24    25    26    28    32
+//     1.3 GB in turn        1.11  1.16  1.07  1.11  1.12  1.13  1.07  1.08  1.10  1.11  1.11  1.09  1.10  1.10  1.11
+//     six states in turn    0.93  1.00  0.96  0.98  1.00  1.03  0.97  0.99  1.02  1.04  1.07  1.06  1.09  1.10  1.11
+//     three in turn         0.94  0.94  0.88  0.92  0.93  0.94  0.88  0.89  0.90  0.91  0.91  0.89  0.92  0.94  0.98
+//     one again and again   0.93  0.99  0.91  0.96  1.01  1.04  0.98  0.97  0.99  1.00  1.01  0.96  0.99  0.96  0.96
+//     mean of the four      0.98  1.02  0.95  0.99  1.01  1.03  0.97  0.98  1.00  1.01  1.02  1.00  1.02  1.02  1.04
+// A line lies where the mean crosses for good.  With bf16 gradients that is behind 3 * 2^19 elements (with a copy at
+// 5 * 2^18, where six states in turn tie; the three rows here would put it at 3 * 2^19, too).  With fp32 ones the mean goes to and fro between 14 and
+// 22 * 2^18, as 16 per lane needs one more wavefront per SIMD behind every 2^20 elements (0.95 right behind 16, 1.04 at 20, 0.98 right behind it); from
+// 11 * 2^19 on 16 is ahead, with and without a copy.  In that range the line costs a state out of HBM up to 11 % and saves one out of
+// the last-level cache 3 to 9 %.  With a large rank, whose rounds cost 8 twice the instructions, the line lies at 2^19.
+// (No line is within 3 % of a size for every format.)
 constexpr bool narrow_buffer(uint64_t n, bool bf16, bool copy, uint32_t rank)
 {
     if (rank > 24) return n <= 1ull << 19;
-    if (!bf16) return n <= 5ull << 20;
+    if (!bf16) return n <= 11ull << 19;
     return n <= (copy ? 5ull << 18 : 3ull << 19);
 }
 // Up to how many pieces (pieces16) a table does.
