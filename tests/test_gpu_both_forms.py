@@ -1,8 +1,11 @@
 """Every instantiation of the kernels with 16 elements per lane against those with 8, which the other GPU tests
 compare with the oracle: the same inputs leave the same bytes.  A flat buffer in one call runs the first, in
 pieces of 512,000 elements the second; a table of a million elements the first, its tensors one by one the second."""
+import math
+
 import pytest
 
+from test_dispatch_lines import PIECES8, last8
 from test_gpu_parity import gpu  # noqa: F401
 from test_gpu_table_forms import bits, table_against_flat
 
@@ -33,10 +36,9 @@ def gradients(n, B, gen, dtype):
 @pytest.mark.parametrize("k,bm,bv,B", [(k, *f) for k, f in enumerate(FORMATS)])
 def test_flat(gpu, k, bm, bv, B, bf16, de, ext):  # noqa: F811
     import torch
-    large = ((5 << 18) if ext else (3 << 20)) if bf16 else 6 << 20        # the 8-per-lane kernels' largest buffer
     dtype = torch.bfloat16 if bf16 else torch.float32
-    for j, (p, above) in enumerate(((0.1, large), (0.45, 1 << 19))):      # (ranks above 24 have a line of their own)
-        n = above + 2048 + ENDS[(2 * k + j) % len(ENDS)]
+    for j, p in enumerate((0.1, 0.45)):
+        n = last8(bf16, ext, math.ceil(p * B)) + 2048 + ENDS[(2 * k + j) % len(ENDS)]
         flags = 1 | (2 if de else 0) | ((4, 8)[j] if ext else 0)          # AdaBelief, coupled decay
         off = 8 * ((1 << 32) - 700)
 
@@ -69,5 +71,5 @@ def test_flat(gpu, k, bm, bv, B, bf16, de, ext):  # noqa: F811
 def test_table(gpu, k, bm, bv, B, bf16, de, ext):  # noqa: F811
     ends = ENDS[k % len(ENDS):] + ENDS[:k % len(ENDS)]
     sizes = [300 * 1024 + ends[0], 1, 5120 + ends[1], 2560, 400 * 1024 + ends[2], 7680 + ends[3], 200 * 1024 + ends[4], 77]
-    assert all(n <= PIECE for n in sizes) and sum(n // 1024 for n in sizes) > 3 << 8
+    assert all(n <= PIECE for n in sizes) and sum(n // 1024 for n in sizes) > PIECES8
     table_against_flat(gpu, sizes, bm, bv, B, bf16, de, flags=4 if ext else 0, mp=ext, p=(0.1, 0.3)[k % 2], steps=3)

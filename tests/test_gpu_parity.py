@@ -6,6 +6,7 @@ the named configurations at their full sizes are in test_gpu_protocol.py.
 import numpy as np
 import pytest
 
+from test_dispatch_lines import PIECES8, QUAD_BLOCKS
 from parity_common import (TILE, FLIP_MARGIN, FLIP_RATE, flip_budget, flip_allowance, dev, host_words,
                            make_cfgs, bits_equal, compare_step, note)
 
@@ -33,7 +34,7 @@ class GpuSide:
         # test's size, or a table of it alone, runs those with 8)
         self.multi = multi
         if multi:
-            k = 1025 * 2048
+            k = max((QUAD_BLOCKS + 1) * 2048, (PIECES8 + 1) * 1024)
             self.second = (torch.zeros(k, device="cuda"),
                            torch.zeros(k, dtype=torch.bfloat16 if cfg.grad_dtype == solo.SOLO_GRAD_BF16 else torch.float32, device="cuda"),
                            solo.SoloState(k, cfg))
@@ -208,7 +209,7 @@ def test_all_formats(so, gpu, bm, bv):
 @pytest.mark.parametrize("bm", (2, 3, 4))
 @pytest.mark.parametrize("bv", (2, 3, 4))
 def test_streaming_kernels_all_formats(so, gpu, bm, bv):
-    """The kernels with 16 elements per lane serve flat buffers only from 2^19 to 6 * 2^20 elements on; in
+    """The kernels with 16 elements per lane serve flat buffers only behind the lines of test_dispatch_lines.py; in
     a table with a large second tensor they run at any size.  Every format, both block sizes, both
     codebooks with bf16 gradients, the dynamic-exponent codebook with fp32 gradients, plain and with
     every extra: several chunks and a ragged end."""

@@ -1,10 +1,11 @@
-"""GPU parity of blocks of 2048, full and short: up to 1024 blocks of a launch run on four wavefronts with 8
+"""GPU parity of blocks of 2048, full and short: up to QUAD_BLOCKS blocks of a launch run on four wavefronts with 8
 elements per lane, more on two with 16.  The first form against the oracle (same bar as
 test_gpu_parity.py), the second against the first, byte for byte, and against the oracle on a few buffers."""
 import numpy as np
 import pytest
 
 from parity_common import compare_step, flip_budget, make_cfgs
+from test_dispatch_lines import QUAD_BLOCKS
 from test_gpu_parity import GpuSide, dev, gpu, run_teacher_forced  # noqa: F401
 from test_gpu_table_forms import table_against_flat
 
@@ -69,12 +70,12 @@ def block_kinds(n, rng):
 @pytest.mark.parametrize("de", (False, True))
 @pytest.mark.parametrize("k,bm,bv", [(k, *f) for k, f in enumerate(FORMATS)])
 def test_both_forms_leave_the_same_bytes(gpu, k, bm, bv, de, mp, optimizer):  # noqa: F811
-    """A buffer of more than 1024 blocks in one call and in two, which take the other form."""
+    """A buffer of more than QUAD_BLOCKS blocks in one call and in two, which take the other form."""
     import torch
-    cut, off = 600 * B, 8 * 99                      # (cut: whole blocks and whole code words)
+    cut, off = (QUAD_BLOCKS * 3 // 5 // 5 * 5) * B, 8 * 99                      # (cut: whole blocks and whole code words)
     for bf16 in (False, True):
         for p, end in ((0.1, ENDS[(3 * k) % len(ENDS)]), (0.3, 0), (0.97, ENDS[(3 * k + 1) % len(ENDS)])):
-            n = 1030 * B + end
+            n = (QUAD_BLOCKS + 6) * B + end
             flags = 1 | (2 if de else 0) | optimizer
 
             def config(offset):
@@ -104,7 +105,7 @@ def test_both_forms_leave_the_same_bytes(gpu, k, bm, bv, de, mp, optimizer):  # 
 @pytest.mark.parametrize("bm,bv,bf16,de", [(2, 3, True, False), (4, 4, False, True), (3, 2, False, False)])
 def test_many_blocks(so, gpu, bm, bv, bf16, de):  # noqa: F811
     for end in (0, 1, 1030):
-        run_teacher_forced(so, gpu, 1025 * B + end, bm, bv, B, bf16=bf16, steps=2, seed0=end, de=de)
+        run_teacher_forced(so, gpu, (QUAD_BLOCKS + 1) * B + end, bm, bv, B, bf16=bf16, steps=2, seed0=end, de=de)
 
 
 @pytest.mark.parametrize("bm,bv,bf16,de,mp", [(2, 3, True, False, False), (4, 2, False, True, True), (3, 3, True, False, True),
@@ -117,7 +118,7 @@ def test_tables(gpu, bm, bv, bf16, de, mp):  # noqa: F811
         table_against_flat(gpu, sizes, bm, bv, B, bf16, de, mp=mp)
 
 
-@pytest.mark.parametrize("n", (1000, 2047, 3 * B + 1000, 1030 * B + 700))
+@pytest.mark.parametrize("n", (1000, 2047, 3 * B + 1000, (QUAD_BLOCKS + 6) * B + 700))
 def test_nothing_behind_the_end_is_written(gpu, n):  # noqa: F811
     """Buffers that go on behind the last element, its code word and its block keep what is there."""
     import torch

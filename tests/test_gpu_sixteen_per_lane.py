@@ -1,32 +1,32 @@
-"""GPU parity of the kernels that give a lane 16 elements: flat buffers of more than 6 * 2^20
-elements (some formats from 2^19 on), tables of more than 3 * 2^8 pieces.  Same bar as
+"""GPU parity of the kernels that give a lane 16 elements: flat buffers behind the lines of
+test_dispatch_lines.py, and the largest ones in front of them, which run 8; tables of many pieces.  Same bar as
 test_gpu_parity.py.  (Every instantiation of them is compared with the 8-per-lane kernels in
-test_gpu_both_forms.py; blocks of 2048 give a lane 16 elements from 1025 of them on, see
+test_gpu_both_forms.py; blocks of 2048 have a test file of their own,
 test_gpu_short_blocks.py.)"""
 import numpy as np
 import pytest
 
 from parity_common import compare_step, flip_budget, make_cfgs
+from test_dispatch_lines import LAST8_FP32, last8
 from test_gpu_parity import GpuSide, dev, gpu, run_teacher_forced  # noqa: F401
 
 pytestmark = pytest.mark.gpu
 
-LAST8 = 6 << 20                    # the largest flat buffer of any format that runs 8 elements per lane
 FORMATS = [(bm, bv, B) for B in (64, 128) for bm in (2, 3, 4) for bv in (2, 3, 4)]
-# whole chunks of 1024 only; a chunk short of one element, of all but one; ends in either half of a
-# chunk, on and next to a code word's and a block's end
-SIZES = [LAST8, LAST8 + 1, LAST8 + 1023, LAST8 + 1024, LAST8 + 1025, LAST8 + 512, LAST8 + 511, LAST8 + 1024 + 513,
-         LAST8 + 2048 + 8, LAST8 + 1024 + 80]
+# elements behind the line (the first: the largest buffer with 8 per lane): whole chunks of 1024 only; a chunk short of one
+# element, of all but one; ends in either half of a chunk, on and next to a code word's and a block's end
+BEHIND = [0, 1, 1023, 1024, 1025, 512, 511, 1024 + 513, 2048 + 8, 1024 + 80]
 
 
 @pytest.mark.parametrize("k,bm,bv,B", [(k, *f) for k, f in enumerate(FORMATS)])
 def test_formats_and_ragged_ends(so, gpu, k, bm, bv, B):  # noqa: F811
     for j in range(3):
-        # (the last one: 8 per lane with fp32 gradients, 16 with bf16 ones and a copy)
-        n = SIZES[(2 * k + j) % len(SIZES)] if j < 2 else (5 << 18) + 1 + (k * 401) % 1100
+        # (the last one: 8 per lane but with bf16 gradients and a copy)
+        bf16, copy = (k + j) % 2 == 0, (k + 2 * j) % 4 == 0
+        n = last8(bf16, copy) + BEHIND[(2 * k + j) % len(BEHIND)] if j < 2 else last8(True, True) + 1 + (k * 401) % 1100
         opt = ("adamw", "adam_l2", "adabelief")[(k + j) % 3]
-        ext = dict(grad_scale=0.5, bf16_copy=True) if (k + j) % 4 == 0 else {}
-        run_teacher_forced(so, gpu, n, bm, bv, B, bf16=(k + j) % 2 == 0, steps=2 if j < 2 else 3, seed0=10 * k, de=(k // 2 + j) % 2 == 1,
+        ext = dict(grad_scale=0.5, bf16_copy=True) if copy else {}
+        run_teacher_forced(so, gpu, n, bm, bv, B, bf16=bf16, steps=2 if j < 2 else 3, seed0=10 * k, de=(k // 2 + j) % 2 == 1,
                            optimizer=opt, eps=1e-12 if opt == "adabelief" else 1e-8, **ext)
 
 
@@ -36,7 +36,7 @@ def test_ties_zeros_and_quantiles(so, gpu, bm, bv, B, p):  # noqa: F811
     """Blocks in which most or all lanes tie, blocks of zeros, single entries, a wide range of
     magnitudes, from a state two steps old, over the ranks of small and large quantiles."""
     from paper_2505_00347_amd import synth
-    n = LAST8 + 3 * 1024 + 77
+    n = LAST8_FP32 + 3 * 1024 + 77
     oc, gc = make_cfgs(so, gpu, bm, bv, B, False, p=p, off=8 * ((1 << 32) - 700))
     rng = np.random.default_rng(5)
     block = np.arange(n) // B
