@@ -6,6 +6,7 @@ import numpy as np
 import pytest
 
 from parity_common import compare_step, flip_budget, make_cfgs
+from test_dispatch_lines import QUAD_BLOCKS
 from test_gpu_both_forms import PIECE
 from test_gpu_parity import GpuSide, dev, gpu  # noqa: F401
 from test_gpu_table_forms import bits
@@ -48,25 +49,83 @@ def test_crowded_lanes(gpu, B, rank):  # noqa: F811
         assert torch.equal(bits(x), bits(y))
 
 
+# Forms of a launch over blocks of 2048: four wavefronts per block or two, flat or a table, plain or with the variants
+# (a table of the buffer alone has few blocks; "large table": with a second tensor of many)
+FORMS = [(5, 2, 3, "flat", {}), (5, 2, 3, "flat", dict(optimizer="adabelief")), (QUAD_BLOCKS + 3, 2, 3, "flat", {}),
+         (QUAD_BLOCKS + 3, 3, 3, "flat", dict(de=True, bf16=True)), (QUAD_BLOCKS + 3, 4, 2, "flat", dict(optimizer="adabelief", mp=True)),
+         (QUAD_BLOCKS + 3, 2, 4, "flat", dict(optimizer="adam_l2", de=True)), (5, 4, 3, "flat", dict(de=True, bf16=True, mp=True)),
+         (6, 2, 3, "table", dict(bf16=True)), (6, 4, 4, "table", dict(de=True, optimizer="adabelief", mp=True)),
+         (6, 3, 2, "large table", dict(bf16=True)), (6, 4, 3, "large table", dict(de=True, mp=True, optimizer="adabelief"))]
+
+
+def sides(so, gpu, n, bm, bv, launch, p, optimizer="adamw", de=False, bf16=False, mp=False):  # noqa: F811
+    """The oracle's config and state, and the GPU's side with a step(gradients, step)."""
+    from paper_2505_00347_amd import synth
+    scale = 0.5 if mp else None
+    oc, gc = make_cfgs(so, gpu, bm, bv, 2048, bf16, p=p, optimizer=optimizer, de=de, grad_scale=scale,
+                       eps=1e-12 if optimizer == "adabelief" else 1e-8)
+    side = GpuSide(gpu, n, gc, scale, mp, launch == "large table")
+
+    def step(g, k):
+        x = dev((g.view(np.uint32) >> 16).astype(np.uint16)) if bf16 else dev(g)
+        if launch == "table":
+            gpu.SoloMultiTable([(side.p, x, side.state, side.p_bf16)], gc).step(k, grad_scale=side.grad_scale)
+        else:
+            side.step(x, k)
+
+    def gradients(x):
+        x = x.astype(np.float32)
+        return (x.view(np.uint32) & np.uint32(0xFFFF0000)).view(np.float32) if bf16 else x
+
+    return oc, synth.make_params(n), so.State(n, oc), side, step, gradients
+
+
 @pytest.mark.parametrize("p", (0.05, 0.1, 0.3, 0.97))
-@pytest.mark.parametrize("blocks,opt", [(5, "adamw"), (5, "adabelief"), (1027, "adamw")])
-def test_bound_of_the_old_state(so, gpu, blocks, opt, p):  # noqa: F811
+@pytest.mark.parametrize("blocks,bm,bv,launch,more", FORMS)
+def test_bound_of_the_old_state(so, gpu, blocks, bm, bv, launch, more, p):  # noqa: F811
     """Late step numbers on a state (the bound is used then): quantiles right above the bound, beyond the first pass's
     quarter octave (gradients that jump), on it (idle blocks), and blocks that have no state yet."""
-    from paper_2505_00347_amd import synth
     n = blocks * 2048 + 77
-    oc, gc = make_cfgs(so, gpu, 2, 3, 2048, False, p=p, optimizer=opt, eps=1e-12 if opt == "adabelief" else 1e-8)
+    oc, prm, st, side, step, gradients = sides(so, gpu, n, bm, bv, launch, p, **more)
     rng = np.random.default_rng(blocks)
     kind = np.arange(n) // 2048 % 5
-    prm, st = synth.make_params(n), so.State(n, oc)
-    side = GpuSide(gpu, n, gc)
     flips = 0
-    for k, step in enumerate((1, 8, 60, 1000, 1001)):
+    for k, late in enumerate((1, 8, 60, 1000, 1001)):
         x = rng.standard_normal(n).astype(np.float32) * np.float32(1e-3)
-        g = np.where(kind == 1, x * (k == 0), np.where(kind == 2, x * 1000.0 ** (k % 2), np.where(kind == 3, x * (k >= 3), x))).astype(np.float32)
+        g = gradients(np.where(kind == 1, x * (k == 0), np.where(kind == 2, x * 1000.0 ** (k % 2), np.where(kind == 3, x * (k >= 3), x))))
         side.load(prm, st)
-        side.step(dev(g), step)
+        step(g, late)
         before = prm.astype(np.float64)
-        margin = so.step_packed(prm, g, st, step, oc, want_margin=True, threads=8)
+        margin = so.step_packed(prm, g, st, late, oc, want_margin=True, threads=8)
         flips += compare_step(so, oc, n, prm, st, margin, side.fetch(), 1e-6, 2e-6 * oc.lr, p_before=before)
+        side.check_bf16_copy(so)
     assert flips <= flip_budget(5 * n)
+
+
+@pytest.mark.parametrize("blocks,bm,bv,launch,more", [f for f in FORMS if f[4].get("optimizer") != "adam_l2"])
+def test_late_non_finite_gradients_stay_inside_their_blocks(so, gpu, blocks, bm, bv, launch, more):  # noqa: F811
+    """A NaN or an infinity in the gradient of a late step, and the step after it, whose bound comes from what that left of
+    the block's scale and base: every other block equals the oracle's, which has neither."""
+    n = blocks * 2048 + 77
+    oc, prm, st, side, step, gradients = sides(so, gpu, n, bm, bv, launch, 0.1, **more)
+    rng = np.random.default_rng(bm)
+    for late in (1, 2, 999):
+        so.step_packed(prm, gradients(rng.standard_normal(n) * 1e-3), st, late, oc, threads=8)
+    side.load(prm, st)
+    spoiled = np.zeros(-(-n // 2048), bool)
+    for k, late in enumerate((1000, 1001)):
+        g = gradients(rng.standard_normal(n) * 1e-3)
+        dirty = g.copy()
+        if k == 0:
+            bad = rng.choice(4 * 2048, 12, replace=False)        # of the first four blocks
+            bad = np.concatenate([bad, bad[:1] + (blocks - 4) // 2 * 2048 + 2048])
+            dirty[bad[:4]], dirty[bad[4:8]], dirty[bad[8:]] = np.nan, np.inf, -np.inf
+            spoiled[bad // 2048] = True
+        step(dirty, late)
+        before = prm.astype(np.float64)
+        margin = so.step_packed(prm, g, st, late, oc, want_margin=True, threads=8)
+        tainted = spoiled.copy()
+        flips = compare_step(so, oc, n, prm, st, margin, side.fetch(), 1e-5, 1e-5 * oc.lr, tainted, p_before=before)
+        assert flips <= flip_budget(n) and (tainted & ~spoiled).sum() <= flips
+        spoiled = tainted
+    assert not spoiled.all()
