@@ -5,7 +5,7 @@
 // (step_chunk8).  A block of 128 (64) elements is held by 8 (4) or 16 (8) neighbouring lanes, i.e.
 // by half a DPP row or a row, and every per-block reduction is a few DPP steps.  Nothing is shared
 // between wavefronts but a constant table: the only workgroup barrier, with dynamic-exponent codes
-// of 3 and 4 bits, waits for that table while the elements' loads are under way.  No software prefetch: 60-90 registers leave room for five to seven
+// of 3 and 4 bits, waits for that table while the elements' loads are under way.  No software prefetch: 56-90 registers leave room for five to eight
 // wavefronts per SIMD, which hide each other's memory latency, and the whole machine sweeps one
 // compact window of memory.
 //
@@ -69,7 +69,7 @@ constexpr int kIter = 512;         // elements of a chunk with 8 per lane
 constexpr int kIter16 = 1024;      // elements of a chunk with 16 per lane
 constexpr int kWaves = 4;          // wavefronts per workgroup
 constexpr int kMinWaves = 5;       // wavefronts per SIMD that the register allocator must leave room for, 8 elements per lane
-constexpr int kMinWaves16 = 4;     // and 16 per lane (70-80 registers, i.e. six, in most formats; forcing six spills in the others)
+constexpr int kMinWaves16 = 4;     // and 16 per lane (70-80 registers, i.e. six, in two of three formats, 99-105, i.e. four, in eight; forcing six spills in the others)
 constexpr int kColStride16 = 18;   // words per lane of the sorted columns (16 keys, two +inf; written 8 bytes at a time)
 constexpr float kTiny = 0x1p-100f; // block maxima below this are stored as 0
 constexpr float kRhoMin = 0x1p-64f;

@@ -239,7 +239,8 @@ __device__ __forceinline__ uint32_t largest_key(const uint32_t *const xch)
 // A rank below that pass's range (28 octaves under the maximum, or zeros) starts over from 0.
 // (Against a first pass over the 28 octaves, in turn, us: a layer of the 7B shapes 444 -> 377, as a table 472 -> 399, 2^26
 // elements 4-bit/2-bit DE fp32 with a copy 203 -> 182, 4.2 million 15.96 -> 14.77; 2^25 elements over four formats, quantiles from
-// 0.05 to 0.5 and idle rows 1.07 to 1.30 times as fast, without a state 1.03.  Before that, four fixed passes over
+// 0.05 to 0.5 and idle rows 1.07 to 1.30 times as fast, without a state 1.03.  A step in which the gradients of all blocks jump takes
+// the first pass for nothing: 2^25 elements, 2-bit/3-bit, ten times the gradients at once, 68 -> 74, with a hundredth of the blocks jumping 78 -> 66.  Before that, four fixed passes over
 // 8 + 8 + 8 + 7 bits took 6 % longer than the 28 octaves on scattered values, 45 % with nine of ten gradients at zero.)
 // BARRIER: whether the exchange's maxima still need one.
 template <int NK, int W, bool BARRIER>
@@ -570,7 +571,8 @@ __device__ __forceinline__ void step_block_quad(const StepArgs &a, const uint64_
     if (wave == 0 && lane == 0) { a.m_scale[blk] = dm; a.v_scale[blk] = dv; a.v_base[blk] = codec.alpha; }
 }
 
-// (Five wavefronts per SIMD: 77-97 registers, and LDS allows six.)
+// (Two wavefronts per block: five per SIMD, 79-96 registers, and LDS allows six; four: seven or eight, 62-68 registers, and LDS allows thirteen.  The
+// plain forms of the table kernel hold both forms of a block and spill 16 bytes per lane in 19 of 36 instantiations, 32 in two.)
 
 #define SOLO_BIG_LDS(WAVES_, WORK_, SLAB_)                                                             \
     constexpr int kDeWords = de_words<BM, MDE>();                                                      \
@@ -659,15 +661,20 @@ void multi_big_quad_kernel(const MultiArgs ma)
 }
 #undef SOLO_BIG_LDS
 
-// Up to how many blocks a launch gives four wavefronts to each: up to four workgroups on a CU the time is the
-// chain of one block, behind that the two-wavefront form has the fewer instructions and reads whole lines.  Measured on MI355X,
-// us per launch, four | two wavefronts per block:
-//   blocks                             1            128          488          1000           1500           2000           5000
-//   2-bit/3-bit bf16                   4.61 | 5.98  5.46 | 6.74  6.55 | 8.15  9.26 | 9.03    11.91 | 12.59  14.03 | 14.03  25.2 | 25.0
-//   2-bit/3-bit AdaBelief fp32         4.87 | 7.08  5.56 | 7.76  6.71 | 9.17  10.10 | 10.36  12.60 | 14.28  15.03 | 16.11  27.6 | 29.0
-//   4-bit/2-bit DE fp32                5.04 | 6.81  6.26 | 7.65  7.26 | 8.98  10.66 | 10.71  13.04 | 14.40  15.53 | 16.29  28.4 | 29.0
-//   2-bit/2-bit bf16, p 0.3            5.08 | 6.81  6.15 | 7.63  7.23 | 8.96  9.94 | 9.91    12.61 | 13.37  15.08 | 15.23  25.8 | 26.9
-//   (three states in turn.  From 1000 blocks on the two are close: four lead by up to 12 % at 1500 blocks, two by 3 % at 1000.)
+// Up to how many blocks a launch gives four wavefronts to each: with few blocks the time is the
+// chain of one, which four make shorter; the two-wavefront form has the fewer instructions and reads whole lines.  Measured on MI355X,
+// us per launch, four | two wavefronts per block, three states in turn:
+//   blocks                             1            128          488          750          1000           1500           2000           3000           5000
+//   2-bit/3-bit bf16                   4.71 | 6.10  5.43 | 6.73  6.53 | 8.14  7.44 | 8.69  9.31 | 9.09    11.88 | 12.60  14.25 | 14.24  18.35 | 18.72  25.4 | 25.3
+//   2-bit/3-bit AdaBelief fp32         4.95 | 7.11  5.59 | 7.71  6.70 | 9.14  8.36 | 9.63  10.07 | 10.35  12.45 | 14.12  14.96 | 16.16  18.80 | 21.23  27.5 | 29.0
+//   4-bit/2-bit DE fp32                5.13 | 6.77  6.20 | 7.69  7.14 | 9.06  9.01 | 9.53  10.61 | 10.75  13.10 | 14.47  15.63 | 16.40  19.71 | 21.52  28.8 | 29.1
+//   2-bit/2-bit bf16, p 0.3            5.11 | 6.84  6.18 | 7.59  7.30 | 8.96  8.33 | 9.44  10.10 | 9.86   12.81 | 13.32  15.43 | 15.38  19.03 | 19.79  26.4 | 27.2
+//   3-bit/3-bit DE bf16, copy          5.33 | 7.50  6.16 | 8.25  7.27 | 9.57  8.69 | 10.2  11.03 | 10.58  13.97 | 13.96  16.57 | 16.84  20.74 | 21.46  30.8 | 29.9
+//   time of four over time of two, geometric mean of these five, states of 1.3 GB together in turn / three in turn / one again and again:
+//   flat      488 blocks .85 .78 .78,  750 .96 .88 .85,  1000 1.01 1.01 .92,  1200 1.01 .99 .92,  1500 .99 .94 .92,  1800 1.02 .96 1.01,  2000 1.04 .97 1.01,  5000 1.08 .99 1.00
+//   table     488 blocks .86 .80 .80,  1000 1.01 .97 .90,  1500 1.07 1.01 .95,  2000 1.10 1.01 1.01,  3000 1.09 .98 1.04
+//   (Both cross between 1000 and 1800 blocks, tables first.  One line for both, at four workgroups on each CU: flat launches of 1100 to 1700
+//   blocks would be 3-5 % faster by four in the mean of the three, tables of that size 1 % slower.)
 //   4000 tensors of 1000 elements (a block each): 27 | 42 with earlier kernels, so a table of which at least three in four
 //   blocks are the only one of their tensor takes four at any size.
 constexpr uint64_t kQuadUpTo = 1024;
