@@ -37,9 +37,10 @@
 //     them in LDS; an element costs one shift, one bitop3 and
 //     one ds_read per moment; the launch's constants are in vector registers;
 //   * the p-quantile is exact: each lane sorts its 8 or 16 values with min3/med3/max3
-//     and merges, and the group runs rounds of "row minimum by DPP, the
-//     lowest lane that holds it pops its column"; four scalar instructions pick
-//     that lane for all groups, ties or not; 16 per lane keeps the eight smallest of a lane for small ranks and
+//     and merges; 8 per lane goes on to merge lanes, with as many of the smallest keys as the rank asks for
+//     (merged_rth()); with 16, the group runs rounds of "row minimum by DPP, the
+//     lowest lane that holds it pops its column"; scalar instructions pick
+//     that lane for all groups, ties or not; it keeps the eight smallest of a lane for small ranks and
 //     pops two of them at a time while the rank allows it;
 //   * the two per-block divisions share one IEEE division sequence (even lanes
 //     divide x_p by Delta_v, odd lanes L by Delta_m);
@@ -647,24 +648,12 @@ constexpr bool narrow_buffer(uint64_t n, bool bf16, bool copy, uint32_t rank)
 // Up to how many pieces (pieces16) a table does.
 constexpr uint64_t narrow_table_up_to() { return 3ull << 8; }
 
-// The lowest set bit of every G-bit field of a ballot, one field per group of lanes.  Every field
-// has a bit set (the lanes whose key equals the group's minimum), so ~h + 1 does not carry out of
-// its field and one 64-bit add serves all groups: four scalar instructions, no branch on ties.
-// (A population count with a branch into a vector tie-break cost about as much without ties and
-// six more vector instructions in every round with one: 2^24 elements, 3-bit/3-bit, nine of ten
-// gradients zero, so that every round ties: 44.9 us with the branch, 40.1 without.)
-template <int G>
-__device__ __forceinline__ uint64_t lowest_holders(uint64_t h)
-{
-    constexpr uint64_t kOnes = G == 16 ? 0x0001000100010001ull : G == 8 ? 0x0101010101010101ull : 0x1111111111111111ull;
-    return h & (~h + kOnes);
-}
-
 // The rank-th smallest key of every group of G = 4 or 8 lanes (full blocks).  Each lane has parked its
 // sorted column at `haddr` (+inf behind it) and passes its four smallest keys.  A round:
-// group minimum of the heads by DPP; the lowest lane that holds it (lowest_holders()) pops its column, so
+// group minimum of the heads by DPP; the lowest lane that holds it pops its column, so
 // exactly one key leaves a group per round and the last minimum is the order statistic, multiplicities
-// included.  While more than G + 1 keys are asked for, a round pops two at once: the lane whose second
+// included.  (That lane is the lowest set bit of every G-bit field h of a ballot, h & (~h + 1) for all fields at once: each
+// has a bit set, so the addition does not carry out of a field.)  While more than G + 1 keys are asked for, a round pops two at once: the lane whose second
 // key is the smallest drops both.  In front of that key there are at most its own first one and
 // one of every other lane, so both are among the first G + 1.  (Rank 13 of 128: 10 rounds instead of 12; 39: 23 instead of
 // 38.)  The keys behind the head are fetched a round ahead, so that their LDS latency lies outside the chain.
@@ -730,72 +719,120 @@ __device__ __forceinline__ uint32_t extract_rth(uint32_t head, uint32_t behind, 
     return group_reduce<G>(head, UMin());
 }
 
-// The lanes of `pop` drop the first of their sorted keys: the N keys behind it move up by one
-// (N = 8: the seventh and the +inf behind the column).  The two wait states that a DPP read of
-// k[0] needs behind its write are the instructions that follow it.
-template <int N>
-__device__ __forceinline__ void pop_column(uint32_t (&k)[8], uint64_t pop)
+// ---- the r-th smallest of a group's keys, 8 sorted ones per lane in registers, by merging.
+//
+// Neighbouring sorted lists are merged bitonically, pairs of lanes first, then fours, eights and sixteens; a list
+// keeps its C smallest keys only (C >= r, a power of two), so once it has C each merge halves the keys that a lane
+// holds: 8, 8, 4, 2, 1 for rank 13 of 128.  A list of S = R 2^t keys lies in 2^t lanes, R to a lane in order; merging it with the
+// next one is the exchange of every key with its mirror image there (the smaller half is the result where C is reached), then exchanges
+// over halving distances, between lanes while the distance is R or more and inside a lane below.
+// Lanes count by coordinates (lane_coordinates()) in which the exchange partner over each one is a
+// single DPP pattern, and the lists of lanes with the next coordinate set are sorted the other way round, so that a
+// key's mirror image lies in the partner lane.  Which of two lanes keeps the smaller key is a third operand of the
+// median: 0 for the smaller, all ones for the larger.
+// No scalar instruction and no exec mask is in the chain: about 100 vector instructions, most of
+// them independent of each other, for rank 13 of 128, where rounds of "minimum of the heads by DPP, the lowest lane that
+// holds it shifts its column" took 12 times about 170 cycles one after the other (38 times at rank 39).  us per launch in a graph, rounds |
+// merges: 4096 elements 2-bit/3-bit 3.52 | 3.15, at rank 39 5.12 | 3.40; 1000 elements 4.42 | 3.67; 2^20 4-bit/4-bit fp32
+// 4.87 | 4.56, 3-bit/3-bit 5.08 | 4.85; 2^19 at rank 39 5.56 | 3.77; 1000 tensors of 600 6.70 | 5.88; 5 million, where
+// the number of instructions counts, 14.1 | 13.9.
+// (With 16 per lane a round pops two keys, fewer lanes share a block, and the other wavefronts of the SIMD fill the gaps: extract_rth().)
+
+// The lane whose coordinate J differs: lane ^ 1, ^ 2, ^ 7 (mirror of the half row) and ^ 8 (rotation of the row by 8).
+template <int J>
+__device__ __forceinline__ uint32_t across(const uint32_t x)
 {
-#define SOLO_MOVE(D_, S_) "v_mov_b32_e32 " D_ ", " S_ "\n\t"
-#define SOLO_POP(MOVES_)                                                                                  \
-    asm volatile("s_mov_b64 exec, %8\n\t" MOVES_ "s_mov_b64 exec, -1"                                   \
-                 : "+v"(k[0]), "+v"(k[1]), "+v"(k[2]), "+v"(k[3]), "+v"(k[4]), "+v"(k[5]), "+v"(k[6]), "+v"(k[7]) \
-                 : "s"(pop))
-#define SOLO_M1 SOLO_MOVE("%0", "%1")
-#define SOLO_M2 SOLO_M1 SOLO_MOVE("%1", "%2")
-#define SOLO_M3 SOLO_M2 SOLO_MOVE("%2", "%3")
-#define SOLO_M4 SOLO_M3 SOLO_MOVE("%3", "%4")
-#define SOLO_M5 SOLO_M4 SOLO_MOVE("%4", "%5")
-#define SOLO_M6 SOLO_M5 SOLO_MOVE("%5", "%6")
-#define SOLO_M7 SOLO_M6 SOLO_MOVE("%6", "%7")
-    if (N == 1) SOLO_POP(SOLO_M1 "s_nop 0\n\t");
-    else if (N == 2) SOLO_POP(SOLO_M2);
-    else if (N == 3) SOLO_POP(SOLO_M3);
-    else if (N == 4) SOLO_POP(SOLO_M4);
-    else if (N == 5) SOLO_POP(SOLO_M5);
-    else if (N == 6) SOLO_POP(SOLO_M6);
-    else if (N == 7) SOLO_POP(SOLO_M7);
-    else SOLO_POP(SOLO_M7 SOLO_MOVE("%7", "0x7f800000"));
-#undef SOLO_M1
-#undef SOLO_M2
-#undef SOLO_M3
-#undef SOLO_M4
-#undef SOLO_M5
-#undef SOLO_M6
-#undef SOLO_M7
-#undef SOLO_POP
-#undef SOLO_MOVE
+    return dpp<J == 0 ? 0xB1 : J == 1 ? 0x4E : J == 2 ? 0x141 : 0x128>(x);
+}
+__device__ __forceinline__ uint32_t lane_coordinates(const uint32_t lane)       // bit J: coordinate J
+{
+    return (lane ^ (lane & 4u ? 3u : 0u)) & 15u;
 }
 
-// One round of the selection on columns that live in registers: the group's minimum, which the
-// lowest lane that holds it drops.
-template <int G, int N>
-__device__ __forceinline__ uint32_t extract_round8(uint32_t (&k)[8])
+// One exchange over coordinate J; `sides`: bit J set in the lanes that keep the larger keys.  MIRROR: key i meets key R - 1 - i.
+template <int J, bool MIRROR, int R>
+__device__ __forceinline__ void exchange(uint32_t (&k)[R], const uint32_t sides)
 {
-    const uint32_t mn = group_reduce<G>(k[0], UMin());
-    pop_column<N>(k, lowest_holders<G>(__builtin_amdgcn_ballot_w64(k[0] == mn)));
-    return mn;
+    const uint32_t upper = (uint32_t)__builtin_amdgcn_sbfe((int)sides, J, 1);
+    uint32_t o[R];
+#pragma unroll
+    for (int i = 0; i < R; ++i) o[i] = across<J>(k[MIRROR ? R - 1 - i : i]);
+#pragma unroll
+    for (int i = 0; i < R; ++i) k[i] = umax(umin(k[i], o[i]), umin(umax(k[i], o[i]), upper));   // (one median)
 }
-
-// The r-th smallest key of every group of G lanes, each with its 8 sorted keys in registers: a pop
-// shifts the column instead of fetching from LDS.  More moves than extract_rth(), but no LDS
-// latency in the chain of rounds, which is what a short buffer's time is made of (a round of the
-// LDS form takes 185-280 cycles with one wavefront on a SIMD; a launch of 4096 elements went from
-// 6.63 to 6.25 us, of 2^20 with 4-bit codes from 7.52 to 6.91).  The last seven rounds shift only
-// the keys that can still come up.
-template <int G>
-__device__ __forceinline__ uint32_t extract_rth8(uint32_t (&k)[8], uint32_t rank)
+// Over the coordinates of ORDER (N of them, four bits each), the highest first.
+template <uint32_t ORDER, int N, int R>
+__device__ __forceinline__ void exchange_lanes(uint32_t (&k)[R], const uint32_t sides)
 {
-    if (rank >= 8) {
-#pragma unroll 1
-        for (uint32_t i = 8; i < rank; ++i) extract_round8<G, 8>(k);
-        extract_round8<G, 7>(k); extract_round8<G, 6>(k); extract_round8<G, 5>(k); extract_round8<G, 4>(k);
-        extract_round8<G, 3>(k); extract_round8<G, 2>(k); extract_round8<G, 1>(k);
-    } else {
-#pragma unroll 1
-        for (uint32_t i = 1; i < rank; ++i) extract_round8<G, 7>(k);
+    if constexpr (N > 0) {
+        exchange<(ORDER >> (4 * (N - 1))) & 15, false>(k, sides);
+        exchange_lanes<ORDER, N - 1>(k, sides);
     }
-    return group_reduce<G>(k[0], UMin());
+}
+template <int R>
+__device__ __forceinline__ void merge_in_lane(uint32_t (&k)[R])
+{
+#pragma unroll
+    for (int w = R / 2; w >= 1; w /= 2)
+#pragma unroll
+        for (int i = 0; i < R; ++i) if ((i & w) == 0) cswap(k[i], k[i + w]);
+}
+
+// From lists over 2^T lanes on (R keys per lane; their blocks of R are ordered by the N coordinates of ORDER, the lowest four bits counting
+// least) to the rank-th smallest key of the group, in all its lanes.  `rank`: 1 to C, at most the group's keys.
+template <int G, int C, int T = 0, uint32_t ORDER = 0, int N = 0, int R>
+__device__ __forceinline__ uint32_t merged_rth(uint32_t (&k)[R], const uint32_t coords, const uint32_t rank)
+{
+    static_assert(R << N <= C && C <= 8 * G, "a list holds at most C keys");
+    if constexpr (1 << T < G) {
+        const uint32_t sides = 2 << T == G ? coords : coords ^ (uint32_t)__builtin_amdgcn_sbfe((int)coords, T + 1, 1);
+        if constexpr (R << N < C) {
+            exchange<T, true>(k, sides);
+            exchange_lanes<ORDER, N>(k, sides);
+            merge_in_lane(k);
+            return merged_rth<G, C, T + 1, ORDER | T << (4 * N), N + 1>(k, coords, rank);
+        } else if constexpr (R > 1) {
+            uint32_t h[R / 2];
+#pragma unroll
+            for (int i = 0; i < R / 2; ++i) h[i] = umin(k[i], across<T>(k[R - 1 - i]));      // (the partner makes the other half)
+            exchange_lanes<ORDER, N>(h, sides);
+            exchange<T, true>(h, sides);
+            merge_in_lane(h);
+            return merged_rth<G, C, T + 1, ORDER << 4 | T, N + 1>(h, coords, rank);
+        } else {
+            k[0] = umin(k[0], across<T>(k[0]));                                              // (both sides hold the result)
+            exchange_lanes<ORDER, N>(k, sides);
+            return merged_rth<G, C, T + 1, ORDER, N>(k, coords, rank);
+        }
+    } else {
+        const uint32_t at = rank - 1u, in_lane = at % R, block = at / R;
+        uint32_t want = 0, mask = 0;
+#pragma unroll
+        for (int b = 0; b < N; ++b) {
+            const int j = (ORDER >> (4 * b)) & 15;
+            want |= (block >> b & 1u) << j;
+            mask |= 1u << j;
+        }
+#pragma unroll
+        for (int w = R / 2; w >= 1; w /= 2)
+#pragma unroll
+            for (int i = 0; i < w; ++i) {
+                const uint32_t low = k[i], high = k[i + w];      // (values: of two elements of an array it would be their addresses that are selected)
+                k[i] = in_lane & (uint32_t)w ? high : low;
+            }
+        return group_reduce<G>(((coords ^ want) & mask) == 0u ? k[0] : 0u, UMax());
+    }
+}
+
+// The r-th smallest key of every group of G lanes (`rank`: 1 to at_most, the same or smaller in each group), 8 sorted keys per lane.
+template <int G>
+__device__ __forceinline__ uint32_t merged_rth8(uint32_t (&k)[8], const uint32_t lane, const uint32_t rank, const uint32_t at_most)
+{
+    const uint32_t coords = lane_coordinates(lane);
+    if (at_most <= 8u) return merged_rth<G, 8>(k, coords, rank);
+    if (at_most <= 16u) return merged_rth<G, 16>(k, coords, rank);
+    if (G == 8 || at_most <= 64u) return merged_rth<G, 64>(k, coords, rank);
+    return merged_rth<G, 8 * G>(k, coords, rank);
 }
 
 // The 2nd-moment code is rounded down by the conversion of code * 2^-24 to binary16 toward zero: a binary16
@@ -1297,21 +1334,14 @@ __device__ __forceinline__ void step_chunk8(const StepArgs &a, const uint64_t ch
     if (dv < kTiny) dv = 0.0f;
 
     // ---- the r-th smallest v^ of the block
-    uint32_t xp_bits;
-    if (!TAIL) {
-        xp_bits = extract_rth8<G>(key, a.rank_full);
-    } else {
-        // (a shorter last block has a smaller rank; absent elements are +inf behind the others)
+    // (a shorter last block has a smaller rank; absent elements are +inf behind the others)
+    uint32_t rank = a.rank_full;
+    if (TAIL) {
         const float x = __builtin_ceilf(a.quantile_p * (float)nb);
-        uint32_t r_mine = x < 1.0f ? 1u : (uint32_t)x;
-        r_mine = r_mine > nb ? nb : r_mine;
-        xp_bits = 0;
-#pragma unroll 1
-        for (uint32_t k = 1; k <= a.rank_full; ++k) {
-            const uint32_t mn = extract_round8<G, 8>(key);
-            xp_bits = k == r_mine ? mn : xp_bits;
-        }
+        rank = x < 1.0f ? 1u : (uint32_t)x;
+        rank = umax(umin(rank, nb), 1u);
     }
+    const uint32_t xp_bits = merged_rth8<G>(key, lane, rank, a.rank_full);
 
     // ---- the block's encoder constants, then this lane's 8 codes of each moment
     const BlockCodec codec = block_codec<BV, G, L, MDE>(xp_bits, dm, dv, lane, lig, gshift);

@@ -1,4 +1,4 @@
-"""The selection of the kernels with 16 elements per lane where a lane holds more of a block's smallest values than the
+"""The selection of the kernels with 8 elements per lane at the ranks where its form changes, against the oracle.  That of the kernels with 16 elements per lane where a lane holds more of a block's smallest values than the
 shortened columns keep, around the ranks at which its forms change, against the kernels with 8 per lane
 (compared with the oracle elsewhere): the same inputs leave the same bytes.  And the selection in blocks of 2048 from the bound
 that the old state gives, against the oracle."""
@@ -47,6 +47,40 @@ def test_crowded_lanes(gpu, B, rank):  # noqa: F811
     torch.cuda.synchronize()
     for x, y in zip((sides[0][0], *sides[0][1]), (sides[1][0], *sides[1][1])):
         assert torch.equal(bits(x), bits(y))
+
+
+def ordered(n, B, rng):
+    """Magnitudes by block: scattered, rising, falling, ties, equal, the smallest ones in one run of 8 (a lane's), or spread
+    one to a run, mostly zero, a wide range."""
+    i, block = np.arange(n) % B, np.arange(n) // B
+    x = 1.0 + rng.random(n)
+    kinds = (x, 1.0 + i, float(B) - i, 1.0 + i // 5, np.ones(n), np.where(i // 8 == block % (B // 8), x, 100 * x),
+             np.where(i % 8 == block % 8, x, 100 * x), np.where(rng.random(n) < 0.9, 0.0, x), x * 10.0 ** rng.integers(-9, 3, n))
+    return np.choose(block % len(kinds), kinds) * np.where(rng.random(n) < 0.5, -1e-3, 1e-3)
+
+
+@pytest.mark.parametrize("bf16", (False, True))
+@pytest.mark.parametrize("B,rank", [(128, r) for r in (1, 2, 7, 8, 9, 13, 15, 16, 17, 32, 39, 63, 64, 65, 100, 127, 128)]
+                         + [(64, r) for r in (1, 2, 7, 8, 9, 15, 16, 17, 33, 63, 64)])
+def test_merged_lists(so, gpu, B, rank, bf16):  # noqa: F811
+    """8 per lane: the ranks at which the length of the merged lists changes, full blocks and a shorter last one."""
+    rng = np.random.default_rng(rank)
+    flips = total = 0
+    for n in (48 * 128 + 77, 48 * 128 + B // 2, 5):
+        oc, gc = make_cfgs(so, gpu, 2, 3, B, bf16, p=(rank - 0.5) / B)
+        prm, st = rng.standard_normal(n).astype(np.float32), so.State(n, oc)
+        side = GpuSide(gpu, n, gc)
+        for step in (1, 2, 3):
+            g = ordered(n, B, rng).astype(np.float32)
+            if bf16:
+                g = (g.view(np.uint32) & np.uint32(0xFFFF0000)).view(np.float32)
+            side.load(prm, st)
+            side.step(dev((g.view(np.uint32) >> 16).astype(np.uint16)) if bf16 else dev(g), step)
+            before = prm.astype(np.float64)
+            margin = so.step_packed(prm, g, st, step, oc, want_margin=True)
+            flips += compare_step(so, oc, n, prm, st, margin, side.fetch(), 1e-6, 2e-6 * oc.lr, p_before=before)
+            total += n
+    assert flips <= flip_budget(total)
 
 
 # Forms of a launch over blocks of 2048: four wavefronts per block or two, flat or a table, plain or with the variants
