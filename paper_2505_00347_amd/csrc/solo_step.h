@@ -361,9 +361,10 @@ struct Run3 {
         word = __umul24(q, 52429u) >> 19;          // q / 10
         shift = 3u * q - 30u * word;
     }
-    __device__ __forceinline__ uint32_t codes(const uint32_t *const img) const
+    // (the two bits of a word that no code owns are ignored)
+    __device__ __forceinline__ uint32_t codes(const uint32_t w0, const uint32_t w1) const
     {
-        return (img[word] >> shift | img[word + 1] << (30u - shift)) & 0xFFFFFFu;
+        return ((w0 & 0x3FFFFFFFu) >> shift | w1 << (30u - shift)) & 0xFFFFFFu;
     }
     // changes codes by exclusive or: what lanes that share a word own of it stays
     __device__ __forceinline__ void change(uint32_t *const img, const uint32_t x) const
@@ -906,7 +907,17 @@ struct XiGroups {
     }
 };
 
-// Encodes a lane's run of 8 consecutive elements, the group `xi_word` (XiGroups::words) of the xi stream: returns the packed 1st- and 2nd-moment codes (element j in bits [b j, b j + b)).
+// The words of a run of 8 consecutive elements in the xi stream: element j owns X + j Y (xi_finalize()).
+struct XiRun {
+    uint32_t X, Y;
+    // word: of the run's group (XiGroups::words)
+    __device__ __forceinline__ XiRun(const StepArgs &a, const uint32_t word) : X(mix32(word)), Y(mix32(X ^ a.key1) | 1u)
+    {
+        if (!a.stochastic) { X = kXiZeroWord; Y = 0u; }     // xi = 0: the float is 1.5
+    }
+};
+
+// Encodes a lane's run of 8 consecutive elements, `xi` of the xi stream: returns the packed 1st- and 2nd-moment codes (element j in bits [b j, b j + b)).
 // xi: one hashed start and stride per 8 elements, every element's word finalized on its own;
 // 2^-24 * (1.5 + xi - 2^-24) is built as a float by one bit-align of the finalized word.
 // m: code - L = rint(m^ * L/Delta_m) in [-L, L], rounded to an integer by adding 1.5 * 2^23, whose low
@@ -921,24 +932,21 @@ struct XiGroups {
 // 150.7 -> 146.2, AdaBelief 4-bit/4-bit fp32 at 5 million elements, 8 per lane, 14.9 -> 14.5.)
 // `ok` (TAIL only): the elements that exist.  What is not finite spoils codes of its own run only.
 template <int BM, int BV, bool MDE, bool TAIL>
-__device__ __forceinline__ void encode_run(const StepArgs &a, const uint32_t xi_word, const float *mh, const float *vh,
+__device__ __forceinline__ void encode_run(const XiRun &xi, const float *mh, const float *vh,
                                            const bool *ok, const BlockCodec &c, uint32_t de_base,
                                            uint32_t &m8, uint32_t &v8)
 {
     constexpr int L = (1 << (BM - 1)) - 1;
     constexpr int K = (1 << BV) - 1;
     constexpr bool kDeTable = MDE && BM >= 3;
-    uint32_t X = mix32(xi_word);
-    uint32_t Y = mix32(X ^ a.key1) | 1u;
-    if (!a.stochastic) { X = kXiZeroWord; Y = 0u; }     // xi = 0: the float is 1.5
-    uint32_t xj = X;                                    // X + j Y, walked up from j = 0
+    uint32_t xj = xi.X;                                 // X + j Y, walked up from j = 0
     float y[8];                                         // kCodeScale * (code + 1 + fraction)
     uint32_t t[8];                                      // m: code - L in the low bits, kRound's bits above
     uint32_t m8_de = 0;
     constexpr float kRound = 0x1.8p23f;
     constexpr uint32_t kRoundBits = 0x4B400000u;
 #pragma unroll
-    for (int j = 0; j < 8; ++j, xj += Y) {
+    for (int j = 0; j < 8; ++j, xj += xi.Y) {
         const float z = mh[j] * c.inv_s;
         if (!MDE) {
             t[j] = f2u(z + kRound);
@@ -1002,32 +1010,28 @@ __device__ __forceinline__ void encode_run(const StepArgs &a, const uint32_t xi_
 // The level tables of a block that G lanes share (decode by table look-up): lane `lig` of the group
 // fills entries lig, lig + G, ... of the 2nd-moment table (Delta_v alpha^q, alpha^q by binary
 // powering) and of the 1st-moment table (linear: (c - L) (Delta_m / L); dynamic exponent: the
-// lane's levels `de_level` times Delta_m).
+// levels times Delta_m).  Lanes beyond the entries fill one again, and the linear 1st-moment table its unused last one,
+// so that nothing is conditional and the code around it stays one block for the compiler's scheduler.
 template <int BM, int BV, bool MDE, int G>
 __device__ __forceinline__ void fill_level_tables(float *const my_tv, float *const my_tm, const uint32_t lig,
-                                                  const float dm_old, const float dv_old, const float al_old,
-                                                  const float *de_level)
+                                                  const float dm_old, const float dv_old, const float al_old)
 {
     constexpr int L = (1 << (BM - 1)) - 1;
-    constexpr int VT = 1 << BV;
-    constexpr int MT = MDE ? 2 * L + 2 : 2 * L + 1;
-    // (The scales are here: a load whose value is used under the condition below only would be moved behind it, and
-    // its latency with it.)
-    asm volatile("" : : "v"(dm_old), "v"(dv_old), "v"(al_old));
+    constexpr int VT = 1 << BV, MT = m_table_stride<BM>();
+    static_assert(MT >= (MDE ? 2 * L + 2 : 2 * L + 1), "entries");
     const float s_m = (L == 1) ? dm_old : dm_old / (float)L;
     const float P1 = al_old, P2 = P1 * P1, P4 = P2 * P2, P8 = P4 * P4;
 #pragma unroll
     for (int r = 0; r < (VT + G - 1) / G; ++r) {
-        const uint32_t q = lig + r * G;
-        if (q < VT) my_tv[q] = log_level<BV>(q, P1, P2, P4, P8) * dv_old;
+        const uint32_t q = (lig + r * G) & (uint32_t)(VT - 1);
+        my_tv[q] = log_level<BV>(q, P1, P2, P4, P8) * dv_old;
     }
 #pragma unroll
     for (int r = 0; r < (MT + G - 1) / G; ++r) {
-        const uint32_t c = lig + r * G;
-        if (c < MT) my_tm[c] = MDE ? de_level[r] * dm_old : (float)((int)c - L) * s_m;
+        const uint32_t c = (lig + r * G) & (uint32_t)(MT - 1);
+        my_tm[c] = MDE ? DeLevels<BM>::level(c) * dm_old : (float)((int)c - L) * s_m;
     }
 }
-
 
 template <bool BF16>
 __device__ __forceinline__ void unpack_pg(const RawPG &raw, float (&p)[8], float (&g)[8])
@@ -1045,14 +1049,28 @@ __device__ __forceinline__ void unpack_pg(const RawPG &raw, float (&p)[8], float
     }
 }
 
+// Parameter: decoupled decay, bias-corrected Adam direction,
+// p <- p * decay - step_size * m^ / (sqrt(v^ / bc2) + eps), with step_size folded into the denominator.
+__device__ __forceinline__ float new_param(const float p, const float mh, const float vh, const float decay, const float denom_scale, const float denom_eps)
+{
+    const float denom = __builtin_fmaf(__builtin_amdgcn_sqrtf(vh), denom_scale, denom_eps);
+    return __builtin_fmaf(p, decay, -(mh * __builtin_amdgcn_rcpf(denom)));
+}
+// Those of a lane's 8 elements, in a place where the chain of the block's statistics leaves issue slots free.
+__device__ __forceinline__ void new_param8(const StepArgs &a, const float (&mh)[8], const float (&vh)[8], float (&p)[8])
+{
+    const float decay = in_vector(a.decay), denom_scale = in_vector(a.denom_scale), denom_eps = in_vector(a.denom_eps);
+#pragma unroll
+    for (int j = 0; j < 8; ++j) p[j] = new_param(p[j], mh[j], vh[j], decay, denom_scale, denom_eps);
+}
+
 // Dequantize (table look-up: byte offset 4 * code, OR-ed into the aligned table base), both EMAs
 // and the parameter for a lane's N = 8 or 16 consecutive elements; mc8 / vc8: the packed old
 // codes of every run of 8.  VMAX: also the largest v^ (the callers that sort take it from the
 // sorted keys).  TAIL: elements that do not exist (`ok`) leave zeros in m^ and v^.
 // AdaBelief without a branch: d = g - kb * m^ is g itself when kb = 0 and fl(g - m^) when kb = 1
 // (one rounding either way), and eps_state = 0 leaves v^ unchanged.
-// Parameter: decoupled decay, bias-corrected Adam direction,
-// p <- p * decay - step_size * m^ / (sqrt(v^ / bc2) + eps), with step_size folded into the denominator.
+// 16 per lane also makes the new parameters here; 8 per lane later (new_param8()).
 template <int N, int BM, int BV, bool EXT, bool TAIL, bool VMAX>
 __device__ __forceinline__ void ema_param(const StepArgs &a, const uint32_t tm_addr, const uint32_t tv_addr,
                                           const uint32_t *mc8, const uint32_t *vc8, const bool *ok,
@@ -1071,7 +1089,8 @@ __device__ __forceinline__ void ema_param(const StepArgs &a, const uint32_t tm_a
         }
     }
     const float beta1 = in_vector(a.beta1), omb1 = in_vector(a.omb1), beta2 = in_vector(a.beta2), omb2 = in_vector(a.omb2);
-    const float denom_scale = in_vector(a.denom_scale), denom_eps = in_vector(a.denom_eps), decay = in_vector(a.decay);
+    float denom_scale = 0.0f, denom_eps = 0.0f, decay = 0.0f;
+    if (N != 8) { denom_scale = in_vector(a.denom_scale); denom_eps = in_vector(a.denom_eps); decay = in_vector(a.decay); }
     m_absmax = 0.0f;
     v_max = 0.0f;
     float kb = 0.0f, eps_state = 0.0f;
@@ -1092,8 +1111,7 @@ __device__ __forceinline__ void ema_param(const StepArgs &a, const uint32_t tm_a
         } else {
             vh[j] = __builtin_fmaf(beta2, vt[j], omb2 * (g[j] * g[j]));
         }
-        const float denom = __builtin_fmaf(__builtin_amdgcn_sqrtf(vh[j]), denom_scale, denom_eps);
-        p[j] = __builtin_fmaf(p[j], decay, -(mh[j] * __builtin_amdgcn_rcpf(denom)));
+        if (N != 8) p[j] = new_param(p[j], mh[j], vh[j], decay, denom_scale, denom_eps);
         if (TAIL && !ok[j]) { mh[j] = 0.0f; vh[j] = 0.0f; }
         m_absmax = __builtin_fmaxf(m_absmax, __builtin_fabsf(mh[j]));
         if (VMAX) v_max = __builtin_fmaxf(v_max, vh[j]);
@@ -1132,26 +1150,38 @@ __device__ __forceinline__ void write_back_word(uint32_t *const word, const uint
     if (changed) atomicXor(word, changed);
 }
 
+// The first word of a stream of ten-to-a-word codes that `chunk`'s elements touch (chunks of 512 or 1024, at most 2^31 of them:
+// five fill whole words), and the slot of the first element in it.
+template <int ELEMS>
+__device__ __forceinline__ uint64_t first_word10(const uint32_t chunk, uint32_t &slot)
+{
+    static_assert(5 * ELEMS % 10 == 0 && ELEMS <= 1024, "five chunks fill whole words");
+    const uint32_t five = chunk / 5u, r = chunk - 5u * five, words = r * (uint32_t)ELEMS / 10u;
+    slot = r * (uint32_t)ELEMS - 10u * words;
+    return (uint64_t)five * (5 * ELEMS / 10) + words;
+}
+
 // The codes of the 512 elements that a wavefront steps on its own (8 consecutive elements per lane).  Eight 2- or
-// 4-bit codes are a half or a whole word of the stream: the lane loads and stores it.  Words of 3-bit codes are
-// staged in LDS, at most one of a stream per lane; once all codes have been read the image is cleared and collects what
-// changes of the words, and the lane that staged a word writes that back.  The first word may begin in the share before.
+// 4-bit codes are a half or a whole word of the stream: the lane loads and stores it.  Eight 3-bit codes lie in one word or two
+// neighbouring ones: the lane loads both, so that nothing has to be staged and waited for in LDS; what changes of a word
+// is collected in LDS, in an image that starts from zeros, and lane i writes back the i-th one.  The first word may begin in the share before.
 // TAIL: words behind the buffer are left alone.
 template <int BITS, bool TAIL>
 struct LaneCodes8 {
     static constexpr int C = 32 / BITS;                // codes per word
-    static constexpr int kImage = BITS == 3 ? 68 : 0;  // words of the image (<= 64, + 1)
+    static constexpr int kImage = BITS == 3 ? 64 : 0;  // words of the image (54 are used)
     uint32_t *word;                            // the first word of the share (uniform)
     bool has;                                  // this lane has a word, or half a one, to write
-    uint32_t own;                              // as it was loaded (3-bit: until it is staged)
+    uint32_t own[2];                           // as loaded
     uint32_t first;                            // 3-bit: slot of the first element in the first word
 
-    // ew0: first element of the wavefront's share.  Issues the load.
+    // ew0: first element of the wavefront's share.  Issues the loads.
     __device__ __forceinline__ void load(uint32_t *const words, const uint64_t n, const uint64_t ew0, const uint32_t lane)
     {
-        const uint64_t lo = ew0 / C;
+        uint64_t lo;
+        if (BITS == 3) lo = first_word10<kIter>((uint32_t)(ew0 / kIter), first);
+        else { lo = ew0 / C; first = 0; }
         word = words + lo;
-        first = (uint32_t)(ew0 - lo * C);
         // (Lanes without a word load the last one again: a load under a condition whose fields are masked
         // behind it was waited for inside, in front of all the loads that follow.  2^20 elements,
         // 3-bit/3-bit fp32: 5.46 us under conditions, 5.27 without; the 1.3e9 elements of the 1.3B shapes, 3-bit/3-bit
@@ -1165,22 +1195,21 @@ struct LaneCodes8 {
             has = has && lo + at <= end;
             from = umin64(from, end); last = (uint32_t)umin64(last, end - from);
         }
-        if (BITS == 2) own = reinterpret_cast<const uint16_t *>(words + from)[umin(lane, 2u * last + 1u)];
-        else own = words[from + umin(at, last)];
+        if (BITS == 2) own[0] = reinterpret_cast<const uint16_t *>(words + from)[umin(lane, 2u * last + 1u)];
+        else if (BITS == 4) own[0] = words[from + umin(lane, last)];
+        else {
+            const uint32_t w = Run3(first + lane * 8u).word;
+            own[0] = words[from + umin(w, last)];
+            own[1] = words[from + umin(w + 1u, last)];     // (a run that ends with its word does not use it)
+        }
     }
-    __device__ __forceinline__ void stage(uint32_t *const img, const uint32_t lane)
+    __device__ __forceinline__ void clear(uint32_t *const img, const uint32_t lane) const
     {
-        if (BITS != 3) return;
-        img[lane] = own & 0x3FFFFFFFu;
-        if (lane == 0) img[64] = 0;                // (a run that ends with its word reads the word behind it without using it)
+        if (BITS == 3) img[lane] = 0;
     }
-    __device__ __forceinline__ uint32_t codes(uint32_t *const img, const uint32_t lane) const
+    __device__ __forceinline__ uint32_t codes(const uint32_t lane) const
     {
-        if (BITS != 3) return own;
-        const uint32_t c = Run3(first + lane * 8u).codes(img);
-        wave_lds_sync();
-        img[lane] = 0;
-        return c;
+        return BITS == 3 ? Run3(first + lane * 8u).codes(own[0], own[1]) : own[0];
     }
     // the lane's new codes (`old`: what codes() gave), in front of write_back()
     __device__ __forceinline__ void change(uint32_t *const img, const uint32_t lane, const uint32_t old, const uint32_t now) const
@@ -1250,6 +1279,11 @@ struct ChunkLayout8 {
 // The whole step for the 512 elements from 512 * chunk on (TAIL: clipped to a.n, with bounds checks
 // on every element), by the calling wavefront on its own.  `slab` is its LDS, `de` the
 // workgroup's DE bucket table.
+// A launch of few wavefronts is the chain of one, so what is not part of that chain is done where it waits: the hash of xi
+// while the loads are under way, the parameters in the gaps of the divisions and of the base.  (With that, level tables filled without
+// conditions, 3-bit codes straight from the words a lane loads and the position of those words by 32-bit arithmetic, us per launch in a
+// graph, before | after: 4096 elements 2-bit/3-bit 3.15 | 3.01, 2^20 4-bit/4-bit fp32 4.55 | 4.46, 3-bit/3-bit 4.78 | 4.61, 2-bit/3-bit bf16
+// 4.71 | 4.54, 5 million 4-bit/4-bit fp32 13.7 | 13.4.)
 // EXT: the code that also serves the variants of the step (gradient scale, coupled decay,
 // AdaBelief, bf16 weight copy); the plain AdamW step runs the one without them.
 template <int BM, int BV, int B, bool BF16, bool MDE, bool TAIL, bool EXT>
@@ -1260,7 +1294,6 @@ __device__ __forceinline__ void step_chunk8(const StepArgs &a, const uint64_t ch
     constexpr int NG = 64 / G;                     // blocks of the chunk
     constexpr int L = (1 << (BM - 1)) - 1;
     constexpr int VT = 1 << BV;
-    constexpr int MT = MDE ? 2 * L + 2 : 2 * L + 1;    // entries of a block's m level table (3, 7, 15; DE: 4, 8, 16)
     using Lay = ChunkLayout8<BM, BV, B>;
     constexpr bool kDeTable = MDE && BM >= 3;
 
@@ -1295,23 +1328,23 @@ __device__ __forceinline__ void step_chunk8(const StepArgs &a, const uint64_t ch
     const bool whole = !TAIL || __builtin_expect(ew0 + kIter <= a.n, 0);
     const RawPG raw = load_pg<BF16, TAIL>(a, e0, whole);
     const float gscale = (EXT && a.grad_scale) ? *a.grad_scale : 1.0f;      // uniform: the gradient is transformed first
+
+    // ---- while they are under way: what does not depend on them
+    uint32_t xi_word[1];
+    XiGroups(a, ew0).words<1>(a, lane, xi_word);
+    XiRun xi(a, xi_word[0]);
+    xi.X = fresh(xi.X); xi.Y = fresh(xi.Y);
+    mw.clear(img_m, lane);
+    vw.clear(img_v, lane);
     de.ready();
-    mw.stage(img_m, lane);
-    vw.stage(img_v, lane);
 
     // ---- level tables of this lane's block: entries lig, lig + G, ...
-    float de_level[(16 + G - 1) / G];                  // DE codebook: the levels of the entries this lane fills
-    uint32_t de_base = 0;                              // bucket table address, less the first bucket's index
-    if (MDE) {
-#pragma unroll
-        for (int r = 0; r < (MT + G - 1) / G; ++r) de_level[r] = DeLevels<BM>::level(lig + r * G);
-        if (kDeTable) de_base = lds_addr(de.lds) - 16u * DeBuckets<BM>::kLo;
-    }
-    fill_level_tables<BM, BV, MDE, G>(my_tv, my_tm, lig, dm_old, dv_old, al_old, de_level);
+    const uint32_t de_base = kDeTable ? lds_addr(de.lds) - 16u * DeBuckets<BM>::kLo : 0u;    // bucket table address, less the first bucket's index
+    fill_level_tables<BM, BV, MDE, G>(my_tv, my_tm, lig, dm_old, dv_old, al_old);
     wave_lds_sync();
-    const uint32_t mc8 = mw.codes(img_m, lane), vc8 = vw.codes(img_v, lane);
+    const uint32_t mc8 = mw.codes(lane), vc8 = vw.codes(lane);
 
-    // ---- dequantize (table look-up), EMA, parameter
+    // ---- dequantize (table look-up), EMA
     float p[8], g[8];
     unpack_pg<BF16>(raw, p, g);
     if (EXT) {                                 // g <- fl(g * scale), then one fused g + l2 * p (l2 = 0: exact)
@@ -1321,7 +1354,6 @@ __device__ __forceinline__ void step_chunk8(const StepArgs &a, const uint64_t ch
     float mh[8], vh[8];
     float m_absmax, v_max;                     // (v_max of full chunks: the last sorted key below)
     ema_param<8, BM, BV, EXT, TAIL, TAIL>(a, tm_addr, tv_addr, &mc8, &vc8, ok, p, g, mh, vh, m_absmax, v_max);
-    store_params8<EXT, TAIL>(a, e0, whole, ok, p);
 
     // ---- the lane's v^ sorted (non-negative floats order like their bit patterns); block maxima
     uint32_t key[8];
@@ -1343,12 +1375,12 @@ __device__ __forceinline__ void step_chunk8(const StepArgs &a, const uint64_t ch
     }
     const uint32_t xp_bits = merged_rth8<G>(key, lane, rank, a.rank_full);
 
-    // ---- the block's encoder constants, then this lane's 8 codes of each moment
+    // ---- parameter; the block's encoder constants, then this lane's 8 codes of each moment
+    new_param8(a, mh, vh, p);
+    store_params8<EXT, TAIL>(a, e0, whole, ok, p);
     const BlockCodec codec = block_codec<BV, G, L, MDE>(xp_bits, dm, dv, lane, lig, gshift);
     uint32_t m8, v8;
-    uint32_t xi_word[1];
-    XiGroups(a, ew0).words<1>(a, lane, xi_word);
-    encode_run<BM, BV, MDE, TAIL>(a, xi_word[0], mh, vh, ok, codec, de_base, m8, v8);
+    encode_run<BM, BV, MDE, TAIL>(xi, mh, vh, ok, codec, de_base, m8, v8);
     mw.change(img_m, lane, mc8, m8);
     vw.change(img_v, lane, vc8, v8);
     if (lig == 0 && blk_ok) { a.m_scale[gb] = dm; a.v_scale[gb] = dv; a.v_base[gb] = codec.alpha; }
@@ -1626,9 +1658,10 @@ struct LaneCodes16 {
     template <bool FULL>
     __device__ __forceinline__ void load(uint32_t *const words, const uint64_t ew0, const uint32_t lane, const uint32_t here)
     {
-        const uint64_t lo = ew0 / C;
+        uint64_t lo;
+        if (BITS == 3) lo = first_word10<kIter16>((uint32_t)(ew0 / kIter16), first);
+        else { lo = ew0 / C; first = 0; }
         word = words + lo;
-        first = (uint32_t)(ew0 - lo * C);
         nw = here ? (first + here + C - 1) / C : 0;
         if (FULL && BITS == 4 && !STAGED) {
             const uint2 two = *reinterpret_cast<const uint2 *>(word + 2u * lane);
@@ -1644,15 +1677,16 @@ struct LaneCodes16 {
     {
         if (!STAGED) return;
 #pragma unroll
-        for (int k = 0; k < K; ++k) img[lane + 64u * k] = BITS == 3 ? own[k] & 0x3FFFFFFFu : own[k];
+        for (int k = 0; k < K; ++k) img[lane + 64u * k] = own[k];
         if (BITS == 3 && lane < 4) img[64 * K + lane] = 0;
     }
+    static __device__ __forceinline__ uint32_t run_from(const uint32_t *const img, const Run3 run) { return run.codes(img[run.word], img[run.word + 1]); }
     // the lane's old codes, eight to a run (2-bit: the upper half of the register is not clear)
     __device__ __forceinline__ void codes(uint32_t *const img, const uint32_t lane, uint32_t (&c8)[2]) const
     {
 #pragma unroll
         for (int r = 0; r < 2; ++r)
-            c8[r] = BITS == 3 ? Run3(first + lane * 16u + 8u * r).codes(img) : BITS == 2 ? own[0] >> (16 * r) : STAGED ? img[2u * lane + r] : own[r % K];
+            c8[r] = BITS == 3 ? run_from(img, Run3(first + lane * 16u + 8u * r)) : BITS == 2 ? own[0] >> (16 * r) : STAGED ? img[2u * lane + r] : own[r % K];
         if (BITS != 3) return;
         wave_lds_sync();
 #pragma unroll
@@ -1698,7 +1732,7 @@ __device__ __forceinline__ void encode16(const StepArgs &a, const uint64_t ew0, 
     XiGroups(a, ew0).words<2>(a, 2u * lane, xi_word);
 #pragma unroll
     for (int r = 0; r < 2; ++r) {
-        encode_run<BM, BV, MDE, false>(a, xi_word[r], mh + 8 * r, vh + 8 * r, nullptr, codec, de_base, m8[r], v8[r]);
+        encode_run<BM, BV, MDE, false>(XiRun(a, xi_word[r]), mh + 8 * r, vh + 8 * r, nullptr, codec, de_base, m8[r], v8[r]);
         if (__builtin_expect(!all, 0)) {
             const uint32_t run = mine <= 8u * r ? 0u : umin(mine - 8u * r, 8u);
             m8[r] &= (uint32_t)((1ull << (BM * run)) - 1ull);
@@ -1736,7 +1770,6 @@ __device__ __forceinline__ void step_chunk16(const StepArgs &a, const uint64_t c
     constexpr int NG = 64 / G;                     // blocks of the chunk
     constexpr int L = (1 << (BM - 1)) - 1;
     constexpr int VT = 1 << BV;
-    constexpr int MT = MDE ? 2 * L + 2 : 2 * L + 1;
     using Lay = ChunkLayout16<BM, BV, B, MDE>;
     constexpr bool kDeTable = MDE && BM >= 3;
 
@@ -1762,14 +1795,8 @@ __device__ __forceinline__ void step_chunk16(const StepArgs &a, const uint64_t c
 
     mw.stage(img_m, lane);
     vw.stage(img_v, lane);
-    float de_level[(16 + G - 1) / G];
-    uint32_t de_base = 0;
-    if (MDE) {
-#pragma unroll
-        for (int r = 0; r < (MT + G - 1) / G; ++r) de_level[r] = DeLevels<BM>::level(lig + r * G);
-        if (kDeTable) de_base = lds_addr(de.lds) - 16u * DeBuckets<BM>::kLo;
-    }
-    fill_level_tables<BM, BV, MDE, G>(my_tv, my_tm, lig, dm_old, dv_old, al_old, de_level);
+    const uint32_t de_base = kDeTable ? lds_addr(de.lds) - 16u * DeBuckets<BM>::kLo : 0u;
+    fill_level_tables<BM, BV, MDE, G>(my_tv, my_tm, lig, dm_old, dv_old, al_old);
     wave_lds_sync();
     uint32_t mc8[2], vc8[2];
     mw.codes(img_m, lane, mc8);

@@ -382,10 +382,7 @@ __device__ __forceinline__ void step_block(const StepArgs &a, const uint64_t blk
     vw.stage(img_v, lane);
 
     // ---- level tables of the block (every wavefront its own copy)
-    {
-        const float de_level = MDE ? DeLevels<BM>::level(lane) : 0.0f;
-        fill_level_tables<BM, BV, MDE, 64>(my_tv, my_tm, lane, dm_old, dv_old, al_old, &de_level);
-    }
+    fill_level_tables<BM, BV, MDE, 64>(my_tv, my_tm, lane, dm_old, dv_old, al_old);
     wave_lds_sync();
     uint32_t mc8[2], vc8[2];
     mw.codes(img_m, lane, mc8);
@@ -513,15 +510,16 @@ __device__ __forceinline__ void step_block_quad(const StepArgs &a, const uint64_
 #pragma unroll
         for (uint32_t i = 0; i < 512u / (64u * kQuadWaves); ++i) z[wave * 64u + lane + 64u * kQuadWaves * i] = make_uint4(0, 0, 0, 0);
     }
+    uint32_t xi_word[1];
+    XiGroups(a, ew0).words<1>(a, lane, xi_word);
+    XiRun xi(a, xi_word[0]);
+    xi.X = fresh(xi.X); xi.Y = fresh(xi.Y);
+    mw.clear(img_m, lane);
+    vw.clear(img_v, lane);
     de.store();
-    mw.stage(img_m, lane);
-    vw.stage(img_v, lane);
-    {
-        const float de_level = MDE ? DeLevels<BM>::level(lane) : 0.0f;
-        fill_level_tables<BM, BV, MDE, 64>(my_tv, my_tm, lane, dm_old, dv_old, al_old, &de_level);
-    }
+    fill_level_tables<BM, BV, MDE, 64>(my_tv, my_tm, lane, dm_old, dv_old, al_old);
     wave_lds_sync();
-    const uint32_t mc8 = mw.codes(img_m, lane), vc8 = vw.codes(img_v, lane);
+    const uint32_t mc8 = mw.codes(lane), vc8 = vw.codes(lane);
     const uint32_t floor = key_floor<BV, EXT>(a, my_tv);
     __syncthreads();                               // (the histogram is cleared, the DE table is there)
 
@@ -535,7 +533,6 @@ __device__ __forceinline__ void step_block_quad(const StepArgs &a, const uint64_
     float mh[8], vh[8];
     float m_absmax, v_max;
     ema_param<8, BM, BV, EXT, TAIL, true>(a, tm_addr, tv_addr, &mc8, &vc8, ok, p, g, mh, vh, m_absmax, v_max);
-    store_params8<EXT, TAIL>(a, e0, ok[7], ok, p);
 
     // ---- block maxima over the four wavefronts (read behind the selection's barriers)
     {
@@ -548,6 +545,8 @@ __device__ __forceinline__ void step_block_quad(const StepArgs &a, const uint64_
 #pragma unroll
     for (int j = 0; j < 8; ++j) key[j] = ok[j] ? f2u(vh[j]) : kNoKey;
     const uint32_t xp_bits = select_rank<8, kQuadWaves, true>(key, floor, rank_among(a, present), present, lane, wave, work, xch);
+    new_param8(a, mh, vh, p);
+    store_params8<EXT, TAIL>(a, e0, ok[7], ok, p);
     float dm = u2f(umax(umax(xch[Xch::kMaxM], xch[Xch::kMaxM + 1]), umax(xch[Xch::kMaxM + 2], xch[Xch::kMaxM + 3])));
     float dv = u2f(largest_key<kQuadWaves>(xch));
     if (dm < kTiny) dm = 0.0f;
@@ -559,9 +558,7 @@ __device__ __forceinline__ void step_block_quad(const StepArgs &a, const uint64_
     if (kDeTable) de_base = lds_addr(de.lds) - 16u * DeBuckets<BM>::kLo;
     const BlockCodec codec = block_codec<BV, 16, L, MDE>(xp_bits, dm, dv, lane, lig, gshift);
     uint32_t m8, v8;
-    uint32_t xi_word[1];
-    XiGroups(a, ew0).words<1>(a, lane, xi_word);
-    encode_run<BM, BV, MDE, TAIL>(a, xi_word[0], mh, vh, ok, codec, de_base, m8, v8);
+    encode_run<BM, BV, MDE, TAIL>(xi, mh, vh, ok, codec, de_base, m8, v8);
     mw.change(img_m, lane, mc8, m8);
     vw.change(img_v, lane, vc8, v8);
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
