@@ -523,8 +523,11 @@ __device__ __forceinline__ uint32_t pack_bf16(float lo, float hi)
 // kilobytes, twice the requests of a coalesced one, but nothing has to be turned around through LDS:
 // the code for 8 elements per lane runs where a launch is all latency (the transposition and its
 // waits were 500 of the 6400-7200 cycles of a wavefront).  TAIL: unless `whole` says that
-// all of them exist, element by element, bounds-checked.  (A caller asks for a wavefront, whose loads
+// all of them exist, element by element, the last one again in place of those that don't: under conditions the loads waited for each other
+// (100,003 elements 2-bit/2-bit B 64, us in a graph: 3.95 | 3.45 with the last one again).  (A caller asks for a wavefront, whose loads
 // are then all under way at once, or, with a long chain behind them, for every lane.)
+// The parameters last: nothing needs them before the step's end (states out of HBM, in front | behind, us: 2^20 elements 4-bit/4-bit fp32 6.22 | 5.90,
+// 3-bit/3-bit 5.90 | 5.59; out of the last-level cache the same).
 struct RawPG { float4 p0, p1; uint4 g0, g1; };
 
 template <bool BF16, bool TAIL>
@@ -533,22 +536,28 @@ __device__ __forceinline__ RawPG load_pg(const StepArgs &a, const uint64_t e0, c
     RawPG r;
     r.g1 = make_uint4(0, 0, 0, 0);
     if (!TAIL || whole) {
-        const float4 *pp = reinterpret_cast<const float4 *>(a.param + e0);
-        r.p0 = pp[0]; r.p1 = pp[1];
         if (BF16) {
             r.g0 = *reinterpret_cast<const uint4 *>(static_cast<const uint16_t *>(a.grad) + e0);
         } else {
             const uint4 *gp = reinterpret_cast<const uint4 *>(static_cast<const float *>(a.grad) + e0);
             r.g0 = gp[0]; r.g1 = gp[1];
         }
+        const float4 *pp = reinterpret_cast<const float4 *>(a.param + e0);
+        r.p0 = pp[0]; r.p1 = pp[1];
     } else {
         float p[8]; uint32_t g[8];
 #pragma unroll
+        for (int j = 0; j < 8; ++j) {                  // (the last element in place of one that does not exist, to keep conditions off the loads)
+            const uint64_t e = umin64(e0 + j, a.n - 1u);
+            p[j] = a.param[e];
+            if (BF16) g[j] = static_cast<const uint16_t *>(a.grad)[e];
+            else      g[j] = static_cast<const uint32_t *>(a.grad)[e];
+        }
+#pragma unroll
         for (int j = 0; j < 8; ++j) {
-            const bool ok = (e0 + j) < a.n;
-            p[j] = ok ? a.param[e0 + j] : 0.0f;
-            if (BF16) g[j] = ok ? (uint32_t)static_cast<const uint16_t *>(a.grad)[e0 + j] : 0u;
-            else      g[j] = ok ? static_cast<const uint32_t *>(a.grad)[e0 + j] : 0u;
+            const bool ok = e0 + j < a.n;
+            p[j] = ok ? p[j] : 0.0f;
+            g[j] = ok ? g[j] : 0u;
         }
         r.p0 = make_float4(p[0], p[1], p[2], p[3]); r.p1 = make_float4(p[4], p[5], p[6], p[7]);
         if (BF16) r.g0 = make_uint4(g[0] | (g[1] << 16), g[2] | (g[3] << 16), g[4] | (g[5] << 16), g[6] | (g[7] << 16));
@@ -1329,8 +1338,8 @@ __device__ __forceinline__ void step_chunk8(const StepArgs &a, const uint64_t ch
     LaneCodes8<BV, TAIL> vw;
     mw.load(a.m_words, a.n, ew0, lane);
     vw.load(a.v_words, a.n, ew0, lane);
-    float dm_old = 0.0f, dv_old = 0.0f, al_old = 1.0f;
-    if (blk_ok) { dm_old = a.m_scale[gb]; dv_old = a.v_scale[gb]; al_old = a.v_base[gb]; }
+    const uint64_t gb_here = TAIL ? umin64(gb, (a.n - 1u) / B) : gb;
+    const float dm_old = a.m_scale[gb_here], dv_old = a.v_scale[gb_here], al_old = a.v_base[gb_here];
     const bool whole = !TAIL || __builtin_expect(ew0 + kIter <= a.n, 0);
     const RawPG raw = load_pg<BF16, TAIL>(a, e0, whole);
     const float gscale = (EXT && a.grad_scale) ? *a.grad_scale : 1.0f;      // uniform: the gradient is transformed first
@@ -1835,11 +1844,26 @@ __device__ __forceinline__ void step_chunk16(const StepArgs &a, const uint64_t c
     vw.template write_back<true>(img_v, lane, v8);
 }
 
+// What a wavefront of a short launch needs for its first loads, in front of the other arguments: the hardware puts the first 14 words of a
+// kernel's arguments into scalar registers before the wavefront starts (the build asks for it), so that these loads
+// don't wait for scalar ones.  (us in a graph, without | with: 4096 elements 2-bit/3-bit 3.11 | 3.03, 2^20 2-bit/3-bit bf16 4.70 | 4.61,
+// 4-bit/4-bit fp32 4.58 | 4.52, out of HBM 5.46 | 5.23 and 6.20 | 6.22.)
+// `whole`: chunks or blocks of UNIT elements; `more`: the elements behind them, and in the upper half how many wavefronts or blocks take those.
+#define SOLO_FIRST_ARGS const uint32_t whole, const uint32_t more, const void *const grad, uint32_t *const m_words, \
+                        uint32_t *const v_words, float *const m_scale, float *const v_scale, float *const v_base
+constexpr int kFirstArgsBytes = 56;
+template <int UNIT>
+__device__ __forceinline__ void take_first_args(StepArgs &a, SOLO_FIRST_ARGS)
+{
+    a.n = (uint64_t)whole * UNIT + (more & 0xFFFFu);
+    a.grad = grad; a.m_words = m_words; a.v_words = v_words; a.m_scale = m_scale; a.v_scale = v_scale; a.v_base = v_base;
+}
+
 // The step over one flat buffer, 8 elements per lane: one wavefront per 512 elements, the last
-// ones (a.rest: up to the end of the last code word) with bounds checks where the buffer ends.
+// ones (up to the end of the last code word) with bounds checks where the buffer ends.
 template <int BM, int BV, int B, bool BF16, bool MDE, bool EXT>
 __global__ __launch_bounds__(kWaves * 64, kMinWaves)
-void chunk8_kernel(const StepArgs a)
+void chunk8_kernel(SOLO_FIRST_ARGS, const StepArgs args)
 {
     using Lay = ChunkLayout8<BM, BV, B>;
     __shared__ __attribute__((aligned(64))) uint32_t lds_slab[kWaves * Lay::kSlab];
@@ -1849,11 +1873,13 @@ void chunk8_kernel(const StepArgs a)
     // the wavefront index is uniform: keeping it (and every address derived from the chunk) in
     // scalar registers frees vector registers
     const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    const uint64_t c = (uint64_t)blockIdx.x * kWaves + wave;
+    const uint32_t c = blockIdx.x * kWaves + wave;
     uint32_t *const slab = lds_slab + wave * Lay::kSlab;
-    if ((c + 1) * kIter <= a.n)
+    StepArgs a = args;
+    take_first_args<kIter>(a, whole, more, grad, m_words, v_words, m_scale, v_scale, v_base);
+    if (c < whole)
         step_chunk8<BM, BV, B, BF16, MDE, false, EXT>(a, c, lane, slab, de);
-    else if (c < a.rest)
+    else if (c < whole + (more >> 16))
         step_chunk8<BM, BV, B, BF16, MDE, true, EXT>(a, c, lane, slab, de);
     else
         de.ready();
@@ -1946,8 +1972,10 @@ __device__ __forceinline__ StepArgs tensor_args(const MultiArgs &ma, const Tenso
 // infinite or NaN into a gradient that is, also with l2 = 0, and spoils the state of its block.)
 template <int BM, int BV, int B, bool BF16, bool MDE, bool EXT>
 __global__ __launch_bounds__(kWaves * 64, kMinWaves)
-void multi_chunk8_kernel(const MultiArgs ma)
+void multi_chunk8_kernel(const TensorEntry *const entries, const uint32_t count, const MultiArgs args)
 {
+    MultiArgs ma = args;                       // (the first two: as SOLO_FIRST_ARGS)
+    ma.entries = entries; ma.count = count;
     using Lay = ChunkLayout8<BM, BV, B>;
     __shared__ __attribute__((aligned(64))) uint32_t lds_slab[kWaves * Lay::kSlab];
     __shared__ __attribute__((aligned(64))) uint32_t lds_de[de_words<BM, MDE>()];
@@ -2017,14 +2045,19 @@ hipError_t launch_one(const StepArgs &args_in, hipStream_t stream)
     if (args.n == 0) return hipSuccess;
     const bool narrow = narrow_buffer(args.n, BF16, args.param_bf16 != nullptr, args.rank_full);
     const uint64_t whole = narrow ? 0 : args.n / kIter16;
-    args.rest = narrow ? pieces8(args.n) : rest_pieces(args.n, whole);
+    args.rest = narrow ? pieces8(args.n) : rest_pieces(args.n, whole);      // (narrow: all of them)
     const uint64_t groups = (whole + args.rest + kWaves - 1) / kWaves;
     if (groups > kMaxGroups) return hipErrorInvalidValue;
     const bool ext = args.param_bf16 || args.grad_scale || args.belief || args.l2 != 0.0f;
 #define SOLO_LAUNCH(KERNEL_, EXT_)                                                                              \
     hipLaunchKernelGGL((KERNEL_<BM, BV, B, BF16, MDE, EXT_>), dim3((uint32_t)groups), dim3(kWaves * 64), 0, stream, args)
-    if (narrow) { if (ext) SOLO_LAUNCH(chunk8_kernel, true); else SOLO_LAUNCH(chunk8_kernel, false); }
+    const uint32_t whole8 = (uint32_t)(args.n / kIter), more = (uint32_t)(args.n % kIter) | (uint32_t)(args.rest - whole8) << 16;
+#define SOLO_LAUNCH8(EXT_)                                                                                      \
+    hipLaunchKernelGGL((chunk8_kernel<BM, BV, B, BF16, MDE, EXT_>), dim3((uint32_t)groups), dim3(kWaves * 64), 0, stream, whole8, more, \
+                       args.grad, args.m_words, args.v_words, args.m_scale, args.v_scale, args.v_base, args)
+    if (narrow) { if (ext) SOLO_LAUNCH8(true); else SOLO_LAUNCH8(false); }
     else        { if (ext) SOLO_LAUNCH(chunk16_kernel, true); else SOLO_LAUNCH(chunk16_kernel, false); }
+#undef SOLO_LAUNCH8
 #undef SOLO_LAUNCH
     return hipGetLastError();
 }
@@ -2045,14 +2078,14 @@ hipError_t launch_multi_impl(uint32_t bits_v, uint32_t block_size, bool bf16, co
     const bool narrow = pieces <= narrow_table_up_to();
     const uint64_t grid = ((narrow ? 2 * pieces : pieces) + kWaves - 1) / kWaves;
     if (grid == 0 || grid > kMaxGroups || args.count == 0) return hipErrorInvalidValue;
-#define SOLO_KERNEL(KERNEL_, BV_, B_, BF_, EXT_)                                                        \
-    hipLaunchKernelGGL((KERNEL_<BM, BV_, B_, BF_, MDE, EXT_>), dim3((uint32_t)grid), dim3(kWaves * 64), 0, stream, args)
+#define SOLO_KERNEL(KERNEL_, BV_, B_, BF_, EXT_, ...)                                                   \
+    hipLaunchKernelGGL((KERNEL_<BM, BV_, B_, BF_, MDE, EXT_>), dim3((uint32_t)grid), dim3(kWaves * 64), 0, stream, __VA_ARGS__)
 #define SOLO_LAUNCH(BV_, B_, BF_)                                                                       \
     do {                                                                                                \
-        if (narrow && ext) SOLO_KERNEL(multi_chunk8_kernel, BV_, B_, BF_, true);                        \
-        else if (narrow)   SOLO_KERNEL(multi_chunk8_kernel, BV_, B_, BF_, false);                       \
-        else if (ext)      SOLO_KERNEL(multi_chunk16_kernel, BV_, B_, BF_, true);                       \
-        else               SOLO_KERNEL(multi_chunk16_kernel, BV_, B_, BF_, false);                      \
+        if (narrow && ext) SOLO_KERNEL(multi_chunk8_kernel, BV_, B_, BF_, true, args.entries, args.count, args);                        \
+        else if (narrow)   SOLO_KERNEL(multi_chunk8_kernel, BV_, B_, BF_, false, args.entries, args.count, args);                       \
+        else if (ext)      SOLO_KERNEL(multi_chunk16_kernel, BV_, B_, BF_, true, args);                       \
+        else               SOLO_KERNEL(multi_chunk16_kernel, BV_, B_, BF_, false, args);                      \
     } while (0)
 #define SOLO_CASE(BV_, B_)                                                                              \
     if (bits_v == BV_ && block_size == B_) {                                                            \

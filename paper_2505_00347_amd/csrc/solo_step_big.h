@@ -582,13 +582,14 @@ __device__ __forceinline__ void step_block_quad(const StepArgs &a, const uint64_
     const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));           \
     uint32_t *const slab = lds_slab + wave * SLAB_
 
-// The kernel's arguments, loaded behind this point: loaded in front of the branch between the two forms of a
+// The kernel's arguments (BEHIND bytes behind the first one), loaded behind this point: loaded in front of the branch between the two forms of a
 // block, the union of what they need of them is spilled for the full blocks, too.
-template <typename T>
+template <typename T, int BEHIND = 0>
 __device__ __forceinline__ T arguments_here()
 {
     typedef const __attribute__((address_space(4))) T arg_t;
-    arg_t *p = (arg_t *)__builtin_amdgcn_kernarg_segment_ptr();
+    typedef const __attribute__((address_space(4))) char byte_t;
+    arg_t *p = (arg_t *)((byte_t *)__builtin_amdgcn_kernarg_segment_ptr() + BEHIND);
     asm volatile("" : "+s"(p));
     T a;
     __builtin_memcpy(&a, (const T *)p, sizeof(T));
@@ -618,14 +619,16 @@ void big_kernel(const StepArgs args)
 // Four wavefronts per block.
 template <int BM, int BV, bool BF16, bool MDE, bool EXT>
 __global__ __launch_bounds__(kQuadWaves * 64, kMinWaves)
-void big_quad_kernel(const StepArgs args)
+void big_quad_kernel(SOLO_FIRST_ARGS, const StepArgs)
 {
     SOLO_BIG_LDS(kQuadWaves, 2048, QuadLayout::kSlab);
-    if (blockIdx.x < args.n / kBigBlock) {
-        const StepArgs a = arguments_here<StepArgs>();
+    if (blockIdx.x < whole) {
+        StepArgs a = arguments_here<StepArgs, kFirstArgsBytes>();
+        take_first_args<kBigBlock>(a, whole, more, grad, m_words, v_words, m_scale, v_scale, v_base);
         step_block_quad<BM, BV, BF16, MDE, EXT, false>(a, blockIdx.x, lane, wave, slab, lds_work, lds_xch, de);
     } else {
-        const StepArgs a = arguments_here<StepArgs>();
+        StepArgs a = arguments_here<StepArgs, kFirstArgsBytes>();
+        take_first_args<kBigBlock>(a, whole, more, grad, m_words, v_words, m_scale, v_scale, v_base);
         step_block_quad<BM, BV, BF16, MDE, EXT, true>(a, blockIdx.x, lane, wave, slab, lds_work, lds_xch, de);
     }
 }
@@ -722,12 +725,13 @@ hipError_t launch_big_impl(uint32_t bits_v, bool bf16, const StepArgs &args_in, 
     if (blocks == 0 || blocks > 0xFFFFFFFFull / threads) return hipErrorInvalidValue;
     args.rest = args.n % kBigBlock ? 1 : 0;
     const bool ext = args.param_bf16 || args.grad_scale || args.belief || args.l2 != 0.0f;
-#define SOLO_KERNEL(KERNEL_, BV_, BF_, EXT_)                                                        \
-    hipLaunchKernelGGL((KERNEL_<BM, BV_, BF_, MDE, EXT_>), dim3((uint32_t)blocks), dim3(threads), 0, stream, args)
+#define SOLO_KERNEL(KERNEL_, BV_, BF_, EXT_, ...)                                                   \
+    hipLaunchKernelGGL((KERNEL_<BM, BV_, BF_, MDE, EXT_>), dim3((uint32_t)blocks), dim3(threads), 0, stream, __VA_ARGS__)
 #define SOLO_LAUNCH(BV_, BF_, EXT_)                                                                 \
     do {                                                                                            \
-        if (quad) SOLO_KERNEL(big_quad_kernel, BV_, BF_, EXT_);                                     \
-        else      SOLO_KERNEL(big_kernel, BV_, BF_, EXT_);                                          \
+        if (quad) SOLO_KERNEL(big_quad_kernel, BV_, BF_, EXT_, (uint32_t)(args.n / kBigBlock), (uint32_t)(args.n % kBigBlock), args.grad, \
+                              args.m_words, args.v_words, args.m_scale, args.v_scale, args.v_base, args); \
+        else      SOLO_KERNEL(big_kernel, BV_, BF_, EXT_, args);                                    \
     } while (0)
 #define SOLO_CASE(BV_)                                                                              \
     if (bits_v == BV_) {                                                                            \
