@@ -692,23 +692,14 @@ hipError_t launch_multi_big_impl(uint32_t bits_v, bool bf16, const MultiArgs &ar
     if (args.total_units > 0xFFFFFFFFull / threads) return hipErrorInvalidValue;
     const StepArgs &c = args.common;
     const bool ext = args.any_bf16_copy || c.grad_scale || c.belief || c.l2 != 0.0f;
-#define SOLO_KERNEL(KERNEL_, BV_, BF_, EXT_)                                                        \
-    hipLaunchKernelGGL((KERNEL_<BM, BV_, BF_, MDE, EXT_>), dim3((uint32_t)args.total_units), dim3(threads), 0, stream, args)
-#define SOLO_LAUNCH(BV_, BF_, EXT_)                                                                 \
-    do {                                                                                            \
-        if (quad) SOLO_KERNEL(multi_big_quad_kernel, BV_, BF_, EXT_);                               \
-        else      SOLO_KERNEL(multi_big_kernel, BV_, BF_, EXT_);                                    \
-    } while (0)
-#define SOLO_CASE(BV_)                                                                              \
-    if (bits_v == BV_) {                                                                            \
-        if (bf16) { if (ext) SOLO_LAUNCH(BV_, true, true); else SOLO_LAUNCH(BV_, true, false); }    \
-        else      { if (ext) SOLO_LAUNCH(BV_, false, true); else SOLO_LAUNCH(BV_, false, false); }  \
-        return hipGetLastError();                                                                   \
-    }
+#define SOLO_LAUNCH(BV_, BF_)                                                                       \
+    return launch(quad ? ext ? multi_big_quad_kernel<BM, BV_, BF_, MDE, true> : multi_big_quad_kernel<BM, BV_, BF_, MDE, false> \
+                       : ext ? multi_big_kernel<BM, BV_, BF_, MDE, true> : multi_big_kernel<BM, BV_, BF_, MDE, false>,          \
+                  (uint32_t)args.total_units, threads, stream, args)
+#define SOLO_CASE(BV_) if (bits_v == BV_) { if (bf16) SOLO_LAUNCH(BV_, true); else SOLO_LAUNCH(BV_, false); }
     SOLO_CASE(2) SOLO_CASE(3) SOLO_CASE(4)
 #undef SOLO_CASE
 #undef SOLO_LAUNCH
-#undef SOLO_KERNEL
     return hipErrorInvalidValue;
 }
 
@@ -725,24 +716,15 @@ hipError_t launch_big_impl(uint32_t bits_v, bool bf16, const StepArgs &args_in, 
     if (blocks == 0 || blocks > 0xFFFFFFFFull / threads) return hipErrorInvalidValue;
     args.rest = args.n % kBigBlock ? 1 : 0;
     const bool ext = args.param_bf16 || args.grad_scale || args.belief || args.l2 != 0.0f;
-#define SOLO_KERNEL(KERNEL_, BV_, BF_, EXT_, ...)                                                   \
-    hipLaunchKernelGGL((KERNEL_<BM, BV_, BF_, MDE, EXT_>), dim3((uint32_t)blocks), dim3(threads), 0, stream, __VA_ARGS__)
-#define SOLO_LAUNCH(BV_, BF_, EXT_)                                                                 \
-    do {                                                                                            \
-        if (quad) SOLO_KERNEL(big_quad_kernel, BV_, BF_, EXT_, (uint32_t)(args.n / kBigBlock), (uint32_t)(args.n % kBigBlock), args.grad, \
-                              args.m_words, args.v_words, args.m_scale, args.v_scale, args.v_base, args); \
-        else      SOLO_KERNEL(big_kernel, BV_, BF_, EXT_, args);                                    \
-    } while (0)
-#define SOLO_CASE(BV_)                                                                              \
-    if (bits_v == BV_) {                                                                            \
-        if (bf16) { if (ext) SOLO_LAUNCH(BV_, true, true); else SOLO_LAUNCH(BV_, true, false); }    \
-        else      { if (ext) SOLO_LAUNCH(BV_, false, true); else SOLO_LAUNCH(BV_, false, false); }  \
-        return hipGetLastError();                                                                   \
-    }
+#define SOLO_LAUNCH(BV_, BF_)                                                                       \
+    return quad ? launch(ext ? big_quad_kernel<BM, BV_, BF_, MDE, true> : big_quad_kernel<BM, BV_, BF_, MDE, false>, (uint32_t)blocks, threads, stream, \
+                         (uint32_t)(args.n / kBigBlock), (uint32_t)(args.n % kBigBlock), args.grad, args.m_words, args.v_words,             \
+                         args.m_scale, args.v_scale, args.v_base, args)                             \
+                : launch(ext ? big_kernel<BM, BV_, BF_, MDE, true> : big_kernel<BM, BV_, BF_, MDE, false>, (uint32_t)blocks, threads, stream, args)
+#define SOLO_CASE(BV_) if (bits_v == BV_) { if (bf16) SOLO_LAUNCH(BV_, true); else SOLO_LAUNCH(BV_, false); }
     SOLO_CASE(2) SOLO_CASE(3) SOLO_CASE(4)
 #undef SOLO_CASE
 #undef SOLO_LAUNCH
-#undef SOLO_KERNEL
     return hipErrorInvalidValue;
 }
 
