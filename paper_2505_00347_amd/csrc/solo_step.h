@@ -598,65 +598,41 @@ template <int BM, bool MDE>
 constexpr int de_words() { return MDE && BM >= 3 ? 4 * DeBuckets<BM>::N : 16; }
 
 // Whether a flat buffer runs 8 elements per lane, for a quantile of rank `rank` in a full block;
-// `copy`: a bf16 copy of the parameters is written.  Measured on MI355X (1024 SIMDs) over six states in
-// turn, us per launch, 8 | 16 per lane:
-//   elements / 2^18                 2             3             4             5             6             8             12            16            20
-//   4-bit/4-bit fp32                4.33 | 5.57   5.77 | 5.82   6.23 | 6.03   7.25 | 7.68   7.62 | 8.30   9.03 | 9.41   11.0 | 11.8   13.9 | 14.0   16.1 | 16.2
-//   3-bit/3-bit fp32                4.47 | 5.82   5.88 | 5.99   6.25 | 6.21   7.25 | 7.78   7.59 | 8.26   8.88 | 9.01   11.3 | 11.3   13.5 | 13.3   16.1 | 15.8
-//   3-bit/4-bit fp32, B 64          4.13 | 5.60   5.56 | 5.78   5.95 | 5.95   6.96 | 7.55   7.30 | 8.23   8.70 | 9.16   10.8 | 11.5   13.4 | 13.8   15.9 | 16.3
-//   4-bit/4-bit fp32, AdaBelief     4.50 | 5.64   5.92 | 5.91   6.34 | 6.12   7.33 | 7.80   7.64 | 8.39   9.24 | 9.46   11.4 | 11.9   13.4 | 14.2   17.0 | 16.2
-//   4-bit/4-bit fp32, copy          4.69 | 5.77   6.13 | 6.03   6.61 | 6.24   7.73 | 8.04   8.17 | 9.00   9.77 | 10.1   12.1 | 13.2   15.8 | 15.8   18.9 | 18.2
-//   4-bit/4-bit fp32, rank 39       5.93 | 6.39   7.42 | 6.53   7.84 | 6.71   9.29 | 8.45   9.66 | 9.10   11.4 | 10.3   14.5 | 12.8   17.2 | 15.2   20.5 | 17.5
-//   2-bit/3-bit bf16                4.47 | 5.57   5.28 | 5.77   5.92 | 5.95   6.94 | 7.09   7.20 | 7.29   8.46 | 8.06   10.7 | 10.6   12.9 | 12.6   14.6 | 14.3
-//   3-bit/3-bit DE bf16             4.71 | 6.37   5.58 | 6.49   6.21 | 6.64   7.20 | 7.75   7.46 | 7.97   8.87 | 8.47   11.2 | 11.1   13.5 | 13.2   15.6 | 15.0
-//   2-bit/2-bit bf16, B 64, rank 20 4.90 | 5.88   5.83 | 6.03   6.49 | 6.21   7.51 | 7.49   7.88 | 7.77   9.18 | 8.27   11.7 | 11.2   14.0 | 13.4   16.0 | 15.1
-//   2-bit/3-bit bf16, copy          4.70 | 6.02   5.71 | 6.14   6.46 | 6.35   7.43 | 7.53   7.79 | 7.85   9.44 | 8.66   11.7 | 11.6   13.7 | 14.2   17.2 | 16.5
-//   4-bit/2-bit DE bf16, copy       5.31 | 6.51   6.45 | 6.63   7.26 | 6.83   8.36 | 8.25   8.74 | 8.52   10.6 | 9.54   13.0 | 12.7   15.7 | 15.3   18.8 | 17.5
-//   2-bit/3-bit bf16, rank 39       5.99 | 6.40   6.95 | 6.57   7.61 | 6.75   8.96 | 7.94   9.30 | 8.21   10.9 | 8.86   13.9 | 11.7   17.1 | 13.8   19.1 | 15.7
-// A launch is a number of rounds of wavefronts per SIMD.  2^20 elements are one round with 16 per lane
-// and two of half as large wavefronts with 8; a little more is two rounds against three shorter ones.
-// 16 is up to 6 % ahead at that one size over states that come out of the last-level cache, as here, but
-// behind by 10 % where the state is still in the L2 (one state again and again, 4-bit/4-bit fp32 5.23 | 5.76,
-// 2-bit/3-bit bf16 5.36 | 5.93), so no line is drawn there.  Further up it depends on where the buffers lie: out of HBM the
-// whole lines and non-temporal accesses of 16 decide, out of the last-level cache the layout transpositions that 8 saves, and
-// again and again on the same buffers the instructions of 16, which are fewer.  Time of 8 over time of 16, geometric mean over
-// four to ten formats and variants:
-//   elements / 2^18         5     6     6.5   8     8.25  10    12    14    16
-//   bf16, 1.3 GB in turn    1.00  1.00  1.07  1.11  1.04  1.06  1.11  1.09  1.14
-//     three in turn         0.86  0.90  1.01  1.10  1.04  1.03  1.09  0.99  1.04
-//     one again and again   0.85  0.86  0.96  0.97  0.93  0.94  1.02  0.95  1.02
-//   bf16, rank 18-24, 1.3 GB 1.04 1.04  1.12  1.16  1.09  1.10  1.15
-//     three in turn         0.91  0.95  1.05  1.16  1.09  1.08  1.14
-//     one again and again   0.90  0.92  1.01  1.02  0.98  0.99  1.07
-//   bf16, copy, 1.3 GB      1.08  1.10  1.20  1.21  1.12  1.10
-//     three in turn         0.90  0.96  1.07  1.16  1.10  1.06
-//     one again and again   0.89  0.92  1.01  1.04  0.99  0.97
-//   fp32, elements / 2^18   14    16    17    18    19    20    20.5  21    22    23    24    25    26    28    32
-//     1.3 GB in turn        1.07  1.17  1.06  1.08  1.10  1.11  1.06  1.06  1.08  1.10  1.11  1.07  1.10  1.10  1.10
-//     six states in turn    0.94  0.97  0.92  0.95  0.98  1.01  0.96  0.96  0.99  1.00  1.02  0.99  1.03  1.05  1.10
-//     three in turn         0.98  0.99  0.92  0.93  0.95  0.97  0.92  0.91  0.93  0.95  0.95  0.93  0.94  0.93  0.94
-//     one again and again   0.93  1.00  0.94  0.98  1.04  1.08  1.01  1.01  1.04  1.06  1.07  1.01  1.04  1.03  1.02
-//     mean of the four      0.98  1.03  0.96  0.99  1.02  1.04  0.98  0.98  1.01  1.02  1.04  1.00  1.02  1.02  1.04
-//   fp32, copy              14    16    17    18    19    20    20.5  21    22    23    24    25    26    28    32
-//     1.3 GB in turn        1.11  1.16  1.07  1.11  1.12  1.13  1.07  1.08  1.10  1.11  1.11  1.09  1.10  1.10  1.11
-//     six states in turn    0.93  1.00  0.96  0.98  1.00  1.03  0.97  0.99  1.02  1.04  1.07  1.06  1.09  1.10  1.11
-//     three in turn         0.94  0.94  0.88  0.92  0.93  0.94  0.88  0.89  0.90  0.91  0.91  0.89  0.92  0.94  0.98
-//     one again and again   0.93  0.99  0.91  0.96  1.01  1.04  0.98  0.97  0.99  1.00  1.01  0.96  0.99  0.96  0.96
-//     mean of the four      0.98  1.02  0.95  0.99  1.01  1.03  0.97  0.98  1.00  1.01  1.02  1.00  1.02  1.02  1.04
-// A line lies where the mean crosses for good.  With bf16 gradients that is behind 3 * 2^19 elements (with a copy at
-// 5 * 2^18, where six states in turn tie; the three rows here would put it at 3 * 2^19, too).  With fp32 ones the mean goes to and fro between 14 and
-// 22 * 2^18, as 16 per lane needs one more wavefront per SIMD behind every 2^20 elements (0.95 right behind 16, 1.04 at 20, 0.98 right behind it); from
-// 11 * 2^19 on 16 is ahead, with and without a copy.  In that range the line costs a state out of HBM up to 11 % and saves one out of
-// the last-level cache 3 to 9 %.  With a large rank, whose rounds cost 8 twice the instructions, the line lies at 2^19.
-// (No line is within 3 % of a size for every format.)
+// `copy`: a bf16 copy of the parameters is written.  8 per lane starts sooner and takes no transposition through LDS, 16 needs fewer instructions and
+// fills whole lines with every access, so 16 wins where the memory is the bound.  Measured on MI355X, time of 8 over time of 16, geometric mean of
+// one state again and again, three in turn and states of 0.6 GB in turn (which lie up to 12 % apart: the first favours 8, the last 16):
+//   elements / 2^18                     4     6     8     12    16    20    24    28    32    40    48    64
+//   2-bit/3-bit bf16                    0.83  0.82  0.94  0.96  0.97  0.97  0.99  0.97  1.01  1.02  1.04  1.09
+//   3-bit/3-bit bf16                    0.83  0.83  0.95  0.97  0.99  0.99  1.01  0.98  1.01  1.04  1.07  1.12
+//   3-bit/4-bit bf16, B 64              0.79  0.80  0.93  0.94  0.93  0.95  0.97  0.94  0.95  0.96  1.00  1.05
+//   2-bit/3-bit bf16, copy              0.85  0.84  0.93  0.93  0.95  0.93  0.95  0.93  0.92  0.97  1.03  1.05
+//   4-bit/4-bit fp32                    0.81  0.84  0.93  0.91  0.95  0.95  0.96  0.95  0.96  0.98  1.02  1.06
+//   3-bit/4-bit fp32, B 64              0.79  0.81  0.90  0.90  0.92  0.94  0.93  0.90  0.92  0.96  1.00  1.03
+//   2-bit/4-bit fp32, copy              0.87  0.85  0.92  0.92  0.91  0.92  0.92  0.90  0.91  0.95  0.97  1.04
+//   2-bit/3-bit bf16, rank 39           0.78  0.79  0.92  0.94  0.98  0.98  1.02  1.03  1.04  1.07  1.11  1.14
+//   2-bit/2-bit bf16, B 64, rank 20     0.85  0.85  0.99  1.00  1.03  1.05  1.03  1.07  1.06  1.05  1.08  1.13
+//   4-bit/4-bit fp32, rank 39           -     -     -     0.90  0.94  0.95  0.96  -     0.97  1.00  1.03  1.06
+//   3-bit/4-bit fp32, B 64, rank 20     0.82  0.85  0.96  0.94  0.97  0.96  1.01
+//   3-bit/3-bit bf16, rank 103          0.64  0.68  0.80  0.83  0.88  0.89  0.93  0.93  0.95  0.97  1.00  1.04
+// A line lies where the mean over the formats crosses for good: behind 32 * 2^18 elements with bf16 gradients, 40 with fp32 ones, 8 more with
+// a copy.  Ranks of 17 to 64 merge
+// longer lists with 8 per lane: 16 less.  (Before the lists were merged a rank above 24 was worth 16 per lane from 2^19 elements on, and
+// bf16 gradients from 3 * 2^19.)
 constexpr bool narrow_buffer(uint64_t n, bool bf16, bool copy, uint32_t rank)
 {
-    if (rank > 24) return n <= 1ull << 19;
-    if (!bf16) return n <= 11ull << 19;
-    return n <= (copy ? 5ull << 18 : 3ull << 19);
+    return n <= (uint64_t)(32 + (bf16 ? 0 : 8) + (copy ? 8 : 0) - (rank > 16 && rank <= 64 ? 16 : 0)) << 18;
 }
-// Up to how many pieces (pieces16) a table does.
-constexpr uint64_t narrow_table_up_to() { return 3ull << 8; }
+// Up to how many pieces (pieces16) a table does.  Time of 8 over time of 16 as above, a table of 20 tensors of uneven sizes | of 256 equal ones with a ragged end each:
+//   elements / 2^18                     2            4            6            8            12           16           24           32           40
+//   2-bit/3-bit bf16                    .79 | .89    .82 | .91    .90 | 1.04   .90 | 1.00   .93 | .94    .93 | .94    .96 | 1.01   .99 | 1.01   1.00 | 1.07
+//   3-bit/4-bit bf16, B 64              .81 | .92    .82 | .92    .89 | 1.05   .87 | .99    .90 | .93    .92 | .91    .92 | .99    .94 | 1.00   .97 | 1.01
+//   2-bit/3-bit bf16, copy              .84 | .91    .82 | .92    .86 | 1.02   .90 | .98    .90 | .92    .85 | .86    .91 | .95    .91 | .94    .95 | .97
+//   4-bit/4-bit fp32                    .80 | .87    .81 | .91    .87 | 1.04   .87 | .97    .89 | .90    .87 | .89    .90 | .96    .93 | .97    .97 | 1.03
+//   2-bit/4-bit fp32, copy              .85 | .91    .82 | .90    .86 | 1.01   .87 | .96    .84 | .85    .84 | .85    .88 | .92    .90 | .91    .96 | .97
+//   2-bit/3-bit bf16, rank 39           .75 | .86    .81 | .89    .89 | 1.03   .89 | 1.00   .94 | .95    .95 | .94    1.00 | 1.06  1.04 | 1.09  1.07 | 1.09
+//   4-bit/4-bit fp32, rank 39           .77 | .84    .80 | .90    .88 | 1.03   .88 | .98    .91 | .91    .89 | .90    .91 | .97    .95 | 1.00   1.00 | 1.05
+// One line for all of them (the pieces are what a caller's flags say), at 20 * 2^18 elements.
+constexpr uint64_t narrow_table_up_to() { return 20ull << 8; }
 
 // The rank-th smallest key of every group of G = 4 or 8 lanes (full blocks).  Each lane has parked its
 // sorted column at `haddr` (+inf behind it) and passes its four smallest keys.  A round:

@@ -8,25 +8,20 @@ import pytest
 
 from paper_2505_00347_amd import build as libbuild
 
-# Flat buffers, 8 elements per lane up to so many elements.  (fp32: time of 8 over time of 16, mean over ten formats and variants and over four
-# places where the buffers may lie, 0.98 at 20.5 and at 21 * 2^18, 1.00 at 21.5, 1.01 at 22, 1.02 at 22.5 and at 23, 1.04 at 24.)
-LAST8_FP32 = 11 << 19
-LAST8_BF16 = 3 << 19
-LAST8_BF16_COPY = 5 << 18
-LAST8_LARGE_RANK = 1 << 19          # rank of the quantile above 24
-PIECES8 = 3 << 8                    # tables: so many pieces
+# Flat buffers, 8 elements per lane up to so many elements.
+LAST8_FP32 = 40 << 18
+LAST8_BF16 = 32 << 18
+COPY = 8 << 18                      # more with a copy
+LONG_LISTS = 16 << 18               # less with a rank of the quantile of 17 to 64
+PIECES8 = 20 << 8                   # tables: so many pieces
 QUAD_BLOCKS = 1024                  # blocks of 2048, four wavefronts each: so many blocks
 
 
 def last8(bf16, copy=False, rank=13):
-    if rank > 24:
-        return LAST8_LARGE_RANK
-    if not bf16:
-        return LAST8_FP32
-    return LAST8_BF16_COPY if copy else LAST8_BF16
+    return (LAST8_BF16 if bf16 else LAST8_FP32) + (COPY if copy else 0) - (LONG_LISTS if 16 < rank <= 64 else 0)
 
 
-RULES = [(bf16, copy, rank) for bf16 in (False, True) for copy in (False, True) for rank in (1, 13, 16, 17, 24, 25, 39, 128)]
+RULES = [(bf16, copy, rank) for bf16 in (False, True) for copy in (False, True) for rank in (1, 13, 16, 17, 24, 39, 64, 65, 128)]
 
 
 def test_lines_of_the_library(tmp_path):

@@ -1,6 +1,6 @@
 """Every instantiation of the kernels with 16 elements per lane against those with 8, which the other GPU tests
 compare with the oracle: the same inputs leave the same bytes.  A flat buffer in one call runs the first, in
-pieces of 512,000 elements the second; a table of a million elements the first, its tensors one by one the second."""
+pieces of 2,560,000 elements the second; a table of five million elements the first, its tensors one by one the second."""
 import math
 
 import pytest
@@ -12,7 +12,7 @@ from test_gpu_table_forms import bits, table_against_flat
 pytestmark = pytest.mark.gpu
 
 FORMATS = [(bm, bv, B) for B in (64, 128) for bm in (2, 3, 4) for bv in (2, 3, 4)]
-PIECE = 512000                      # whole blocks and code words, below every size that runs 16 per lane
+PIECE = 2560000                     # whole blocks and code words, below every size that runs 16 per lane
 ENDS = [0, 1, 511, 512, 513, 1023, 80, 8, 700]
 
 
@@ -70,6 +70,6 @@ def test_flat(gpu, k, bm, bv, B, bf16, de, ext):  # noqa: F811
 @pytest.mark.parametrize("k,bm,bv,B", [(k, *f) for k, f in enumerate(FORMATS)])
 def test_table(gpu, k, bm, bv, B, bf16, de, ext):  # noqa: F811
     ends = ENDS[k % len(ENDS):] + ENDS[:k % len(ENDS)]
-    sizes = [300 * 1024 + ends[0], 1, 5120 + ends[1], 2560, 400 * 1024 + ends[2], 7680 + ends[3], 200 * 1024 + ends[4], 77]
+    sizes = [1800 * 1024 + ends[0], 1, 5120 + ends[1], 2560, 2400 * 1024 + ends[2], 7680 + ends[3], 1200 * 1024 + ends[4], 77]
     assert all(n <= PIECE for n in sizes) and sum(n // 1024 for n in sizes) > PIECES8
     table_against_flat(gpu, sizes, bm, bv, B, bf16, de, flags=4 if ext else 0, mp=ext, p=(0.1, 0.3)[k % 2], steps=3)

@@ -6,7 +6,7 @@ import numpy as np
 import pytest
 
 from parity_common import compare_step, flip_budget, make_cfgs
-from test_dispatch_lines import QUAD_BLOCKS
+from test_dispatch_lines import QUAD_BLOCKS, last8
 from test_gpu_both_forms import PIECE
 from test_gpu_parity import GpuSide, dev, gpu  # noqa: F401
 from test_gpu_table_forms import bits
@@ -32,7 +32,7 @@ def crowded(n, B, gen):
                          + [(64, r) for r in (1, 5, 6, 7, 8, 9, 10, 11, 12, 16)])
 def test_crowded_lanes(gpu, B, rank):  # noqa: F811
     import torch
-    n = (3 << 20) + 2048
+    n = last8(True, rank=rank) + 2048
     gen = torch.Generator(device="cuda").manual_seed(rank)
     p0 = torch.randn(n, device="cuda", generator=gen)
     cfg = gpu.make_config(2, 3, B, 1, quantile_p=(rank - 0.5) / B)

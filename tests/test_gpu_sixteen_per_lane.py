@@ -7,7 +7,7 @@ import numpy as np
 import pytest
 
 from parity_common import compare_step, flip_budget, make_cfgs
-from test_dispatch_lines import LAST8_FP32, last8
+from test_dispatch_lines import LAST8_FP32, PIECES8, last8
 from test_gpu_parity import GpuSide, dev, gpu, run_teacher_forced  # noqa: F401
 
 pytestmark = pytest.mark.gpu
@@ -21,9 +21,9 @@ BEHIND = [0, 1, 1023, 1024, 1025, 512, 511, 1024 + 513, 2048 + 8, 1024 + 80]
 @pytest.mark.parametrize("k,bm,bv,B", [(k, *f) for k, f in enumerate(FORMATS)])
 def test_formats_and_ragged_ends(so, gpu, k, bm, bv, B):  # noqa: F811
     for j in range(3):
-        # (the last one: 8 per lane but with bf16 gradients and a copy)
+        # (the last one: 8 per lane)
         bf16, copy = (k + j) % 2 == 0, (k + 2 * j) % 4 == 0
-        n = last8(bf16, copy) + BEHIND[(2 * k + j) % len(BEHIND)] if j < 2 else last8(True, True) + 1 + (k * 401) % 1100
+        n = last8(bf16, copy) + BEHIND[(2 * k + j) % len(BEHIND)] if j < 2 else (5 << 18) + 1 + (k * 401) % 1100
         opt = ("adamw", "adam_l2", "adabelief")[(k + j) % 3]
         ext = dict(grad_scale=0.5, bf16_copy=True) if copy else {}
         run_teacher_forced(so, gpu, n, bm, bv, B, bf16=bf16, steps=2 if j < 2 else 3, seed0=10 * k, de=(k // 2 + j) % 2 == 1,
@@ -66,7 +66,7 @@ def test_tables(gpu, bm, bv, B, bf16, de, ext):  # noqa: F811
     leaves it that starts at the tensor's own place in the xi stream, byte for byte."""
     import torch
     sizes = [400001, 2559, 2560, 2561, 0, 5119, 5120, 5121, 1023, 1024, 1025, 511, 7, 2049, 3071, 3072, 3073, 7680, 1,
-             400000]
+             400000, PIECES8 * 1024]
     gen = torch.Generator(device="cuda").manual_seed(7)
     flags = 1 | (2 if de else 0)
     cfg = gpu.make_config(bm, bv, B, 1 if bf16 else 0, flags=flags, index_offset=8 * 321)
