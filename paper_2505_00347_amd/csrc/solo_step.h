@@ -77,16 +77,10 @@ constexpr float kRhoMin = 0x1p-64f;
 constexpr uint32_t kInfBits = 0x7F800000u;
 constexpr uint32_t kOneBits = 0x3F800000u;
 
-struct StepArgs {
+// What the first loads of a wavefront do not need (SOLO_FIRST_ARGS).  (Apart, so that a launch copies 160 bytes of arguments instead of 224: in
+// long runs of calls of 4096 elements the host takes 4.35 instead of 4.60 us for one.)
+struct StepRest {
     float *param;
-    const void *grad;
-    uint32_t *m_words;
-    float *m_scale;
-    uint32_t *v_words;
-    float *v_scale;
-    float *v_base;
-    uint64_t n;             // elements
-    uint64_t rest;          // 512-element iterations behind the last whole chunk, up to the end of the last code word
     uint64_t index_offset;  // global index of element 0 (multiple of 8)
     float beta1, omb1, beta2, omb2;
     float decay;            // 1 - lr * weight_decay
@@ -103,6 +97,17 @@ struct StepArgs {
     float eps_state;        // AdaBelief: eps, added to the 2nd EMA itself at every step
     uint32_t belief;        // AdaBelief: the 2nd EMA follows (g - m^)^2 instead of g^2
     uint32_t settled;       // the newest gradient is a small part of the 2nd EMA (blocks of 2048: key_floor())
+};
+
+struct StepArgs : StepRest {
+    const void *grad;
+    uint32_t *m_words;
+    float *m_scale;
+    uint32_t *v_words;
+    float *v_scale;
+    float *v_base;
+    uint64_t n;             // elements
+    uint64_t rest;          // 512-element iterations behind the last whole chunk, up to the end of the last code word
 };
 
 // One tensor of a multi-tensor launch, as the kernel reads it from the caller's table
@@ -542,6 +547,9 @@ __device__ __forceinline__ RawPG load_pg(const StepArgs &a, const uint64_t e0, c
             const uint4 *gp = reinterpret_cast<const uint4 *>(static_cast<const float *>(a.grad) + e0);
             r.g0 = gp[0]; r.g1 = gp[1];
         }
+        // (nothing so far has to wait for a scalar load, and the scheduler must not change that: 2^20 elements out of HBM, us, without | with:
+        // 4-bit/4-bit fp32 5.89 | 5.43, 3-bit/3-bit 5.64 | 5.38, 2-bit/3-bit bf16 5.14 | 4.91)
+        __builtin_amdgcn_sched_barrier(0);
         const float4 *pp = reinterpret_cast<const float4 *>(a.param + e0);
         r.p0 = pp[0]; r.p1 = pp[1];
     } else {
@@ -1004,6 +1012,14 @@ __device__ __forceinline__ void fill_level_tables(float *const my_tv, float *con
     constexpr int L = (1 << (BM - 1)) - 1;
     constexpr int VT = 1 << BV, MT = m_table_stride<BM>();
     static_assert(MT >= (MDE ? 2 * L + 2 : 2 * L + 1), "entries");
+    float level[(MT + G - 1) / G];
+    if (MDE) {                                 // (while the scales are under way: nothing of them is read in front of this point)
+#pragma unroll
+        for (int r = 0; r < (MT + G - 1) / G; ++r) {
+            level[r] = DeLevels<BM>::level((lig + r * G) & (uint32_t)(MT - 1));
+            asm volatile("" : "+v"(level[r]));
+        }
+    }
     const float s_m = (L == 1) ? dm_old : dm_old / (float)L;
     const float P1 = al_old, P2 = P1 * P1, P4 = P2 * P2, P8 = P4 * P4;
 #pragma unroll
@@ -1014,7 +1030,7 @@ __device__ __forceinline__ void fill_level_tables(float *const my_tv, float *con
 #pragma unroll
     for (int r = 0; r < (MT + G - 1) / G; ++r) {
         const uint32_t c = (lig + r * G) & (uint32_t)(MT - 1);
-        my_tm[c] = MDE ? DeLevels<BM>::level(c) * dm_old : (float)((int)c - L) * s_m;
+        my_tm[c] = MDE ? level[r] * dm_old : (float)((int)c - L) * s_m;
     }
 }
 
@@ -1829,17 +1845,20 @@ __device__ __forceinline__ void step_chunk16(const StepArgs &a, const uint64_t c
                         uint32_t *const v_words, float *const m_scale, float *const v_scale, float *const v_base
 constexpr int kFirstArgsBytes = 56;
 template <int UNIT>
-__device__ __forceinline__ void take_first_args(StepArgs &a, SOLO_FIRST_ARGS)
+__device__ __forceinline__ StepArgs all_args(const StepRest &rest, SOLO_FIRST_ARGS)
 {
+    StepArgs a;
+    static_cast<StepRest &>(a) = rest;
     a.n = (uint64_t)whole * UNIT + (more & 0xFFFFu);
     a.grad = grad; a.m_words = m_words; a.v_words = v_words; a.m_scale = m_scale; a.v_scale = v_scale; a.v_base = v_base;
+    return a;
 }
 
 // The step over one flat buffer, 8 elements per lane: one wavefront per 512 elements, the last
 // ones (up to the end of the last code word) with bounds checks where the buffer ends.
 template <int BM, int BV, int B, bool BF16, bool MDE, bool EXT>
 __global__ __launch_bounds__(kWaves * 64, kMinWaves)
-void chunk8_kernel(SOLO_FIRST_ARGS, const StepArgs args)
+void chunk8_kernel(SOLO_FIRST_ARGS, const StepRest rest)
 {
     using Lay = ChunkLayout8<BM, BV, B>;
     __shared__ __attribute__((aligned(64))) uint32_t lds_slab[kWaves * Lay::kSlab];
@@ -1851,8 +1870,7 @@ void chunk8_kernel(SOLO_FIRST_ARGS, const StepArgs args)
     const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const uint32_t c = blockIdx.x * kWaves + wave;
     uint32_t *const slab = lds_slab + wave * Lay::kSlab;
-    StepArgs a = args;
-    take_first_args<kIter>(a, whole, more, grad, m_words, v_words, m_scale, v_scale, v_base);
+    const StepArgs a = all_args<kIter>(rest, whole, more, grad, m_words, v_words, m_scale, v_scale, v_base);
     if (c < whole)
         step_chunk8<BM, BV, B, BF16, MDE, false, EXT>(a, c, lane, slab, de);
     else if (c < whole + (more >> 16))

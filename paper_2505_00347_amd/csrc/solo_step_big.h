@@ -619,16 +619,16 @@ void big_kernel(const StepArgs args)
 // Four wavefronts per block.
 template <int BM, int BV, bool BF16, bool MDE, bool EXT>
 __global__ __launch_bounds__(kQuadWaves * 64, kMinWaves)
-void big_quad_kernel(SOLO_FIRST_ARGS, const StepArgs)
+void big_quad_kernel(SOLO_FIRST_ARGS, const StepRest)
 {
     SOLO_BIG_LDS(kQuadWaves, 2048, QuadLayout::kSlab);
     if (blockIdx.x < whole) {
-        StepArgs a = arguments_here<StepArgs, kFirstArgsBytes>();
-        take_first_args<kBigBlock>(a, whole, more, grad, m_words, v_words, m_scale, v_scale, v_base);
+        const StepArgs a = all_args<kBigBlock>(arguments_here<StepRest, kFirstArgsBytes>(), whole, more, grad, m_words, v_words, m_scale,
+                                               v_scale, v_base);
         step_block_quad<BM, BV, BF16, MDE, EXT, false>(a, blockIdx.x, lane, wave, slab, lds_work, lds_xch, de);
     } else {
-        StepArgs a = arguments_here<StepArgs, kFirstArgsBytes>();
-        take_first_args<kBigBlock>(a, whole, more, grad, m_words, v_words, m_scale, v_scale, v_base);
+        const StepArgs a = all_args<kBigBlock>(arguments_here<StepRest, kFirstArgsBytes>(), whole, more, grad, m_words, v_words, m_scale,
+                                               v_scale, v_base);
         step_block_quad<BM, BV, BF16, MDE, EXT, true>(a, blockIdx.x, lane, wave, slab, lds_work, lds_xch, de);
     }
 }
