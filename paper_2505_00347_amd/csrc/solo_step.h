@@ -5,15 +5,15 @@
 // (step_chunk8).  A block of 128 (64) elements is held by 8 (4) or 16 (8) neighbouring lanes, i.e.
 // by half a DPP row or a row, and every per-block reduction is a few DPP steps.  Nothing is shared
 // between wavefronts but a constant table: the only workgroup barrier, with dynamic-exponent codes
-// of 3 and 4 bits, waits for that table while the elements' loads are under way.  No software prefetch: 56-90 registers leave room for five to eight
+// of 3 and 4 bits, waits for that table while the elements' loads are under way.  No software prefetch: 70-96 registers (a few forms 105) leave room for five or six
 // wavefronts per SIMD, which hide each other's memory latency, and the whole machine sweeps one
 // compact window of memory.
 //
 // Which of the two: what is done once per lane and block (level tables, maxima, divisions, the
 // base, the hash, packing) is spread over twice as many elements with 16 per lane, so that form
-// needs an eighth fewer instructions and is the faster one as soon as there is work for several
-// rounds of wavefronts on every SIMD; a buffer that is shorter than that takes the latency of one
-// wavefront, and 8 elements per lane have the shorter one (narrow_buffer()).  The ragged end of a
+// needs fewer instructions, and its accesses fill whole lines: the faster one where the memory is the bound, from
+// about 10^7 elements on; a shorter buffer takes the latency of a wavefront or a few one after the other, and
+// 8 elements per lane have the shorter one (narrow_buffer()).  The ragged end of a
 // buffer always runs the 8-per-lane form with bounds checks.  chunk8_kernel and chunk16_kernel run
 // over a flat buffer, multi_chunk8_kernel and multi_chunk16_kernel over the tensors of a
 // caller-built table.
