@@ -622,13 +622,22 @@ constexpr int de_words() { return MDE && BM >= 3 ? 4 * DeBuckets<BM>::N : 16; }
 //   4-bit/4-bit fp32, rank 39           -     -     -     0.90  0.94  0.95  0.96  -     0.97  1.00  1.03  1.06
 //   3-bit/4-bit fp32, B 64, rank 20     0.82  0.85  0.96  0.94  0.97  0.96  1.01
 //   3-bit/3-bit bf16, rank 103          0.64  0.68  0.80  0.83  0.88  0.89  0.93  0.93  0.95  0.97  1.00  1.04
-// A line lies where the mean over the formats crosses for good: behind 32 * 2^18 elements with bf16 gradients, 40 with fp32 ones, 8 more with
+//   states out of HBM only:
+//   2-bit/3-bit bf16                    0.86  0.84  0.95  0.96  1.03  1.00  1.01  1.00  1.03  1.07  1.08  1.17
+//   3-bit/3-bit bf16 (DE: 16 1.06, 28 1.04) 0.85 0.86 0.97 0.95 1.05  1.00  1.02  1.00  1.04  1.07  1.08  1.17
+//   2-bit/3-bit bf16, copy              0.90  0.82  0.89  0.90  0.98  0.98  1.00  0.98  1.00  1.05  1.06  1.10
+//   4-bit/4-bit fp32 (DE, AdaBelief: 32 1.08) 0.89 0.86 0.95 0.97 1.02 0.99 0.97  0.96  1.02  1.04  1.11  1.12
+//   2-bit/4-bit fp32, copy              0.93  0.80  0.87  0.92  0.96  0.95  0.96  0.93  0.94  1.00  1.06  1.12
+//   2-bit/3-bit bf16, rank 39           0.80  0.80  0.90  0.93  1.03  0.97  1.08  1.00  1.04  1.07  1.16  1.16
+//   2-bit/2-bit bf16, B 64, rank 20     0.88  0.89  0.99  0.99  1.08  1.07  1.04  1.09  1.05  1.06  1.09  1.19
+// A line lies in front of where the mean over the formats crosses for good, so that a state out of HBM, which a step between two
+// backward passes finds, loses nowhere more than a few per cent: at 24 * 2^18 elements with bf16 gradients, 28 with fp32 ones, 8 more with
 // a copy.  Ranks of 17 to 64 merge
-// longer lists with 8 per lane: 16 less.  (Before the lists were merged a rank above 24 was worth 16 per lane from 2^19 elements on, and
+// longer lists with 8 per lane: 12 less.  (Before the lists were merged a rank above 24 was worth 16 per lane from 2^19 elements on, and
 // bf16 gradients from 3 * 2^19.)
 constexpr bool narrow_buffer(uint64_t n, bool bf16, bool copy, uint32_t rank)
 {
-    return n <= (uint64_t)(32 + (bf16 ? 0 : 8) + (copy ? 8 : 0) - (rank > 16 && rank <= 64 ? 16 : 0)) << 18;
+    return n <= (uint64_t)(24 + (bf16 ? 0 : 4) + (copy ? 8 : 0) - (rank > 16 && rank <= 64 ? 12 : 0)) << 18;
 }
 // Up to how many pieces (pieces16) a table does.  Time of 8 over time of 16 as above, a table of 20 tensors of uneven sizes | of 256 equal ones with a ragged end each:
 //   elements / 2^18                     2            4            6            8            12           16           24           32           40
@@ -639,8 +648,9 @@ constexpr bool narrow_buffer(uint64_t n, bool bf16, bool copy, uint32_t rank)
 //   2-bit/4-bit fp32, copy              .85 | .91    .82 | .90    .86 | 1.01   .87 | .96    .84 | .85    .84 | .85    .88 | .92    .90 | .91    .96 | .97
 //   2-bit/3-bit bf16, rank 39           .75 | .86    .81 | .89    .89 | 1.03   .89 | 1.00   .94 | .95    .95 | .94    1.00 | 1.06  1.04 | 1.09  1.07 | 1.09
 //   4-bit/4-bit fp32, rank 39           .77 | .84    .80 | .90    .88 | 1.03   .88 | .98    .91 | .91    .89 | .90    .91 | .97    .95 | 1.00   1.00 | 1.05
-// One line for all of them (the pieces are what a caller's flags say), at 20 * 2^18 elements.
-constexpr uint64_t narrow_table_up_to() { return 20ull << 8; }
+// One line for all of them (the pieces are what a caller's flags say), at 16 * 2^18 elements; out of HBM 8 is ahead there by 3 to 10 %, at 24 by 5 % in
+// the first table and behind by 3 to 7 % in the second.
+constexpr uint64_t narrow_table_up_to() { return 16ull << 8; }
 
 // The rank-th smallest key of every group of G = 4 or 8 lanes (full blocks).  Each lane has parked its
 // sorted column at `haddr` (+inf behind it) and passes its four smallest keys.  A round:

@@ -9,11 +9,11 @@ import pytest
 from paper_2505_00347_amd import build as libbuild
 
 # Flat buffers, 8 elements per lane up to so many elements.
-LAST8_FP32 = 40 << 18
-LAST8_BF16 = 32 << 18
+LAST8_FP32 = 28 << 18
+LAST8_BF16 = 24 << 18
 COPY = 8 << 18                      # more with a copy
-LONG_LISTS = 16 << 18               # less with a rank of the quantile of 17 to 64
-PIECES8 = 20 << 8                   # tables: so many pieces
+LONG_LISTS = 12 << 18               # less with a rank of the quantile of 17 to 64
+PIECES8 = 16 << 8                   # tables: so many pieces
 QUAD_BLOCKS = 1024                  # blocks of 2048, four wavefronts each: so many blocks
 
 
