@@ -568,8 +568,8 @@ __device__ __forceinline__ void step_block_quad(const StepArgs &a, const uint64_
     if (wave == 0 && lane == 0) { a.m_scale[blk] = dm; a.v_scale[blk] = dv; a.v_base[blk] = codec.alpha; }
 }
 
-// (Two wavefronts per block: five per SIMD, 79-96 registers, and LDS allows six; four: seven or eight, 62-68 registers, and LDS allows thirteen.  The
-// plain forms of the table kernel hold both forms of a block and spill 16 bytes per lane in 19 of 36 instantiations, 32 in two.)
+// (Two wavefronts per block: five per SIMD, 79-96 registers, and LDS allows six; four: five or six, 74-85 registers, and LDS allows thirteen.  The
+// plain forms of the table kernel hold both forms of a block and spill 16 bytes per lane in 19 of 36 instantiations, 32 in three.)
 
 #define SOLO_BIG_LDS(WAVES_, WORK_, SLAB_)                                                             \
     constexpr int kDeWords = de_words<BM, MDE>();                                                      \
