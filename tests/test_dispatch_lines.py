@@ -21,6 +21,11 @@ def last8(bf16, copy=False, rank=13):
     return (LAST8_BF16 if bf16 else LAST8_FP32) + (COPY if copy else 0) - (LONG_LISTS if 16 < rank <= 64 else 0)
 
 
+def pieces(sizes):
+    """Pieces of a table: whole chunks of 1024, and 512 elements each behind them up to the end of the last code word."""
+    return sum(n // 1024 + -(-(-(-n // 80) * 80 - n // 1024 * 1024) // 512) * (n % 1024 > 0) for n in sizes)
+
+
 RULES = [(bf16, copy, rank) for bf16 in (False, True) for copy in (False, True) for rank in (1, 13, 16, 17, 24, 39, 64, 65, 128)]
 
 

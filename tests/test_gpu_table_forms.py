@@ -2,6 +2,7 @@
 starts at the tensor's own place in the xi stream, byte for byte."""
 import pytest
 
+from test_dispatch_lines import PIECES8, QUAD_BLOCKS, pieces
 from test_gpu_parity import gpu  # noqa: F401
 
 pytestmark = pytest.mark.gpu
@@ -58,8 +59,10 @@ def test_a_parameter_that_is_not_finite_leaves_the_state_alone(gpu, bf16, B):  #
     def spoil(ps):
         ps[0][17], ps[0][5119], ps[1][0] = float("inf"), float("nan"), float("-inf")
 
-    for n in (10240, 400 * 2560):               # 8 and 16 elements per lane
-        for q, st, _ in table_against_flat(gpu, [n, 5120 + 77], 2, 3, B, bf16, spoil=spoil):
+    for n in (10240, max((QUAD_BLOCKS + 1) * 2048, (PIECES8 + 1) * 1024)):      # 8 and 16 elements per lane (blocks of 2048: four wavefronts and two)
+        sizes, many = [n, 5120 + 77], n > 10240
+        assert (pieces(sizes) > PIECES8) == many and (n // 2048 > QUAD_BLOCKS) == many
+        for q, st, _ in table_against_flat(gpu, sizes, 2, 3, B, bf16, spoil=spoil):
             assert all(bool(torch.isfinite(x).all()) for x in (st.m_scale, st.v_scale, st.v_base))
 
 
@@ -68,14 +71,19 @@ def test_a_parameter_that_is_not_finite_leaves_the_state_alone(gpu, bf16, B):  #
 ENDS = [600, 1, 0, 79, 512, 513, 1023, 1024, 1025, 1535, 1537, 2047, 2048, 2560, 5119, 5120, 5121, 7, 3000, 0, 0]
 
 
-@pytest.mark.parametrize("count,bm,bv,B,bf16,de,mp", [(1, 2, 3, 128, True, False, False), (2, 4, 2, 64, True, True, True),
-                                                       (63, 3, 3, 128, False, False, True), (64, 2, 2, 64, False, True, False),
-                                                       (65, 3, 4, 128, False, False, False), (400, 4, 4, 128, True, False, True),
-                                                       (4097, 2, 3, 64, True, False, False)])
-def test_many_short_tensors(gpu, count, bm, bv, B, bf16, de, mp):  # noqa: F811
+# (the last one: behind them a tensor that makes the table one of many pieces, stepped with 16 elements per lane)
+@pytest.mark.parametrize("count,bm,bv,B,bf16,de,mp,long", [(1, 2, 3, 128, True, False, False, False), (2, 4, 2, 64, True, True, True, False),
+                                                            (63, 3, 3, 128, False, False, True, False), (64, 2, 2, 64, False, True, False, False),
+                                                            (65, 3, 4, 128, False, False, False, False), (400, 4, 4, 128, True, False, True, False),
+                                                            (4097, 2, 3, 64, True, False, False, False),
+                                                            (2, 4, 2, 64, True, True, True, True), (63, 3, 3, 128, False, False, True, True),
+                                                            (65, 3, 4, 128, False, False, False, True), (400, 4, 4, 128, True, False, True, True)])
+def test_many_short_tensors(gpu, count, bm, bv, B, bf16, de, mp, long):  # noqa: F811
     """The search for the tensor of a wavefront (64 tensors at a step) and the pieces of tensors that are
     mostly ends, in tables of few pieces and of many."""
-    table_against_flat(gpu, [ENDS[k % len(ENDS)] for k in range(count)], bm, bv, B, bf16, de, mp=mp)
+    sizes = [ENDS[k % len(ENDS)] for k in range(count)] + [PIECES8 * 1024] * long
+    assert pieces(sizes) > PIECES8 or not long
+    table_against_flat(gpu, sizes, bm, bv, B, bf16, de, mp=mp)
 
 
 @pytest.mark.parametrize("bf16", (True, False))
@@ -91,8 +99,7 @@ def test_a_launch_sized_by_the_units(gpu, bf16):  # noqa: F811
         items = [(torch.randn(n, device="cuda", generator=gen), torch.randn(n, device="cuda", generator=gen).to(dtype),
                   gpu.SoloState(n, cfg)) for n in sizes]
         table = gpu.SoloMultiTable(items, cfg)
-        assert table.flags >> 2 == sum(n // 1024 + -(-(-(-n // 80) * 80 - n // 1024 * 1024) // 512) * (n % 1024 > 0)
-                                       for n in sizes)
+        assert table.flags >> 2 == pieces(sizes)
         table.flags &= bits_kept
         table.step(1)
         table.step(2)
