@@ -302,8 +302,7 @@ class SoloState:
         # (solo_adamw_step_mp without its frame: 0.2 of the 3.9 us that a call of 4096 elements takes)
         if _step is None:
             lib()
-        rc = _step(param, param_bf16, grad, grad_scale, self.m_codes, self.m_scale, self.v_codes, self.v_scale, self.v_base,
-                   self.n, step, self.cfg, stream)
+        rc = _step(param, param_bf16, grad, grad_scale, *self.buffers(), self.n, step, self.cfg, stream)
         if rc != SOLO_OK:
             raise SoloError(rc)
         return rc

@@ -85,3 +85,20 @@ def test_a_thread_that_finds_the_library_loaded_finds_all_of_it(tmp_path):
     finally:
         sys.settrace(before)
     assert calls and b._lib is not None and not torn
+
+
+def test_a_state_steps_the_buffers_it_names(monkeypatch):
+    """SoloState.step() steps what buffers() returns, also of a subclass that returns others."""
+    class Elsewhere(solo.SoloState):
+        def __init__(self):
+            self.n, self.cfg, self.m_codes = 7, solo.make_config(), None
+
+        def buffers(self):
+            return 1, 2, 3, 4, 5
+
+    solo.lib()
+    calls = []
+    monkeypatch.setattr(solo, "_step", lambda *args: calls.append(args) or solo.SOLO_OK)
+    state = Elsewhere()
+    assert state.step(11, 12, 13, stream=14, param_bf16=15, grad_scale=16) == solo.SOLO_OK
+    assert calls == [(11, 15, 12, 16, 1, 2, 3, 4, 5, 7, 13, state.cfg, 14)]
