@@ -1853,10 +1853,22 @@ __device__ __forceinline__ void step_chunk16(const StepArgs &a, const uint64_t c
 // `whole`: chunks or blocks of UNIT elements; `more`: the elements behind them, and in the upper half how many wavefronts or blocks take those.
 #define SOLO_FIRST_ARGS const uint32_t whole, const uint32_t more, const void *const grad, uint32_t *const m_words, \
                         uint32_t *const v_words, float *const m_scale, float *const v_scale, float *const v_base
-constexpr int kFirstArgsBytes = 56;
+typedef void first_args_t(SOLO_FIRST_ARGS);
+// Where a kernel's arguments P end, each at its own alignment.
+template <typename... P>
+constexpr size_t args_end(void (*)(P...))
+{
+    size_t at = 0;
+    ((at = (at + alignof(P) - 1) / alignof(P) * alignof(P) + sizeof(P)), ...);
+    return at;
+}
+// (big_quad_kernel reads the StepRest behind them by its place)
+constexpr int kFirstArgsBytes = (int)((args_end((first_args_t *)nullptr) + alignof(StepRest) - 1) / alignof(StepRest) * alignof(StepRest));
+static_assert(kFirstArgsBytes <= 14 * 4, "more words than are loaded in front");
 template <int UNIT>
 __device__ __forceinline__ StepArgs all_args(const StepRest &rest, SOLO_FIRST_ARGS)
 {
+    static_assert(UNIT <= 0x10000, "the elements behind the whole units fit the lower half of `more`");
     StepArgs a;
     static_cast<StepRest &>(a) = rest;
     a.n = (uint64_t)whole * UNIT + (more & 0xFFFFu);
