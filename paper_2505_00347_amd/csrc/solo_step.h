@@ -1013,34 +1013,40 @@ __device__ __forceinline__ void encode_run(const XiRun &xi, const float *mh, con
 // The level tables of a block that G lanes share (decode by table look-up): lane `lig` of the group
 // fills entries lig, lig + G, ... of the 2nd-moment table (Delta_v alpha^q, alpha^q by binary
 // powering) and of the 1st-moment table (linear: (c - L) (Delta_m / L); dynamic exponent: the
-// levels times Delta_m).  Lanes beyond the entries fill one again, and the linear 1st-moment table its unused last one,
-// so that nothing is conditional and the code around it stays one block for the compiler's scheduler.
-template <int BM, int BV, bool MDE, int G>
+// levels times Delta_m).  ALL (where a launch is all latency): lanes beyond the entries fill one again, and the linear 1st-moment table its unused last one,
+// so that nothing is conditional and the code around it stays one block for the compiler's scheduler.  (With 16 elements per lane that schedule takes
+// more registers, 81-88 instead of 75-80, a wavefront per SIMD less, in 23 of 288 instantiations and fewer in about as many.  2^26 elements, us, with conditions |
+// without: tables 3-bit/2-bit with a copy 145.8 | 148.6, 4-bit/2-bit DE with a copy 152.6 | 157.0, 4-bit/3-bit DE fp32 149.0 | 152.7; 3-bit/4-bit with a copy 137.8 | 142.1;
+// where it took fewer, 2-bit/3-bit fp32 B 64 DE with a copy 165.6 | 164.2.)
+template <int BM, int BV, bool MDE, int G, bool ALL>
 __device__ __forceinline__ void fill_level_tables(float *const my_tv, float *const my_tm, const uint32_t lig,
                                                   const float dm_old, const float dv_old, const float al_old)
 {
     constexpr int L = (1 << (BM - 1)) - 1;
-    constexpr int VT = 1 << BV, MT = m_table_stride<BM>();
-    static_assert(MT >= (MDE ? 2 * L + 2 : 2 * L + 1), "entries");
+    constexpr int VT = 1 << BV, kEntries = MDE ? 2 * L + 2 : 2 * L + 1, MT = ALL ? m_table_stride<BM>() : kEntries;
+    static_assert(m_table_stride<BM>() >= kEntries, "entries");
     float level[(MT + G - 1) / G];
-    if (MDE) {                                 // (while the scales are under way: nothing of them is read in front of this point)
+    if (MDE) {                                 // (ALL: while the scales are under way: nothing of them is read in front of this point)
 #pragma unroll
         for (int r = 0; r < (MT + G - 1) / G; ++r) {
-            level[r] = DeLevels<BM>::level((lig + r * G) & (uint32_t)(MT - 1));
-            asm volatile("" : "+v"(level[r]));
+            level[r] = DeLevels<BM>::level(ALL ? (lig + r * G) & (uint32_t)(MT - 1) : lig + r * G);
+            if (ALL) asm volatile("" : "+v"(level[r]));
         }
     }
+    // (The scales are here: a load whose value is used under the conditions below only would be moved behind them, and
+    // its latency with it.)
+    if (!ALL) asm volatile("" : : "v"(dm_old), "v"(dv_old), "v"(al_old));
     const float s_m = (L == 1) ? dm_old : dm_old / (float)L;
     const float P1 = al_old, P2 = P1 * P1, P4 = P2 * P2, P8 = P4 * P4;
 #pragma unroll
     for (int r = 0; r < (VT + G - 1) / G; ++r) {
-        const uint32_t q = (lig + r * G) & (uint32_t)(VT - 1);
-        my_tv[q] = log_level<BV>(q, P1, P2, P4, P8) * dv_old;
+        const uint32_t q = ALL ? (lig + r * G) & (uint32_t)(VT - 1) : lig + r * G;
+        if (ALL || q < VT) my_tv[q] = log_level<BV>(q, P1, P2, P4, P8) * dv_old;
     }
 #pragma unroll
     for (int r = 0; r < (MT + G - 1) / G; ++r) {
-        const uint32_t c = (lig + r * G) & (uint32_t)(MT - 1);
-        my_tm[c] = MDE ? level[r] * dm_old : (float)((int)c - L) * s_m;
+        const uint32_t c = ALL ? (lig + r * G) & (uint32_t)(MT - 1) : lig + r * G;
+        if (ALL || c < MT) my_tm[c] = MDE ? level[r] * dm_old : (float)((int)c - L) * s_m;
     }
 }
 
@@ -1167,15 +1173,14 @@ __device__ __forceinline__ void write_back_word(uint32_t *const word, const uint
     if (changed) atomicXor(word, changed);
 }
 
-// The first word of a stream of ten-to-a-word codes that `chunk`'s elements touch (chunks of 512 or 1024, at most 2^31 of them:
-// five fill whole words), and the slot of the first element in it.
-template <int ELEMS>
+// The first word of a stream of ten-to-a-word codes that the 512 elements of `chunk` (at most 2^31 of them:
+// five fill whole words) touch, and the slot of the first element in it, in 32-bit arithmetic.
 __device__ __forceinline__ uint64_t first_word10(const uint32_t chunk, uint32_t &slot)
 {
-    static_assert(5 * ELEMS % 10 == 0 && ELEMS <= 1024, "five chunks fill whole words");
-    const uint32_t five = chunk / 5u, r = chunk - 5u * five, words = r * (uint32_t)ELEMS / 10u;
-    slot = r * (uint32_t)ELEMS - 10u * words;
-    return (uint64_t)five * (5 * ELEMS / 10) + words;
+    static_assert(5 * kIter % 10 == 0, "five chunks fill whole words");
+    const uint32_t five = chunk / 5u, r = chunk - 5u * five, words = r * (uint32_t)kIter / 10u;
+    slot = r * (uint32_t)kIter - 10u * words;
+    return (uint64_t)five * (5 * kIter / 10) + words;
 }
 
 // The codes of the 512 elements that a wavefront steps on its own (8 consecutive elements per lane).  Eight 2- or
@@ -1196,7 +1201,7 @@ struct LaneCodes8 {
     __device__ __forceinline__ void load(uint32_t *const words, const uint64_t n, const uint64_t ew0, const uint32_t lane)
     {
         uint64_t lo;
-        if (BITS == 3) lo = first_word10<kIter>((uint32_t)(ew0 / kIter), first);
+        if (BITS == 3) lo = first_word10((uint32_t)(ew0 / kIter), first);
         else { lo = ew0 / C; first = 0; }
         word = words + lo;
         // (Lanes without a word load the last one again: a load under a condition whose fields are masked
@@ -1357,7 +1362,7 @@ __device__ __forceinline__ void step_chunk8(const StepArgs &a, const uint64_t ch
 
     // ---- level tables of this lane's block: entries lig, lig + G, ...
     const uint32_t de_base = kDeTable ? lds_addr(de.lds) - 16u * DeBuckets<BM>::kLo : 0u;    // bucket table address, less the first bucket's index
-    fill_level_tables<BM, BV, MDE, G>(my_tv, my_tm, lig, dm_old, dv_old, al_old);
+    fill_level_tables<BM, BV, MDE, G, true>(my_tv, my_tm, lig, dm_old, dv_old, al_old);
     wave_lds_sync();
     const uint32_t mc8 = mw.codes(lane), vc8 = vw.codes(lane);
 
@@ -1675,10 +1680,9 @@ struct LaneCodes16 {
     template <bool FULL>
     __device__ __forceinline__ void load(uint32_t *const words, const uint64_t ew0, const uint32_t lane, const uint32_t here)
     {
-        uint64_t lo;
-        if (BITS == 3) lo = first_word10<kIter16>((uint32_t)(ew0 / kIter16), first);
-        else { lo = ew0 / C; first = 0; }
+        const uint64_t lo = ew0 / C;
         word = words + lo;
+        first = (uint32_t)(ew0 - lo * C);
         nw = here ? (first + here + C - 1) / C : 0;
         if (FULL && BITS == 4 && !STAGED) {
             const uint2 two = *reinterpret_cast<const uint2 *>(word + 2u * lane);
@@ -1813,7 +1817,7 @@ __device__ __forceinline__ void step_chunk16(const StepArgs &a, const uint64_t c
     mw.stage(img_m, lane);
     vw.stage(img_v, lane);
     const uint32_t de_base = kDeTable ? lds_addr(de.lds) - 16u * DeBuckets<BM>::kLo : 0u;
-    fill_level_tables<BM, BV, MDE, G>(my_tv, my_tm, lig, dm_old, dv_old, al_old);
+    fill_level_tables<BM, BV, MDE, G, false>(my_tv, my_tm, lig, dm_old, dv_old, al_old);
     wave_lds_sync();
     uint32_t mc8[2], vc8[2];
     mw.codes(img_m, lane, mc8);

@@ -382,7 +382,7 @@ __device__ __forceinline__ void step_block(const StepArgs &a, const uint64_t blk
     vw.stage(img_v, lane);
 
     // ---- level tables of the block (every wavefront its own copy)
-    fill_level_tables<BM, BV, MDE, 64>(my_tv, my_tm, lane, dm_old, dv_old, al_old);
+    fill_level_tables<BM, BV, MDE, 64, false>(my_tv, my_tm, lane, dm_old, dv_old, al_old);
     wave_lds_sync();
     uint32_t mc8[2], vc8[2];
     mw.codes(img_m, lane, mc8);
@@ -517,7 +517,7 @@ __device__ __forceinline__ void step_block_quad(const StepArgs &a, const uint64_
     mw.clear(img_m, lane);
     vw.clear(img_v, lane);
     de.store();
-    fill_level_tables<BM, BV, MDE, 64>(my_tv, my_tm, lane, dm_old, dv_old, al_old);
+    fill_level_tables<BM, BV, MDE, 64, true>(my_tv, my_tm, lane, dm_old, dv_old, al_old);
     wave_lds_sync();
     const uint32_t mc8 = mw.codes(lane), vc8 = vw.codes(lane);
     const uint32_t floor = key_floor<BV, EXT>(a, my_tv);
