@@ -528,14 +528,17 @@ __device__ __forceinline__ uint32_t pack_bf16(float lo, float hi)
 // kilobytes, twice the requests of a coalesced one, but nothing has to be turned around through LDS:
 // the code for 8 elements per lane runs where a launch is all latency (the transposition and its
 // waits were 500 of the 6400-7200 cycles of a wavefront).  TAIL: unless `whole` says that
-// all of them exist, element by element, the last one again in place of those that don't: under conditions the loads waited for each other
-// (100,003 elements 2-bit/2-bit B 64, us in a graph: 3.95 | 3.45 with the last one again).  (A caller asks for a wavefront, whose loads
-// are then all under way at once, or, with a long chain behind them, for every lane.)
+// all of them exist, element by element; a caller asks for a wavefront, whose loads
+// are then all under way at once, or for every lane.  ALONE: the last element again in place of those that don't exist: under conditions the loads wait for each other,
+// which a short launch feels (100,003 elements 2-bit/2-bit B 64, us in a graph: 3.95 | 3.45 with the last one again).  What a long buffer or a table has behind its
+// chunks of 1024 runs between wavefronts that wait for memory anyway, and sixteen loads per lane at once go in front of theirs: there every lane whose elements all exist loads
+// vectors, and the one that holds the end loads under conditions.  (Tables, 2-bit/3-bit bf16, conditions for every lane | the last one again | this, us: 256 tensors,
+// 4.4 million elements 14.40 | 14.95 | 14.47, 20 tensors of them 14.73 | 15.09 | 14.72, 1000 tensors of 12.5 million 30.15 | 30.75 | 28.96, 4000 tensors of 12.2 million 37.97 | 36.12 | 33.50.)
 // The parameters last: nothing needs them before the step's end (states out of HBM, in front | behind, us: 2^20 elements 4-bit/4-bit fp32 6.22 | 5.90,
 // 3-bit/3-bit 5.90 | 5.59; out of the last-level cache the same).
 struct RawPG { float4 p0, p1; uint4 g0, g1; };
 
-template <bool BF16, bool TAIL>
+template <bool BF16, bool TAIL, bool ALONE = true>
 __device__ __forceinline__ RawPG load_pg(const StepArgs &a, const uint64_t e0, const bool whole)
 {
     RawPG r;
@@ -555,17 +558,17 @@ __device__ __forceinline__ RawPG load_pg(const StepArgs &a, const uint64_t e0, c
     } else {
         float p[8]; uint32_t g[8];
 #pragma unroll
-        for (int j = 0; j < 8; ++j) {                  // (the last element in place of one that does not exist, to keep conditions off the loads)
-            const uint64_t e = umin64(e0 + j, a.n - 1u);
+        for (int j = 0; j < 8; ++j) {
+            const uint64_t e = ALONE ? umin64(e0 + j, a.n - 1u) : e0 + j;
+            p[j] = 0.0f; g[j] = 0u;
+            if (!ALONE && e >= a.n) continue;
             p[j] = a.param[e];
             if (BF16) g[j] = static_cast<const uint16_t *>(a.grad)[e];
             else      g[j] = static_cast<const uint32_t *>(a.grad)[e];
         }
 #pragma unroll
         for (int j = 0; j < 8; ++j) {
-            const bool ok = e0 + j < a.n;
-            p[j] = ok ? p[j] : 0.0f;
-            g[j] = ok ? g[j] : 0u;
+            if (ALONE && e0 + j >= a.n) { p[j] = 0.0f; g[j] = 0u; }
         }
         r.p0 = make_float4(p[0], p[1], p[2], p[3]); r.p1 = make_float4(p[4], p[5], p[6], p[7]);
         if (BF16) r.g0 = make_uint4(g[0] | (g[1] << 16), g[2] | (g[3] << 16), g[4] | (g[5] << 16), g[6] | (g[7] << 16));
@@ -1306,9 +1309,11 @@ struct ChunkLayout8 {
 // conditions, 3-bit codes straight from the words a lane loads and the position of those words by 32-bit arithmetic, us per launch in a
 // graph, before | after: 4096 elements 2-bit/3-bit 3.15 | 3.01, 2^20 4-bit/4-bit fp32 4.55 | 4.46, 3-bit/3-bit 4.78 | 4.61, 2-bit/3-bit bf16
 // 4.71 | 4.54, 5 million 4-bit/4-bit fp32 13.7 | 13.4.)
+// ALONE: in a launch of such wavefronts; otherwise between wavefronts with 16 elements per lane, where the chain of one does not count: the
+// parameters are then made, and stored, in front of the selection (tables as above, behind it | in front of it: 13.86 | 13.49 of 4.4 million elements).
 // EXT: the code that also serves the variants of the step (gradient scale, coupled decay,
 // AdaBelief, bf16 weight copy); the plain AdamW step runs the one without them.
-template <int BM, int BV, int B, bool BF16, bool MDE, bool TAIL, bool EXT>
+template <int BM, int BV, int B, bool BF16, bool MDE, bool TAIL, bool EXT, bool ALONE = true>
 __device__ __forceinline__ void step_chunk8(const StepArgs &a, const uint64_t chunk, const uint32_t lane,
                                             uint32_t *const slab, const DeTable<BM, MDE> &de)
 {
@@ -1347,15 +1352,15 @@ __device__ __forceinline__ void step_chunk8(const StepArgs &a, const uint64_t ch
     vw.load(a.v_words, a.n, ew0, lane);
     const uint64_t gb_here = TAIL ? umin64(gb, (a.n - 1u) / B) : gb;
     const float dm_old = a.m_scale[gb_here], dv_old = a.v_scale[gb_here], al_old = a.v_base[gb_here];
-    const bool whole = !TAIL || __builtin_expect(ew0 + kIter <= a.n, 0);
-    const RawPG raw = load_pg<BF16, TAIL>(a, e0, whole);
+    const bool whole = !TAIL || (ALONE ? __builtin_expect(ew0 + kIter <= a.n, 0) : e0 + 8u <= a.n);
+    const RawPG raw = load_pg<BF16, TAIL, ALONE>(a, e0, whole);
     const float gscale = (EXT && a.grad_scale) ? *a.grad_scale : 1.0f;      // uniform: the gradient is transformed first
 
     // ---- while they are under way: what does not depend on them
     uint32_t xi_word[1];
     XiGroups(a, ew0).words<1>(a, lane, xi_word);
     XiRun xi(a, xi_word[0]);
-    xi.X = fresh(xi.X); xi.Y = fresh(xi.Y);
+    if (ALONE) { xi.X = fresh(xi.X); xi.Y = fresh(xi.Y); }
     mw.clear(img_m, lane);
     vw.clear(img_v, lane);
     de.ready();
@@ -1376,6 +1381,10 @@ __device__ __forceinline__ void step_chunk8(const StepArgs &a, const uint64_t ch
     float mh[8], vh[8];
     float m_absmax, v_max;                     // (v_max of full chunks: the last sorted key below)
     ema_param<8, BM, BV, EXT, TAIL, TAIL>(a, tm_addr, tv_addr, &mc8, &vc8, ok, p, g, mh, vh, m_absmax, v_max);
+    if (!ALONE) {
+        new_param8(a, mh, vh, p);
+        store_params8<EXT, TAIL>(a, e0, whole, ok, p);
+    }
 
     // ---- the lane's v^ sorted (non-negative floats order like their bit patterns); block maxima
     uint32_t key[8];
@@ -1398,8 +1407,10 @@ __device__ __forceinline__ void step_chunk8(const StepArgs &a, const uint64_t ch
     const uint32_t xp_bits = merged_rth8<G>(key, lane, rank, a.rank_full);
 
     // ---- parameter; the block's encoder constants, then this lane's 8 codes of each moment
-    new_param8(a, mh, vh, p);
-    store_params8<EXT, TAIL>(a, e0, whole, ok, p);
+    if (ALONE) {
+        new_param8(a, mh, vh, p);
+        store_params8<EXT, TAIL>(a, e0, whole, ok, p);
+    }
     const BlockCodec codec = block_codec<BV, G, L, MDE>(xp_bits, dm, dv, lane, lig, gshift);
     uint32_t m8, v8;
     encode_run<BM, BV, MDE, TAIL>(xi, mh, vh, ok, codec, de_base, m8, v8);
@@ -1927,7 +1938,7 @@ void chunk16_kernel(const StepArgs a)
         else
             de.ready();
     } else {
-        step_chunk8<BM, BV, B, BF16, MDE, true, EXT>(a, a.n / kIter16 * (kIter16 / kIter) + c, lane, slab, de);
+        step_chunk8<BM, BV, B, BF16, MDE, true, EXT, false>(a, a.n / kIter16 * (kIter16 / kIter) + c, lane, slab, de);
     }
 }
 
@@ -2047,7 +2058,7 @@ void multi_chunk16_kernel(const MultiArgs ma)
     if (c < whole)
         step_chunk16<BM, BV, B, BF16, MDE, EXT>(a, c, lane, slab, de);
     else if ((whole + c) * kIter < end_of_words(a.n))
-        step_chunk8<BM, BV, B, BF16, MDE, true, EXT>(a, whole + c, lane, slab, de);
+        step_chunk8<BM, BV, B, BF16, MDE, true, EXT, false>(a, whole + c, lane, slab, de);
     else
         de.ready();
 }
