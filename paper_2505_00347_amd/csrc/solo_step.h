@@ -535,7 +535,10 @@ __device__ __forceinline__ uint32_t pack_bf16(float lo, float hi)
 // vectors, and the one that holds the end loads under conditions.  (Tables, 2-bit/3-bit bf16, conditions for every lane | the last one again | this, us: 256 tensors,
 // 4.4 million elements 14.40 | 14.95 | 14.47, 20 tensors of them 14.73 | 15.09 | 14.72, 1000 tensors of 12.5 million 30.15 | 30.75 | 28.96, 4000 tensors of 12.2 million 37.97 | 36.12 | 33.50.)
 // The parameters last: nothing needs them before the step's end (states out of HBM, in front | behind, us: 2^20 elements 4-bit/4-bit fp32 6.22 | 5.90,
-// 3-bit/3-bit 5.90 | 5.59; out of the last-level cache the same).
+// 3-bit/3-bit 5.90 | 5.59; out of the last-level cache the same).  And past the caches: a step mostly runs behind other work, whose written lines still fill the
+// last-level cache, and a load that allocates there waits for one of them to be written back.  (Behind 512 MB of other writes, kernel time in us, through the
+// caches | past them: 2^20 elements 4-bit/4-bit fp32 6.7 | 5.8, 3-bit/3-bit 6.8 | 5.5, 5 million 2-bit/3-bit bf16 20.9 | 16.9, 4-bit/4-bit fp32 AdaBelief 22.6 | 20.7, 2 million
+// in blocks of 2048 13.0 | 10.9; states out of HBM in turn 2^20 4-bit/4-bit fp32 5.4 | 5.0; the same buffers again and again 4.30 | 4.35, 5 million 13.8 | 13.2.)
 struct RawPG { float4 p0, p1; uint4 g0, g1; };
 
 template <bool BF16, bool TAIL, bool ALONE = true>
@@ -553,8 +556,9 @@ __device__ __forceinline__ RawPG load_pg(const StepArgs &a, const uint64_t e0, c
         // (nothing so far has to wait for a scalar load, and the scheduler must not change that: 2^20 elements out of HBM, us, without | with:
         // 4-bit/4-bit fp32 5.89 | 5.43, 3-bit/3-bit 5.64 | 5.38, 2-bit/3-bit bf16 5.14 | 4.91)
         __builtin_amdgcn_sched_barrier(0);
-        const float4 *pp = reinterpret_cast<const float4 *>(a.param + e0);
-        r.p0 = pp[0]; r.p1 = pp[1];
+        const f32x4_t *const pp = reinterpret_cast<const f32x4_t *>(a.param + e0);
+        const f32x4_t low = __builtin_nontemporal_load(pp), high = __builtin_nontemporal_load(pp + 1);
+        r.p0 = make_float4(low.x, low.y, low.z, low.w); r.p1 = make_float4(high.x, high.y, high.z, high.w);
     } else {
         float p[8]; uint32_t g[8];
 #pragma unroll
