@@ -477,6 +477,10 @@ struct QuadLayout {
 };
 static_assert(2 * LaneCodes8<3, true>::kImage <= QuadLayout::kOffTv, "images");
 
+// The parameters are made behind the selection, out of the chain of the block, but for TAIL in front of it: the kernel for tables runs that form for all
+// blocks, in launches of thousands of them too, and with eight values less alive across the selection it takes 64-68 registers instead of 74-85, seven or eight
+// wavefronts per SIMD instead of five or six.  (4000 tensors of 1000 elements, behind | in front, us: 2-bit/3-bit bf16 23.8 | 22.7, 4-bit/2-bit DE fp32 24.5 | 23.2,
+// 3-bit/3-bit DE bf16 with a copy 25.4 | 24.6; 20 tensors, 1000 blocks 9.67 | 9.92, 10.98 | 11.19; 1,000,003 elements 6.78 | 6.66.)
 template <int BM, int BV, bool BF16, bool MDE, bool EXT, bool TAIL>
 __device__ __forceinline__ void step_block_quad(const StepArgs &a, const uint64_t blk, const uint32_t lane,
                                                 const uint32_t wave, uint32_t *const slab, uint32_t *const work,
@@ -533,6 +537,10 @@ __device__ __forceinline__ void step_block_quad(const StepArgs &a, const uint64_
     float mh[8], vh[8];
     float m_absmax, v_max;
     ema_param<8, BM, BV, EXT, TAIL, true>(a, tm_addr, tv_addr, &mc8, &vc8, ok, p, g, mh, vh, m_absmax, v_max);
+    if (TAIL) {
+        new_param8(a, mh, vh, p);
+        store_params8<EXT, TAIL>(a, e0, ok[7], ok, p);
+    }
 
     // ---- block maxima over the four wavefronts (read behind the selection's barriers)
     {
@@ -545,8 +553,10 @@ __device__ __forceinline__ void step_block_quad(const StepArgs &a, const uint64_
 #pragma unroll
     for (int j = 0; j < 8; ++j) key[j] = ok[j] ? f2u(vh[j]) : kNoKey;
     const uint32_t xp_bits = select_rank<8, kQuadWaves, true>(key, floor, rank_among(a, present), present, lane, wave, work, xch);
-    new_param8(a, mh, vh, p);
-    store_params8<EXT, TAIL>(a, e0, ok[7], ok, p);
+    if (!TAIL) {
+        new_param8(a, mh, vh, p);
+        store_params8<EXT, TAIL>(a, e0, ok[7], ok, p);
+    }
     float dm = u2f(umax(umax(xch[Xch::kMaxM], xch[Xch::kMaxM + 1]), umax(xch[Xch::kMaxM + 2], xch[Xch::kMaxM + 3])));
     float dv = u2f(largest_key<kQuadWaves>(xch));
     if (dm < kTiny) dm = 0.0f;
@@ -568,7 +578,7 @@ __device__ __forceinline__ void step_block_quad(const StepArgs &a, const uint64_
     if (wave == 0 && lane == 0) { a.m_scale[blk] = dm; a.v_scale[blk] = dv; a.v_base[blk] = codec.alpha; }
 }
 
-// (Two wavefronts per block: five per SIMD, 79-96 registers, and LDS allows six; four: five or six, 74-85 registers, and LDS allows thirteen.  The
+// (Two wavefronts per block: five per SIMD, 79-96 registers, and LDS allows six; four: six to eight, 60-74 registers, and LDS allows thirteen.  The
 // plain forms of the table kernel hold both forms of a block and spill 16 bytes per lane in 19 of 36 instantiations, 32 in three.)
 
 #define SOLO_BIG_LDS(WAVES_, WORK_, SLAB_)                                                             \
@@ -664,19 +674,18 @@ void multi_big_quad_kernel(const MultiArgs ma)
 // Up to how many blocks a launch gives four wavefronts to each: with few blocks the time is the
 // chain of one, which four make shorter; the two-wavefront form has the fewer instructions and reads whole lines.  Measured on MI355X,
 // us per launch, four | two wavefronts per block, three states in turn:
-//   blocks                             1            128          488          750          1000           1500           2000           3000           5000
-//   2-bit/3-bit bf16                   4.71 | 6.10  5.43 | 6.73  6.53 | 8.14  7.44 | 8.69  9.31 | 9.09    11.88 | 12.60  14.25 | 14.24  18.35 | 18.72  25.4 | 25.3
-//   2-bit/3-bit AdaBelief fp32         4.95 | 7.11  5.59 | 7.71  6.70 | 9.14  8.36 | 9.63  10.07 | 10.35  12.45 | 14.12  14.96 | 16.16  18.80 | 21.23  27.5 | 29.0
-//   4-bit/2-bit DE fp32                5.13 | 6.77  6.20 | 7.69  7.14 | 9.06  9.01 | 9.53  10.61 | 10.75  13.10 | 14.47  15.63 | 16.40  19.71 | 21.52  28.8 | 29.1
-//   2-bit/2-bit bf16, p 0.3            5.11 | 6.84  6.18 | 7.59  7.30 | 8.96  8.33 | 9.44  10.10 | 9.86   12.81 | 13.32  15.43 | 15.38  19.03 | 19.79  26.4 | 27.2
-//   3-bit/3-bit DE bf16, copy          5.33 | 7.50  6.16 | 8.25  7.27 | 9.57  8.69 | 10.2  11.03 | 10.58  13.97 | 13.96  16.57 | 16.84  20.74 | 21.46  30.8 | 29.9
-//   time of four over time of two, geometric mean of these five, states of 1.3 GB together in turn / three in turn / one again and again:
-//   flat      488 blocks .85 .78 .78,  750 .96 .88 .85,  1000 1.01 1.01 .92,  1200 1.01 .99 .92,  1500 .99 .94 .92,  1800 1.02 .96 1.01,  2000 1.04 .97 1.01,  5000 1.08 .99 1.00
-//   table     488 blocks .86 .80 .80,  1000 1.01 .97 .90,  1500 1.07 1.01 .95,  2000 1.10 1.01 1.01,  3000 1.09 .98 1.04
-//   (Both cross between 1000 and 1800 blocks, tables first.  One line for both, at four workgroups on each CU: flat launches of 1100 to 1700
-//   blocks would be 3-5 % faster by four in the mean of the three, tables of that size 1 % slower.)
-//   4000 tensors of 1000 elements (a block each): 27 | 42 with earlier kernels, so a table of which at least three in four
-//   blocks are the only one of their tensor takes four at any size.
+//   blocks                             1            128          488          750           1000          1200           1500
+//   2-bit/3-bit bf16                   4.81 | 6.41  5.64 | 8.17  6.53 | 8.86  7.56 | 9.44   8.56 | 10.24  9.47 | 11.36   10.45 | 13.06
+//   2-bit/3-bit AdaBelief fp32         5.05 | 7.30  6.04 | 8.07  7.30 | 9.65  8.27 | 10.41  9.28 | 11.03  10.61 | 12.66  12.11 | 14.88
+//   4-bit/2-bit DE fp32                5.23 | 6.87  6.32 | 8.11  7.37 | 9.37  8.40 | 10.05  9.55 | 11.09  10.94 | 12.85  12.28 | 14.82
+//   2-bit/2-bit bf16, p 0.3            4.53 | 6.33  5.58 | 7.63  6.55 | 8.51  7.47 | 9.10   8.42 | 9.92   9.31 | 11.25   10.29 | 13.02
+//   3-bit/3-bit DE bf16, copy          5.34 | 7.82  6.17 | 9.08  7.20 | 9.95  8.25 | 10.57  9.18 | 11.16  10.22 | 12.44  13.43 | 14.61
+//   time of four over time of two, geometric mean of these five, states of 0.7 GB in turn / three in turn / one again and again / behind 512 MB of other writes:
+//   488 blocks .75 .75 .77 .80,  750 .79 .81 .84 .86,  1000 .82 .84 .89 .93,  1200 .81 .83 .86 .94,  1500 .82 .82 .84 .98
+//   (With earlier kernels the two crossed between 1000 and 1800 blocks, tables first.  The line is four workgroups on each CU, the last size with a margin
+//   behind other writes too, where AdaBelief is behind by 3 % already.)
+//   Tables of 1000-element tensors, a block each, three in turn: 500 of them 7.3 | 10.2, 1100 9.8 | 12.7, 2000 14.1 | 16.1, 4000 22.7 | 27.3, 4-bit/2-bit DE fp32 23.2 | 29.0,
+//   so a table of which at least three in four blocks are the only one of their tensor takes four at any size.
 constexpr uint64_t kQuadUpTo = 1024;
 constexpr bool quad_table(uint64_t blocks, uint64_t tensors) { return blocks <= kQuadUpTo || 4 * blocks <= 5 * tensors; }
 
