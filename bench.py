@@ -13,7 +13,6 @@ oracle timed on the host cores of this machine on a bounded sample of the same workl
 import argparse
 import contextlib
 import json
-import math
 import os
 import sys
 import time
@@ -55,8 +54,7 @@ def step_kernel_name(w, n, mp, launch):
     if multi:                                    # chunks of 1024, then 512 elements each to the end of the last code word
         pieces = sum(k // 1024 + (-(-(-(-k // 80) * 80 - k // 1024 * 1024) // 512) if k % 1024 else 0) for k in sizes)
         return f"solo::multi_chunk{8 if pieces <= 16 << 8 else 16}_kernel"
-    rank = min(B, max(1, math.ceil(w.quantile_p * B)))
-    up_to = (24 + (0 if bf16 else 4) + (8 if mp else 0) - (12 if 16 < rank <= 64 else 0)) << 18
+    up_to = (12 if bf16 and mp else 20) << 18
     return f"solo::chunk{8 if n <= up_to else 16}_kernel"
 
 

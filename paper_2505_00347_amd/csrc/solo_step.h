@@ -12,7 +12,7 @@
 // Which of the two: what is done once per lane and block (level tables, maxima, divisions, the
 // base, the hash, packing) is spread over twice as many elements with 16 per lane, so that form
 // needs fewer instructions, and its accesses fill whole lines: the faster one where the memory is the bound, from
-// about 10^7 elements on; a shorter buffer takes the latency of a wavefront or a few one after the other, and
+// about 5 * 10^6 elements on; a shorter buffer takes the latency of a wavefront or a few one after the other, and
 // 8 elements per lane have the shorter one (narrow_buffer()).  The ragged end of a
 // buffer always runs the 8-per-lane form with bounds checks.  chunk8_kernel and chunk16_kernel run
 // over a flat buffer, multi_chunk8_kernel and multi_chunk16_kernel over the tensors of a
@@ -539,16 +539,20 @@ __device__ __forceinline__ uint32_t pack_bf16(float lo, float hi)
 // last-level cache, and a load that allocates there waits for one of them to be written back.  (Behind 512 MB of other writes, kernel time in us, through the
 // caches | past them: 2^20 elements 4-bit/4-bit fp32 6.7 | 5.8, 3-bit/3-bit 6.8 | 5.5, 5 million 2-bit/3-bit bf16 20.9 | 16.9, 4-bit/4-bit fp32 AdaBelief 22.6 | 20.7, 2 million
 // in blocks of 2048 13.0 | 10.9; states out of HBM in turn 2^20 4-bit/4-bit fp32 5.4 | 5.0; the same buffers again and again 4.30 | 4.35, 5 million 13.8 | 13.2.)
+// PAST: bf16 gradients, too (in blocks of 128 and 64: behind other writes, parameters only | both, us: 2.5 million elements 2-bit/3-bit 11.1 | 10.3, 5 million 16.9 | 16.0;
+// states in turn 7.1 | 7.3, 12.3 | 12.6).  Not fp32 ones (20.7 | 18.0, but three states in turn 14.6 | 15.8), nor in blocks of 2048 (8.6 | 8.7 and 9.2 | 9.6 in turn, 10.7 | 10.7 and 12.2 | 12.0).
 struct RawPG { float4 p0, p1; uint4 g0, g1; };
 
-template <bool BF16, bool TAIL, bool ALONE = true>
+template <bool BF16, bool TAIL, bool ALONE = true, bool PAST = false>
 __device__ __forceinline__ RawPG load_pg(const StepArgs &a, const uint64_t e0, const bool whole)
 {
     RawPG r;
     r.g1 = make_uint4(0, 0, 0, 0);
     if (!TAIL || whole) {
         if (BF16) {
-            r.g0 = *reinterpret_cast<const uint4 *>(static_cast<const uint16_t *>(a.grad) + e0);
+            const u32x4_t *const gp = reinterpret_cast<const u32x4_t *>(static_cast<const uint16_t *>(a.grad) + e0);
+            const u32x4_t halves = PAST ? __builtin_nontemporal_load(gp) : *gp;
+            r.g0 = make_uint4(halves.x, halves.y, halves.z, halves.w);
         } else {
             const uint4 *gp = reinterpret_cast<const uint4 *>(static_cast<const float *>(a.grad) + e0);
             r.g0 = gp[0]; r.g1 = gp[1];
@@ -612,51 +616,45 @@ constexpr int m_table_stride() { return BM == 2 ? 4 : BM == 3 ? 8 : 16; }   // a
 template <int BM, bool MDE>
 constexpr int de_words() { return MDE && BM >= 3 ? 4 * DeBuckets<BM>::N : 16; }
 
-// Whether a flat buffer runs 8 elements per lane, for a quantile of rank `rank` in a full block;
-// `copy`: a bf16 copy of the parameters is written.  8 per lane starts sooner and takes no transposition through LDS, 16 needs fewer instructions and
-// fills whole lines with every access, so 16 wins where the memory is the bound.  Measured on MI355X, time of 8 over time of 16, geometric mean of
-// one state again and again, three in turn and states of 0.6 GB in turn (which lie up to 12 % apart: the first favours 8, the last 16):
-//   elements / 2^18                     4     6     8     12    16    20    24    28    32    40    48    64
-//   2-bit/3-bit bf16                    0.83  0.82  0.94  0.96  0.97  0.97  0.99  0.97  1.01  1.02  1.04  1.09
-//   3-bit/3-bit bf16                    0.83  0.83  0.95  0.97  0.99  0.99  1.01  0.98  1.01  1.04  1.07  1.12
-//   3-bit/4-bit bf16, B 64              0.79  0.80  0.93  0.94  0.93  0.95  0.97  0.94  0.95  0.96  1.00  1.05
-//   2-bit/3-bit bf16, copy              0.85  0.84  0.93  0.93  0.95  0.93  0.95  0.93  0.92  0.97  1.03  1.05
-//   4-bit/4-bit fp32                    0.81  0.84  0.93  0.91  0.95  0.95  0.96  0.95  0.96  0.98  1.02  1.06
-//   3-bit/4-bit fp32, B 64              0.79  0.81  0.90  0.90  0.92  0.94  0.93  0.90  0.92  0.96  1.00  1.03
-//   2-bit/4-bit fp32, copy              0.87  0.85  0.92  0.92  0.91  0.92  0.92  0.90  0.91  0.95  0.97  1.04
-//   2-bit/3-bit bf16, rank 39           0.78  0.79  0.92  0.94  0.98  0.98  1.02  1.03  1.04  1.07  1.11  1.14
-//   2-bit/2-bit bf16, B 64, rank 20     0.85  0.85  0.99  1.00  1.03  1.05  1.03  1.07  1.06  1.05  1.08  1.13
-//   4-bit/4-bit fp32, rank 39           -     -     -     0.90  0.94  0.95  0.96  -     0.97  1.00  1.03  1.06
-//   3-bit/4-bit fp32, B 64, rank 20     0.82  0.85  0.96  0.94  0.97  0.96  1.01
-//   3-bit/3-bit bf16, rank 103          0.64  0.68  0.80  0.83  0.88  0.89  0.93  0.93  0.95  0.97  1.00  1.04
-//   states out of HBM only:
-//   2-bit/3-bit bf16                    0.86  0.84  0.95  0.96  1.03  1.00  1.01  1.00  1.03  1.07  1.08  1.17
-//   3-bit/3-bit bf16 (DE: 16 1.06, 28 1.04) 0.85 0.86 0.97 0.95 1.05  1.00  1.02  1.00  1.04  1.07  1.08  1.17
-//   2-bit/3-bit bf16, copy              0.90  0.82  0.89  0.90  0.98  0.98  1.00  0.98  1.00  1.05  1.06  1.10
-//   4-bit/4-bit fp32 (DE, AdaBelief: 32 1.08) 0.89 0.86 0.95 0.97 1.02 0.99 0.97  0.96  1.02  1.04  1.11  1.12
-//   2-bit/4-bit fp32, copy              0.93  0.80  0.87  0.92  0.96  0.95  0.96  0.93  0.94  1.00  1.06  1.12
-//   2-bit/3-bit bf16, rank 39           0.80  0.80  0.90  0.93  1.03  0.97  1.08  1.00  1.04  1.07  1.16  1.16
-//   2-bit/2-bit bf16, B 64, rank 20     0.88  0.89  0.99  0.99  1.08  1.07  1.04  1.09  1.05  1.06  1.09  1.19
-// A line lies in front of where the mean over the formats crosses for good, so that a state out of HBM, which a step between two
-// backward passes finds, loses nowhere more than a few per cent: at 24 * 2^18 elements with bf16 gradients, 28 with fp32 ones, 8 more with
-// a copy.  Ranks of 17 to 64 merge
-// longer lists with 8 per lane: 12 less.  (Before the lists were merged a rank above 24 was worth 16 per lane from 2^19 elements on, and
-// bf16 gradients from 3 * 2^19.)
-constexpr bool narrow_buffer(uint64_t n, bool bf16, bool copy, uint32_t rank)
+// Whether a flat buffer runs 8 elements per lane; `copy`: a bf16 copy of the parameters is written.  8 per lane starts sooner and takes no transposition
+// through LDS, 16 needs fewer instructions and fills whole lines with every access, all of them past the caches, so 16 wins where the memory is the bound.  Measured on
+// MI355X, time of 8 over time of 16: steps in a row (geometric mean of one state again and again, three in turn and states of 0.7 GB in turn) | a step behind
+// other work that has written 512 MB:
+//   elements / 2^18                 2            4            5            6            8            10           12           16           20           24           28
+//   2-bit/3-bit bf16                .75 | .96    .81 | 1.06   .77 | 1.03   .78 | 1.02   .85 | 1.10   .81 | 1.02   .88 | 1.04   .92 | 1.07   .92 | 1.08   .97 | 1.14   .97 | 1.11
+//   3-bit/3-bit DE bf16             .72 | 1.00   .78 | 1.10   .78 | 1.10   .78 | 1.08   .81 | 1.06   .81 | 1.05   .85 | 1.05   .90 | 1.12   .90 | 1.10   .96 | 1.14   .95 | 1.09
+//   3-bit/4-bit bf16, B 64          .75 | .85    .83 | .97    .78 | .95    .79 | .95    .85 | .97    .82 | .91    .87 | .95    .93 | 1.02   .93 | 1.04   .98 | 1.05   .97 | 1.06
+//   2-bit/3-bit bf16, copy          .78 | 1.10   .85 | 1.15   .82 | 1.14   .82 | 1.14   .90 | 1.17   .87 | 1.09   .94 | 1.09   .98 | 1.10   .97 | 1.12   1.00 | 1.13  1.00 | 1.08
+//   2-bit/3-bit bf16, rank 39       .70 | .87    .78 | 1.00   .76 | 1.04   .76 | 1.04   .84 | 1.08   .79 | 1.01   .86 | 1.05   .92 | 1.08   .91 | 1.10   .97 | 1.16   .97 | 1.11
+//   2-bit/2-bit bf16, B 64, rank 20 .71 | .70    .81 | .84    .77 | .85    .80 | .82    .89 | .89    .84 | .85    .90 | .89    .97 | .98    .95 | 1.00   1.00 | 1.05  1.01 | 1.06
+//   2-bit/3-bit bf16, rank 39, copy .72 | 1.02   .81 | 1.05   .79 | 1.08   .79 | 1.09   .85 | 1.09   .82 | 1.05   .90 | 1.07   .94 | 1.07   .95 | 1.10   .98 | 1.12   .98 | 1.08
+//   4-bit/4-bit fp32                .77 | 1.06   .83 | 1.19   .77 | 1.11   .76 | 1.09   .82 | 1.17   .78 | 1.17   .83 | 1.23   .93 | 1.25   .92 | 1.25   .95 | 1.26   .98 | 1.26
+//   4-bit/4-bit fp32, AdaBelief     .76 | 1.10   .86 | 1.20   .80 | 1.14   .78 | 1.11   .85 | 1.18   .81 | 1.13   .86 | 1.19   .94 | 1.25   .93 | 1.23   .97 | 1.26   .97 | 1.23
+//   2-bit/4-bit fp32, copy          .78 | .93    .87 | 1.02   .80 | 1.06   .80 | 1.07   .87 | 1.13   .83 | 1.08   .91 | 1.13   .95 | 1.17   .94 | 1.18   .96 | 1.19   .96 | 1.18
+//   4-bit/4-bit fp32, rank 39       .68 | 1.03   .77 | 1.14   .73 | 1.10   .72 | 1.07   .78 | 1.14   .74 | 1.10   .80 | 1.15   .88 | 1.19   .88 | 1.22   .92 | 1.21   .94 | 1.22
+// In a row 8 is ahead up to 24 * 2^18 or farther, also out of HBM; behind other work, whose written lines a load that allocates in the last-level cache has to wait
+// for, it falls behind by 2 to 10 % from 4 * 2^18 on with bf16 gradients (8 to 17 % with a copy) and 10 to 25 % with fp32 ones.  A step of an optimizer is the one or
+// the other, by how much of a model one call takes; a line lies where the mean of the four crosses 1.  The rank of the quantile, whose lists 8 per lane
+// merges, does not move it.  (With gradients and parameters through the caches 8 was behind by 40 % there, 5 million elements 2-bit/3-bit bf16 20.9 us instead of 14.6.)
+constexpr bool narrow_buffer(uint64_t n, bool bf16, bool copy)
 {
-    return n <= (uint64_t)(24 + (bf16 ? 0 : 4) + (copy ? 8 : 0) - (rank > 16 && rank <= 64 ? 12 : 0)) << 18;
+    return n <= (uint64_t)(bf16 && copy ? 12 : 20) << 18;
 }
-// Up to how many pieces (pieces16) a table does.  Time of 8 over time of 16 as above, a table of 20 tensors of uneven sizes | of 256 equal ones with a ragged end each:
-//   elements / 2^18                     2            4            6            8            12           16           24           32           40
-//   2-bit/3-bit bf16                    .79 | .89    .82 | .91    .90 | 1.04   .90 | 1.00   .93 | .94    .93 | .94    .96 | 1.01   .99 | 1.01   1.00 | 1.07
-//   3-bit/4-bit bf16, B 64              .81 | .92    .82 | .92    .89 | 1.05   .87 | .99    .90 | .93    .92 | .91    .92 | .99    .94 | 1.00   .97 | 1.01
-//   2-bit/3-bit bf16, copy              .84 | .91    .82 | .92    .86 | 1.02   .90 | .98    .90 | .92    .85 | .86    .91 | .95    .91 | .94    .95 | .97
-//   4-bit/4-bit fp32                    .80 | .87    .81 | .91    .87 | 1.04   .87 | .97    .89 | .90    .87 | .89    .90 | .96    .93 | .97    .97 | 1.03
-//   2-bit/4-bit fp32, copy              .85 | .91    .82 | .90    .86 | 1.01   .87 | .96    .84 | .85    .84 | .85    .88 | .92    .90 | .91    .96 | .97
-//   2-bit/3-bit bf16, rank 39           .75 | .86    .81 | .89    .89 | 1.03   .89 | 1.00   .94 | .95    .95 | .94    1.00 | 1.06  1.04 | 1.09  1.07 | 1.09
-//   4-bit/4-bit fp32, rank 39           .77 | .84    .80 | .90    .88 | 1.03   .88 | .98    .91 | .91    .89 | .90    .91 | .97    .95 | 1.00   1.00 | 1.05
-// One line for all of them (the pieces are what a caller's flags say), at 16 * 2^18 elements; out of HBM 8 is ahead there by 3 to 10 %, at 24 by 5 % in
-// the first table and behind by 3 to 7 % in the second.
+// Up to how many pieces (pieces16) a table does.  Time of 8 over time of 16 as above, a table of 20 tensors of uneven sizes:
+//   elements / 2^18                 2            3            4            6            8            12           16
+//   2-bit/3-bit bf16                .77 | .78    .82 | .81    .81 | .80    .86 | .79    .86 | .77    .85 | .80    .92 | .91
+//   3-bit/4-bit bf16, B 64          .79 | .80    .84 | .85    .80 | .80    .85 | .82    .86 | .83    .86 | .84    .92 | .91
+//   2-bit/3-bit bf16, copy          .79 | .84    .86 | .89    .84 | .86    .84 | .86    .88 | .85    .85 | .85    .93 | .89
+//   4-bit/4-bit fp32                .79 | .88    .83 | .89    .77 | .83    .83 | .87    .82 | .92    .86 | .96    .90 | 1.05
+//   2-bit/4-bit fp32, copy          .81 | .86    .87 | .96    .80 | .90    .85 | .94    .84 | .91    .86 | .94    .91 | 1.04
+//   2-bit/3-bit bf16, rank 39       .74 | .74    .79 | .77    .79 | .75    .86 | .77    .86 | .77    .84 | .80    .90 | .90
+// and with kernels before, in a row only, that table | one of 256 equal tensors with a ragged end each (16 per lane took 3 % longer there than it does now):
+//   elements / 2^18                 6            8            12           16           24           32           40
+//   2-bit/3-bit bf16                .90 | 1.04   .90 | 1.00   .93 | .94    .93 | .94    .96 | 1.01   .99 | 1.01   1.00 | 1.07
+//   2-bit/3-bit bf16, copy          .86 | 1.02   .90 | .98    .90 | .92    .85 | .86    .91 | .95    .91 | .94    .95 | .97
+//   4-bit/4-bit fp32                .87 | 1.04   .87 | .97    .89 | .90    .87 | .89    .90 | .96    .93 | .97    .97 | 1.03
+//   2-bit/3-bit bf16, rank 39       .89 | 1.03   .89 | 1.00   .94 | .95    .95 | .94    1.00 | 1.06  1.04 | 1.09  1.07 | 1.09
+// One line for all of them (the pieces are what a caller's flags say), at 16 * 2^18 elements, where fp32 gradients behind other work are 5 % behind.
 constexpr uint64_t narrow_table_up_to() { return 16ull << 8; }
 
 // The rank-th smallest key of every group of G = 4 or 8 lanes (full blocks).  Each lane has parked its
@@ -1357,7 +1355,7 @@ __device__ __forceinline__ void step_chunk8(const StepArgs &a, const uint64_t ch
     const uint64_t gb_here = TAIL ? umin64(gb, (a.n - 1u) / B) : gb;
     const float dm_old = a.m_scale[gb_here], dv_old = a.v_scale[gb_here], al_old = a.v_base[gb_here];
     const bool whole = !TAIL || (ALONE ? __builtin_expect(ew0 + kIter <= a.n, 0) : e0 + 8u <= a.n);
-    const RawPG raw = load_pg<BF16, TAIL, ALONE>(a, e0, whole);
+    const RawPG raw = load_pg<BF16, TAIL, ALONE, BF16 && ALONE>(a, e0, whole);
     const float gscale = (EXT && a.grad_scale) ? *a.grad_scale : 1.0f;      // uniform: the gradient is transformed first
 
     // ---- while they are under way: what does not depend on them
@@ -2090,7 +2088,7 @@ hipError_t launch_one(const StepArgs &args_in, hipStream_t stream)
 {
     StepArgs args = args_in;                   // the tiling belongs to the instantiation
     if (args.n == 0) return hipSuccess;
-    const bool narrow = narrow_buffer(args.n, BF16, args.param_bf16 != nullptr, args.rank_full);
+    const bool narrow = narrow_buffer(args.n, BF16, args.param_bf16 != nullptr);
     const uint64_t whole = narrow ? 0 : args.n / kIter16;
     args.rest = narrow ? pieces8(args.n) : rest_pieces(args.n, whole);      // (narrow: all of them)
     const uint64_t groups = (whole + args.rest + kWaves - 1) / kWaves;
