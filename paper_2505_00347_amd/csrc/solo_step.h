@@ -1143,8 +1143,7 @@ __device__ __forceinline__ void ema_param(const StepArgs &a, const uint32_t tm_a
 // The new parameters of a lane's 8 elements and their bf16 copy, if asked for.  (Non-temporal: the lines leave the L2 as they are
 // written instead of when the kernel ends.  4-bit/4-bit fp32, one state again and again, us: 2 * 2^20 elements 6.62 -> 6.45, 2.5 7.75 -> 7.34,
 // 3 9.11 -> 8.41, 5 14.5 -> 13.7, 4.5 12.9 -> 13.1; three states in turn and states out of HBM +-2 %, in the mean 0.3 % less.  Written
-// through at device scope, as 16 per lane does, costs 13 to 28 % here, since a store covers every other 16 bytes only; non-temporal loads of the gradient
-// cost 2 to 11 % where the state is in the last-level cache and save 4 to 10 % where it is not.)
+// through at device scope, as 16 per lane does, costs 13 to 28 % here, since a store covers every other 16 bytes only.)
 template <bool EXT, bool TAIL>
 __device__ __forceinline__ void store_params8(const StepArgs &a, const uint64_t e0, const bool whole, const bool *ok, const float (&p)[8])
 {
@@ -2007,7 +2006,7 @@ template <int BM, int BV, int B, bool BF16, bool MDE, bool EXT>
 __global__ __launch_bounds__(kWaves * 64, kMinWaves)
 void multi_chunk8_kernel(const TensorEntry *const entries, const uint32_t count, const MultiArgs args)
 {
-    MultiArgs ma = args;                       // (the first two: as SOLO_FIRST_ARGS)
+    MultiArgs ma = args;                       // (the first two: as SOLO_FIRST_ARGS; those in `args` are not read)
     ma.entries = entries; ma.count = count;
     using Lay = ChunkLayout8<BM, BV, B>;
     __shared__ __attribute__((aligned(64))) uint32_t lds_slab[kWaves * Lay::kSlab];
